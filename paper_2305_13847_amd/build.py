@@ -11,7 +11,8 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 OUT = os.path.join(HERE, "libdgmoist.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["dg_api.hip", "dg_f64.hip", "dg_f32.hip", "dg_tri_api.hip"]
+SOURCES = ["dg_stage_f64.hip", "dg_stage_f32.hip", "dg_gauss_f64.hip", "dg_gauss_f32.hip", "dg_adjoint_f64.hip",
+           "dg_adjoint_f32.hip", "dg_point_f64.hip", "dg_point_f32.hip", "dg_tri_api.hip", "dg_api.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
          # no packed-FP32 instructions in generated code
@@ -30,7 +31,7 @@ def _compile(src: str) -> str:
 
 def build(verbose: bool = True) -> str:
     os.makedirs(BUILD, exist_ok=True)
-    with cf.ThreadPoolExecutor(max_workers=len(SOURCES)) as ex:
+    with cf.ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as ex:
         objs = list(ex.map(_compile, SOURCES))
     tmp = OUT + ".tmp"
     cmd = [HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs

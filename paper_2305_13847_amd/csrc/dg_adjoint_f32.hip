@@ -1,0 +1,6 @@
+// The adjoint kernels in FP32 bulk.
+#include "dg_launch_impl.h"
+
+namespace dgm {
+template struct LaunchAdjoint<float>;
+}

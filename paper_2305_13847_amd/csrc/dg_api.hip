@@ -21,8 +21,11 @@
 using namespace dgm;
 
 namespace dgm {
-extern template struct Launch<double>;
-extern template struct Launch<float>;
+#define DGM_EXTERN(L)             \
+  extern template struct L<double>; \
+  extern template struct L<float>;
+DGM_EXTERN(LaunchPoint) DGM_EXTERN(LaunchStage) DGM_EXTERN(LaunchGauss) DGM_EXTERN(LaunchAdjoint)
+#undef DGM_EXTERN
 }
 
 // ---------------------------------------------------------------------------
@@ -792,6 +795,13 @@ static bool do_rhs(dg_handle* h, int mode, const void* U, const double* aT, cons
     ka.tr_a_in = h->tr_a[tin];
     ka.tr_u_out = h->tr_u[tout];
     ka.tr_a_out = h->tr_a[tout];
+  }
+  if (h->P.basis == DG_BASIS_GAUSS) {
+    if (h->prec == DG_FP64)
+      return Launch<double>::rhs_gauss(ka, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, h->dt_d, c0, c1,
+                                       c2, oT, oS, flags, s);
+    return Launch<float>::rhs_gauss(ka, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, h->dt_d, c0, c1, c2,
+                                    oT, oS, flags, s);
   }
   if (h->prec == DG_FP64)
     return Launch<double>::rhs(ka, h->ka_d, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0,

@@ -12,6 +12,14 @@
 
 namespace dgm {
 
+// The constant address space (read-only global memory; scalar loads) in the
+// device pass.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define DGM_AS_CONST __attribute__((address_space(4)))
+#else
+#define DGM_AS_CONST
+#endif
+
 template <int D, int RAIN>
 struct Vars {
   static constexpr int NV = 3 + D + RAIN;
@@ -275,23 +283,184 @@ __device__ __forceinline__ SplitOut split_point(const KArgs& a, double rd, doubl
   return split_point_anchor(a, rd, rm, rr, re, guess, A);
 }
 
-// Status words: only exceptional events touch global memory.  Iteration
-// maxima are merged per wave and written only when they exceed the stored
-// value; counts of non-converged or invalid states are rare.
+// ---------------------------------------------------------------------------
+// the split near a point of the saturation curve, without iterations
+// ---------------------------------------------------------------------------
+// With (T0, r0 = rho_vs(T0)) known and y = (T - T0)/T0, rho_vs is
+//   r0 (1 + Q y + P2 y^2 + P3 y^3 + P4 y^4),
+// the Taylor series of exp(phi), phi = (a - 1) ln T - b/T, with
+// Q = T0 phi'(T0) = a - 1 + b/T0.  For |Q y| <= kNearQ the truncation,
+// |Q y|^5/120 < 3e-16, is below rounding.  On the saturated branch
+//   f(y) = Cs (T - T_ref) + rho_vs (dc (T - T_ref) + L_p) - rho e,
+//   Cs = c_vd rd + c_l (rm + rr), dc = c_vv - c_l,
+// is then a quartic f0 + f1 y + ... + f4 y^4; its root is -f0/f1 corrected by
+// one quadratic term and one Newton step on the quartic, whose relative
+// error is of the order (Q y)^4 (1.6e-11 of a change of at most 0.1 K).  The
+// unsaturated candidate is the closed form T_u.  The caller names the branch
+// (`sat`); `ok` says that the candidate passed that branch's own exact test
+// (the root is unique, so it is then the solution).  Everything else (branch
+// changes, large changes, invalid states) is left to split_point_anchor.
+// Bound by VALU issue: the warm solve replaces two or three iterations (one
+// rvs_near each) of every stage; with the cold solve below, steps of five
+// 3D Q3 FP32 calls 6.20 -> 5.82 ms, the 64-member 2D ensemble 3.28 -> 3.01 ms.
+constexpr double kNearQ = 2.0e-3;
+constexpr int kEstIters = 8;   // single-precision steps of split_scratch at most
+
+struct NearOut {
+  double T, rvs;
+  bool ok;
+};
+
+__device__ __forceinline__ NearOut split_near(const KArgs& a, double rd, double rm, double rr, double re,
+                                              double T0, double r0, double inv0, bool sat) {
+  NearOut o;
+  const double dc = a.cvv - a.cl;
+  const double Cs = fma(a.cvd, rd, a.cl * (rm + rr));
+  const double Cu = fma(dc, rm, Cs);
+  const double beta = a.b * inv0;
+  const double Q = a.am1 + beta;
+  // T0^n times the n-th derivative of phi, n = 2, 3, 4
+  const double c2 = -(Q + beta), c3 = 2.0 * (Q + 2.0 * beta), c4 = -6.0 * (Q + 3.0 * beta);
+  const double Q2 = Q * Q;
+  const double P2 = 0.5 * (Q2 + c2);
+  const double P3 = (1.0 / 6.0) * fma(Q, Q2 + 3.0 * c2, c3);
+  const double P4 = (1.0 / 24.0) * (fma(Q2, Q2 + 6.0 * c2, fma(4.0 * Q, c3, fma(3.0 * c2, c2, c4))));
+  double y;
+  if (sat) {
+    const double Tm = T0 - a.Tref;
+    const double g = fma(dc, Tm, a.Lp);
+    const double rg = r0 * g, rt = r0 * dc * T0;
+    const double f0 = fma(Cs, Tm, rg - re);
+    const double f1 = fma(Cs, T0, fma(rg, Q, rt));
+    double i1 = __builtin_amdgcn_rcp(f1);
+    i1 = fma(fma(-f1, i1, 1.0), i1, i1);
+    const double y0 = -f0 * i1;
+    const double k2 = fma(rg, P2, rt * Q) * i1;
+    const double k3 = fma(rg, P3, rt * P2) * i1;
+    const double k4 = fma(rg, P4, rt * P3) * i1;
+    const double y1 = fma(-k2 * y0, y0, y0);
+    const double p = fma(y1 * y1, fma(y1, fma(y1, k4, k3), k2), y1 - y0);
+    y = fma(-p, fma(-2.0 * k2, y1, 1.0), y1);
+  } else {
+    const double Tu = a.Tref + (re - rm * a.Lp) * rcp64(Cu);
+    y = (Tu - T0) * inv0;
+  }
+  const double e = y * fma(y, fma(y, fma(y, P4, P3), P2), Q);
+  o.T = fma(y, T0, T0);
+  o.rvs = fma(r0, e, r0);
+  const bool branch = sat ? o.rvs <= rm : rm <= o.rvs;
+  o.ok = branch && fabs(Q * y) <= kNearQ && Cu > 0.0 && T0 > 150.0 && T0 < 600.0 && r0 > 0.0;
+  return o;
+}
+
+// The split warm-started at the node's previous (T, rho_vs(T)); the branch that
+// held there before is tried first.
+__device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double rm, double rr, double re, double T,
+                                               double rvs) {
+  const double inv = rcp64(T);
+  const bool sat = rvs < rm;
+  SplitOut o;
+  o.iters = sat ? 1 : 0;
+  o.bad = 0;
+  const NearOut n = split_near(a, rd, rm, rr, re, T, rvs, inv, sat);
+  o.T = n.T;
+  o.rvs = n.rvs;
+  if (!n.ok || a.maxit <= kEstIters) {
+    Anchor A;
+    A.T0 = 0.0; A.r0 = 0.0; A.inv0 = 0.0;
+    if (T > 150.0 && T < 600.0 && rvs > 0.0) {
+      A.T0 = T; A.r0 = rvs; A.inv0 = inv;
+    }
+    o = split_point_anchor(a, rd, rm, rr, re, T, A, sat);
+  }
+  return o;
+}
+
+// rho_vs in single precision (hardware exp2/log2; relative error below 1e-5)
+// and d ln rho_vs / dT
+__device__ __forceinline__ float rho_vs_est(const KArgs& a, float T, float* q) {
+  const float iT = __builtin_amdgcn_rcpf(T);
+  const float l = __builtin_amdgcn_logf(T * (float)a.inv_Tref);
+  *q = ((float)a.am1 + (float)a.b * iT) * iT;
+  return (float)a.C0 *
+         __builtin_amdgcn_exp2f((float)a.am1 * l + (float)(a.b * 1.4426950408889634) * ((float)a.inv_Tref - iT));
+}
+
+// The split from scratch (no rho_vs known nearby).  Single precision finds the
+// branch and, on the saturated one, the temperature to about 1e-4 K (Newton
+// from the guess if it lies above T_u, else from T_u); one FP64 rho_vs there
+// is the anchor of split_near, which gives the FP64 result.  Within 1e-4 of
+// the branch point the anchor is T_u itself and the FP64 value decides.  The
+// returned rho_vs(T) comes from a fresh evaluation at most 0.03 K away (the
+// estimate's error), so it can anchor later splits.  `iters` counts the
+// estimate's steps and the FP64 solve; a cap (newton_maxit) below what this
+// may use takes the general path.
+// FP64 iterations throughout took 970-1100 VALU instructions per wavefront
+// (three or four exp/log anchors) and kept the VALU 75-100 % busy; two cold
+// splits and a right-hand side on 50 x 42 x 26 Q3 in FP32: 272 -> 177 us.
+
+__device__ __forceinline__ SplitOut split_scratch(const KArgs& a, double rd, double rm, double rr, double re,
+                                                  double guess) {
+  SplitOut o;
+  bool ok = false;
+  if (a.maxit > kEstIters) {
+    const double Cs = fma(a.cvd, rd, a.cl * (rm + rr));
+    const double Cu = fma(a.cvv - a.cl, rm, Cs);
+    const double Tu = a.Tref + (re - rm * a.Lp) * rcp64(Cu);
+    float q;
+    bool sat = (float)rm > 1.0001f * rho_vs_est(a, (float)Tu, &q);
+    double T1 = Tu;
+    int it = 0;
+    if (sat) {
+      const float dc = (float)(a.cvv - a.cl), tref = (float)a.Tref, Lp = (float)a.Lp, cs = (float)Cs, ref = (float)re;
+      float T = (float)(guess > Tu && guess < 600.0 ? guess : Tu);
+      float dT;
+      do {
+        const float r = rho_vs_est(a, T, &q);
+        const float g = dc * (T - tref) + Lp;
+        dT = (cs * (T - tref) + (r * g - ref)) * __builtin_amdgcn_rcpf(cs + r * (q * g + dc));
+        T -= dT;
+        ++it;
+      } while (fabsf(dT) > 0.02f && it < kEstIters);
+      T1 = (double)T;
+    }
+    const double r0 = rho_vs(a, T1);
+    sat = sat || rm > r0;
+    const NearOut n = split_near(a, rd, rm, rr, re, T1, r0, rcp64(T1), sat);
+    ok = n.ok;
+    o.T = n.T;
+    o.rvs = n.rvs;
+    o.iters = sat ? it + 1 : 0;
+    o.bad = 0;
+  }
+  if (!ok) {
+    o = split_point(a, rd, rm, rr, re, guess);
+    if (o.iters > 0 && o.bad == 0) o.rvs = rho_vs(a, o.T);
+  }
+  return o;
+}
+
+// Status words: only exceptional events touch global memory.  `seen` is the
+// stored iteration maximum as it stood when the kernel began (a uniform load
+// issued with the first ones, not a round trip at the end of every wave): a
+// stale value costs at most a redundant atomic.  The maximum is formed only
+// in waves that exceed it; non-converged or invalid states are rare.
 __device__ __forceinline__ int wave_max(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
   return v;
 }
 
-__device__ __forceinline__ void record_stats(const KArgs& a, int iters, int bad) {
-  const int m = wave_max(iters);
-  const int anybad = wave_max(bad);
-  const int lane = threadIdx.x & 63;
-  if (lane == 0) {
-    if (m > 0 && (unsigned)m > __builtin_nontemporal_load(&a.stats[0])) atomicMax(&a.stats[0], (unsigned)m);
+__device__ __forceinline__ int stats_seen(const KArgs& a) {
+  return (int)*(const unsigned DGM_AS_CONST*)(unsigned long long)a.stats;
+}
+
+__device__ __forceinline__ void record_stats(const KArgs& a, int seen, int iters, int bad) {
+  if (__any(iters > seen)) {
+    const int m = wave_max(iters);
+    if ((threadIdx.x & 63) == 0) atomicMax(&a.stats[0], (unsigned)m);
   }
-  if (anybad) {
+  if (__any(bad != 0)) {
     if (bad == 2) atomicAdd(&a.stats[1], 1u);
     if (bad == 1) atomicOr(&a.stats[2], 1u);
   }

@@ -295,6 +295,7 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
   // registers (and halves the occupancy)
   const int it_ = ItemWalk(a.nitems, a.walk_rev).item(0);
   if (it_ < 0) return;
+  const int seen = MODE == 2 ? stats_seen(a) : 0;
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
@@ -394,7 +395,7 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
     }
   }
   if (MODE == 2) {
-    record_stats(a, iters, bad);
+    record_stats(a, seen, iters, bad);
     __syncthreads();
     // 4. the traces of the new state for the next stage
     write_traces<R, K, D, RAIN>(a, md, item, epb, sU, sT, sRv, sL);

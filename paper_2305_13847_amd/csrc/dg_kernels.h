@@ -1,5 +1,5 @@
 // Kernels of libdgmoist and their launch dispatch (instantiated per precision
-// in dg_f64.hip and dg_f32.hip).
+// in dg_stage_f64.hip and its siblings).
 //
 // Work decomposition: a block owns EPB consecutive elements of one member
 // (a work item); one thread owns one node of one element and computes every
@@ -9,14 +9,6 @@
 #include "dg_device.h"
 
 namespace dgm {
-
-// The constant address space (read-only global memory; scalar loads) in the
-// device pass.
-#if defined(__HIP_DEVICE_COMPILE__)
-#define DGM_AS_CONST __attribute__((address_space(4)))
-#else
-#define DGM_AS_CONST
-#endif
 
 template <int D>
 struct ElemCoord {
@@ -135,6 +127,7 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
   // live across the body)
   const int it_ = ItemWalk(nitems).item(0);
   if (it_ < 0) return;
+  const int seen = stats_seen(a);
   const int t = threadIdx.x;
   const Item item = a.items[item0 + it_];
   const MemberDesc& md = a.mem[item.member];
@@ -163,7 +156,7 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
     }
     const double re = a.bg_E[iz] + (double)Uq[V::E] - 0.5 * ke / rho;
     const double guess = Tguess ? Tguess[g] : 0.0;
-    const SplitOut s = split_point(a, rd, rm, rr, re, guess);
+    const SplitOut s = split_scratch(a, rd, rm, rr, re, guess);
     iters = s.iters;
     bad = s.bad;
     oT[g] = s.T;
@@ -172,11 +165,10 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
       if (o1) o1[g] = rv;
       if (o2) o2[g] = rm - rv;
     } else {
-      // the stored rho_vs(T) must be a fresh evaluation: it anchors later splits
-      o1[g] = (s.iters > 0 && s.bad == 0) ? rho_vs(a, s.T) : s.rvs;
+      o1[g] = s.rvs;   // from a fresh evaluation: it anchors later splits
     }
   }
-  record_stats(a, iters, bad);
+  record_stats(a, seen, iters, bad);
 }
 
 // ---------------------------------------------------------------------------
@@ -492,13 +484,7 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const double* bg,
       ke += mi * mi;
     }
     const double re = bg[3] + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
-    Anchor A;
-    A.T0 = 0.0; A.r0 = 0.0; A.inv0 = 0.0;
-    if (T > 150.0 && T < 600.0 && rvs > 0.0) {
-      A.T0 = T; A.r0 = rvs; A.inv0 = rcp64(T);
-    }
-    // the branch that held at this node before is tried first
-    const SplitOut s = split_point_anchor(a, rd, rm, rr, re, T, A, rvs < rm);
+    const SplitOut s = split_warm(a, rd, rm, rr, re, T, rvs);
     iters = s.iters;
     bad = s.bad;
     const double rvs_st = ((flags & kRefreshRvs) && s.bad == 0) ? rho_vs(a, s.T) : s.rvs;
@@ -526,6 +512,7 @@ __device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R
   using FS = FaceShape<K, D>;
   constexpr int P1 = S::P1, NP = S::NP, NV = V::NV, NT = S::NT;
   static_assert(K >= 2, "pair face pass needs K >= 2");
+  const int seen = MODE == 2 ? stats_seen(a) : 0;
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
@@ -655,7 +642,7 @@ __device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R
     stage_epilogue<R, D, RAIN, MODE>(a, bg, iz, g, N, Us, U0q, Rv, T, rvs, out, dtm, c0, c1, c2, oT, oS, flags,
                                      iters, bad);
   }
-  if (MODE == 2) record_stats(a, iters, bad);
+  if (MODE == 2) record_stats(a, seen, iters, bad);
 }
 
 template <typename R, int K, int D, int RAIN, int MODE>
@@ -669,6 +656,7 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
   using S = Shape<K, D, block_threads<R>()>;
   using V = Vars<D, RAIN>;
   constexpr int P1 = S::P1, NP = S::NP, NV = V::NV;
+  const int seen = MODE == 2 ? stats_seen(a) : 0;
   const int t = threadIdx.x;
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
@@ -762,13 +750,7 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
           ke += mi * mi;
         }
         const double re = a.bg_E[iz] + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
-        Anchor A;
-        A.T0 = 0.0; A.r0 = 0.0; A.inv0 = 0.0;
-        if (T > 150.0 && T < 600.0 && rvs > 0.0) {
-          A.T0 = T; A.r0 = rvs; A.inv0 = rcp64(T);
-        }
-        // the branch that held at this node before is tried first
-        const SplitOut s = split_point_anchor(a, rd, rm, rr, re, T, A, rvs < rm);
+        const SplitOut s = split_warm(a, rd, rm, rr, re, T, rvs);
         iters = s.iters;
         bad = s.bad;
         oT[g] = s.T;
@@ -776,7 +758,7 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
       }
     }
   }
-  if (MODE == 2) record_stats(a, iters, bad);
+  if (MODE == 2) record_stats(a, seen, iters, bad);
 }
 
 // one work item per block

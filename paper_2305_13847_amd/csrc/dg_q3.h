@@ -122,6 +122,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const ItemWalk walk(a.nitems, a.walk_rev);
   const int it_ = walk.item(0);
   if (it_ < 0) return;
+  const int seen = MODE == 2 ? stats_seen(a) : 0;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = (int)(threadIdx.x & 63);
   const Item item = a.items[it_];
@@ -325,7 +326,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const double wq = md.J * a.w[li] * a.w[lj] * a.w[ll];
   stage_epilogue<R, D, RAIN, MODE>(a, bg, iz, g, N, Uq, U0q, Rv, T, rvs, out, dtm, c0, c1, c2, oT, oS, flags,
                                    iters, bad, nullptr, nullptr, nullptr, wq, at);
-  if (MODE == 2) record_stats(a, iters, bad);
+  if (MODE == 2) record_stats(a, seen, iters, bad);
   if (MODE == 2 && (flags & kSipAlpha)) {
 #pragma unroll
     for (int h = 1; h < NP; h <<= 1) {

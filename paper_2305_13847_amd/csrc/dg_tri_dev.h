@@ -157,7 +157,7 @@ __device__ __forceinline__ SplitOut tri_split_point(const KArgs& a, const double
   const double rho = rd + rm + rr;
   const double m0 = Uq[V::M0], m1 = Uq[V::M0 + 1];
   const double re = (b[3] + Uq[V::E]) - 0.5 * (m0 * m0 + m1 * m1) / rho;
-  const SplitOut s = split_point(a, rd, rm, rr, re, Tg);
+  const SplitOut s = split_scratch(a, rd, rm, rr, re, Tg);
   *rv = fmin(s.rvs, rm);
   return s;
 }
@@ -324,6 +324,7 @@ __global__ void __launch_bounds__(256) tri_split_kernel(KArgs a, TriArgs t, cons
   const int el = lane ? tid / NQ : 0, q = lane ? tid - el * NQ : 0;
   const long long e0 = tri_first_element<K>(t.ne);
   if (e0 < 0) return;
+  const int seen = stats_seen(a);
   const bool act = lane && e0 + el < t.ne;
   const long long e = min(e0 + el, (long long)t.ne - 1);
   tri_copy_tab<R, K>(S);
@@ -333,7 +334,7 @@ __global__ void __launch_bounds__(256) tri_split_kernel(KArgs a, TriArgs t, cons
   if (lane) tri_split_at<R, K, RAIN>(a, t, S, el, q, tri_z(t, (int)e), &it, &bd);
   __syncthreads();
   if (lane) tri_project_split<R, K, RAIN>(S, el, q, e, act, Tn, Rn);
-  record_stats(a, act ? it : 0, act ? bd : 0);
+  record_stats(a, seen, act ? it : 0, act ? bd : 0);
 }
 
 // Stage kernel.  MODE 0: out = dC/dt.  MODE 2: out = c0 U0 + c1 U + c2 dt dC/dt
@@ -354,6 +355,7 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
   const int el = lane ? tid / NQ : 0, q = lane ? tid - el * NQ : 0;
   const long long e0 = tri_first_element<K>(t.ne);
   if (e0 < 0) return;
+  const int seen = stats_seen(a);
   const bool act = lane && e0 + el < t.ne;
   const int e = (int)min(e0 + el, (long long)t.ne - 1);
   const size_t N = (size_t)t.ne * NP;
@@ -592,7 +594,7 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
     if (lane) tri_split_at<R, K, RAIN>(a, t, S, el, q, g, &it, &bd);
     __syncthreads();
     if (lane) tri_project_split<R, K, RAIN>(S, el, q, e, act, Tn, Rn);
-    record_stats(a, act ? it : 0, act ? bd : 0);
+    record_stats(a, seen, act ? it : 0, act ? bd : 0);
   }
 }
 
