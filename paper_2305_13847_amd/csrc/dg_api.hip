@@ -99,6 +99,7 @@ struct dg_handle {
   void* stage_x[4] = {nullptr, nullptr, nullptr, nullptr};          // adjoint workspace
   void* stage_w = nullptr;       // adjoint of the step's end state through the sponge
   double* sponge_d = nullptr;    // sponge blending factor per vertical node index
+  double* bgt_d = nullptr;       // background per index (KArgs::bgt)
   double* bgf_d = nullptr;       // Gauss basis: background traces on horizontal faces
   void* tr_u[2] = {nullptr, nullptr};     // Gauss basis: face traces of U' (ping-pong like aux)
   double* tr_a[2] = {nullptr, nullptr};   // and of T, rho_v
@@ -347,7 +348,7 @@ static void free_all(dg_handle* h) {
   for (auto& b : h->bg_d) F(b);
   for (auto& b : h->stage) F(b);
   for (auto& b : h->stage_x) F(b);
-  F(h->stage_w); F(h->sponge_d); F(h->bgf_d);
+  F(h->stage_w); F(h->sponge_d); F(h->bgt_d); F(h->bgf_d);
   F(h->sip_aK); F(h->sip_av); F(h->sip_out);
   for (int i = 0; i < 2; ++i) { F(h->tr_u[i]); F(h->tr_a[i]); }
   F(h->auxT); F(h->auxS); F(h->auxT2); F(h->auxS2);
@@ -384,7 +385,7 @@ static void build_items(dg_handle* h, int epb, int order = -1) {
     h->item_off.push_back((int)h->items.size());
     const MemberDesc& md = h->mem[m];
     for (int e0 = 0; e0 < md.ne; e0 += epb) {
-      Item it;
+      Item it{};
       it.member = m;
       it.e0 = e0;
       it.c0 = e0 % md.n[0];
@@ -392,6 +393,13 @@ static void build_items(dg_handle* h, int epb, int order = -1) {
       const int c1 = row % md.n[1];
       const int c2 = row / md.n[1];
       it.c12 = c1 + (c2 << 16);
+      for (int j = 0; j < 3; ++j) {
+        it.n[j] = md.n[j];
+        it.bc[j] = md.bc[j];
+      }
+      it.ne = md.ne;
+      it.eoff = (int)md.eoff;
+      it.hoff = md.hoff;
       h->items.push_back(it);
     }
     if (h->dim == 3 && order != 1) {
@@ -543,6 +551,7 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   ok = ok && A((void**)&h->items_d, sizeof(Item) * h->items_cap);
   ok = ok && A((void**)&h->ka_d, sizeof(KArgs));
   for (auto& b : h->bg_d) ok = ok && A((void**)&b, sizeof(double) * hoff);
+  ok = ok && A((void**)&h->bgt_d, sizeof(double) * kBgStride * hoff);
   for (auto& b : h->stage) ok = ok && A(&b, h->state_bytes);
   ok = ok && A((void**)&h->auxT, sizeof(double) * h->nnodes);
   ok = ok && A((void**)&h->auxS, sizeof(double) * h->nnodes);
@@ -577,7 +586,7 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   ok = ok && A((void**)&h->partial, sizeof(double) * 3 * h->items_cap);
   ok = ok && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) == hipSuccess;
   ok = ok && A((void**)&h->red_out, sizeof(double) * 4);
-  ok = ok && A((void**)&h->stats, sizeof(unsigned) * 8);
+  ok = ok && A((void**)&h->stats, sizeof(unsigned) * kStatsWords);
   ok = ok && hipHostMalloc((void**)&h->dt_h, sizeof(double) * nmembers) == hipSuccess;
   if (!ok) {
     const size_t sb = h->state_bytes;
@@ -587,7 +596,7 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   }
   if (hipMemcpy(h->mem_d, h->mem.data(), sizeof(MemberDesc) * nmembers, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(h->items_d, h->items.data(), sizeof(Item) * h->items.size(), hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemset(h->stats, 0, sizeof(unsigned) * 8) != hipSuccess ||
+      hipMemset(h->stats, 0, sizeof(unsigned) * kStatsWords) != hipSuccess ||
       hipMemset(h->auxT, 0, sizeof(double) * h->nnodes) != hipSuccess ||
       hipMemset(h->auxS, 0, sizeof(double) * h->nnodes) != hipSuccess) {
     free_all(h);
@@ -623,11 +632,13 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   a.mem = h->mem_d;
   a.items = h->items_d;
   a.nitems = (int)h->items.size();
+  a.epb = h->epb;
   a.nmembers = nmembers;
   a.etot = h->etot;
   a.nnodes = (unsigned)h->nnodes;
   a.bg_rd = h->bg_d[0]; a.bg_rm = h->bg_d[1]; a.bg_rr = h->bg_d[2]; a.bg_E = h->bg_d[3];
   a.bg_p = h->bg_d[4];
+  a.bgt = h->bgt_d;
   a.stats = h->stats;
   a.sponge = nullptr;
   if (h->sponge) {
@@ -686,14 +697,18 @@ extern "C" dg_status dg_member_offset(const dg_handle* h, int member, long long*
   return DG_OK;
 }
 
-// background pressure: equation of state of the split background (FP64)
+// background pressure: equation of state of the split background (FP64), and
+// the table of the background per index
 __global__ void bg_pressure_kernel(KArgs a, int i0, int n, int rain) {
   const int i = i0 + blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= i0 + n) return;
   const double rd = a.bg_rd[i], rm = a.bg_rm[i], rr = rain ? a.bg_rr[i] : 0.0;
   const SplitOut s = split_point(a, rd, rm, rr, a.bg_E[i], 0.0);
   const double rv = fmin(s.rvs, rm);
-  const_cast<double*>(a.bg_p)[i] = (rd * a.Rd + rv * a.Rv) * s.T;
+  const double p = (rd * a.Rd + rv * a.Rv) * s.T;
+  const_cast<double*>(a.bg_p)[i] = p;
+  double* t = const_cast<double*>(a.bgt) + (size_t)i * kBgStride;
+  t[0] = rd; t[1] = rm; t[2] = p; t[3] = a.bg_E[i] + p; t[4] = rr; t[5] = a.bg_E[i];
 }
 
 // Background traces on the horizontal faces of the Gauss basis, for the
@@ -1043,10 +1058,10 @@ extern "C" dg_status dg_reduce_mass_member(dg_handle* h, const void* U, double* 
 
 extern "C" dg_status dg_get_stats(dg_handle* h, dg_stats* out) {
   if (!h || !out) return fail(DG_EINVAL, "null pointer");
-  unsigned w[8];
+  std::vector<unsigned> w(kStatsWords);
   HIP_TRY(hipDeviceSynchronize());
-  HIP_TRY(hipMemcpy(w, h->stats, sizeof w, hipMemcpyDeviceToHost));
-  out->max_iters = (int)w[0];
+  HIP_TRY(hipMemcpy(w.data(), h->stats, sizeof(unsigned) * kStatsWords, hipMemcpyDeviceToHost));
+  out->max_iters = (int)stats_max_iters(w.data());
   out->nonconverged = w[1];
   out->nonfinite = w[2] ? 1 : 0;
   out->splits = h->splits;
@@ -1058,7 +1073,7 @@ extern "C" dg_status dg_get_stats(dg_handle* h, dg_stats* out) {
 extern "C" dg_status dg_reset_stats(dg_handle* h) {
   if (!h) return fail(DG_EINVAL, "null handle");
   HIP_TRY(hipDeviceSynchronize());
-  HIP_TRY(hipMemset(h->stats, 0, sizeof(unsigned) * 8));
+  HIP_TRY(hipMemset(h->stats, 0, sizeof(unsigned) * kStatsWords));
   h->splits = 0;
   return DG_OK;
 }
@@ -1192,6 +1207,7 @@ extern "C" dg_status dg_timing_read(dg_handle* h, int kclass, double* total_ms, 
 static dg_status upload_items(dg_handle* h) {
   HIP_TRY(hipMemcpy(h->items_d, h->items.data(), sizeof(Item) * h->items.size(), hipMemcpyHostToDevice));
   h->ka.nitems = (int)h->items.size();
+  h->ka.epb = h->epb;
   HIP_TRY(hipMemcpy(h->ka_d, &h->ka, sizeof(KArgs), hipMemcpyHostToDevice));
   return DG_OK;
 }

@@ -9,6 +9,23 @@ namespace dgm {
 constexpr int kMaxOrder = 7;     // 2D; 3D kernels are instantiated up to 4
 constexpr int kMaxP1 = kMaxOrder + 1;
 
+// Status words of a handle (KArgs::stats).  Blocks spread their iteration
+// maxima over kStatSlots lines: with a single word, the first launch on a new
+// handle (or after a reset) waited about 400 us for its wavefronts' atomics.
+constexpr int kStatSlots = 64, kStatStride = 32;
+constexpr int kStatsWords = kStatStride * (1 + kStatSlots);
+
+inline unsigned stats_max_iters(const unsigned* w) {
+  unsigned m = 0;
+  for (int s = 0; s < kStatSlots; ++s) {
+    const unsigned v = w[kStatStride * (1 + s)];
+    if (v > m) m = v;
+  }
+  return m;
+}
+
+constexpr int kBgStride = 6;
+
 // One ensemble member: a structured box.  Elements of all members are
 // concatenated; eoff is this member's first global element.
 struct MemberDesc {
@@ -30,12 +47,21 @@ struct MemberDesc {
 };
 
 // A work item: EPB consecutive elements of one member, starting at element e0
-// with element coordinates (c0, c1, c2) packed as c12 = c1 + (c2 << 16).
-struct Item {
+// with element coordinates (c0, c1, c2) packed as c12 = c1 + (c2 << 16).  It
+// carries what addresses depend on (the member's mesh and offsets), one 64-byte
+// scalar load: read through the member table these values were a second and
+// third scalar round trip before a wavefront's first vector load, half of its
+// life in a 64-member ensemble.
+struct alignas(64) Item {
   int member;
   int e0;
   int c0;
   int c12;
+  int n[3];    // the member's elements per axis,
+  int bc[3];   // boundary types,
+  int ne;      // elements,
+  int eoff;    // first global element
+  int hoff;    // and first background index
 };
 
 // Everything the kernels need besides the state arrays.
@@ -82,6 +108,7 @@ struct KArgs {
   const MemberDesc* mem;
   const Item* items;
   int nitems;
+  int epb;                         // elements per work item
   int nmembers;
   long long etot;                  // elements of all members
   unsigned nnodes;                 // nodes of all members: the stride between variables
@@ -91,10 +118,13 @@ struct KArgs {
   const double* bg_rr;
   const double* bg_E;
   const double* bg_p;
+  // the same per index as kBgStride consecutive values (rho_d, rho_m, p, E + p,
+  // rho_r, E): a node's background is two or three 16-byte loads of one address
+  const double* bgt;
   // sponge blending factor per vertical node index (nullptr: no sponge)
   const double* sponge;
-  // status words: [0] max iterations, [1] non-converged, [2] invalid, [3] spare,
-  // [4..5] split count (64-bit)
+  // status words: [1] non-converged, [2] invalid; the iteration maximum in
+  // kStatSlots words of a cache line each (stat_slot), the host takes the largest
   unsigned* stats;
   // stage kernels: walk the work items from the last one (every other stage,
   // so a stage starts on the data the previous one wrote last)

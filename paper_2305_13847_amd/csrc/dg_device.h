@@ -441,10 +441,14 @@ __device__ __forceinline__ SplitOut split_scratch(const KArgs& a, double rd, dou
 }
 
 // Status words: only exceptional events touch global memory.  `seen` is the
-// stored iteration maximum as it stood when the kernel began (a uniform load
-// issued with the first ones, not a round trip at the end of every wave): a
-// stale value costs at most a redundant atomic.  The maximum is formed only
-// in waves that exceed it; non-converged or invalid states are rare.
+// block's stored iteration maximum as it stood when the kernel began (a uniform
+// load issued with the first ones, not a round trip at the end of every wave);
+// a wave that exceeds it forms its maximum and checks the current value before
+// the atomic.  Non-converged or invalid states are rare.
+__device__ __forceinline__ unsigned* stat_slot(const KArgs& a) {
+  return a.stats + kStatStride * (1 + (blockIdx.x & (kStatSlots - 1)));
+}
+
 __device__ __forceinline__ int wave_max(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
@@ -452,13 +456,16 @@ __device__ __forceinline__ int wave_max(int v) {
 }
 
 __device__ __forceinline__ int stats_seen(const KArgs& a) {
-  return (int)*(const unsigned DGM_AS_CONST*)(unsigned long long)a.stats;
+  return (int)*(const unsigned DGM_AS_CONST*)(unsigned long long)stat_slot(a);
 }
 
 __device__ __forceinline__ void record_stats(const KArgs& a, int seen, int iters, int bad) {
   if (__any(iters > seen)) {
     const int m = wave_max(iters);
-    if ((threadIdx.x & 63) == 0) atomicMax(&a.stats[0], (unsigned)m);
+    unsigned* const w = stat_slot(a);
+    if ((threadIdx.x & 63) == 0 &&
+        (unsigned)m > __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(w, (unsigned)m);
   }
   if (__any(bad != 0)) {
     if (bad == 2) atomicAdd(&a.stats[1], 1u);
@@ -477,6 +484,20 @@ __device__ __forceinline__ float pow_b(float x, float p) {
   return __builtin_amdgcn_exp2f(p * __builtin_amdgcn_logf(x));
 }
 __device__ __forceinline__ double pow_b(double x, double p) { return pow(x, p); }
+// x^(3/16), x^(1/2) and x^(7/8) of the Kessler terms: in FP64 from square
+// roots, x^(1/8) x^(1/16) and x / x^(1/8) (two library pow calls were 40 % of
+// the FP64 stage kernel's instructions)
+__device__ __forceinline__ void kessler_pow(float x, float& p316, float& p12, float& p78) {
+  p316 = pow_b(x, 0.1875f);
+  p12 = sqrt(x);
+  p78 = pow_b(x, 0.875f);
+}
+__device__ __forceinline__ void kessler_pow(double x, double& p316, double& p12, double& p78) {
+  p12 = sqrt(x);
+  const double p18 = sqrt(sqrt(p12));
+  p316 = p18 * sqrt(p18);
+  p78 = x / p18;
+}
 
 template <typename R, int D, int RAIN>
 struct Pt {
@@ -493,11 +514,11 @@ struct Pt {
 };
 
 // Full state from the perturbation Uq, the temperature T, the vapour density
-// rho_v and the background (rho_d, rho_m, rho_r, E, p) at the point; rho_vs
+// rho_v and the background (rho_d, rho_m, rho_r, p, E + p) at the point; rho_vs
 // enters only the evaporation source.  The reconstruction is FP64.
 template <typename R, int D, int RAIN>
 __device__ __forceinline__ void eval_core(const KArgs& a, const R* Uq, double T, double rv, double rvs,
-                                          double bd, double bm, double br, double bE, double bp,
+                                          double bd, double bm, double br, double bp, double bEp,
                                           Pt<R, D, RAIN>& q) {
   using V = Vars<D, RAIN>;
   const double rd = bd + (double)Uq[V::RD];
@@ -511,7 +532,7 @@ __device__ __forceinline__ void eval_core(const KArgs& a, const R* Uq, double T,
   const double Cv = a.cvd * rd + a.cvv * rv + a.cl * (rc + rr);
   q.rd = (R)rd; q.rm = (R)rm; q.rr = (R)rr; q.rho = (R)rho;
   q.pp = (R)ppd;
-  q.H = (R)(bE + bp + (double)Uq[V::E] + ppd);
+  q.H = (R)(bEp + (double)Uq[V::E] + ppd);
   R uu = R(0);
   const R irho = inv_b(q.rho);
   for (int i = 0; i < D; ++i) {
@@ -535,16 +556,30 @@ __device__ __forceinline__ void eval_core(const KArgs& a, const R* Uq, double T,
   }
 }
 
-// Full state at a node from the stored perturbation U at vertical index iz and
+// Background at vertical index iz.
+struct Bg {
+  double rd, rm, p, Ep, rr, E;
+};
+
+__device__ __forceinline__ Bg bg_at(const KArgs& a, int iz) {
+  const double2* b = (const double2*)a.bgt + (unsigned)iz * (kBgStride / 2);
+  const double2 x = b[0], y = b[1], z = b[2];
+  return Bg{x.x, x.y, y.x, y.y, z.x, z.y};
+}
+
+// Full state at a node from the stored perturbation U, the background there and
 // the split result (T, rho_vs(T)): rho_v = min(rho_vs, rho_m).
+template <typename R, int D, int RAIN>
+__device__ __forceinline__ void eval_bg(const KArgs& a, const R* Uq, double T, double rvs, const Bg& b,
+                                        Pt<R, D, RAIN>& q) {
+  const double rm = b.rm + (double)Uq[Vars<D, RAIN>::RM];
+  eval_core<R, D, RAIN>(a, Uq, T, fmin(rvs, rm), rvs, b.rd, b.rm, RAIN ? b.rr : 0.0, b.p, b.Ep, q);
+}
+
 template <typename R, int D, int RAIN>
 __device__ __forceinline__ void eval_point(const KArgs& a, const R* Uq, double T, double rvs, int iz,
                                            Pt<R, D, RAIN>& q) {
-  using V = Vars<D, RAIN>;
-  const double rm = a.bg_rm[iz] + (double)Uq[V::RM];
-  const double rv = fmin(rvs, rm);
-  eval_core<R, D, RAIN>(a, Uq, T, rv, rvs, a.bg_rd[iz], a.bg_rm[iz], RAIN ? a.bg_rr[iz] : 0.0, a.bg_E[iz],
-                        a.bg_p[iz], q);
+  eval_bg<R, D, RAIN>(a, Uq, T, rvs, bg_at(a, iz), q);
 }
 
 // Physical flux in direction j (Section 2.3 perturbation form).
@@ -593,9 +628,7 @@ __device__ __forceinline__ void sources(const KArgs& a, const R* Uq, const Pt<R,
     const R rrp = q.rr > R(0) ? q.rr : R(0);
     R p316 = R(0), p12 = R(0), p78 = R(0);
     if (rrp > R(0)) {
-      p316 = pow_b(rrp, R(0.1875));
-      p12 = sqrt(rrp);
-      p78 = pow_b(rrp, R(0.875));
+      kessler_pow(rrp, p316, p12, p78);
     }
     const R Sev = (R(3.86e-3) - R(9.41e-5) * q.Tm) * (R(1) + R(9.1) * p316) * q.dvs * p12;
     const R au = q.rc - (R)a.q_au * q.rho;

@@ -93,7 +93,7 @@ __device__ __forceinline__ void write_traces(const KArgs& a, const MemberDesc& m
   for (int task = threadIdx.x; task < epb * NFE; task += (int)blockDim.x) {
     const int fle = task / NFE;
     const int r = task - fle * NFE;
-    if (item.e0 + fle >= md.ne) continue;
+    if (item.e0 + fle >= item.ne) continue;
     const int f = r / NF;
     const int fp = r - f * NF;
     const int J = f >> 1, side = f & 1;
@@ -102,7 +102,7 @@ __device__ __forceinline__ void write_traces(const KArgs& a, const MemberDesc& m
     if (J == 0) gauss_trace<R, K, D, RAIN, 0>(fle, side, fp, sU, sT, sRv, sL, Ut, Tt, Rvt);
     else if (J == 1 || D == 2) gauss_trace<R, K, D, RAIN, 1>(fle, side, fp, sU, sT, sRv, sL, Ut, Tt, Rvt);
     else if constexpr (D == 3) gauss_trace<R, K, D, RAIN, 2>(fle, side, fp, sU, sT, sRv, sL, Ut, Tt, Rvt);
-    const size_t eg = (size_t)(md.eoff + item.e0 + fle);
+    const size_t eg = (size_t)(item.eoff + item.e0 + fle);
     const size_t et = (size_t)a.etot;
 #pragma unroll
     for (int v = 0; v < NV; ++v) tu[((size_t)v * et + eg) * NFE + r] = Ut[v];
@@ -125,27 +125,27 @@ __device__ __forceinline__ void gauss_face(const KArgs& a, const MemberDesc& md,
   R Uo[NV];
   double To, Rvo;
   gauss_trace<R, K, D, RAIN, J>(le, side, fp, sU, sT, sRv, sL, Uo, To, Rvo);
-  const ElemCoord<D> ec = item_coord<D>(md, item, le);
+  const ElemCoord<D> ec = item_coord<D>(item, le);
   const int e = item.e0 + le;
   const int c = ec.c[J];
-  const bool at_end = side ? (c == md.n[J] - 1) : (c == 0);
-  const bool wall = at_end && md.bc[J] == 1;
+  const bool at_end = side ? (c == item.n[J] - 1) : (c == 0);
+  const bool wall = at_end && item.bc[J] == 1;
   int cn = side ? c + 1 : c - 1;
-  if (cn < 0) cn += md.n[J];
-  if (cn >= md.n[J]) cn -= md.n[J];
+  if (cn < 0) cn += item.n[J];
+  if (cn >= item.n[J]) cn -= item.n[J];
   // background at the face point, own and neighbour side
   double bo[5], bn[5];
   if constexpr (J == D - 1) {
-    const int r0 = md.hoff / P1;
+    const int r0 = item.hoff / P1;
 #pragma unroll
     for (int f = 0; f < 5; ++f) {
       bo[f] = a.bgf[f * a.bgf_n + 2 * (r0 + c) + side];
       bn[f] = a.bgf[f * a.bgf_n + 2 * (r0 + cn) + 1 - side];
     }
   } else {
-    const int izf = md.hoff + ec.c[D - 1] * P1 + face_level<K, D, J>(fp);
-    bo[0] = a.bg_rd[izf]; bo[1] = a.bg_rm[izf]; bo[2] = RAIN ? a.bg_rr[izf] : 0.0;
-    bo[3] = a.bg_E[izf]; bo[4] = a.bg_p[izf];
+    const int izf = item.hoff + ec.c[D - 1] * P1 + face_level<K, D, J>(fp);
+    const Bg b = bg_at(a, izf);
+    bo[0] = b.rd; bo[1] = b.rm; bo[2] = RAIN ? b.rr : 0.0; bo[3] = b.E; bo[4] = b.p;
 #pragma unroll
     for (int f = 0; f < 5; ++f) bn[f] = bo[f];
   }
@@ -161,7 +161,7 @@ __device__ __forceinline__ void gauss_face(const KArgs& a, const MemberDesc& md,
     Tn = To;
     Rvn = Rvo;
   } else {
-    const size_t en = (size_t)(md.eoff + e + (cn - c) * elem_stride(md, J));
+    const size_t en = (size_t)(item.eoff + e + (cn - c) * elem_stride(item, J));
     const size_t et = (size_t)a.etot;
     const int rn = (2 * J + 1 - side) * NF + fp;
     const R* tu = (const R*)a.tr_u_in;
@@ -171,8 +171,8 @@ __device__ __forceinline__ void gauss_face(const KArgs& a, const MemberDesc& md,
     Rvn = a.tr_a_in[(et + en) * NFE + rn];
   }
   Pt<R, D, RAIN> qo, qn;
-  eval_core<R, D, RAIN>(a, Uo, To, Rvo, Rvo, bo[0], bo[1], bo[2], bo[3], bo[4], qo);
-  eval_core<R, D, RAIN>(a, Un, Tn, Rvn, Rvn, bn[0], bn[1], bn[2], bn[3], bn[4], qn);
+  eval_core<R, D, RAIN>(a, Uo, To, Rvo, Rvo, bo[0], bo[1], bo[2], bo[4], bo[3] + bo[4], qo);
+  eval_core<R, D, RAIN>(a, Un, Tn, Rvn, Rvn, bn[0], bn[1], bn[2], bn[4], bn[3] + bn[4], qn);
   // minus side = lower coordinate along J
   const Pt<R, D, RAIN>& qm = side ? qo : qn;
   const Pt<R, D, RAIN>& qp = side ? qn : qo;
@@ -230,12 +230,12 @@ gauss_trace_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ 
     const MemberDesc& md = a.mem[item.member];
     const int le = t / NP, n = t - le * NP;
     const int e = item.e0 + le;
-    const bool active = e < md.ne;
+    const bool active = e < item.ne;
     const unsigned N = a.nnodes;
-    const unsigned g = (unsigned)(md.eoff + (active ? e : 0)) * NP + n;
-    const ElemCoord<D> ec = item_coord<D>(md, item, active ? le : 0);
+    const unsigned g = (unsigned)(item.eoff + (active ? e : 0)) * NP + n;
+    const ElemCoord<D> ec = item_coord<D>(item, active ? le : 0);
     const int l = (D == 2) ? n / P1 : n / (P1 * P1);
-    const int iz = md.hoff + ec.c[D - 1] * P1 + l;
+    const int iz = item.hoff + ec.c[D - 1] * P1 + l;
     R Uq[NV];
     double T = 300.0, rvs = 0.0;
     if (active) {
@@ -300,15 +300,15 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
-  const bool active = e < md.ne;
+  const bool active = e < item.ne;
   const unsigned N = a.nnodes;
-  const unsigned g = (unsigned)(md.eoff + (active ? e : 0)) * NP + n;
-  const ElemCoord<D> ec = item_coord<D>(md, item, active ? le : 0);
+  const unsigned g = (unsigned)(item.eoff + (active ? e : 0)) * NP + n;
+  const ElemCoord<D> ec = item_coord<D>(item, active ? le : 0);
   int idx[3];
   idx[0] = n % P1;
   idx[1] = (n / P1) % P1;
   idx[2] = (D == 3) ? n / (P1 * P1) : 0;
-  const int iz = md.hoff + ec.c[D - 1] * P1 + idx[D - 1];
+  const int iz = item.hoff + ec.c[D - 1] * P1 + idx[D - 1];
   // 1. node pass
   R Uq[NV];
   double T = 300.0, rvs = 0.0;
@@ -322,7 +322,7 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
     for (int v = 0; v < NV; ++v) Uq[v] = R(0);
   }
   Pt<R, D, RAIN> q;
-  eval_point<R, D, RAIN>(a, Uq, T, rvs, active ? iz : md.hoff, q);
+  eval_point<R, D, RAIN>(a, Uq, T, rvs, active ? iz : item.hoff, q);
   stage_flux<R, K, D, RAIN, 0>(q, sF);
   stage_flux<R, K, D, RAIN, 1>(q, sF + NV * NT);
   if constexpr (D == 3) stage_flux<R, K, D, RAIN, 2>(q, sF + 2 * NV * NT);
@@ -346,7 +346,7 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
     const int fp = r - f * NF;
     const int J = f >> 1, side = f & 1;
     R Fs[NV];
-    if (item.e0 + fle < md.ne) {
+    if (item.e0 + fle < item.ne) {
       if (J == 0) gauss_face<R, K, D, RAIN, 0>(a, md, item, fle, side, fp, sU, sT, sRv, sL, Fs);
       else if (J == 1 || D == 2) gauss_face<R, K, D, RAIN, 1>(a, md, item, fle, side, fp, sU, sT, sRv, sL, Fs);
       else if constexpr (D == 3) gauss_face<R, K, D, RAIN, 2>(a, md, item, fle, side, fp, sU, sT, sRv, sL, Fs);
@@ -380,7 +380,7 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
 #pragma unroll
       for (int v = 0; v < NV; ++v) U0q[v] = ld(U0, N, v, g);
     }
-    double bg[4] = {a.bg_rd[iz], a.bg_rm[iz], RAIN ? a.bg_rr[iz] : 0.0, a.bg_E[iz]};
+    const Bg bg = bg_at(a, iz);
     if (MODE == 2) {
       // the new state and its split go back to the tiles: every face-pass
       // read of them ended at the barrier above

@@ -18,14 +18,14 @@ struct ElemCoord {
 // Coordinates of element e0 + le of a work item (items may run past the end of
 // an x-row; the carry moves to the next row).
 template <int D>
-__device__ __forceinline__ ElemCoord<D> item_coord(const MemberDesc& md, const Item& it, int le) {
+__device__ __forceinline__ ElemCoord<D> item_coord(const Item& item, int le) {
   ElemCoord<D> ec;
-  ec.c[0] = it.c0 + le;
-  ec.c[1] = it.c12 & 0xffff;
-  ec.c[2] = it.c12 >> 16;
-  while (ec.c[0] >= md.n[0]) {
-    ec.c[0] -= md.n[0];
-    if (++ec.c[1] >= md.n[1] && D == 3) {
+  ec.c[0] = item.c0 + le;
+  ec.c[1] = item.c12 & 0xffff;
+  ec.c[2] = item.c12 >> 16;
+  while (ec.c[0] >= item.n[0]) {
+    ec.c[0] -= item.n[0];
+    if (++ec.c[1] >= item.n[1] && D == 3) {
       ec.c[1] = 0;
       ++ec.c[2];
     }
@@ -33,8 +33,8 @@ __device__ __forceinline__ ElemCoord<D> item_coord(const MemberDesc& md, const I
   return ec;
 }
 
-__device__ __forceinline__ int elem_stride(const MemberDesc& md, int j) {
-  return j == 0 ? 1 : (j == 1 ? md.n[0] : md.n[0] * md.n[1]);
+__device__ __forceinline__ int elem_stride(const Item& item, int j) {
+  return j == 0 ? 1 : (j == 1 ? item.n[0] : item.n[0] * item.n[1]);
 }
 
 // Work items (member, first element) of EPB elements are dealt to blocks.
@@ -133,20 +133,21 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
-  const bool active = e < md.ne;
+  const bool active = e < item.ne;
   int iters = 0, bad = 0;
   if (active) {
     const unsigned N = a.nnodes;
-    const unsigned g = (unsigned)(md.eoff + e) * NP + n;
-    const ElemCoord<D> ec = item_coord<D>(md, item, le);
+    const unsigned g = (unsigned)(item.eoff + e) * NP + n;
+    const ElemCoord<D> ec = item_coord<D>(item, le);
     const int l = (D == 2) ? n / P1 : n / (P1 * P1);
-    const int iz = md.hoff + ec.c[D - 1] * P1 + l;
+    const int iz = item.hoff + ec.c[D - 1] * P1 + l;
     R Uq[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = (U + (size_t)v * N)[g];
-    const double rd = a.bg_rd[iz] + (double)Uq[V::RD];
-    const double rm = a.bg_rm[iz] + (double)Uq[V::RM];
-    const double rr = RAIN ? a.bg_rr[iz] + (double)Uq[V::RR] : 0.0;
+    const Bg bg = bg_at(a, iz);
+    const double rd = bg.rd + (double)Uq[V::RD];
+    const double rm = bg.rm + (double)Uq[V::RM];
+    const double rr = RAIN ? bg.rr + (double)Uq[V::RR] : 0.0;
     const double rho = rd + rm + rr;
     double ke = 0.0;
 #pragma unroll
@@ -154,7 +155,7 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
       const double mi = (double)Uq[V::M0 + i];
       ke += mi * mi;
     }
-    const double re = a.bg_E[iz] + (double)Uq[V::E] - 0.5 * ke / rho;
+    const double re = bg.E + (double)Uq[V::E] - 0.5 * ke / rho;
     const double guess = Tguess ? Tguess[g] : 0.0;
     const SplitOut s = split_scratch(a, rd, rm, rr, re, guess);
     iters = s.iters;
@@ -189,7 +190,7 @@ struct Nb {
 };
 
 template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void gather_nb(const MemberDesc& md, const ElemCoord<D>& ec, int e, int n,
+__device__ __forceinline__ void gather_nb(const Item& item, const ElemCoord<D>& ec, int e, int n,
                                           int ij, const R* __restrict__ U,
                                           const double* __restrict__ auxT,
                                           const double* __restrict__ auxS, unsigned N,
@@ -200,15 +201,15 @@ __device__ __forceinline__ void gather_nb(const MemberDesc& md, const ElemCoord<
   constexpr int STR = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
   const bool plus = (ij == K);
   const int c = ec.c[J];
-  const bool at_end = plus ? (c == md.n[J] - 1) : (c == 0);
-  wall = at_end && md.bc[J] == 1;
+  const bool at_end = plus ? (c == item.n[J] - 1) : (c == 0);
+  wall = at_end && item.bc[J] == 1;
   if (wall) return;
   int cn = plus ? c + 1 : c - 1;
-  if (cn < 0) cn += md.n[J];
-  if (cn >= md.n[J]) cn -= md.n[J];
-  const int en = e + (cn - c) * elem_stride(md, J);
+  if (cn < 0) cn += item.n[J];
+  if (cn >= item.n[J]) cn -= item.n[J];
+  const int en = e + (cn - c) * elem_stride(item, J);
   const int nn = plus ? n - K * STR : n + K * STR;
-  const unsigned gn = (unsigned)(md.eoff + en) * S::NP + nn;
+  const unsigned gn = (unsigned)(item.eoff + en) * S::NP + nn;
 #pragma unroll
   for (int v = 0; v < NV; ++v) nb.U[v] = (U + (size_t)v * N)[gn];
   nb.T = auxT[gn];
@@ -241,6 +242,38 @@ __device__ __forceinline__ void volume_dir(const MemberDesc& md, int ij, const R
   }
 }
 
+// The three directions of volume_dir, variable by variable: the scheduling
+// barrier keeps the compiler from issuing the LDS reads of every variable at
+// once (their results would need more registers than the kernel has).
+template <typename R, int K, int RAIN>
+__device__ __forceinline__ void volume_3d(const MemberDesc& md, const int* idx, const R* sF, R* Rv, const R* sD,
+                                          int t) {
+  using S = Shape<K, 3, block_threads<R>()>;
+  constexpr int P1 = S::P1, NV = Vars<3, RAIN>::NV, NT = S::NT;
+  R s[3], d[3][P1];
+  int base[3];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) {
+    const int str = j == 0 ? 1 : (j == 1 ? P1 : P1 * P1);
+    s[j] = (R)md.two_over_h[j];
+    base[j] = j * (NV * NT) + t - idx[j] * str;
+#pragma unroll
+    for (int b = 0; b < P1; ++b) d[j][b] = sD[idx[j] * P1 + b];
+  }
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      const int str = j == 0 ? 1 : (j == 1 ? P1 : P1 * P1);
+      R acc = R(0);
+#pragma unroll
+      for (int b = 0; b < P1; ++b) acc += d[j][b] * sF[v * NT + base[j] + b * str];
+      Rv[v] += s[j] * acc;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 template <typename R, int K, int D, int RAIN, int J>
 __device__ __forceinline__ void stage_flux(const Pt<R, D, RAIN>& q, R* sFJ) {
   using V = Vars<D, RAIN>;
@@ -253,7 +286,7 @@ __device__ __forceinline__ void stage_flux(const Pt<R, D, RAIN>& q, R* sFJ) {
 }
 
 template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void face_dir(const KArgs& a, const MemberDesc& md, int ij, int iz,
+__device__ __forceinline__ void face_dir(const KArgs& a, const Item& item, const MemberDesc& md, int ij, int iz,
                                          const R* Uq, const Pt<R, D, RAIN>& q, const Nb<R, D, RAIN>& nb,
                                          bool wall, int izn_off, R* Rv) {
   using V = Vars<D, RAIN>;
@@ -270,7 +303,7 @@ __device__ __forceinline__ void face_dir(const KArgs& a, const MemberDesc& md, i
   } else {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Un[v] = nb.U[v];
-    const int izn = (J == D - 1) ? md.hoff + izn_off : iz;
+    const int izn = (J == D - 1) ? item.hoff + izn_off : iz;
     eval_point<R, D, RAIN>(a, Un, nb.T, nb.rvs, izn, qn);
   }
   R F[NV], Fn[NV];
@@ -292,12 +325,12 @@ __device__ __forceinline__ void face_dir(const KArgs& a, const MemberDesc& md, i
   }
 }
 
-// Face work of a block as (element, direction J, side, face node) pairs, PE =
-// 2 (K+1)^(D-1) per element and direction.  The pairs of one direction are cut
-// into slot-waves of WL = min(64, NT) lanes; full wavefronts take the
-// slot-waves in turn, so every lane of a pass holds one face node (a
-// node-per-thread face loop leaves the lanes of interior nodes idle in each
-// of the D directions) and J is uniform across a wavefront.
+// Face work of a block: the epb 2 D (K+1)^(D-1) (direction, element, side, face
+// node) tasks in that order, one per lane, taken by all of the block's
+// wavefronts in turn, so a lane's direction is a run-time value.  (One
+// direction per wavefront, as before, left the remainder of every direction
+// idle and a block's last, partly filled wavefront out: with 125 threads all
+// face work ran on one wavefront.)
 template <int K, int D>
 struct FaceShape {
   static constexpr int P1 = K + 1;
@@ -305,130 +338,172 @@ struct FaceShape {
   static constexpr int NP = Shape<K, D>::NP;
 };
 
-struct SlotPlan {
-  int wl, pj, swj, sw, nfull, wave, lane;
-  __device__ __forceinline__ SlotPlan(int NT, int NP, int FN, int dim, int t) {
-    wl = NT < 64 ? NT : 64;
-    pj = (NT / NP) * 2 * FN;
-    swj = (pj + wl - 1) / wl;
-    sw = dim * swj;
-    nfull = NT / wl;
-    wave = t / wl;
-    lane = t - wave * wl;
-  }
-  // slot-wave of pass k for this thread's wavefront, or -1
-  __device__ __forceinline__ int slot_wave(int k) const {
-    if (wave >= nfull) return -1;
-    const int s = wave + k * nfull;
-    return s < sw ? __builtin_amdgcn_readfirstlane(s) : -1;
-  }
+// Per element of the block (3D): the first height index, the matching height
+// index of the vertical neighbours below and above, and per (direction, side)
+// the neighbour's first node (kWall: a slip wall, kNone: no element).  Formed
+// once per block by one thread per element and face; the nodes and the face
+// tasks read it.
+//
+// On a slip wall the neighbour of a face node is its own mirror image: the
+// task reads the own node and reverses the normal momentum.
+constexpr unsigned kWall = 0xffffffffu, kNone = 0xfffffffeu;
+template <int D>
+struct ElemTab {
+  int iz, izn[2];
+  unsigned nb[2 * D];
 };
+
+template <int K, int D>
+__device__ __forceinline__ void elem_table(const Item& item, int epb, int t, ElemTab<D>* tab) {
+  constexpr int P1 = K + 1, NP = FaceShape<K, D>::NP;
+  if (t >= epb * 2 * D) return;
+  const int le = t / (2 * D), f = t - le * (2 * D);
+  const int j = f >> 1, side = f & 1;
+  const int e = item.e0 + le;
+  if (e >= item.ne) {
+    tab[le].nb[f] = kNone;
+    return;
+  }
+  const ElemCoord<D> ec = item_coord<D>(item, le);
+  const int c = j == 0 ? ec.c[0] : (j == 1 ? ec.c[1] : ec.c[2]);
+  // (copies in scalar registers: a select of array elements would put the item
+  // into scratch memory)
+  int ns[3], bs[3];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    ns[k] = __builtin_amdgcn_readfirstlane(item.n[k]);
+    bs[k] = __builtin_amdgcn_readfirstlane(item.bc[k]);
+  }
+  const int n = j == 0 ? ns[0] : (j == 1 ? ns[1] : ns[2]);
+  const int bc = j == 0 ? bs[0] : (j == 1 ? bs[1] : bs[2]);
+  const int st = j == 0 ? 1 : (j == 1 ? ns[0] : ns[0] * ns[1]);
+  const bool at_end = side ? c == n - 1 : c == 0;
+  const int step = at_end ? (side ? 1 - n : n - 1) : (side ? 1 : -1);
+  tab[le].nb[f] = at_end && bc == 1 ? kWall : (unsigned)(item.eoff + e + step * st) * NP;
+  if (j == D - 1) tab[le].izn[side] = item.hoff + (c + step) * P1 + (side ? 0 : K);
+  if (f == 0) tab[le].iz = item.hoff + ec.c[D - 1] * P1;
+}
+
+// Physical flux in a direction chosen per lane.
+template <typename R, int D, int RAIN>
+__device__ __forceinline__ void flux_sel(const Pt<R, D, RAIN>& q, int J, R uj, R* F) {
+  using V = Vars<D, RAIN>;
+  const bool vert = J == D - 1;
+  const R fall = RAIN && vert ? q.rrvr : R(0);
+  F[V::RD] = q.rd * uj;
+  F[V::RM] = q.rm * uj;
+  if (RAIN) F[V::RR] = q.rr * uj - fall;
+#pragma unroll
+  for (int i = 0; i < D; ++i) {
+    R f = q.m[i] * uj + (i == J ? q.pp : R(0));
+    if (RAIN) f -= fall * q.u[i];
+    F[V::M0 + i] = f;
+  }
+  F[V::E] = RAIN ? q.H * uj - (vert ? q.rain_e : R(0)) : q.H * uj;
+}
 
 template <typename R, int D, int RAIN>
 struct Pair {
   Nb<R, D, RAIN> nb;
   int slot;   // block slot (le * NP + n) of the own node; -1: nothing to do
-  int side, izn;
+  int J, side, izn;
+  bool wall;
 };
 
-// Pair q of direction J: decode the own node and gather the neighbour's trace.
-// Inactive elements and wall faces get slot = -1 (the node's own thread handles
-// walls: the ghost is its own reflected point state).
-template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void pair_gather(const MemberDesc& md, const Item& item, int q, int pj,
-                                            const R* __restrict__ U, const double* __restrict__ auxT,
-                                            const double* __restrict__ auxS, unsigned N,
-                                            Pair<R, D, RAIN>& pr) {
-  using FS = FaceShape<K, D>;
-  using V = Vars<D, RAIN>;
-  constexpr int P1 = FS::P1, FN = FS::FN, NP = FS::NP, NV = V::NV;
-  constexpr int STR = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
-  pr.slot = -1;
-  pr.side = 0;
-  pr.izn = 0;
-  if (q >= pj) return;
-  const int le = q / (2 * FN);
-  const int r = q - le * (2 * FN);
-  const int side = r / FN;
-  const int f = r - side * FN;
-  const int e = item.e0 + le;
-  if (e >= md.ne) return;
-  // own node: index K*side along J, the face node f over the other axes
-  const int fa = f % P1, fb = f / P1;
-  int n;
-  if (J == 0) n = side * K + P1 * fa + P1 * P1 * fb;
-  else if (J == 1) n = fa + P1 * side * K + P1 * P1 * fb;
-  else n = fa + P1 * fb + P1 * P1 * side * K;
-  const ElemCoord<D> ec = item_coord<D>(md, item, le);
-  const int c = ec.c[J];
-  const bool at_end = side ? (c == md.n[J] - 1) : (c == 0);
-  if (at_end && md.bc[J] == 1) return;
-  int cn = side ? c + 1 : c - 1;
-  if (cn < 0) cn += md.n[J];
-  if (cn >= md.n[J]) cn -= md.n[J];
-  const int en = e + (cn - c) * elem_stride(md, J);
-  const int nn = side ? n - K * STR : n + K * STR;
-  const unsigned gn = (unsigned)(md.eoff + en) * NP + nn;
-#pragma unroll
-  for (int v = 0; v < NV; ++v) pr.nb.U[v] = ld(U, N, v, gn);
-  pr.nb.T = ld(auxT, N, 0, gn);
-  pr.nb.rvs = ld(auxS, N, 0, gn);
-  const int lz = (D == 2) ? (J == 0 ? fa : side * K) : (J == 2 ? side * K : fb);
-  pr.izn = md.hoff + ((J == D - 1) ? cn * P1 + (side ? 0 : K) : ec.c[D - 1] * P1 + lz);
-  pr.slot = le * NP + n;
-  pr.side = side;
+// own node of face node (fa, fb) of side `side` in direction J, and the step
+// to the matching node of the neighbour's element
+template <int K, int D>
+__device__ __forceinline__ int face_node(int J, int side, int fa, int fb, int& match) {
+  constexpr int P1 = K + 1;
+  const int str = J == 0 ? 1 : (D == 2 || J == 1 ? P1 : P1 * P1);
+  match = side ? -K * str : K * str;
+  return side * K * str + fa * (J == 0 ? P1 : 1) + (D == 3 ? fb * (J == 2 ? P1 : P1 * P1) : 0);
 }
 
-template <typename R, int K, int D, int RAIN>
-__device__ __forceinline__ void pair_gather_rt(int J, const MemberDesc& md, const Item& item, int q, int pj,
-                                               const R* __restrict__ U, const double* __restrict__ auxT,
-                                               const double* __restrict__ auxS, unsigned N,
-                                               Pair<R, D, RAIN>& pr) {
-  if (J == 0) pair_gather<R, K, D, RAIN, 0>(md, item, q, pj, U, auxT, auxS, N, pr);
-  else if (D == 2 || J == 1) pair_gather<R, K, D, RAIN, 1>(md, item, q, pj, U, auxT, auxS, N, pr);
-  else pair_gather<R, K, D, RAIN, (D == 3 ? 2 : 1)>(md, item, q, pj, U, auxT, auxS, N, pr);
+template <typename R, int D, int RAIN>
+__device__ __forceinline__ void pair_load(const R* __restrict__ U, const double* __restrict__ auxT,
+                                          const double* __restrict__ auxS, unsigned N, unsigned gn,
+                                          Pair<R, D, RAIN>& pr) {
+#pragma unroll
+  for (int v = 0; v < Vars<D, RAIN>::NV; ++v) pr.nb.U[v] = ld(U, N, v, gn);
+  pr.nb.T = ld(auxT, N, 0, gn);
+  pr.nb.rvs = ld(auxS, N, 0, gn);
+}
+
+// 3D task q (direction, element, side, face node): the own node, and the
+// neighbour's trace.  g0: the block's first node.
+template <typename R, int K, int RAIN>
+__device__ __forceinline__ void pair_gather(const ElemTab<3>* tab, unsigned g0, int q, int pj, const R* __restrict__ U,
+                                            const double* __restrict__ auxT, const double* __restrict__ auxS,
+                                            unsigned N, Pair<R, 3, RAIN>& pr) {
+  using FS = FaceShape<K, 3>;
+  constexpr int P1 = FS::P1, FN = FS::FN, NP = FS::NP;
+  pr.slot = -1;
+  if (q >= 3 * pj) return;
+  const int J = (q >= pj ? 1 : 0) + (q >= 2 * pj ? 1 : 0);
+  const int rq = q - J * pj;
+  const int le = rq / (2 * FN);
+  const int r = rq - le * (2 * FN);
+  const int side = r >= FN ? 1 : 0;
+  const int f = r - side * FN;
+  const unsigned nb = tab[le].nb[2 * J + side];
+  if (nb == kNone) return;
+  const int fb = f / P1, fa = f - fb * P1;
+  int match;
+  const int n = face_node<K, 3>(J, side, fa, fb, match);
+  pr.wall = nb == kWall;
+  pr.slot = le * NP + n;
+  pr.J = J;
+  pr.side = side;
+  pair_load<R, 3, RAIN>(U, auxT, auxS, N, pr.wall ? g0 + (unsigned)pr.slot : nb + (unsigned)(n + match), pr);
+  pr.izn = J == 2 ? (pr.wall ? tab[le].iz + side * K : tab[le].izn[side]) : tab[le].iz + fb;
+}
+
+// The neighbour's side of a pair: its normal flux Fn and wave speed; on a wall
+// the mirrored state.
+template <typename R, int D, int RAIN>
+__device__ __forceinline__ void pair_eval(const KArgs& a, Pair<R, D, RAIN>& pr, R* Fn, R& ln) {
+  using V = Vars<D, RAIN>;
+  const int J = pr.J;
+#pragma unroll
+  for (int i = 0; i < D; ++i) pr.nb.U[V::M0 + i] = pr.wall && i == J ? -pr.nb.U[V::M0 + i] : pr.nb.U[V::M0 + i];
+  Pt<R, D, RAIN> qn;
+  eval_point<R, D, RAIN>(a, pr.nb.U, pr.nb.T, pr.nb.rvs, pr.izn, qn);
+  const R uj = J == 0 ? qn.u[0] : (D == 3 && J == 1 ? qn.u[1] : qn.u[D - 1]);
+  flux_sel<R, D, RAIN>(qn, J, uj, Fn);
+  ln = fabs(uj) + qn.cm;
+  if (RAIN) ln += J == D - 1 ? fabs(qn.vr) : R(0);
 }
 
 // Lax-Friedrichs flux of one pair (Section 3.2): the own trace (U, F_J,
-// lambda_J) comes from the block's LDS tiles, the neighbour's is evaluated
-// here.  The lifted correction replaces F_J at the own slot of sF:
-// +-(lift/2)(F + F_n) + (lift/2) Lambda (U_n - U), + on the minus face.
-template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void pair_flux(const KArgs& a, const MemberDesc& md, const Pair<R, D, RAIN>& pr,
-                                          R* sF, const R* sU, const R* sL) {
+// lambda_J) comes from the block's LDS tiles.  The lifted correction
+// +-(lift/2)(F + F_n) + (lift/2) Lambda (U_n - U), + on the minus face, goes to
+// out[v * stride].
+template <typename R, int K, int D, int RAIN>
+__device__ __forceinline__ void pair_flux(const MemberDesc& md, const Pair<R, D, RAIN>& pr, const R* Fn, R ln,
+                                          const R* sF, const R* sU, const R* sL, R* out, int stride) {
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
   constexpr int NT = Shape<K, D, block_threads<R>()>::NT;
-  if (pr.slot < 0) return;
-  Pt<R, D, RAIN> qn;
-  eval_point<R, D, RAIN>(a, pr.nb.U, pr.nb.T, pr.nb.rvs, pr.izn, qn);
-  R Fn[NV];
-  flux<R, D, RAIN, J>(qn, Fn);
-  const R ln = wave_speed<R, D, RAIN, J>(qn);
-  R* F = sF + J * (NV * NT) + pr.slot;
+  const int J = pr.J;
+  const R* F = sF + J * (NV * NT) + pr.slot;
   const R* Uo = sU + pr.slot;
   const R lo = sL[J * NT + pr.slot];
   // Lambda = max over the two sides, ties to the minus side
   const bool own = pr.side ? (lo >= ln) : !(ln >= lo);
   const R Lam = own ? lo : ln;
-  const R hl = R(0.5) * (pr.side ? (R)md.lift[J][1] : (R)md.lift[J][0]);
+  // (the Lobatto weights are symmetric: both sides lift alike)
+  const R lift = (R)(J == 0 ? md.lift[0][0] : (D == 3 && J == 1 ? md.lift[1][0] : md.lift[D - 1][0]));
+  const R hl = R(0.5) * lift;
   const R kf = pr.side ? -hl : hl;
   const R kj = hl * Lam;
 #pragma unroll
-  for (int v = 0; v < NV; ++v) F[v * NT] = fma(kf, F[v * NT] + Fn[v], kj * (pr.nb.U[v] - Uo[v * NT]));
-}
-
-template <typename R, int K, int D, int RAIN>
-__device__ __forceinline__ void pair_flux_rt(int J, const KArgs& a, const MemberDesc& md,
-                                             const Pair<R, D, RAIN>& pr, R* sF, const R* sU, const R* sL) {
-  if (J == 0) pair_flux<R, K, D, RAIN, 0>(a, md, pr, sF, sU, sL);
-  else if (D == 2 || J == 1) pair_flux<R, K, D, RAIN, 1>(a, md, pr, sF, sU, sL);
-  else pair_flux<R, K, D, RAIN, (D == 3 ? 2 : 1)>(a, md, pr, sF, sU, sL);
+  for (int v = 0; v < NV; ++v) out[v * stride] = fma(kf, F[v * NT] + Fn[v], kj * (pr.nb.U[v] - Uo[v * NT]));
 }
 
 // Stage update and the split epilogue shared by both face schemes.
 template <typename R, int D, int RAIN, int MODE>
-__device__ __forceinline__ void stage_epilogue(const KArgs& a, const double* bg, int iz, unsigned g, unsigned N,
+__device__ __forceinline__ void stage_epilogue(const KArgs& a, const Bg& bg, int iz, unsigned g, unsigned N,
                                                const R* Uq, const R* U0q, const R* Rv, double T, double rvs,
                                                R* __restrict__ out, double dtm, double c0, double c1,
                                                double c2, double* __restrict__ oT,
@@ -464,8 +539,8 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const double* bg,
     double m[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) m[i] = (double)Un[V::M0 + i];
-    sip_alpha_terms<D, RAIN>(a, wq, bg[0] + (double)Un[V::RD], bg[1] + (double)Un[V::RM],
-                             RAIN ? bg[2] + (double)Un[V::RR] : 0.0, m, alpha_terms[0], alpha_terms[1]);
+    sip_alpha_terms<D, RAIN>(a, wq, bg.rd + (double)Un[V::RD], bg.rm + (double)Un[V::RM],
+                             RAIN ? bg.rr + (double)Un[V::RR] : 0.0, m, alpha_terms[0], alpha_terms[1]);
   }
   if (Unew) {
 #pragma unroll
@@ -473,17 +548,17 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const double* bg,
   }
   if (MODE == 2) {
     // split of the new state (FP64), warm-started at this node's (T, rho_vs);
-    // bg = (rho_d, rho_m, rho_r, E) of the background at this node
-    const double rd = bg[0] + (double)Un[V::RD];
-    const double rm = bg[1] + (double)Un[V::RM];
-    const double rr = RAIN ? bg[2] + (double)Un[V::RR] : 0.0;
+    // bg: the background at this node
+    const double rd = bg.rd + (double)Un[V::RD];
+    const double rm = bg.rm + (double)Un[V::RM];
+    const double rr = RAIN ? bg.rr + (double)Un[V::RR] : 0.0;
     double ke = 0.0;
 #pragma unroll
     for (int i = 0; i < D; ++i) {
       const double mi = (double)Un[V::M0 + i];
       ke += mi * mi;
     }
-    const double re = bg[3] + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
+    const double re = bg.E + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
     const SplitOut s = split_warm(a, rd, rm, rr, re, T, rvs);
     iters = s.iters;
     bad = s.bad;
@@ -495,18 +570,22 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const double* bg,
   }
 }
 
-// Right-hand side / stage of one work item with the lane-dense face pass
+// 3D right-hand side / stage of one work item with the lane-dense face pass
+// (three steps on 45 x 37 x 21 Q2, FP32: 582 -> 491 us against one direction
+// per wavefront and integer decoding of the element in every pass)
 // (K >= 2, where a node lies on at most one face per direction).  LDS tiles
 // use the compile-time stride NT of the largest block; smaller blocks use a
-// prefix of each row.
-template <typename R, int K, int D, int RAIN, int MODE>
-__device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R* sF, R* sU, R* sL,
+// prefix of each row.  The block has whole wavefronts: threads from a.epb NP
+// on own no node and take face tasks only.
+template <typename R, int K, int RAIN, int MODE>
+__device__ __forceinline__ void rhs_item_3d(const KArgs& a, int t, int it_, ElemTab<3>* tab, R* sF, R* sU, R* sL,
                                                const R* sD, const R* __restrict__ U,
                                                const double* __restrict__ auxT,
                                                const double* __restrict__ auxS, R* __restrict__ out,
                                                const R* __restrict__ U0, const double* __restrict__ dt_m,
                                                double c0, double c1, double c2, double* __restrict__ oT,
                                                double* __restrict__ oS, int flags) {
+  constexpr int D = 3;
   using S = Shape<K, D, block_threads<R>()>;
   using V = Vars<D, RAIN>;
   using FS = FaceShape<K, D>;
@@ -515,17 +594,11 @@ __device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R
   const int seen = MODE == 2 ? stats_seen(a) : 0;
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
-  const int le = t / NP, n = t - le * NP;
-  const int e = item.e0 + le;
-  const bool active = e < md.ne;
+  const int epb = a.epb;
   const unsigned N = a.nnodes;
-  const unsigned g = (unsigned)(md.eoff + (active ? e : 0)) * NP + n;
-  const ElemCoord<D> ec = item_coord<D>(md, item, active ? le : 0);
-  int idx[3];
-  idx[0] = n % P1;
-  idx[1] = (n / P1) % P1;
-  idx[2] = (D == 3) ? n / (P1 * P1) : 0;
-  const int iz = md.hoff + ec.c[D - 1] * P1 + idx[D - 1];
+  // the block's nodes are contiguous
+  const unsigned g = (unsigned)(item.eoff + item.e0) * NP + t;
+  const bool active = t < min(epb, item.ne - item.e0) * NP;
   R Uq[NV];
   double T = 300.0, rvs = 0.0;
   if (active) {
@@ -537,11 +610,22 @@ __device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = R(0);
   }
-  const SlotPlan sp((int)blockDim.x, NP, FS::FN, D, t);
-
-  Pt<R, D, RAIN> q;
-  eval_point<R, D, RAIN>(a, Uq, T, rvs, active ? iz : md.hoff, q);
-  {
+  elem_table<K, D>(item, epb, t, tab);
+  const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
+  const int le = t / NP, n = t - le * NP;
+  int idx[3];
+  idx[0] = n % P1;
+  idx[1] = (n / P1) % P1;
+  idx[2] = n / (P1 * P1);
+  __syncthreads();   // the table (and sD)
+  const int iz = active ? tab[le].iz + idx[D - 1] : item.hoff;
+  const int pj = epb * 2 * FS::FN;
+  R Rv[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) Rv[v] = R(0);
+  if (active) {
+    Pt<R, D, RAIN> q;
+    eval_point<R, D, RAIN>(a, Uq, T, rvs, iz, q);
     R F[NV];
     flux<R, D, RAIN, 0>(q, F);
 #pragma unroll
@@ -549,67 +633,35 @@ __device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R
     flux<R, D, RAIN, 1>(q, F);
 #pragma unroll
     for (int v = 0; v < NV; ++v) sF[(NV + v) * NT + t] = F[v];
-    if constexpr (D == 3) {
-      flux<R, D, RAIN, 2>(q, F);
+    flux<R, D, RAIN, 2>(q, F);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sF[(2 * NV + v) * NT + t] = F[v];
-    }
-  }
+    for (int v = 0; v < NV; ++v) sF[(2 * NV + v) * NT + t] = F[v];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) sU[v * NT + t] = Uq[v];
-  sL[t] = wave_speed<R, D, RAIN, 0>(q);
-  sL[NT + t] = wave_speed<R, D, RAIN, 1>(q);
-  if constexpr (D == 3) sL[2 * NT + t] = wave_speed<R, D, RAIN, 2>(q);
-  __syncthreads();
-  R U0q[NV];
-  double bg[4] = {0.0, 0.0, 0.0, 0.0};
-  const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
-  R Rv[NV];
-#pragma unroll
-  for (int v = 0; v < NV; ++v) Rv[v] = R(0);
-  bool fa[3], wl[3];
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    fa[j] = j < D && active && (idx[j] == 0 || idx[j] == K);
-    const bool at_end = (idx[j] == K) ? (ec.c[j] == md.n[j] - 1) : (ec.c[j] == 0);
-    wl[j] = fa[j] && at_end && md.bc[j] == 1;
-  }
-  // 2D: the first face pass's neighbour traces are in flight during the
-  // volume term (in 3D the registers they hold would cost a wavefront per
-  // SIMD at some orders)
-  Pair<R, D, RAIN> p0;
-  const int s0 = sp.slot_wave(0);
-  const int J0 = s0 >= 0 ? s0 / sp.swj : 0;
-  if (D == 2 && s0 >= 0)
-    pair_gather_rt<R, K, D, RAIN>(J0, md, item, (s0 - J0 * sp.swj) * sp.wl + sp.lane, sp.pj, U, auxT, auxS, N, p0);
-  if (active) {
-    volume_dir<R, K, D, RAIN, 0>(md, idx[0], sF, Rv, sD, t);
-    volume_dir<R, K, D, RAIN, 1>(md, idx[1], sF + NV * NT, Rv, sD, t);
-    if constexpr (D == 3) volume_dir<R, K, D, RAIN, 2>(md, idx[2], sF + 2 * NV * NT, Rv, sD, t);
-    // slip walls: the ghost is this node's own reflected state
-    Nb<R, D, RAIN> none;
-    if (wl[0]) face_dir<R, K, D, RAIN, 0>(a, md, idx[0], iz, Uq, q, none, true, -1, Rv);
-    if (wl[1]) face_dir<R, K, D, RAIN, 1>(a, md, idx[1], iz, Uq, q, none, true, -1, Rv);
-    if constexpr (D == 3) {
-      if (wl[2]) face_dir<R, K, D, RAIN, 2>(a, md, idx[2], iz, Uq, q, none, true, -1, Rv);
-    }
+    for (int v = 0; v < NV; ++v) sU[v * NT + t] = Uq[v];
+    sL[t] = wave_speed<R, D, RAIN, 0>(q);
+    sL[NT + t] = wave_speed<R, D, RAIN, 1>(q);
+    sL[2 * NT + t] = wave_speed<R, D, RAIN, 2>(q);
     sources<R, D, RAIN>(a, Uq, q, Rv);
   }
+  __syncthreads();
+  R U0q[NV];
+  Bg bg{};
+  if (active) {
+    volume_3d<R, K, RAIN>(md, idx, sF, Rv, sD, t);
+  }
   __syncthreads();   // the volume term has read sF
-  // face passes: in 3D the neighbour traces are gathered here, not ahead of
-  // the volume term, and every pass runs the same code, so the rounding of a
-  // face flux does not depend on the pass (the launch geometry) that
-  // computes it
-  if (D == 2 && s0 >= 0) pair_flux_rt<R, K, D, RAIN>(J0, a, md, p0, sF, sU, sL);
+  // face passes: every task runs the same code, so the rounding of a face
+  // flux does not depend on the pass (the launch geometry) that computes it
 #pragma clang loop unroll(disable)
-  for (int k = (D == 2 ? 1 : 0); s0 >= 0; ++k) {
-    const int s = sp.slot_wave(k);
-    if (s < 0) break;
-    const int J = s / sp.swj;
-    Pair<R, D, RAIN> p1;
-    pair_gather_rt<R, K, D, RAIN>(J, md, item, (s - J * sp.swj) * sp.wl + sp.lane, sp.pj, U, auxT, auxS, N,
-                                  p1);
-    pair_flux_rt<R, K, D, RAIN>(J, a, md, p1, sF, sU, sL);
+  for (int k = t; k < D * pj; k += (int)blockDim.x) {
+    Pair<R, D, RAIN> pr;
+    pair_gather<R, K, RAIN>(tab, g - (unsigned)t, k, pj, U, auxT, auxS, N, pr);
+    if (pr.slot >= 0) {
+      R Fn[NV], ln;
+      pair_eval<R, D, RAIN>(a, pr, Fn, ln);
+      // the correction replaces F_J at the own slot
+      pair_flux<R, K, D, RAIN>(md, pr, Fn, ln, sF, sU, sL, sF + pr.J * (NV * NT) + pr.slot, NT);
+    }
   }
   // operands of the stage update and the split, fetched while the faces of
   // the other wavefronts finish
@@ -618,20 +670,183 @@ __device__ __forceinline__ void rhs_item_pairs(const KArgs& a, int t, int it_, R
     for (int v = 0; v < NV; ++v) U0q[v] = ld(U0, N, v, g);
   }
   if (MODE == 2 && active) {
-    bg[0] = a.bg_rd[iz];
-    bg[1] = a.bg_rm[iz];
-    if (RAIN) bg[2] = a.bg_rr[iz];
-    bg[3] = a.bg_E[iz];
+    bg = bg_at(a, iz);
   }
   __syncthreads();
-#pragma unroll
-  for (int j = 0; j < D; ++j)
-    if (fa[j] && !wl[j]) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Rv[v] += sF[(j * NV + v) * NT + t];
-    }
   int iters = 0, bad = 0;
   if (active) {
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+      if (idx[j] == 0 || idx[j] == K) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Rv[v] += sF[(j * NV + v) * NT + t];
+      }
+    R Us[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Us[v] = sU[v * NT + t];
+    if (flags & kSip) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Rv[v] += ld((const R*)a.sip_out, N, v, g);
+    }
+    stage_epilogue<R, D, RAIN, MODE>(a, bg, iz, g, N, Us, U0q, Rv, T, rvs, out, dtm, c0, c1, c2, oT, oS, flags,
+                                     iters, bad);
+  }
+  if (MODE == 2) record_stats(a, seen, iters, bad);
+}
+
+// 2D right-hand side / stage of one work item (K >= 2).  A 2D element has
+// about as many face nodes (4 (K+1)) as nodes, so a block's face tasks are one
+// pass of its threads (two for K = 2); they are numbered element by element,
+// and every load of a thread (its node, the neighbour's trace of its first
+// task, both backgrounds) is issued before any arithmetic: the state is read
+// in one round trip, and nothing waits for memory between the barriers.
+//
+// Small calls are one wavefront's chain of dependent instructions, large ones
+// are bound by VALU issue; with the self-contained work items, ten steps on
+// 16 x 16 Q2 (FP64) 405 -> 283 us, 128 x 64 Q4 (FP64) 482 -> 443 us, five of a
+// 64-member Q3 ensemble (FP32) 3.01 -> 2.83 ms.
+//
+// In FP32 the corrections have an LDS tile of their own (SEP), so the faces
+// need not wait for the volume term; in FP64 that tile would cost a quarter
+// of the resident blocks, and they replace F_J at the own slot behind one
+// more barrier.
+template <typename R, int K, int RAIN>
+struct Lds2d {
+  using S = Shape<K, 2, block_threads<R>()>;
+  static constexpr int NV = Vars<2, RAIN>::NV;
+  static constexpr bool SEP = sizeof(R) == 4;
+  static constexpr int NQ = S::EPB * 4 * S::P1;   // face tasks of the largest block
+};
+
+// Task q: element le = q / (4 P1), then direction, side, face node.
+template <typename R, int K, int RAIN>
+__device__ __forceinline__ void pair_gather_2d(const Item& item, unsigned g0, int q,
+                                               const R* __restrict__ U, const double* __restrict__ auxT,
+                                               const double* __restrict__ auxS, unsigned N, Pair<R, 2, RAIN>& pr) {
+  constexpr int P1 = K + 1, NP = P1 * P1;
+  const int le = q / (4 * P1);
+  const int r = q - le * (4 * P1);
+  const int J = r >= 2 * P1 ? 1 : 0;
+  const int side = (J ? r - 2 * P1 : r) >= P1 ? 1 : 0;
+  const int f = r - (2 * J + side) * P1;
+  const ElemCoord<2> ec = item_coord<2>(item, le);
+  const int c = J ? ec.c[1] : ec.c[0], nJ = J ? item.n[1] : item.n[0];
+  const bool at_end = side ? c == nJ - 1 : c == 0;
+  const int step = at_end ? (side ? 1 - nJ : nJ - 1) : (side ? 1 : -1);
+  int match;
+  const int n = face_node<K, 2>(J, side, f, 0, match);
+  pr.wall = at_end && (J ? item.bc[1] : item.bc[0]) == 1;
+  pr.slot = le * NP + n;
+  pr.J = J;
+  pr.side = side;
+  const int off = pr.wall ? 0 : step * (J ? item.n[0] : 1) * NP + match;
+  pair_load<R, 2, RAIN>(U, auxT, auxS, N, g0 + (unsigned)(pr.slot + off), pr);
+  const int row = J && !pr.wall ? c + step : ec.c[1];
+  pr.izn = item.hoff + row * P1 + (J ? ((side != 0) == pr.wall ? K : 0) : f);
+}
+
+template <typename R, int K, int RAIN, int MODE>
+__device__ __forceinline__ void rhs_item_2d(const KArgs& a, int t, int it_, R* sF, R* sU, R* sL, R* sC, const R* sD,
+                                            const R* __restrict__ U, const double* __restrict__ auxT,
+                                            const double* __restrict__ auxS, R* __restrict__ out,
+                                            const R* __restrict__ U0, const double* __restrict__ dt_m, double c0,
+                                            double c1, double c2, double* __restrict__ oT, double* __restrict__ oS,
+                                            int flags) {
+  constexpr int D = 2;
+  using S = Shape<K, D, block_threads<R>()>;
+  using V = Vars<D, RAIN>;
+  using L = Lds2d<R, K, RAIN>;
+  constexpr int P1 = S::P1, NP = S::NP, NV = V::NV, NT = S::NT, NQ = L::NQ;
+  const int seen = MODE == 2 ? stats_seen(a) : 0;
+  const Item item = a.items[it_];
+  const MemberDesc& md = a.mem[item.member];
+  const unsigned N = a.nnodes;
+  const int nel = min(a.epb, item.ne - item.e0);   // elements of this item
+  const unsigned g0 = (unsigned)(item.eoff + item.e0) * NP, g = g0 + (unsigned)t;
+  const bool active = t < nel * NP;
+  const int ntask = nel * 4 * P1;
+  R Uq[NV];
+  double T = 300.0, rvs = 0.0;
+  Pair<R, D, RAIN> pr;
+  const int le = t / NP, n = t - le * NP;
+  const int idx[2] = {n % P1, n / P1};
+  int iz = item.hoff;
+  if (active) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
+    T = ld(auxT, N, 0, g);
+    rvs = ld(auxS, N, 0, g);
+    iz = item.hoff + item_coord<D>(item, le).c[1] * P1 + idx[1];
+  } else {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Uq[v] = R(0);
+  }
+  const bool task = t < ntask;
+  if (task) pair_gather_2d<R, K, RAIN>(item, g0, t, U, auxT, auxS, N, pr);
+  const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
+  R Rv[NV];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) Rv[v] = R(0);
+  if (active) {
+    Pt<R, D, RAIN> q;
+    eval_point<R, D, RAIN>(a, Uq, T, rvs, iz, q);
+    R F[NV];
+    flux<R, D, RAIN, 0>(q, F);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) sF[v * NT + t] = F[v];
+    flux<R, D, RAIN, 1>(q, F);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) sF[(NV + v) * NT + t] = F[v];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) sU[v * NT + t] = Uq[v];
+    sL[t] = wave_speed<R, D, RAIN, 0>(q);
+    sL[NT + t] = wave_speed<R, D, RAIN, 1>(q);
+    sources<R, D, RAIN>(a, Uq, q, Rv);
+  }
+  R Fn[NV], ln;
+  if (task) pair_eval<R, D, RAIN>(a, pr, Fn, ln);
+  __syncthreads();
+  auto dest = [&](int q, const Pair<R, D, RAIN>& p) { return L::SEP ? sC + q : sF + p.J * (NV * NT) + p.slot; };
+  constexpr int dst = L::SEP ? NQ : NT;
+  if (L::SEP && task) pair_flux<R, K, D, RAIN>(md, pr, Fn, ln, sF, sU, sL, dest(t, pr), dst);
+  if (active) {
+    volume_dir<R, K, D, RAIN, 0>(md, idx[0], sF, Rv, sD, t);
+    volume_dir<R, K, D, RAIN, 1>(md, idx[1], sF + NV * NT, Rv, sD, t);
+  }
+  if (!L::SEP) {
+    __syncthreads();   // the volume term has read sF
+    if (task) pair_flux<R, K, D, RAIN>(md, pr, Fn, ln, sF, sU, sL, dest(t, pr), dst);
+  }
+  // further tasks (K = 2); every task runs the same code, so the rounding of a
+  // face flux does not depend on the pass (the launch geometry)
+#pragma clang loop unroll(disable)
+  for (int k = (int)blockDim.x + t; k < ntask; k += (int)blockDim.x) {
+    pair_gather_2d<R, K, RAIN>(item, g0, k, U, auxT, auxS, N, pr);
+    pair_eval<R, D, RAIN>(a, pr, Fn, ln);
+    pair_flux<R, K, D, RAIN>(md, pr, Fn, ln, sF, sU, sL, dest(k, pr), dst);
+  }
+  // operands of the stage update and the split, fetched while the faces of
+  // the other wavefronts finish
+  R U0q[NV];
+  Bg bg{};
+  if (MODE != 0 && active && c0 != 0.0) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) U0q[v] = ld(U0, N, v, g);
+  }
+  if (MODE == 2 && active) {
+    bg = bg_at(a, iz);
+  }
+  __syncthreads();
+  int iters = 0, bad = 0;
+  if (active) {
+#pragma unroll
+    for (int j = 0; j < D; ++j)
+      if (idx[j] == 0 || idx[j] == K) {
+        const R* C = L::SEP ? sC + le * (4 * P1) + (2 * j + (idx[j] == K ? 1 : 0)) * P1 + idx[1 - j]
+                            : sF + j * (NV * NT) + t;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) Rv[v] += C[v * dst];
+      }
     R Us[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) Us[v] = sU[v * NT + t];
@@ -662,15 +877,15 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
-  const bool active = e < md.ne;
+  const bool active = e < item.ne;
   const unsigned N = a.nnodes;
-  const unsigned g = (unsigned)(md.eoff + (active ? e : 0)) * NP + n;
-  const ElemCoord<D> ec = item_coord<D>(md, item, active ? le : 0);
+  const unsigned g = (unsigned)(item.eoff + (active ? e : 0)) * NP + n;
+  const ElemCoord<D> ec = item_coord<D>(item, active ? le : 0);
   int idx[3];
   idx[0] = n % P1;
   idx[1] = (n / P1) % P1;
   idx[2] = (D == 3) ? n / (P1 * P1) : 0;
-  const int iz = md.hoff + ec.c[D - 1] * P1 + idx[D - 1];
+  const int iz = item.hoff + ec.c[D - 1] * P1 + idx[D - 1];
   R Uq[NV];
   double T = 300.0, rvs = 0.0;
   if (active) {
@@ -689,13 +904,13 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
   const bool f0 = active && (idx[0] == 0 || idx[0] == K);
   const bool f1 = active && (idx[1] == 0 || idx[1] == K);
   const bool f2 = (D == 3) && active && (idx[2] == 0 || idx[2] == K);
-  if (f0) gather_nb<R, K, D, RAIN, 0>(md, ec, e, n, idx[0], U, auxT, auxS, N, nb0, w0, z0);
-  if (f1) gather_nb<R, K, D, RAIN, 1>(md, ec, e, n, idx[1], U, auxT, auxS, N, nb1, w1, z1);
+  if (f0) gather_nb<R, K, D, RAIN, 0>(item, ec, e, n, idx[0], U, auxT, auxS, N, nb0, w0, z0);
+  if (f1) gather_nb<R, K, D, RAIN, 1>(item, ec, e, n, idx[1], U, auxT, auxS, N, nb1, w1, z1);
   if constexpr (D == 3) {
-    if (f2) gather_nb<R, K, D, RAIN, 2>(md, ec, e, n, idx[2], U, auxT, auxS, N, nb2, w2, z2);
+    if (f2) gather_nb<R, K, D, RAIN, 2>(item, ec, e, n, idx[2], U, auxT, auxS, N, nb2, w2, z2);
   }
   Pt<R, D, RAIN> q;
-  eval_point<R, D, RAIN>(a, Uq, T, rvs, active ? iz : md.hoff, q);
+  eval_point<R, D, RAIN>(a, Uq, T, rvs, active ? iz : item.hoff, q);
   R Rv[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) Rv[v] = R(0);
@@ -708,10 +923,10 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
     volume_dir<R, K, D, RAIN, 1>(md, idx[1], sF[1], Rv, sD);
     if constexpr (D == 3) volume_dir<R, K, D, RAIN, 2>(md, idx[2], sF[2], Rv, sD);
   }
-  if (f0) face_dir<R, K, D, RAIN, 0>(a, md, idx[0], iz, Uq, q, nb0, w0, z0, Rv);
-  if (f1) face_dir<R, K, D, RAIN, 1>(a, md, idx[1], iz, Uq, q, nb1, w1, z1, Rv);
+  if (f0) face_dir<R, K, D, RAIN, 0>(a, item, md, idx[0], iz, Uq, q, nb0, w0, z0, Rv);
+  if (f1) face_dir<R, K, D, RAIN, 1>(a, item, md, idx[1], iz, Uq, q, nb1, w1, z1, Rv);
   if constexpr (D == 3) {
-    if (f2) face_dir<R, K, D, RAIN, 2>(a, md, idx[2], iz, Uq, q, nb2, w2, z2, Rv);
+    if (f2) face_dir<R, K, D, RAIN, 2>(a, item, md, idx[2], iz, Uq, q, nb2, w2, z2, Rv);
   }
   int iters = 0, bad = 0;
   if (active) {
@@ -740,16 +955,17 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
       for (int v = 0; v < NV; ++v) (out + (size_t)v * N)[g] = Un[v];
       if (MODE == 2) {
         // split of the new state (FP64), warm-started at this node's (T, rho_vs)
-        const double rd = a.bg_rd[iz] + (double)Un[V::RD];
-        const double rm = a.bg_rm[iz] + (double)Un[V::RM];
-        const double rr = RAIN ? a.bg_rr[iz] + (double)Un[V::RR] : 0.0;
+        const Bg bg = bg_at(a, iz);
+        const double rd = bg.rd + (double)Un[V::RD];
+        const double rm = bg.rm + (double)Un[V::RM];
+        const double rr = RAIN ? bg.rr + (double)Un[V::RR] : 0.0;
         double ke = 0.0;
 #pragma unroll
         for (int i = 0; i < D; ++i) {
           const double mi = (double)Un[V::M0 + i];
           ke += mi * mi;
         }
-        const double re = a.bg_E[iz] + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
+        const double re = bg.E + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
         const SplitOut s = split_warm(a, rd, rm, rr, re, T, rvs);
         iters = s.iters;
         bad = s.bad;
@@ -782,13 +998,20 @@ rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   __shared__ R sD[P1 * P1];
   __shared__ R sU[PAIRS ? V::NV * S::NT : 1];
   __shared__ R sL[PAIRS ? D * S::NT : 1];
+  __shared__ ElemTab<D> tab[PAIRS && D == 3 ? S::EPB : 1];
+  __shared__ R sC[PAIRS && D == 2 && Lds2d<R, K, RAIN>::SEP ? V::NV * Lds2d<R, K, RAIN>::NQ : 1];
   if (threadIdx.x < P1 * P1) sD[threadIdx.x] = (R)a.Dhat[threadIdx.x];
   const ItemWalk walk(a.nitems, a.walk_rev);
   const int it_ = walk.item(0);
   if (it_ < 0) return;
-  if constexpr (PAIRS)
-    rhs_item_pairs<R, K, D, RAIN, MODE>(
-        a, threadIdx.x, it_, &sF[0][0], sU, sL, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
+  if constexpr (PAIRS && D == 3)
+    rhs_item_3d<R, K, RAIN, MODE>(a, threadIdx.x, it_, tab, &sF[0][0], sU, sL, sD, U, auxT, auxS, out, U0, dt_m, c0,
+                                  c1, c2, oT, oS, flags);
+  else if constexpr (PAIRS) {
+    __syncthreads();   // sD
+    rhs_item_2d<R, K, RAIN, MODE>(a, threadIdx.x, it_, &sF[0][0], sU, sL, sC, sD, U, auxT, auxS, out, U0, dt_m, c0,
+                                  c1, c2, oT, oS, flags);
+  }
   else
     rhs_item<R, K, D, RAIN, MODE>(a, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
 }
@@ -809,6 +1032,8 @@ rhs_kernel_persistent(KArgs a, const KArgs* __restrict__ a_dev, const R* __restr
   __shared__ R sD[P1 * P1];
   __shared__ R sU[PAIRS ? V::NV * S::NT : 1];
   __shared__ R sL[PAIRS ? D * S::NT : 1];
+  __shared__ ElemTab<D> tab[PAIRS && D == 3 ? S::EPB : 1];
+  __shared__ R sC[PAIRS && D == 2 && Lds2d<R, K, RAIN>::SEP ? V::NV * Lds2d<R, K, RAIN>::NQ : 1];
   if (threadIdx.x < P1 * P1) sD[threadIdx.x] = (R)a.Dhat[threadIdx.x];
   const ItemWalk walk(a.nitems);
 #pragma clang loop unroll(disable)
@@ -826,9 +1051,12 @@ rhs_kernel_persistent(KArgs a, const KArgs* __restrict__ a_dev, const R* __restr
     const KArgs DGM_AS_CONST* ap = (const KArgs DGM_AS_CONST*)apv;
     int t = threadIdx.x;
     asm volatile("" : "+v"(t));
-    if constexpr (PAIRS)
-      rhs_item_pairs<R, K, D, RAIN, MODE>(*ap, t, it_, &sF[0][0], sU, sL, sD, U, auxT, auxS, out, U0, dt_m,
-                                          c0, c1, c2, oT, oS, flags);
+    if constexpr (PAIRS && D == 3)
+      rhs_item_3d<R, K, RAIN, MODE>(*ap, t, it_, tab, &sF[0][0], sU, sL, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2,
+                                    oT, oS, flags);
+    else if constexpr (PAIRS)
+      rhs_item_2d<R, K, RAIN, MODE>(*ap, t, it_, &sF[0][0], sU, sL, sC, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2,
+                                    oT, oS, flags);
     else
       rhs_item<R, K, D, RAIN, MODE>(a, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
     __syncthreads();   // the LDS tiles are reused by the next item
@@ -855,9 +1083,9 @@ mass_kernel(KArgs a, int item0, const R* __restrict__ U, double* __restrict__ pa
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
   double md_ = 0.0, mw = 0.0, fl = 0.0;
-  if (e < md.ne) {
+  if (e < item.ne) {
     const size_t N = a.nnodes;
-    const size_t g = (size_t)(md.eoff + e) * NP + n;
+    const size_t g = (size_t)(item.eoff + e) * NP + n;
     int idx[3] = {n % P1, (n / P1) % P1, (D == 3) ? n / (P1 * P1) : 0};
     double w = md.J;
 #pragma unroll
@@ -868,22 +1096,22 @@ mass_kernel(KArgs a, int item0, const R* __restrict__ U, double* __restrict__ pa
     // layer; with Gauss nodes the thread of the lowest (highest) node of each
     // vertical line takes the trace of rho_r' along it at the floor (lid),
     // plus the background's face trace
-    if (RAIN && md.bc[D - 1] == 1) {
-      const ElemCoord<D> ec = item_coord<D>(md, item, le);
+    if (RAIN && item.bc[D - 1] == 1) {
+      const ElemCoord<D> ec = item_coord<D>(item, le);
       const int l = idx[D - 1];
       const bool bottom = ec.c[D - 1] == 0 && l == 0;
-      const bool top = ec.c[D - 1] == md.n[D - 1] - 1 && l == K;
+      const bool top = ec.c[D - 1] == item.n[D - 1] - 1 && l == K;
       if (bottom || top) {
         double rr;
         if (a.basis == 0) {
-          rr = a.bg_rr[md.hoff + ec.c[D - 1] * P1 + l] + (double)U[V::RR * N + g];
+          rr = a.bg_rr[item.hoff + ec.c[D - 1] * P1 + l] + (double)U[V::RR * N + g];
         } else {
           constexpr int ZS = (D == 2) ? P1 : P1 * P1;   // node stride along the vertical
           const double* Lt = bottom ? a.gl_m : a.gl_p;
           const size_t g0 = g - (size_t)l * ZS;
           double tr = 0.0;
           for (int m = 0; m < P1; ++m) tr += Lt[m] * (double)U[V::RR * N + g0 + (size_t)m * ZS];
-          const int row = md.hoff / P1 + ec.c[D - 1];
+          const int row = item.hoff / P1 + ec.c[D - 1];
           rr = a.bgf[2 * a.bgf_n + 2 * row + (bottom ? 0 : 1)] + tr;
         }
         double vr = a.vr_const;
@@ -936,12 +1164,12 @@ sponge_vjp_kernel(KArgs a, const R* __restrict__ W, R* __restrict__ Wp) {
     const MemberDesc& md = a.mem[item.member];
     const int le = t / NP, n = t - le * NP;
     const int e = item.e0 + le;
-    if (e >= md.ne) continue;
+    if (e >= item.ne) continue;
     const unsigned N = a.nnodes;
-    const unsigned g = (unsigned)(md.eoff + e) * NP + n;
-    const ElemCoord<D> ec = item_coord<D>(md, item, le);
+    const unsigned g = (unsigned)(item.eoff + e) * NP + n;
+    const ElemCoord<D> ec = item_coord<D>(item, le);
     const int l = (D == 2) ? n / P1 : n / (P1 * P1);
-    const R dl = (R)a.sponge[md.hoff + ec.c[D - 1] * P1 + l];
+    const R dl = (R)a.sponge[item.hoff + ec.c[D - 1] * P1 + l];
     const R keep = R(1) - dl;
     const R wd = ld(W, N, V::RD, g);
     st(Wp, N, V::RD, g, wd);

@@ -94,7 +94,7 @@ __device__ __forceinline__ void eval_tab(const KArgs& a, const R* Uq, double T, 
   using V = Vars<D, RAIN>;
   const double bm = sB[1][h];
   const double rv = fmin(rvs, bm + (double)Uq[V::RM]);
-  eval_core<R, D, RAIN>(a, Uq, T, rv, rvs, sB[0][h], bm, RAIN ? sB[2][h] : 0.0, sB[3][h], sB[4][h], q);
+  eval_core<R, D, RAIN>(a, Uq, T, rv, rvs, sB[0][h], bm, RAIN ? sB[2][h] : 0.0, sB[4][h], sB[3][h] + sB[4][h], q);
 }
 
 template <typename R, int RAIN, int MODE>
@@ -128,26 +128,26 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
   const int e = item.e0 + w;
-  if (e >= md.ne) return;                  // wave-uniform
+  if (e >= item.ne) return;                  // wave-uniform
   R(*sF)[NV][NP] = sF_all[w];
   R(*sU)[NP] = sU_all[w];
   R(*sL)[NP] = sL_all[w];
   double(*sB)[6] = sB_all[w];
 
   // element (scalar): coordinates, neighbours per (direction, side), walls
-  const ElemCoord<D> ec = item_coord<D>(md, item, w);
+  const ElemCoord<D> ec = item_coord<D>(item, w);
   int nbe[3][2];
   bool wall[3][2];
 #pragma unroll
   for (int j = 0; j < D; ++j) {
-    const int c = ec.c[j], n = md.n[j], st = elem_stride(md, j);
-    wall[j][0] = (c == 0) && md.bc[j] == 1;
-    wall[j][1] = (c == n - 1) && md.bc[j] == 1;
+    const int c = ec.c[j], n = item.n[j], st = elem_stride(item, j);
+    wall[j][0] = (c == 0) && item.bc[j] == 1;
+    wall[j][1] = (c == n - 1) && item.bc[j] == 1;
     nbe[j][0] = e + ((c == 0) ? (n - 1) * st : -st);
     nbe[j][1] = e + ((c == n - 1) ? -(n - 1) * st : st);
   }
   const unsigned N = a.nnodes;
-  const unsigned gbase = (unsigned)(md.eoff + e) * NP;   // first node of the element
+  const unsigned gbase = (unsigned)(item.eoff + e) * NP;   // first node of the element
   const unsigned g = gbase + lane;
   const int li = lane & 3, lj = (lane >> 2) & 3, ll = lane >> 4;
   // this node on a slip wall (wx, wy, wz) or on a face with a neighbour (fx, fy, fz)
@@ -156,11 +156,11 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const bool wy = (oy0 & wall[1][0]) | (oy1 & wall[1][1]);
   const bool wz = (oz0 & wall[2][0]) | (oz1 & wall[2][1]);
   const bool fx = (ox0 | ox1) & !wx, fy = (oy0 | oy1) & !wy, fz = (oz0 | oz1) & !wz;
-  const int izb = md.hoff + ec.c[2] * P1;                // first height index of the element
+  const int izb = item.hoff + ec.c[2] * P1;                // first height index of the element
   const int iz = izb + ll;
   // height index of the neighbours' face layers below and above (periodic wrap)
-  const int izn_lo = md.hoff + (ec.c[2] == 0 ? md.n[2] - 1 : ec.c[2] - 1) * P1 + K;
-  const int izn_hi = md.hoff + (ec.c[2] == md.n[2] - 1 ? 0 : ec.c[2] + 1) * P1;
+  const int izn_lo = item.hoff + (ec.c[2] == 0 ? item.n[2] - 1 : ec.c[2] - 1) * P1 + K;
+  const int izn_hi = item.hoff + (ec.c[2] == item.n[2] - 1 ? 0 : ec.c[2] + 1) * P1;
 
   // face task of pass 0 (x and y faces): direction jx/jy, side, face node
   const bool t0x = lane < 32;
@@ -172,7 +172,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const int en0 = t0x ? (t0s ? nbe[0][1] : nbe[0][0]) : (t0s ? nbe[1][1] : nbe[1][0]);
   const bool w0 = t0x ? (t0s ? wall[0][1] : wall[0][0]) : (t0s ? wall[1][1] : wall[1][0]);
   // (wall tasks read their own node: in range, unused)
-  const unsigned gn0 = w0 ? g : (unsigned)(md.eoff + en0) * NP + nn0;
+  const unsigned gn0 = w0 ? g : (unsigned)(item.eoff + en0) * NP + nn0;
   // face task of pass 1 (z faces, lanes 0..31)
   const int t1s = (lane >> 4) & 1;
   const int n1 = (lane & 15) + P1 * P1 * K * t1s;
@@ -180,7 +180,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const bool a1 = lane < 32;
   const bool w1 = t1s ? wall[2][1] : wall[2][0];
   const int en1 = t1s ? nbe[2][1] : nbe[2][0];
-  const unsigned gn1 = (!a1 || w1) ? g : (unsigned)(md.eoff + en1) * NP + nn1;
+  const unsigned gn1 = (!a1 || w1) ? g : (unsigned)(item.eoff + en1) * NP + nn1;
 
   // background table: lane 6 f + h loads field f at height h (issued with the
   // own loads, stored after the evaluation)
@@ -232,9 +232,9 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   volume_q3<R, RAIN>(md, li, lj, ll, lane, sF, Rv, sD);
   {
     Nb<R, D, RAIN> none;
-    if (wx) face_dir<R, K, D, RAIN, 0>(a, md, li, iz, Uq, q, none, true, -1, Rv);
-    if (wy) face_dir<R, K, D, RAIN, 1>(a, md, lj, iz, Uq, q, none, true, -1, Rv);
-    if (wz) face_dir<R, K, D, RAIN, 2>(a, md, ll, iz, Uq, q, none, true, -1, Rv);
+    if (wx) face_dir<R, K, D, RAIN, 0>(a, item, md, li, iz, Uq, q, none, true, -1, Rv);
+    if (wy) face_dir<R, K, D, RAIN, 1>(a, item, md, lj, iz, Uq, q, none, true, -1, Rv);
+    if (wz) face_dir<R, K, D, RAIN, 2>(a, item, md, ll, iz, Uq, q, none, true, -1, Rv);
   }
   sources<R, D, RAIN>(a, Uq, q, Rv);
   wave_lds_sync();   // the volume term has read sF before the faces overwrite it
@@ -285,16 +285,16 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   }
   // operands of the update and the split, fetched while the faces finish
   R U0q[NV];
-  double bg[4] = {0.0, 0.0, 0.0, 0.0};
+  Bg bg{};
   if (MODE != 0 && c0 != 0.0) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) U0q[v] = ld(U0, N, v, g);
   }
   if (MODE == 2) {
-    bg[0] = sB[0][ll];
-    bg[1] = sB[1][ll];
-    if (RAIN) bg[2] = sB[2][ll];
-    bg[3] = sB[3][ll];
+    bg.rd = sB[0][ll];
+    bg.rm = sB[1][ll];
+    if (RAIN) bg.rr = sB[2][ll];
+    bg.E = sB[3][ll];
   }
   wave_lds_sync();
 
@@ -334,8 +334,8 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
       at[1] += __shfl_down(at[1], h);
     }
     if (lane == 0) {
-      a.sip_aK[md.eoff + e] = md.sip_pre * sqrt(at[0]);
-      a.sip_aK[a.etot + md.eoff + e] = md.sip_pre * sqrt(at[1]);
+      a.sip_aK[item.eoff + e] = md.sip_pre * sqrt(at[0]);
+      a.sip_aK[a.etot + item.eoff + e] = md.sip_pre * sqrt(at[1]);
     }
   }
 }

@@ -42,15 +42,16 @@ sip_alpha_kernel(KArgs a, const R* __restrict__ U) {
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
   double s0 = 0.0, s1 = 0.0;
-  if (e < md.ne) {
+  if (e < item.ne) {
     const unsigned N = a.nnodes;
-    const unsigned g = (unsigned)(md.eoff + e) * NP + n;
-    const ElemCoord<D> ec = item_coord<D>(md, item, le);
+    const unsigned g = (unsigned)(item.eoff + e) * NP + n;
+    const ElemCoord<D> ec = item_coord<D>(item, le);
     const int idx[3] = {n % P1, (n / P1) % P1, D == 3 ? n / (P1 * P1) : 0};
-    const int iz = md.hoff + ec.c[D - 1] * P1 + idx[D - 1];
-    const double rd = a.bg_rd[iz] + (double)ld(U, N, V::RD, g);
-    const double rm = a.bg_rm[iz] + (double)ld(U, N, V::RM, g);
-    const double rr = RAIN ? a.bg_rr[iz] + (double)ld(U, N, V::RR, g) : 0.0;
+    const int iz = item.hoff + ec.c[D - 1] * P1 + idx[D - 1];
+    const Bg bg = bg_at(a, iz);
+    const double rd = bg.rd + (double)ld(U, N, V::RD, g);
+    const double rm = bg.rm + (double)ld(U, N, V::RM, g);
+    const double rr = RAIN ? bg.rr + (double)ld(U, N, V::RR, g) : 0.0;
     double w = md.J;
 #pragma unroll
     for (int j = 0; j < D; ++j) w *= a.w[idx[j]];
@@ -70,9 +71,9 @@ sip_alpha_kernel(KArgs a, const R* __restrict__ U) {
     }
     __syncthreads();
   }
-  if (n == 0 && e < md.ne) {
-    a.sip_aK[md.eoff + e] = md.sip_pre * sqrt(sm[0][t]);
-    a.sip_aK[a.etot + md.eoff + e] = md.sip_pre * sqrt(sm[1][t]);
+  if (n == 0 && e < item.ne) {
+    a.sip_aK[item.eoff + e] = md.sip_pre * sqrt(sm[0][t]);
+    a.sip_aK[a.etot + item.eoff + e] = md.sip_pre * sqrt(sm[1][t]);
   }
 }
 
@@ -149,9 +150,9 @@ sip_kernel(KArgs a, const R* __restrict__ U) {
   const unsigned N = a.nnodes;
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
-  const bool active = e < md.ne;
-  const unsigned g = (unsigned)(md.eoff + (active ? e : 0)) * NP + n;
-  const ElemCoord<D> ec = item_coord<D>(md, item, active ? le : 0);
+  const bool active = e < item.ne;
+  const unsigned g = (unsigned)(item.eoff + (active ? e : 0)) * NP + n;
+  const ElemCoord<D> ec = item_coord<D>(item, active ? le : 0);
   const int idx[3] = {n % P1, (n / P1) % P1, D == 3 ? n / (P1 * P1) : 0};
   // A. the state, and the viscosity at the element's corners (vertex means)
   if (active) {
@@ -162,7 +163,7 @@ sip_kernel(KArgs a, const R* __restrict__ U) {
 #pragma unroll
       for (int ax = 0; ax < D; ++ax) {
         int va = ec.c[ax] + ((n >> ax) & 1);
-        if (md.bc[ax] == 0 && va == md.n[ax]) va = 0;
+        if (item.bc[ax] == 0 && va == item.n[ax]) va = 0;
         vid += va * stride;
         stride *= md.nvx[ax];
       }
@@ -232,17 +233,17 @@ sip_kernel(KArgs a, const R* __restrict__ U) {
       const int side = r / NF;
       const int fp = r - side * NF;
       const int fe = item.e0 + fle;
-      bool live = fe < md.ne;
+      bool live = fe < item.ne;
       int en = 0;
       if (live) {
-        const ElemCoord<D> fc = item_coord<D>(md, item, fle);
+        const ElemCoord<D> fc = item_coord<D>(item, fle);
         const int c = j == 0 ? fc.c[0] : (j == 1 ? fc.c[1] : fc.c[D - 1]);
-        const bool at_end = side ? (c == md.n[j] - 1) : (c == 0);
-        live = !(at_end && md.bc[j] == 1);
+        const bool at_end = side ? (c == item.n[j] - 1) : (c == 0);
+        live = !(at_end && item.bc[j] == 1);
         int cn = side ? c + 1 : c - 1;
-        if (cn < 0) cn += md.n[j];
-        if (cn >= md.n[j]) cn -= md.n[j];
-        en = fe + (cn - c) * elem_stride(md, j);
+        if (cn < 0) cn += item.n[j];
+        if (cn >= item.n[j]) cn -= item.n[j];
+        en = fe + (cn - c) * elem_stride(item, j);
       }
       // node of the line through face point fp at position 0 along j
       // (fp enumerates the other axes, the lower one fastest)
@@ -256,7 +257,7 @@ sip_kernel(KArgs a, const R* __restrict__ U) {
       const int fo = side ? K : 0;                              // the own face node, along j
       const int l0 = fle * NP + nf0;                            // the own line (LDS index)
       const int fnb = side ? 0 : K;                             // the neighbour's, along j
-      const unsigned gn0 = (unsigned)(md.eoff + en) * NP + nf0;
+      const unsigned gn0 = (unsigned)(item.eoff + en) * NP + nf0;
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         if ((v < VH) == (half != 0)) continue;

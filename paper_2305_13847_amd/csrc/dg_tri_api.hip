@@ -205,7 +205,7 @@ extern "C" dg_status dg_tri_create(const dg_tri_mesh* m, int order, int nvars, c
   ok = ok && A(&h->stage[0], h->state_bytes) && A(&h->stage[1], h->state_bytes);
   ok = ok && A((void**)&h->aux[0], sizeof(double) * 2 * ne * h->np);
   ok = ok && A((void**)&h->aux[1], sizeof(double) * 2 * ne * h->np);
-  ok = ok && A((void**)&h->stats, sizeof(unsigned) * 8);
+  ok = ok && A((void**)&h->stats, sizeof(unsigned) * kStatsWords);
   if (!ok) {
     tri_free(h);
     delete h;
@@ -213,7 +213,7 @@ extern "C" dg_status dg_tri_create(const dg_tri_mesh* m, int order, int nvars, c
   }
   hipError_t e1 = hipMemcpy(h->xy_d, m->xy, sizeof(double) * 6 * ne, hipMemcpyHostToDevice);
   hipError_t e2 = hipMemcpy(h->nbr_d, nbr.data(), sizeof(int) * 3 * ne, hipMemcpyHostToDevice);
-  hipError_t e3 = hipMemset(h->stats, 0, sizeof(unsigned) * 8);
+  hipError_t e3 = hipMemset(h->stats, 0, sizeof(unsigned) * kStatsWords);
   hipError_t e4 = p->precision == DG_FP64 ? (order == 1 ? upload_tab<double, 1>() : order == 2 ? upload_tab<double, 2>()
                                              : order == 3 ? upload_tab<double, 3>() : upload_tab<double, 4>())
                                           : (order == 1 ? upload_tab<float, 1>() : order == 2 ? upload_tab<float, 2>()
@@ -416,10 +416,10 @@ extern "C" dg_status dg_tri_rk_step(dg_tri* h, void* C, double dt, int nsteps, h
 
 extern "C" dg_status dg_tri_get_stats(dg_tri* h, dg_stats* out) {
   if (!h || !out) return tfail(DG_EINVAL, "null pointer");
-  unsigned w[8];
+  std::vector<unsigned> w(kStatsWords);
   TRI_HIP(hipDeviceSynchronize());
-  TRI_HIP(hipMemcpy(w, h->stats, sizeof w, hipMemcpyDeviceToHost));
-  out->max_iters = (int)w[0];
+  TRI_HIP(hipMemcpy(w.data(), h->stats, sizeof(unsigned) * kStatsWords, hipMemcpyDeviceToHost));
+  out->max_iters = (int)stats_max_iters(w.data());
   out->nonconverged = w[1];
   out->nonfinite = w[2] ? 1 : 0;
   out->splits = h->splits;
@@ -431,7 +431,7 @@ extern "C" dg_status dg_tri_get_stats(dg_tri* h, dg_stats* out) {
 extern "C" dg_status dg_tri_reset_stats(dg_tri* h) {
   if (!h) return tfail(DG_EINVAL, "null handle");
   TRI_HIP(hipDeviceSynchronize());
-  TRI_HIP(hipMemset(h->stats, 0, sizeof(unsigned) * 8));
+  TRI_HIP(hipMemset(h->stats, 0, sizeof(unsigned) * kStatsWords));
   h->splits = 0;
   return DG_OK;
 }

@@ -428,7 +428,7 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
     double b[5];
     tri_bg<R, K>(t, T, g.layer, g.z0 + g.dz1 * T.rq[q] + g.dz2 * T.sq[q], b);
     Pt<R, 2, RAIN> p;
-    eval_core<R, 2, RAIN>(a, Uq, Tq, Rq, RAIN ? rho_vs(a, Tq) : 0.0, b[0], b[1], b[2], b[3], b[4], p);
+    eval_core<R, 2, RAIN>(a, Uq, Tq, Rq, RAIN ? rho_vs(a, Tq) : 0.0, b[0], b[1], b[2], b[4], b[3] + b[4], p);
     const R wq = T.w[q];
     R Fr[NV], Fs[NV], Gs[NV];
     flux_dir<R, RAIN>(p, wq * (R)(a11 * idet), wq * (R)(-a01 * idet), Fr);
@@ -513,7 +513,7 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
     const double rvsm = RAIN ? rho_vs(a, Tm) : 0.0;
     {
       Pt<R, 2, RAIN> pm;
-      eval_core<R, 2, RAIN>(a, Um, Tm, Rm, rvsm, b[0], b[1], b[2], b[3], b[4], pm);
+      eval_core<R, 2, RAIN>(a, Um, Tm, Rm, rvsm, b[0], b[1], b[2], b[4], b[3] + b[4], pm);
       flux_dir<R, RAIN>(pm, nx, nz, Fm);
       lm = speed_dir<R, RAIN>(pm, nx, nz);
     }
@@ -526,7 +526,7 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
         const R mn = Um[V::M0] * nx + Um[V::M0 + 1] * nz;
         Up[V::M0] = Um[V::M0] - R(2) * mn * nx;
         Up[V::M0 + 1] = Um[V::M0 + 1] - R(2) * mn * nz;
-        eval_core<R, 2, RAIN>(a, Up, Tm, Rm, rvsm, b[0], b[1], b[2], b[3], b[4], pp);
+        eval_core<R, 2, RAIN>(a, Up, Tm, Rm, rvsm, b[0], b[1], b[2], b[4], b[3] + b[4], pp);
       } else {
         // the neighbour's trace at its face point K - i (the same physical point)
         const int e2 = nb >> 2, f2 = nb & 3, i2 = K - i;
@@ -545,7 +545,7 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
         }
         double b2[5];
         tri_bg<R, K>(t, T, tri_z(t, e2).layer, z, b2);
-        eval_core<R, 2, RAIN>(a, Up, Tp, Rp, RAIN ? rho_vs(a, Tp) : 0.0, b2[0], b2[1], b2[2], b2[3], b2[4], pp);
+        eval_core<R, 2, RAIN>(a, Up, Tp, Rp, RAIN ? rho_vs(a, Tp) : 0.0, b2[0], b2[1], b2[2], b2[4], b2[3] + b2[4], pp);
       }
       flux_dir<R, RAIN>(pp, nx, nz, Fp);
       lp = speed_dir<R, RAIN>(pp, nx, nz);

@@ -74,9 +74,10 @@ __device__ __forceinline__ void pointwise_vjp(const KArgs& a, const R* Uq, doubl
   constexpr int NV = V::NV;
   constexpr int Z = D - 1;
   // forward recomputation (FP64)
-  const double rd = a.bg_rd[iz] + (double)Uq[V::RD];
-  const double rm = a.bg_rm[iz] + (double)Uq[V::RM];
-  const double rr = RAIN ? a.bg_rr[iz] + (double)Uq[V::RR] : 0.0;
+  const Bg bg = bg_at(a, iz);
+  const double rd = bg.rd + (double)Uq[V::RD];
+  const double rm = bg.rm + (double)Uq[V::RM];
+  const double rr = RAIN ? bg.rr + (double)Uq[V::RR] : 0.0;
   const double rho = rd + rm + rr;
   double m[D], u[D], uu = 0.0;
 #pragma unroll
@@ -85,13 +86,13 @@ __device__ __forceinline__ void pointwise_vjp(const KArgs& a, const R* Uq, doubl
     u[i] = m[i] / rho;
     uu += u[i] * u[i];
   }
-  const double E = a.bg_E[iz] + (double)Uq[V::E];
+  const double E = bg.E + (double)Uq[V::E];
   const bool sat = rvs < rm;
   const double rv = sat ? rvs : rm;
   const double rc = rm - rv;
   const double Rg = rd * a.Rd + rv * a.Rv;
   const double p = Rg * T;
-  const double pp = p - a.bg_p[iz];
+  const double pp = p - bg.p;
   const double Cv = a.cvd * rd + a.cvv * rv + a.cl * (rc + rr);
   const double gam = 1.0 + Rg / Cv;
   const double c2 = gam * p / rho;
@@ -242,7 +243,7 @@ __device__ __forceinline__ void pointwise_vjp(const KArgs& a, const R* Uq, doubl
 // at the neighbour's matching node.  For a wall the ghost's own pointwise
 // reverse pass is added to Ub with the reflected momentum.
 template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void face_vjp(const KArgs& a, const MemberDesc& md, int ij, int iz,
+__device__ __forceinline__ void face_vjp(const KArgs& a, const Item& item, const MemberDesc& md, int ij, int iz,
                                          const R* Uq, const Pt<R, D, RAIN>& q, double T, double rvs,
                                          const Nb<R, D, RAIN>& nb, const R* lam_o, const R* lam_n,
                                          bool wall, int izn_off, PwSeed<D, RAIN>& sd, double* Ub) {
@@ -270,7 +271,7 @@ __device__ __forceinline__ void face_vjp(const KArgs& a, const MemberDesc& md, i
       Fsb[v] = plus ? (-lK * (double)lam_o[v] + l0 * (double)lam_n[v])
                     : (-lK * (double)lam_n[v] + l0 * (double)lam_o[v]);
     }
-    const int izn = (J == D - 1) ? md.hoff + izn_off : iz;
+    const int izn = (J == D - 1) ? item.hoff + izn_off : iz;
     eval_point<R, D, RAIN>(a, Un, nb.T, nb.rvs, izn, qn);
   }
   const double lo = (double)wave_speed<R, D, RAIN, J>(q);
@@ -341,15 +342,15 @@ rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
-  const bool active = e < md.ne;
+  const bool active = e < item.ne;
   const unsigned N = a.nnodes;
-  const unsigned g = (unsigned)(md.eoff + (active ? e : 0)) * NP + n;
-  const ElemCoord<D> ec = item_coord<D>(md, item, active ? le : 0);
+  const unsigned g = (unsigned)(item.eoff + (active ? e : 0)) * NP + n;
+  const ElemCoord<D> ec = item_coord<D>(item, active ? le : 0);
   int idx[3];
   idx[0] = n % P1;
   idx[1] = (n / P1) % P1;
   idx[2] = (D == 3) ? n / (P1 * P1) : 0;
-  const int iz = md.hoff + ec.c[D - 1] * P1 + idx[D - 1];
+  const int iz = item.hoff + ec.c[D - 1] * P1 + idx[D - 1];
   R Uq[NV], Lq[NV];
   double T = 300.0, rvs = 0.0;
   if (active) {
@@ -399,28 +400,28 @@ rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT
     bool wall = false;
     int zoff = -1;
     R Ln[NV];
-    if (J == 0) gather_nb<R, K, D, RAIN, 0>(md, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
-    else if (J == 1) gather_nb<R, K, D, RAIN, 1>(md, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
-    else gather_nb<R, K, D, RAIN, (D == 3 ? 2 : 0)>(md, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
+    if (J == 0) gather_nb<R, K, D, RAIN, 0>(item, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
+    else if (J == 1) gather_nb<R, K, D, RAIN, 1>(item, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
+    else gather_nb<R, K, D, RAIN, (D == 3 ? 2 : 0)>(item, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
     if (!wall) {
       // the neighbour's matching node: same rule as gather_nb
       const int str = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
       const bool plus = (ij == K);
       int cn = plus ? ec.c[J] + 1 : ec.c[J] - 1;
-      if (cn < 0) cn += md.n[J];
-      if (cn >= md.n[J]) cn -= md.n[J];
-      const int en = e + (cn - ec.c[J]) * elem_stride(md, J);
+      if (cn < 0) cn += item.n[J];
+      if (cn >= item.n[J]) cn -= item.n[J];
+      const int en = e + (cn - ec.c[J]) * elem_stride(item, J);
       const int nn = plus ? n - K * str : n + K * str;
-      const unsigned gn = (unsigned)(md.eoff + en) * NP + nn;
+      const unsigned gn = (unsigned)(item.eoff + en) * NP + nn;
 #pragma unroll
       for (int v = 0; v < NV; ++v) Ln[v] = (lam + (size_t)v * N)[gn];
     } else {
 #pragma unroll
       for (int v = 0; v < NV; ++v) Ln[v] = R(0);
     }
-    if (J == 0) face_vjp<R, K, D, RAIN, 0>(a, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
-    else if (J == 1) face_vjp<R, K, D, RAIN, 1>(a, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
-    else face_vjp<R, K, D, RAIN, (D == 3 ? 2 : 0)>(a, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
+    if (J == 0) face_vjp<R, K, D, RAIN, 0>(a, item, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
+    else if (J == 1) face_vjp<R, K, D, RAIN, 1>(a, item, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
+    else face_vjp<R, K, D, RAIN, (D == 3 ? 2 : 0)>(a, item, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
   }
   // sources: dU/dt = ... + G
 #pragma unroll
@@ -457,18 +458,19 @@ split_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
   const int e = item.e0 + le;
-  if (e >= md.ne) continue;
+  if (e >= item.ne) continue;
   const unsigned N = a.nnodes;
-  const unsigned g = (unsigned)(md.eoff + e) * NP + n;
-  const ElemCoord<D> ec = item_coord<D>(md, item, le);
+  const unsigned g = (unsigned)(item.eoff + e) * NP + n;
+  const ElemCoord<D> ec = item_coord<D>(item, le);
   const int l = (D == 2) ? n / P1 : n / (P1 * P1);
-  const int iz = md.hoff + ec.c[D - 1] * P1 + l;
+  const int iz = item.hoff + ec.c[D - 1] * P1 + l;
   double Uq[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) Uq[v] = (double)(U + (size_t)v * N)[g];
-  const double rd = a.bg_rd[iz] + Uq[V::RD];
-  const double rm = a.bg_rm[iz] + Uq[V::RM];
-  const double rr = RAIN ? a.bg_rr[iz] + Uq[V::RR] : 0.0;
+  const Bg bg = bg_at(a, iz);
+  const double rd = bg.rd + Uq[V::RD];
+  const double rm = bg.rm + Uq[V::RM];
+  const double rr = RAIN ? bg.rr + Uq[V::RR] : 0.0;
   const double rho = rd + rm + rr;
   double uu = 0.0, u[D];
 #pragma unroll
