@@ -13,7 +13,6 @@
 #include <mutex>
 #include <string>
 #include <vector>
-#include <tuple>
 
 #include "dg.h"
 #include "dg_launch.h"
@@ -86,6 +85,7 @@ struct dg_handle {
   std::vector<MemberDesc> mem;
   std::vector<Item> items;
   std::vector<int> item_off;     // first item of each member (+ total)
+  std::vector<Item> bricks;      // Q3 hexahedra, Lobatto basis: the stage kernel's items
   std::vector<int> hoff;         // first background index of each member (+ total)
   std::vector<char> bg_set;
   long long etot = 0, nnodes = 0;
@@ -94,6 +94,7 @@ struct dg_handle {
   // device
   MemberDesc* mem_d = nullptr;
   Item* items_d = nullptr;
+  Item* bricks_d = nullptr;
   double* bg_d[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // rd, rm, rr, E, p
   void* stage[2] = {nullptr, nullptr};
   void* stage_x[4] = {nullptr, nullptr, nullptr, nullptr};          // adjoint workspace
@@ -344,7 +345,7 @@ static void gauss_tables(int k, double* x, double* w, double* Dhat, double* lm, 
 
 static void free_all(dg_handle* h) {
   auto F = [](void* p) { if (p) (void)hipFree(p); };
-  F(h->mem_d); F(h->items_d); F(h->ka_d);
+  F(h->mem_d); F(h->items_d); F(h->bricks_d); F(h->ka_d);
   for (auto& b : h->bg_d) F(b);
   for (auto& b : h->stage) F(b);
   for (auto& b : h->stage_x) F(b);
@@ -372,49 +373,64 @@ static dg_status validate_mesh(const dg_mesh* m, int dim) {
   return DG_OK;
 }
 
-// (Re)build the work-item table for `epb` elements per block.
+// Item at element (c0, c1, c2) of member m
+static Item make_item(const MemberDesc& md, int m, int c0, int c1, int c2) {
+  Item it{};
+  it.member = m;
+  it.e0 = c0 + md.n[0] * (c1 + md.n[1] * c2);
+  it.c0 = c0;
+  it.c12 = c1 + (c2 << 16);
+  for (int j = 0; j < 3; ++j) {
+    it.n[j] = md.n[j];
+    it.bc[j] = md.bc[j];
+  }
+  it.ne = md.ne;
+  it.eoff = (int)md.eoff;
+  it.hoff = md.hoff;
+  return it;
+}
+
+// Call f(c1, c2) for the rows of a 3D member in the order of its items, `rows`
+// element rows at a time with `per_row` items each: y-bands with z outside y
+// inside a band, so the elements above and below an item were visited at most
+// `span` items earlier and are still in the XCD's L2 when their faces are read.
+// Order 1 is plain (x, then y, then z).
+template <typename F>
+static void for_rows(const MemberDesc& md, int dim, int per_row, int rows, int order, F&& f) {
+  const int nrows = (md.n[1] + rows - 1) / rows;
+  const int span = order == 3 ? 256 : (order == 2 ? 128 : 64);
+  const int by = dim == 3 && order != 1 ? std::max(1, std::min(nrows, span / std::max(1, per_row))) : nrows;
+  for (int b = 0; b < nrows; b += by)
+    for (int c2 = 0; c2 < md.n[2]; ++c2)
+      for (int r = b; r < std::min(nrows, b + by); ++r) f(r * rows, c2);
+}
+
+// (Re)build the work-item table for `epb` elements per block (and the bricks of
+// the Q3 hexahedral stage kernel).
 // Item orders (3D members; a 2D member's items are always in element order):
-//   0: y-bands of `by` rows, z outside y inside a band (below);
+//   0: y-bands of up to 64 items per z level (for_rows);
 //   1: plain element order (x, then y, then z);
-//   2: y-bands twice as wide as in order 0.
+//   2, 3: y-bands twice and four times as wide.
 static void build_items(dg_handle* h, int epb, int order = -1) {
   if (order < 0) order = h->item_order;
   h->items.clear();
   h->item_off.clear();
+  h->bricks.clear();
+  const bool q3 = h->dim == 3 && h->order == 3 && h->P.basis == DG_BASIS_LOBATTO;
   for (int m = 0; m < h->nmembers; ++m) {
     h->item_off.push_back((int)h->items.size());
     const MemberDesc& md = h->mem[m];
-    for (int e0 = 0; e0 < md.ne; e0 += epb) {
-      Item it{};
-      it.member = m;
-      it.e0 = e0;
-      it.c0 = e0 % md.n[0];
-      const int row = e0 / md.n[0];
-      const int c1 = row % md.n[1];
-      const int c2 = row / md.n[1];
-      it.c12 = c1 + (c2 << 16);
-      for (int j = 0; j < 3; ++j) {
-        it.n[j] = md.n[j];
-        it.bc[j] = md.bc[j];
-      }
-      it.ne = md.ne;
-      it.eoff = (int)md.eoff;
-      it.hoff = md.hoff;
-      h->items.push_back(it);
-    }
-    if (h->dim == 3 && order != 1) {
-      // Walk y-bands of `by` rows with z outside y inside a band, so the
-      // elements above and below an item were visited at most ~64 items
-      // earlier and are still in the XCD's L2 when their faces are read.
-      const int per_row = (md.n[0] + epb - 1) / epb;
-      const int span = order == 3 ? 256 : (order == 2 ? 128 : 64);
-      const int by = std::max(1, std::min(md.n[1], span / std::max(1, per_row)));
-      auto key = [&](const Item& it) {
-        const int c1 = it.c12 & 0xffff, c2 = it.c12 >> 16;
-        return std::make_tuple(c1 / by, c2, c1 % by, it.c0);
-      };
-      std::stable_sort(h->items.begin() + h->item_off[m], h->items.end(),
-                       [&](const Item& x, const Item& y) { return key(x) < key(y); });
+    // the items that start in a row: items of epb elements run on over row ends
+    for_rows(md, h->dim, (md.n[0] + epb - 1) / epb, 1, order, [&](int c1, int c2) {
+      const int r0 = md.n[0] * (c1 + md.n[1] * c2);
+      for (int e0 = (r0 + epb - 1) / epb * epb; e0 < r0 + md.n[0]; e0 += epb)
+        h->items.push_back(make_item(md, m, e0 - r0, c1, c2));
+    });
+    if (q3) {
+      const int rows = q3_brick_rows(h->prec == DG_FP64);
+      for_rows(md, 3, (md.n[0] + 1) / 2, rows, order, [&](int c1, int c2) {
+        for (int c0 = 0; c0 < md.n[0]; c0 += 2) h->bricks.push_back(make_item(md, m, c0, c1, c2));
+      });
     }
   }
   h->item_off.push_back((int)h->items.size());
@@ -549,6 +565,7 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   bool ok = true;
   ok = ok && A((void**)&h->mem_d, sizeof(MemberDesc) * nmembers);
   ok = ok && A((void**)&h->items_d, sizeof(Item) * h->items_cap);
+  if (!h->bricks.empty()) ok = ok && A((void**)&h->bricks_d, sizeof(Item) * h->bricks.size());
   ok = ok && A((void**)&h->ka_d, sizeof(KArgs));
   for (auto& b : h->bg_d) ok = ok && A((void**)&b, sizeof(double) * hoff);
   ok = ok && A((void**)&h->bgt_d, sizeof(double) * kBgStride * hoff);
@@ -596,6 +613,8 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   }
   if (hipMemcpy(h->mem_d, h->mem.data(), sizeof(MemberDesc) * nmembers, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(h->items_d, h->items.data(), sizeof(Item) * h->items.size(), hipMemcpyHostToDevice) != hipSuccess ||
+      (!h->bricks.empty() && hipMemcpy(h->bricks_d, h->bricks.data(), sizeof(Item) * h->bricks.size(),
+                                       hipMemcpyHostToDevice) != hipSuccess) ||
       hipMemset(h->stats, 0, sizeof(unsigned) * kStatsWords) != hipSuccess ||
       hipMemset(h->auxT, 0, sizeof(double) * h->nnodes) != hipSuccess ||
       hipMemset(h->auxS, 0, sizeof(double) * h->nnodes) != hipSuccess) {
@@ -633,6 +652,8 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   a.items = h->items_d;
   a.nitems = (int)h->items.size();
   a.epb = h->epb;
+  a.bricks = h->bricks_d;
+  a.nbricks = (int)h->bricks.size();
   a.nmembers = nmembers;
   a.etot = h->etot;
   a.nnodes = (unsigned)h->nnodes;
@@ -1206,6 +1227,8 @@ extern "C" dg_status dg_timing_read(dg_handle* h, int kclass, double* total_ms, 
 
 static dg_status upload_items(dg_handle* h) {
   HIP_TRY(hipMemcpy(h->items_d, h->items.data(), sizeof(Item) * h->items.size(), hipMemcpyHostToDevice));
+  if (!h->bricks.empty())
+    HIP_TRY(hipMemcpy(h->bricks_d, h->bricks.data(), sizeof(Item) * h->bricks.size(), hipMemcpyHostToDevice));
   h->ka.nitems = (int)h->items.size();
   h->ka.epb = h->epb;
   HIP_TRY(hipMemcpy(h->ka_d, &h->ka, sizeof(KArgs), hipMemcpyHostToDevice));

@@ -109,6 +109,8 @@ struct KArgs {
   const Item* items;
   int nitems;
   int epb;                         // elements per work item
+  const Item* bricks;              // Q3 hexahedra: bricks (first element and its coordinates)
+  int nbricks;
   int nmembers;
   long long etot;                  // elements of all members
   unsigned nnodes;                 // nodes of all members: the stride between variables

@@ -64,6 +64,11 @@ struct ItemWalk {
   }
 };
 
+// Q3 hexahedra: rows of elements per brick (2 x rows elements per block)
+constexpr int q3_brick_rows(bool fp64) { return fp64 ? 1 : 2; }
+template <typename R>
+constexpr int q3_brick_rows() { return q3_brick_rows(sizeof(R) == 8); }
+
 __host__ __device__ inline int grid_for_items(int nitems) { return ((nitems + 7) >> 3) << 3; }
 
 // flags of a stage launch

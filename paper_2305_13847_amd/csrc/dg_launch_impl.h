@@ -100,15 +100,16 @@ hipLaunchKernelGGL((KER<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, a
     // the persistent (looping) variant only when the grid is smaller than the items
     const bool persist = (int)grid.x < grid_for_items(a.nitems);
     if (K_ == 3 && D_ == 3) {
-      // Q3 hexahedra: one wavefront per element, one work item per block
-      // whatever the persistence setting (the kernel has no item loop)
-      grid = dim3(grid_for_items(a.nitems));
-      if (mode == 0) hipLaunchKernelGGL((rhs_q3_kernel<R, R_, 0>), grid, block, 0, s, a, (const R*)U, auxT, auxS,
-                                         (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags);
-      else if (mode == 1) hipLaunchKernelGGL((rhs_q3_kernel<R, R_, 1>), grid, block, 0, s, a, (const R*)U, auxT,
-                                              auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags);
-      else hipLaunchKernelGGL((rhs_q3_kernel<R, R_, 2>), grid, block, 0, s, a, (const R*)U, auxT, auxS,
-                              (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags);
+      // Q3 hexahedra: one block per brick whatever the launch geometry of the
+      // other kernels
+      grid = dim3(grid_for_items(a.nbricks));
+#define DGM_Q3(M)                                                                                   \
+  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M>), grid, dim3(128 * q3_brick_rows<R>()), 0, s, a,        \
+                     (const R*)U, auxT, auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
+      if (mode == 0) DGM_Q3(0);
+      else if (mode == 1) DGM_Q3(1);
+      else DGM_Q3(2);
+#undef DGM_Q3
     } else if (mode != 2 || !persist) {
       // rhs_kernel takes one work item per block: the full grid
       grid = dim3(grid_for_items(a.nitems));
