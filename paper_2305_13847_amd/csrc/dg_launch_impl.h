@@ -157,7 +157,7 @@ bool LaunchAdjoint<R>::rhs_vjp(const KArgs& a, LaunchCfg lc, int K, int D, int r
     double c1, double c2, hipStream_t s) {
   return dispatch_shape(K, D, rain, [&](auto k, auto d, auto r) {
     constexpr int K_ = decltype(k)::value, D_ = decltype(d)::value, R_ = decltype(r)::value;
-    hipLaunchKernelGGL((rhs_vjp_kernel<R, K_, D_, R_>), dim3(lc.grid), dim3(lc.threads), 0, s, a, (const R*)U, auxT, auxS, (const R*)lam,
+    hipLaunchKernelGGL((rhs_vjp_kernel<R, K_, D_, R_>), dim3(grid_for_items(a.nitems)), dim3(lc.threads), 0, s, a, (const R*)U, auxT, auxS, (const R*)lam,
                        (R*)out, (const R*)X1, (const R*)X2, dt, cx1, cx2, c1, c2);
   });
 }
@@ -168,7 +168,7 @@ bool LaunchAdjoint<R>::split_vjp(const KArgs& a, LaunchCfg lc, int K, int D, int
     const double* rcb, void* out, hipStream_t s) {
   return dispatch_shape(K, D, rain, [&](auto k, auto d, auto r) {
     constexpr int K_ = decltype(k)::value, D_ = decltype(d)::value, R_ = decltype(r)::value;
-    hipLaunchKernelGGL((split_vjp_kernel<R, K_, D_, R_>), dim3(lc.grid), dim3(lc.threads), 0, s, a, (const R*)U, auxT, auxS, Tb, rvb, rcb,
+    hipLaunchKernelGGL((split_vjp_kernel<R, K_, D_, R_>), dim3(grid_for_items(a.nitems)), dim3(lc.threads), 0, s, a, (const R*)U, auxT, auxS, Tb, rvb, rcb,
                        (R*)out);
   });
 }

@@ -17,27 +17,6 @@
 
 namespace dgm {
 
-// Adjoint seeds of one node's pointwise outputs.
-template <int D, int RAIN>
-struct PwSeed {
-  double F[D][Vars<D, RAIN>::NV];   // physical fluxes per direction
-  double lam[D];                    // wave speeds |u_j| + |v_r e_z.e_j| + c_m
-  double G[Vars<D, RAIN>::NV];      // sources
-};
-
-template <int D, int RAIN>
-__device__ __forceinline__ void seed_zero(PwSeed<D, RAIN>& s) {
-  constexpr int NV = Vars<D, RAIN>::NV;
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    s.lam[j] = 0.0;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) s.F[j][v] = 0.0;
-  }
-#pragma unroll
-  for (int v = 0; v < NV; ++v) s.G[v] = 0.0;
-}
-
 // Reverse pass of the split: adjoints (Tb, rvb) of (T, rho_v) -> adjoints of
 // (rd, rm, rr, re), added to the outputs.  `sat` is the branch of the forward
 // split; T and rvs = rho_vs(T) come from it.
@@ -47,7 +26,7 @@ __device__ __forceinline__ void split_reverse(const KArgs& a, bool sat, double r
   const double Tm = T - a.Tref;
   if (!sat) {
     const double Cu = a.cvd * rd + a.cvv * rm + a.cl * rr;
-    const double t = Tb / Cu;
+    const double t = Tb * rcp64(Cu);
     reb += t;
     rmb += t * (-a.Lp - a.cvv * Tm) + rvb;
     rdb += -t * a.cvd * Tm;
@@ -56,271 +35,299 @@ __device__ __forceinline__ void split_reverse(const KArgs& a, bool sat, double r
   }
   const double dc = a.cvv - a.cl;
   const double Cv = a.cvd * rd + a.cvv * rvs + a.cl * (rm - rvs + rr);
-  const double drvs = rvs * (a.am1 + a.b / T) / T;
+  const double iT = rcp64(T);
+  const double drvs = rvs * (a.am1 + a.b * iT) * iT;
   const double fT = Cv + drvs * (dc * Tm + a.Lp);
-  const double tt = (Tb + rvb * drvs) / fT;
+  const double tt = (Tb + rvb * drvs) * rcp64(fT);
   reb += tt;
   rdb += -tt * a.cvd * Tm;
   rmb += -tt * a.cl * Tm;
   rrb += -tt * a.cl * Tm;
 }
 
-// Pointwise reverse pass of one node: seeds on (F_j, lambda_j, G) -> U_bar.
-// `Uq` is the node's stored state, (T, rvs) its forward split, iz its height.
-template <typename R, int D, int RAIN>
-__device__ __forceinline__ void pointwise_vjp(const KArgs& a, const R* Uq, double T, double rvs, int iz,
-                                              const PwSeed<D, RAIN>& sd, double* Ub) {
+// Reverse pass of one node.  The forward quantities are recomputed in FP64 and
+// the fluxes' adjoints are folded direction by direction into the node's
+// accumulators, so the seeds of one direction only are live (held for all
+// three at once, with the wall ghosts' own reverse passes, the kernel took
+// 375 registers: one wavefront per SIMD).  Bound by FP64 issue and latency at
+// two wavefronts per SIMD (185 registers; 168 would spill 27): a tendency and
+// its product on 40 x 36 x 20 Q3 (FP32) 358 -> 211 us.
+template <int D, int RAIN>
+struct Reverse {
   using V = Vars<D, RAIN>;
-  constexpr int NV = V::NV;
-  constexpr int Z = D - 1;
-  // forward recomputation (FP64)
-  const Bg bg = bg_at(a, iz);
-  const double rd = bg.rd + (double)Uq[V::RD];
-  const double rm = bg.rm + (double)Uq[V::RM];
-  const double rr = RAIN ? bg.rr + (double)Uq[V::RR] : 0.0;
-  const double rho = rd + rm + rr;
-  double m[D], u[D], uu = 0.0;
-#pragma unroll
-  for (int i = 0; i < D; ++i) {
-    m[i] = (double)Uq[V::M0 + i];
-    u[i] = m[i] / rho;
-    uu += u[i] * u[i];
-  }
-  const double E = bg.E + (double)Uq[V::E];
-  const bool sat = rvs < rm;
-  const double rv = sat ? rvs : rm;
-  const double rc = rm - rv;
-  const double Rg = rd * a.Rd + rv * a.Rv;
-  const double p = Rg * T;
-  const double pp = p - bg.p;
-  const double Cv = a.cvd * rd + a.cvv * rv + a.cl * (rc + rr);
-  const double gam = 1.0 + Rg / Cv;
-  const double c2 = gam * p / rho;
-  const double cm = sqrt(c2);
-  const double H = E + p;
-  const double Tm = T - a.Tref;
-  double vr = 0.0;
-  if (RAIN) vr = (a.vr_mode == 0) ? a.vr_const : (rr > 0.0 ? a.vr_pref * pow(rr, 0.125) : 0.0);
-  const double X = a.cl * Tm + 0.5 * uu;            // rain energy factor
-  // adjoint accumulators
-  double rdb = 0, rmb = 0, rrb = 0, rhob = 0, Eb = 0, Tb = 0, rvb = 0, ppb = 0, Hb = 0, cmb = 0, vrb = 0;
-  double mb[D], ub[D];
-#pragma unroll
-  for (int i = 0; i < D; ++i) { mb[i] = 0.0; ub[i] = 0.0; }
-  // fluxes
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    const bool vert = (j == Z);
-    const double* Fb = sd.F[j];
-    rdb += Fb[V::RD] * u[j];
-    ub[j] += Fb[V::RD] * rd;
-    rmb += Fb[V::RM] * u[j];
-    ub[j] += Fb[V::RM] * rm;
-    if (RAIN) {
-      rrb += Fb[V::RR] * (u[j] - (vert ? vr : 0.0));
-      ub[j] += Fb[V::RR] * rr;
-      if (vert) vrb -= Fb[V::RR] * rr;
-    }
+  static constexpr int NV = V::NV, Z = D - 1;
+  // forward
+  double rd, rm, rr, rho, irho, m[D], u[D], uu, E, T, Tm, rvs, rv, rc, Rg, p, pp, iCv, gam, H, c2, cm, vr, X;
+  bool sat;
+  // adjoints
+  double rdb, rmb, rrb, rhob, Eb, Tb, rvb, ppb, Hb, cmb, vrb, mb[D], ub[D];
+
+  template <typename R>
+  __device__ __forceinline__ void forward(const KArgs& a, const R* Uq, double T_, double rvs_, const Bg& bg) {
+    T = T_;
+    rvs = rvs_;
+    rd = bg.rd + (double)Uq[V::RD];
+    rm = bg.rm + (double)Uq[V::RM];
+    rr = RAIN ? bg.rr + (double)Uq[V::RR] : 0.0;
+    rho = rd + rm + rr;
+    irho = rcp64(rho);
+    uu = 0.0;
 #pragma unroll
     for (int i = 0; i < D; ++i) {
-      const double fb = Fb[V::M0 + i];
-      mb[i] += fb * u[j];
-      ub[j] += fb * m[i];
-      if (i == j) ppb += fb;
-      if (RAIN && vert) {
-        rrb -= fb * vr * u[i];
-        vrb -= fb * rr * u[i];
-        ub[i] -= fb * rr * vr;
-      }
+      m[i] = (double)Uq[V::M0 + i];
+      u[i] = m[i] * irho;
+      uu += u[i] * u[i];
     }
-    const double fe = Fb[V::E];
-    Hb += fe * u[j];
-    ub[j] += fe * H;
-    if (RAIN && vert) {
-      Tb -= fe * a.cl * rr * vr;
+    E = bg.E + (double)Uq[V::E];
+    sat = rvs < rm;
+    rv = sat ? rvs : rm;
+    rc = rm - rv;
+    Rg = rd * a.Rd + rv * a.Rv;
+    p = Rg * T;
+    pp = p - bg.p;
+    const double Cv = a.cvd * rd + a.cvv * rv + a.cl * (rc + rr);
+    iCv = rcp64(Cv);
+    gam = 1.0 + Rg * iCv;
+    c2 = gam * p * irho;
+    cm = sqrt(c2);
+    H = E + p;
+    Tm = T - a.Tref;
+    vr = 0.0;
+    if (RAIN) vr = (a.vr_mode == 0) ? a.vr_const : (rr > 0.0 ? a.vr_pref * pow(rr, 0.125) : 0.0);
+    X = a.cl * Tm + 0.5 * uu;            // rain energy factor
+    rdb = rmb = rrb = rhob = Eb = Tb = rvb = ppb = Hb = cmb = vrb = 0.0;
 #pragma unroll
-      for (int i = 0; i < D; ++i) ub[i] -= fe * u[i] * rr * vr;
-      rrb -= fe * X * vr;
-      vrb -= fe * X * rr;
+    for (int i = 0; i < D; ++i) mb[i] = ub[i] = 0.0;
+  }
+
+  // direction J: adjoints Fb of the flux without the rain's fall, Wb of the
+  // fall's part (vertical direction only) and lb of the wave speed
+  template <int J>
+  __device__ __forceinline__ void flux_reverse(const KArgs& a, const double* Fb, const double* Wb, double lb) {
+    constexpr bool vert = (J == Z);
+    rdb += Fb[V::RD] * u[J];
+    rmb += Fb[V::RM] * u[J];
+    if (RAIN) rrb += Fb[V::RR] * u[J];
+    double uJ = Fb[V::RD] * rd + Fb[V::RM] * rm + Fb[V::E] * H;
+    if (RAIN) uJ += Fb[V::RR] * rr;
+#pragma unroll
+    for (int i = 0; i < D; ++i) {
+      mb[i] += Fb[V::M0 + i] * u[J];
+      uJ += Fb[V::M0 + i] * m[i];
     }
-    // wave speed |u_j| + v_r [j vertical] + c_m
-    const double lb = sd.lam[j];
-    ub[j] += lb * (u[j] > 0.0 ? 1.0 : (u[j] < 0.0 ? -1.0 : 0.0));
-    if (RAIN && vert) vrb += lb;
+    ppb += Fb[V::M0 + J];
+    Hb += Fb[V::E] * u[J];
+    // wave speed |u_J| + v_r [J vertical] + c_m
+    uJ += lb * (u[J] > 0.0 ? 1.0 : (u[J] < 0.0 ? -1.0 : 0.0));
     cmb += lb;
-  }
-  // sources: gravity
-  {
-    const double gz = sd.G[V::M0 + Z];
-    rdb -= gz * a.g;   // rho' = rho_d' + rho_m' + rho_r'
-    rmb -= gz * a.g;
-    if (RAIN) rrb -= gz * a.g;
-    const double ge = sd.G[V::E];
-    rhob -= ge * a.g * u[Z];
-    ub[Z] -= ge * rho * a.g;
-  }
-  // Kessler
-  if (RAIN) {
-    const double Sb = sd.G[V::RM] - sd.G[V::RR];
-    const double rrp = rr > 0.0 ? rr : 0.0;
-    const double dvs = rvs - rv;                    // 0 on the saturated branch
-    double rrpb = 0.0, rcb = 0.0, dvsb = 0.0;
-    if (rrp > 0.0) {
-      const double Aev = 3.86e-3 - 9.41e-5 * Tm;
-      const double p316 = pow(rrp, 0.1875), p12 = sqrt(rrp), p78 = pow(rrp, 0.875);
-      const double Bev = 1.0 + 9.1 * p316;
-      Tb += Sb * (-9.41e-5) * Bev * dvs * p12;
-      dvsb += Sb * Aev * Bev * p12;
-      rrpb += Sb * Aev * dvs * (9.1 * 0.1875 * p316 / rrp * p12 + Bev * 0.5 / p12);
-      // accretion
-      rcb -= Sb * 1.72 * p78;
-      rrpb -= Sb * 1.72 * rc * 0.875 * p78 / rrp;
-    }
-    if (rc - a.q_au * rho > 0.0) {                    // autoconversion
-      rcb -= Sb * 1e-3;
-      rhob += Sb * 1e-3 * a.q_au;
-    }
-    if (rr > 0.0) rrb += rrpb;
-    if (!sat) {                                       // dvs = rho_vs(T) - rm
-      Tb += dvsb * rvs * (a.am1 + a.b / T) / T;
-      rmb -= dvsb;
-    }
-    rmb += rcb;
-    rvb -= rcb;
-    if (a.vr_mode != 0 && rr > 0.0) rrb += vrb * vr * 0.125 / rr;
-  }
-  // H = E + p, p' = p - p_bar
-  Eb += Hb;
-  double pb = Hb + ppb;
-  // c_m = sqrt(gamma p / rho), gamma = 1 + Rg / Cv
-  {
-    const double c2b = cmb * 0.5 / cm;
-    const double gb = c2b * p / rho;
-    pb += c2b * gam / rho;
-    rhob -= c2b * c2 / rho;
-    const double Rgb = gb / Cv;
-    const double Cvb = -gb * Rg / (Cv * Cv);
-    rdb += Rgb * a.Rd + Cvb * a.cvd;
-    rvb += Rgb * a.Rv + Cvb * (a.cvv - a.cl);
-    rmb += Cvb * a.cl;
-    rrb += Cvb * a.cl;
-  }
-  // p = (rd R_d + rv R_v) T
-  rdb += pb * a.Rd * T;
-  rvb += pb * a.Rv * T;
-  Tb += pb * Rg;
-  // u_i = m_i / rho
+    ub[J] += uJ;
+    if (RAIN && vert) {
+      // fall: -rho_r v_r (1, u, X) on rho_r, m, E
+      double s = Wb[V::RR] + Wb[V::E] * X;
+      const double f = rr * vr;
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
-    mb[i] += ub[i] / rho;
-    rhob -= ub[i] * u[i] / rho;
+      for (int i = 0; i < D; ++i) {
+        s += Wb[V::M0 + i] * u[i];
+        ub[i] -= (Wb[V::M0 + i] + Wb[V::E] * u[i]) * f;
+      }
+      rrb -= s * vr;
+      vrb += lb - s * rr;
+      Tb -= Wb[V::E] * a.cl * f;
+    }
   }
-  // split: (rd, rm, rr, re) -> (T, rv)
-  double reb = 0.0;
-  split_reverse(a, sat, rd, rm, rr, T, rvs, Tb, rvb, rdb, rmb, rrb, reb);
-  // re = E - |m|^2 / (2 rho)
-  Eb += reb;
+
+  // sources (adjoints Gb), equation of state, split; adds to Ub
+  __device__ __forceinline__ void finish(const KArgs& a, const double* Gb, double* Ub) {
+    // gravity
+    {
+      const double gz = Gb[V::M0 + Z] * a.g;
+      rdb -= gz;   // rho' = rho_d' + rho_m' + rho_r'
+      rmb -= gz;
+      if (RAIN) rrb -= gz;
+      const double ge = Gb[V::E] * a.g;
+      rhob -= ge * u[Z];
+      ub[Z] -= ge * rho;
+    }
+    // Kessler
+    if (RAIN) {
+      const double Sb = Gb[V::RM] - Gb[V::RR];
+      const double dvs = rvs - rv;                    // 0 on the saturated branch
+      double rcb = 0.0, dvsb = 0.0;
+      if (rr > 0.0) {
+        const double Aev = 3.86e-3 - 9.41e-5 * Tm;
+        double p316, p12, p78;
+        kessler_pow(rr, p316, p12, p78);
+        const double irr = rcp64(rr);
+        const double Bev = 1.0 + 9.1 * p316;
+        Tb += Sb * (-9.41e-5) * Bev * dvs * p12;
+        dvsb += Sb * Aev * Bev * p12;
+        // p12' = p12 / (2 rr), p316' = 3/16 p316 / rr, p78' = 7/8 p78 / rr
+        rrb += Sb * irr * (Aev * dvs * p12 * (9.1 * 0.1875 * p316 + 0.5 * Bev) - 1.72 * 0.875 * rc * p78);
+        rcb -= Sb * 1.72 * p78;
+      }
+      if (rc - a.q_au * rho > 0.0) {                    // autoconversion
+        rcb -= Sb * 1e-3;
+        rhob += Sb * 1e-3 * a.q_au;
+      }
+      if (!sat) {                                       // dvs = rho_vs(T) - rm
+        const double iT = rcp64(T);
+        Tb += dvsb * rvs * (a.am1 + a.b * iT) * iT;
+        rmb -= dvsb;
+      }
+      rmb += rcb;
+      rvb -= rcb;
+      if (a.vr_mode != 0 && rr > 0.0) rrb += vrb * vr * 0.125 * rcp64(rr);
+    }
+    // H = E + p, p' = p - p_bar
+    Eb += Hb;
+    double pb = Hb + ppb;
+    // c_m = sqrt(gamma p / rho), gamma = 1 + Rg / Cv
+    {
+      const double c2b = cmb * 0.5 * rcp64(cm);
+      const double gb = c2b * p * irho;
+      pb += c2b * gam * irho;
+      rhob -= c2b * c2 * irho;
+      const double Rgb = gb * iCv;
+      const double Cvb = -Rgb * Rg * iCv;
+      rdb += Rgb * a.Rd + Cvb * a.cvd;
+      rvb += Rgb * a.Rv + Cvb * (a.cvv - a.cl);
+      rmb += Cvb * a.cl;
+      rrb += Cvb * a.cl;
+    }
+    // p = (rd R_d + rv R_v) T
+    rdb += pb * a.Rd * T;
+    rvb += pb * a.Rv * T;
+    Tb += pb * Rg;
+    // u_i = m_i / rho
 #pragma unroll
-  for (int i = 0; i < D; ++i) mb[i] -= reb * u[i];
-  rhob += reb * 0.5 * uu;
-  // rho = rd + rm + rr
-  rdb += rhob;
-  rmb += rhob;
-  if (RAIN) rrb += rhob;
-  Ub[V::RD] += rdb;
-  Ub[V::RM] += rmb;
-  if (RAIN) Ub[V::RR] += rrb;
+    for (int i = 0; i < D; ++i) {
+      const double t = ub[i] * irho;
+      mb[i] += t;
+      rhob -= t * u[i];
+    }
+    // split: (rd, rm, rr, re) -> (T, rv)
+    double reb = 0.0;
+    split_reverse(a, sat, rd, rm, rr, T, rvs, Tb, rvb, rdb, rmb, rrb, reb);
+    // re = E - |m|^2 / (2 rho)
+    Eb += reb;
 #pragma unroll
-  for (int i = 0; i < D; ++i) Ub[V::M0 + i] += mb[i];
-  Ub[V::E] += Eb;
-}
+    for (int i = 0; i < D; ++i) mb[i] -= reb * u[i];
+    rhob += reb * 0.5 * uu;
+    // rho = rd + rm + rr
+    Ub[V::RD] += rdb + rhob;
+    Ub[V::RM] += rmb + rhob;
+    if (RAIN) Ub[V::RR] += rrb + rhob;
+#pragma unroll
+    for (int i = 0; i < D; ++i) Ub[V::M0 + i] += mb[i];
+    Ub[V::E] += Eb;
+  }
+};
 
 // ---------------------------------------------------------------------------
 // adjoint of the right-hand side
 // ---------------------------------------------------------------------------
-// One face of the node in direction J: accumulate the node's seeds and the
-// direct (jump-term) adjoint.  lam_o / lam_n: adjoint of dU/dt at this node and
-// at the neighbour's matching node.  For a wall the ghost's own pointwise
-// reverse pass is added to Ub with the reflected momentum.
+// What a node reads for its face in direction J: the neighbour's matching node
+// (on a wall, and for a node off the J-faces, the own one; then unused).
+template <typename R, int D, int RAIN>
+struct FaceVjp {
+  R U[Vars<D, RAIN>::NV], L[Vars<D, RAIN>::NV];
+  double T, rvs;
+  int izn;
+  bool face, wall;
+};
+
 template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void face_vjp(const KArgs& a, const Item& item, const MemberDesc& md, int ij, int iz,
-                                         const R* Uq, const Pt<R, D, RAIN>& q, double T, double rvs,
-                                         const Nb<R, D, RAIN>& nb, const R* lam_o, const R* lam_n,
-                                         bool wall, int izn_off, PwSeed<D, RAIN>& sd, double* Ub) {
+__device__ __forceinline__ void face_load(const Item& item, const ElemCoord<D>& ec, int ij, int iz, unsigned g,
+                                          unsigned N, const R* __restrict__ U, const double* __restrict__ auxT,
+                                          const double* __restrict__ auxS, const R* __restrict__ lam,
+                                          FaceVjp<R, D, RAIN>& f) {
+  using S = Shape<K, D, block_threads<R>()>;
+  constexpr int P1 = S::P1, NP = S::NP, NV = Vars<D, RAIN>::NV;
+  constexpr int STR = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
+  const bool plus = ij == K;
+  const int c = ec.c[J], n = item.n[J];
+  const bool at_end = plus ? c == n - 1 : c == 0;
+  f.face = ij == 0 || ij == K;
+  f.wall = f.face && at_end && item.bc[J] == 1;
+  const int step = at_end ? (plus ? 1 - n : n - 1) : (plus ? 1 : -1);
+  const bool nb = f.face && !f.wall;
+  const unsigned gn = nb ? g + (unsigned)(step * elem_stride(item, J) * NP + (plus ? -K * STR : K * STR)) : g;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) f.U[v] = ld(U, N, v, gn);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) f.L[v] = ld(lam, N, v, gn);
+  f.T = ld(auxT, N, 0, gn);
+  f.rvs = ld(auxS, N, 0, gn);
+  f.izn = J == D - 1 && nb ? item.hoff + (c + step) * P1 + (plus ? 0 : K) : iz;
+}
+
+// One direction: the volume term's transposed contraction, the node's face in
+// it (the adjoint of the Lax-Friedrichs flux, its jump term straight into Ub),
+// and the reverse pass of the flux.  sL: the adjoint of dU/dt in the block's
+// LDS tile (FP64), sD the weak-form matrix.
+//
+// On a slip wall the flux is (F(U) + F(g U))/2 + Lambda (U - g U)/2 with g the
+// mirror; the two fluxes differ in sign except for the normal momentum (equal)
+// and the rain's fall (equal), so the ghost needs no reverse pass of its own.
+template <typename R, int K, int D, int RAIN, int J>
+__device__ __forceinline__ void direction_vjp(const KArgs& a, const MemberDesc& md, int t, int ij, const double* sL,
+                                              const double* sD, const R* Uq, const R* Lq, R lo,
+                                              const FaceVjp<R, D, RAIN>& f, Reverse<D, RAIN>& rev, double* Ub) {
+  using S = Shape<K, D, block_threads<R>()>;
   using V = Vars<D, RAIN>;
-  constexpr int NV = V::NV;
-  const bool plus = (ij == K);     // own node on its +J face: own side is K-
-  const double lK = md.two_over_h[J] / a.w[K], l0 = md.two_over_h[J] / a.w[0];
-  double Fsb[NV];                  // adjoint of the face flux F*
-  R Un[NV];
-  Pt<R, D, RAIN> qn;
-  if (wall) {
+  constexpr int P1 = S::P1, NV = V::NV, NT = S::NT;
+  constexpr int STR = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
+  double Fb[NV], Wb[NV], lb = 0.0;
+  {
+    const int base = t - ij * STR;
+    const double s = md.two_over_h[J];
+    double d[P1];
+#pragma unroll
+    for (int b = 0; b < P1; ++b) d[b] = s * sD[b * P1 + ij];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      Un[v] = Uq[v];
-      Fsb[v] = plus ? -lK * (double)lam_o[v] : l0 * (double)lam_o[v];
+      double acc = 0.0;
+#pragma unroll
+      for (int b = 0; b < P1; ++b) acc += d[b] * sL[v * NT + base + b * STR];
+      Fb[v] = Wb[v] = acc;
     }
-    Un[V::M0 + J] = -Uq[V::M0 + J];
-    qn = q;
-    reflect<R, D, RAIN, J>(qn);
-  } else {
+  }
+  if (f.face) {
+    const bool plus = ij == K;     // own node on its +J face: own side is K-
+    const double lift = md.lift[J][0];   // (the Lobatto weights are symmetric)
+    const double sgn = plus ? 0.5 : -0.5;
+    R qnU[NV];
+    R ln = lo;
+    if (!f.wall) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) qnU[v] = f.U[v];
+      Pt<R, D, RAIN> qn;
+      eval_point<R, D, RAIN>(a, qnU, f.T, f.rvs, f.izn, qn);
+      ln = wave_speed<R, D, RAIN, J>(qn);
+    }
+    // F* = (F(U-) + F(U+)).n / 2 + Lambda (U- - U+) / 2, Lambda = max(l-, l+),
+    // ties to the minus side
+    const bool own = f.wall || (plus ? lo >= ln : lo > ln);
+    const double Lam = own ? (double)lo : (double)ln;
+    double jump = 0.0;           // Fsb . (own - neighbour)
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      Un[v] = nb.U[v];
-      // R(K-) -= lK F*, R(K+) += l0 F*
-      Fsb[v] = plus ? (-lK * (double)lam_o[v] + l0 * (double)lam_n[v])
-                    : (-lK * (double)lam_n[v] + l0 * (double)lam_o[v]);
+      const bool nrm = v == V::M0 + J;
+      // adjoint of F*: R(K-) -= lift F*, R(K+) += lift F*
+      const double Fsb = (plus ? -lift : lift) * ((double)Lq[v] - (f.wall ? 0.0 : (double)f.L[v]));
+      const double Un = f.wall ? (nrm ? -(double)Uq[v] : (double)Uq[v]) : (double)f.U[v];
+      jump += Fsb * ((double)Uq[v] - Un);
+      Fb[v] += f.wall ? (nrm ? Fsb : 0.0) : 0.5 * Fsb;
+      Wb[v] += f.wall ? (nrm ? 0.0 : Fsb) : 0.5 * Fsb;
+      Ub[v] += (f.wall ? (nrm ? 2.0 : 0.0) : 1.0) * sgn * Lam * Fsb;
     }
-    const int izn = (J == D - 1) ? item.hoff + izn_off : iz;
-    eval_point<R, D, RAIN>(a, Un, nb.T, nb.rvs, izn, qn);
+    if (own) lb = sgn * jump;
   }
-  const double lo = (double)wave_speed<R, D, RAIN, J>(q);
-  const double ln = (double)wave_speed<R, D, RAIN, J>(qn);
-  // F* = (F(U-) + F(U+)).n / 2 + Lambda (U- - U+) / 2, Lambda = max(l-, l+),
-  // ties to the minus side
-  const bool own_sel = plus ? (lo >= ln) : (lo > ln);
-  const double Lam = own_sel ? lo : ln;
-  double jump_dot = 0.0;           // Fsb . (U- - U+)
-#pragma unroll
-  for (int v = 0; v < NV; ++v) {
-    const double d = plus ? ((double)Uq[v] - (double)Un[v]) : ((double)Un[v] - (double)Uq[v]);
-    jump_dot += Fsb[v] * d;
-  }
-  // the node's own flux and (if selected) its wave speed
-#pragma unroll
-  for (int v = 0; v < NV; ++v) sd.F[J][v] += 0.5 * Fsb[v];
-  // jump term: +Lambda/2 on U-, -Lambda/2 on U+
-  const double sgn = plus ? 0.5 : -0.5;
-#pragma unroll
-  for (int v = 0; v < NV; ++v) Ub[v] += sgn * Lam * Fsb[v];
-  if (wall) {
-    // the ghost g(U) reverses the normal momentum: the jump term's ghost part
-    // maps back through g (R = dg/dU), giving -sgn Lambda R Fsb
-    sd.lam[J] += 0.5 * jump_dot;           // Lambda = l(U) = l(g(U)) identically
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      const double rf = (v == V::M0 + J) ? -Fsb[v] : Fsb[v];
-      Ub[v] -= sgn * Lam * rf;
-    }
-    // ghost flux F(g(U)): pointwise reverse at the ghost state, reflected back
-    PwSeed<D, RAIN> gs;
-    seed_zero<D, RAIN>(gs);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) gs.F[J][v] = 0.5 * Fsb[v];
-    double Ug[NV];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Ug[v] = 0.0;
-    pointwise_vjp<R, D, RAIN>(a, Un, T, rvs, iz, gs, Ug);
-    Ug[V::M0 + J] = -Ug[V::M0 + J];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Ub[v] += Ug[v];
-  } else if (own_sel) {
-    sd.lam[J] += 0.5 * jump_dot;
-  }
+  rev.template flux_reverse<J>(a, Fb, Wb, lb);
 }
 
 template <typename R, int K, int D, int RAIN>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
                const double* __restrict__ auxS, const R* __restrict__ lam, R* __restrict__ out,
                const R* __restrict__ X1, const R* __restrict__ X2, const double* __restrict__ dt_m,
@@ -328,23 +335,20 @@ rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT
   using S = Shape<K, D, block_threads<R>()>;
   using V = Vars<D, RAIN>;
   constexpr int P1 = S::P1, NP = S::NP, NV = V::NV;
-  __shared__ R sL[NV * S::NT];
-  __shared__ R sD[P1 * P1];
-  const int NT = blockDim.x;
+  __shared__ double sL[NV * S::NT];
+  __shared__ double sD[P1 * P1];
   const int t = threadIdx.x;
-  if (t < P1 * P1) sD[t] = (R)a.Dhat[t];
-  const ItemWalk walk(a.nitems);
-  for (int kk = 0;; ++kk) {
-  const int it_ = walk.item(kk);
-  if (it_ < 0) break;
-  __syncthreads();   // sL of the previous item is no longer read
+  if (t < P1 * P1) sD[t] = (double)(R)a.Dhat[t];
+  // one work item per block (no item loop: loop-invariant values would stay
+  // live across the body)
+  const int it_ = ItemWalk(a.nitems).item(0);
+  if (it_ < 0) return;
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
-  const int e = item.e0 + le;
-  const bool active = e < item.ne;
+  const bool active = item.e0 + le < item.ne;
   const unsigned N = a.nnodes;
-  const unsigned g = (unsigned)(item.eoff + (active ? e : 0)) * NP + n;
+  const unsigned g = (unsigned)(item.eoff + item.e0) * NP + (active ? t : 0);
   const ElemCoord<D> ec = item_coord<D>(item, active ? le : 0);
   int idx[3];
   idx[0] = n % P1;
@@ -352,90 +356,50 @@ rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT
   idx[2] = (D == 3) ? n / (P1 * P1) : 0;
   const int iz = item.hoff + ec.c[D - 1] * P1 + idx[D - 1];
   R Uq[NV], Lq[NV];
-  double T = 300.0, rvs = 0.0;
-  if (active) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      Uq[v] = (U + (size_t)v * N)[g];
-      Lq[v] = (lam + (size_t)v * N)[g];
-    }
-    T = auxT[g];
-    rvs = auxS[g];
-  } else {
+  for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) { Uq[v] = R(0); Lq[v] = R(0); }
-  }
+  for (int v = 0; v < NV; ++v) Lq[v] = ld(lam, N, v, g);
+  const double T = ld(auxT, N, 0, g), rvs = ld(auxS, N, 0, g);
+  const Bg bg = bg_at(a, iz);
+  // a direction's neighbour values are in flight while the previous one is
+  // worked on
+  FaceVjp<R, D, RAIN> f;
+  face_load<R, K, D, RAIN, 0>(item, ec, idx[0], iz, g, N, U, auxT, auxS, lam, f);
 #pragma unroll
-  for (int v = 0; v < NV; ++v) sL[v * NT + t] = Lq[v];
+  for (int v = 0; v < NV; ++v) sL[v * S::NT + t] = (double)Lq[v];
   __syncthreads();
-  if (!active) continue;
+  if (!active) return;
   Pt<R, D, RAIN> q;
-  eval_point<R, D, RAIN>(a, Uq, T, rvs, iz, q);
-  PwSeed<D, RAIN> sd;
-  seed_zero<D, RAIN>(sd);
+  eval_bg<R, D, RAIN>(a, Uq, T, rvs, bg, q);
+  Reverse<D, RAIN> rev;
+  rev.forward(a, Uq, T, rvs, bg);
   double Ub[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) Ub[v] = 0.0;
-  // volume: transposed contraction, Fbar_J(own) = (2/h_J) sum_a Dhat[a][i_J] lam(node a)
-#pragma unroll
-  for (int J = 0; J < D; ++J) {
-    const int str = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
-    const int ij = idx[J];
-    const int base = t - ij * str;
-    const double s = md.two_over_h[J];
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      double acc = 0.0;
-#pragma unroll
-      for (int b = 0; b < P1; ++b) acc += (double)sD[b * P1 + ij] * (double)sL[v * NT + base + b * str];
-      sd.F[J][v] += s * acc;
-    }
+  {
+    FaceVjp<R, D, RAIN> f1;
+    face_load<R, K, D, RAIN, 1>(item, ec, idx[1], iz, g, N, U, auxT, auxS, lam, f1);
+    direction_vjp<R, K, D, RAIN, 0>(a, md, t, idx[0], sL, sD, Uq, Lq, wave_speed<R, D, RAIN, 0>(q), f, rev, Ub);
+    if constexpr (D == 3)
+      face_load<R, K, D, RAIN, 2>(item, ec, idx[2], iz, g, N, U, auxT, auxS, lam, f);
+    direction_vjp<R, K, D, RAIN, 1>(a, md, t, idx[1], sL, sD, Uq, Lq, wave_speed<R, D, RAIN, 1>(q), f1, rev, Ub);
   }
-  // faces
-#pragma unroll
-  for (int J = 0; J < D; ++J) {
-    const int ij = idx[J];
-    if (ij != 0 && ij != K) continue;
-    Nb<R, D, RAIN> nb;
-    bool wall = false;
-    int zoff = -1;
-    R Ln[NV];
-    if (J == 0) gather_nb<R, K, D, RAIN, 0>(item, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
-    else if (J == 1) gather_nb<R, K, D, RAIN, 1>(item, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
-    else gather_nb<R, K, D, RAIN, (D == 3 ? 2 : 0)>(item, ec, e, n, ij, U, auxT, auxS, N, nb, wall, zoff);
-    if (!wall) {
-      // the neighbour's matching node: same rule as gather_nb
-      const int str = (J == 0) ? 1 : (J == 1 ? P1 : P1 * P1);
-      const bool plus = (ij == K);
-      int cn = plus ? ec.c[J] + 1 : ec.c[J] - 1;
-      if (cn < 0) cn += item.n[J];
-      if (cn >= item.n[J]) cn -= item.n[J];
-      const int en = e + (cn - ec.c[J]) * elem_stride(item, J);
-      const int nn = plus ? n - K * str : n + K * str;
-      const unsigned gn = (unsigned)(item.eoff + en) * NP + nn;
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Ln[v] = (lam + (size_t)v * N)[gn];
-    } else {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) Ln[v] = R(0);
-    }
-    if (J == 0) face_vjp<R, K, D, RAIN, 0>(a, item, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
-    else if (J == 1) face_vjp<R, K, D, RAIN, 1>(a, item, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
-    else face_vjp<R, K, D, RAIN, (D == 3 ? 2 : 0)>(a, item, md, ij, iz, Uq, q, T, rvs, nb, Lq, Ln, wall, zoff, sd, Ub);
-  }
+  if constexpr (D == 3)
+    direction_vjp<R, K, D, RAIN, 2>(a, md, t, idx[2], sL, sD, Uq, Lq, wave_speed<R, D, RAIN, 2>(q), f, rev, Ub);
   // sources: dU/dt = ... + G
+  double Gb[NV];
 #pragma unroll
-  for (int v = 0; v < NV; ++v) sd.G[v] = (double)Lq[v];
-  pointwise_vjp<R, D, RAIN>(a, Uq, T, rvs, iz, sd, Ub);
+  for (int v = 0; v < NV; ++v) Gb[v] = (double)Lq[v];
+  rev.finish(a, Gb, Ub);
   // out = cx1 X1 + cx2 X2 + c1 lam + c2 dt (d rhs/dU)^T lam
   const double k2 = c2 * (dt_m ? dt_m[item.member] : 1.0);
 #pragma unroll
   for (int v = 0; v < NV; ++v) {
     double o = c1 * (double)Lq[v] + k2 * Ub[v];
-    if (X1) o += cx1 * (double)(X1 + (size_t)v * N)[g];
-    if (X2) o += cx2 * (double)(X2 + (size_t)v * N)[g];
-    (out + (size_t)v * N)[g] = (R)o;
-  }
+    if (X1) o += cx1 * (double)ld(X1, N, v, g);
+    if (X2) o += cx2 * (double)ld(X2, N, v, g);
+    st(out, N, v, g, (R)o);
   }
 }
 
@@ -471,11 +435,11 @@ split_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
   const double rd = bg.rd + Uq[V::RD];
   const double rm = bg.rm + Uq[V::RM];
   const double rr = RAIN ? bg.rr + Uq[V::RR] : 0.0;
-  const double rho = rd + rm + rr;
+  const double irho = rcp64(rd + rm + rr);
   double uu = 0.0, u[D];
 #pragma unroll
   for (int i = 0; i < D; ++i) {
-    u[i] = Uq[V::M0 + i] / rho;
+    u[i] = Uq[V::M0 + i] * irho;
     uu += u[i] * u[i];
   }
   const double T = auxT[g], rvs = auxS[g];
