@@ -815,12 +815,13 @@ static bool do_split(dg_handle* h, const void* U, const double* guess, double* o
   return Launch<float>::split(h->ka, lc, h->order, h->dim, h->rain, 0, n, U, guess, oT, o1, o2, api, s);
 }
 
+// dt: time steps of the members (null: c2 holds the only one)
 // tin / tout: the Gauss basis' trace buffers of the stage state (read) and of
 // the new state (written in mode 2)
 static bool do_rhs(dg_handle* h, int mode, const void* U, const double* aT, const double* aS, void* out,
                    const void* U0, double c0, double c1, double c2, hipStream_t s,
                    double* oT = nullptr, double* oS = nullptr, int flags = 0, int tin = 0, int tout = 1,
-                   int rev = 0) {
+                   int rev = 0, const double* dt = nullptr) {
   KTimer kt(h, DG_K_STAGE, s);
   if (mode == 2) h->splits += h->nnodes;
   const LaunchCfg lc = launch_cfg(h);
@@ -834,15 +835,15 @@ static bool do_rhs(dg_handle* h, int mode, const void* U, const double* aT, cons
   }
   if (h->P.basis == DG_BASIS_GAUSS) {
     if (h->prec == DG_FP64)
-      return Launch<double>::rhs_gauss(ka, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, h->dt_d, c0, c1,
+      return Launch<double>::rhs_gauss(ka, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, dt, c0, c1,
                                        c2, oT, oS, flags, s);
-    return Launch<float>::rhs_gauss(ka, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, h->dt_d, c0, c1, c2,
+    return Launch<float>::rhs_gauss(ka, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, dt, c0, c1, c2,
                                     oT, oS, flags, s);
   }
   if (h->prec == DG_FP64)
     return Launch<double>::rhs(ka, h->ka_d, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0,
-                               h->dt_d, c0, c1, c2, oT, oS, flags, s);
-  return Launch<float>::rhs(ka, h->ka_d, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, h->dt_d,
+                               dt, c0, c1, c2, oT, oS, flags, s);
+  return Launch<float>::rhs(ka, h->ka_d, lc, h->order, h->dim, h->rain, mode, U, aT, aS, out, U0, dt,
                             c0, c1, c2, oT, oS, flags, s);
 }
 
@@ -960,12 +961,25 @@ struct Stage { double c0, c1, c2; };
 static const Stage kSSP43[4] = {{0, 1, 0.5}, {0, 1, 0.5}, {2.0 / 3.0, 1.0 / 3.0, 1.0 / 6.0}, {0, 1, 0.5}};
 static const Stage kSSP33[3] = {{0, 1, 1}, {0.75, 0.25, 0.25}, {1.0 / 3.0, 2.0 / 3.0, 2.0 / 3.0}};
 
-static dg_status upload_dt(dg_handle* h, const double* dt, hipStream_t s) {
-  for (int m = 0; m < h->nmembers; ++m) {
+// The time step(s) of a call: one value goes to the kernels with their
+// arguments; an ensemble's, and those a captured graph reads, are uploaded.
+// (A small copy in the stream costs about 3 us between kernels: the gradient of
+// 20 steps on 64 x 32 Q3, 38 of them, 2.14 -> 2.03 ms.)
+struct Dt {
+  const double* dev = nullptr;
+  double value = 1.0;
+};
+
+static dg_status take_dt(dg_handle* h, const double* dt, hipStream_t s, bool device, Dt* out) {
+  for (int m = 0; m < h->nmembers; ++m)
     if (!std::isfinite(dt[m]) || !(dt[m] > 0)) return fail(DG_EINVAL, "dt[%d] must be positive and finite", m);
-    h->dt_h[m] = dt[m];
+  if (h->nmembers == 1 && !device) {
+    out->value = dt[0];
+    return DG_OK;
   }
+  for (int m = 0; m < h->nmembers; ++m) h->dt_h[m] = dt[m];
   HIP_TRY(hipMemcpyAsync(h->dt_d, h->dt_h, sizeof(double) * h->nmembers, hipMemcpyHostToDevice, s));
+  out->dev = h->dt_d;
   return DG_OK;
 }
 
@@ -973,7 +987,7 @@ static dg_status upload_dt(dg_handle* h, const double* dt, hipStream_t s) {
 // fused stage kernel also splits the state it writes, so the next stage reads
 // (T, rho_vs) from the ping-pong aux buffers; only the first stage of a call
 // runs the stand-alone split.  *cur is the aux buffer holding the split of U.
-static dg_status rk_one(dg_handle* h, void* U, bool first, int* cur, hipStream_t s, int step = 0) {
+static dg_status rk_one(dg_handle* h, void* U, const Dt& dt, bool first, int* cur, hipStream_t s, int step = 0) {
   void* B1 = h->stage[0];
   void* B2 = h->stage[1];
   double* aT[2] = {h->auxT, h->auxT2};
@@ -1007,7 +1021,8 @@ static dg_status rk_one(dg_handle* h, void* U, bool first, int* cur, hipStream_t
     // Only states well beyond the L2s take this order (a small state, held
     // by the L2s, ran slower in it: 2D bubble Q4 in FP64, 15.8 -> 19.3 us)
     const bool rev = ((step * ns + st) & 1) && h->state_bytes > (64ull << 20);
-    do_rhs(h, 2, in, aT[a], aS[a], outp, U, c.c0, c.c1, c.c2, s, aT[b], aS[b], flags, a, b, rev ? 1 : 0);
+    do_rhs(h, 2, in, aT[a], aS[a], outp, U, c.c0, c.c1, c.c2 * dt.value, s, aT[b], aS[b], flags, a, b, rev ? 1 : 0,
+           dt.dev);
     *cur = b;
   }
   HIP_TRY(hipGetLastError());
@@ -1019,11 +1034,12 @@ extern "C" dg_status dg_rk_step(dg_handle* h, void* U, const double* dt, int nst
   if (st != DG_OK) return st;
   if (!U || !dt) return fail(DG_EINVAL, "null pointer");
   if (nsteps < 0) return fail(DG_EINVAL, "nsteps must be >= 0");
-  st = upload_dt(h, dt, s);
+  Dt d;
+  st = take_dt(h, dt, s, false, &d);
   if (st != DG_OK) return st;
   int cur = 0;
   for (int i = 0; i < nsteps; ++i) {
-    st = rk_one(h, U, i == 0, &cur, s, i);
+    st = rk_one(h, U, d, i == 0, &cur, s, i);
     if (st != DG_OK) return st;
   }
   return DG_OK;
@@ -1159,7 +1175,8 @@ extern "C" dg_status dg_rk_step_vjp(dg_handle* h, const void* Un, const void* W,
     return fail(DG_EUNSUPPORTED, "adjoints exist for the Lobatto basis without diffusion only");
   if (!Un || !W || !Ub0 || !dt) return fail(DG_EINVAL, "null pointer");
   if (Ub0 == Un || Ub0 == W) return fail(DG_EINVAL, "U_n_bar must not alias U_n or U_np1_bar");
-  st = upload_dt(h, dt, s);
+  Dt d;
+  st = take_dt(h, dt, s, false, &d);
   if (st != DG_OK) return st;
   void* u1 = h->stage_x[0];
   void* u2 = h->stage_x[1];
@@ -1181,19 +1198,24 @@ extern "C" dg_status dg_rk_step_vjp(dg_handle* h, const void* Un, const void* W,
   // recompute the stages
   do_split(h, Un, nullptr, aT[0], aS[0], nullptr, 0, s);
   if (h->rk == DG_SSPRK43) {
-    do_rhs(h, 2, Un, aT[0], aS[0], u1, Un, kSSP43[0].c0, kSSP43[0].c1, kSSP43[0].c2, s, aT[1], aS[1], 0);
-    do_rhs(h, 2, u1, aT[1], aS[1], u2, Un, kSSP43[1].c0, kSSP43[1].c1, kSSP43[1].c2, s, aT[2], aS[2], 0);
-    do_rhs(h, 2, u2, aT[2], aS[2], u3, Un, kSSP43[2].c0, kSSP43[2].c1, kSSP43[2].c2, s, aT[3], aS[3], 0);
-    do_vjp(h, u3, aT[3], aS[3], Wt, B3, nullptr, nullptr, h->dt_d, 0, 0, 1.0, 0.5, s);
-    do_vjp(h, u2, aT[2], aS[2], B3, B2, nullptr, nullptr, h->dt_d, 0, 0, 1.0 / 3.0, 1.0 / 6.0, s);
-    do_vjp(h, u1, aT[1], aS[1], B2, B1, nullptr, nullptr, h->dt_d, 0, 0, 1.0, 0.5, s);
-    do_vjp(h, Un, aT[0], aS[0], B1, Ub0, B3, nullptr, h->dt_d, 2.0 / 3.0, 0, 1.0, 0.5, s);
+    do_rhs(h, 2, Un, aT[0], aS[0], u1, Un, kSSP43[0].c0, kSSP43[0].c1, kSSP43[0].c2 * d.value, s, aT[1], aS[1], 0, 0, 1,
+           0, d.dev);
+    do_rhs(h, 2, u1, aT[1], aS[1], u2, Un, kSSP43[1].c0, kSSP43[1].c1, kSSP43[1].c2 * d.value, s, aT[2], aS[2], 0, 0, 1,
+           0, d.dev);
+    do_rhs(h, 2, u2, aT[2], aS[2], u3, Un, kSSP43[2].c0, kSSP43[2].c1, kSSP43[2].c2 * d.value, s, aT[3], aS[3], 0, 0, 1,
+           0, d.dev);
+    do_vjp(h, u3, aT[3], aS[3], Wt, B3, nullptr, nullptr, d.dev, 0, 0, 1.0, 0.5 * d.value, s);
+    do_vjp(h, u2, aT[2], aS[2], B3, B2, nullptr, nullptr, d.dev, 0, 0, 1.0 / 3.0, 1.0 / 6.0 * d.value, s);
+    do_vjp(h, u1, aT[1], aS[1], B2, B1, nullptr, nullptr, d.dev, 0, 0, 1.0, 0.5 * d.value, s);
+    do_vjp(h, Un, aT[0], aS[0], B1, Ub0, B3, nullptr, d.dev, 2.0 / 3.0, 0, 1.0, 0.5 * d.value, s);
   } else {
-    do_rhs(h, 2, Un, aT[0], aS[0], u1, Un, kSSP33[0].c0, kSSP33[0].c1, kSSP33[0].c2, s, aT[1], aS[1], 0);
-    do_rhs(h, 2, u1, aT[1], aS[1], u2, Un, kSSP33[1].c0, kSSP33[1].c1, kSSP33[1].c2, s, aT[2], aS[2], 0);
-    do_vjp(h, u2, aT[2], aS[2], Wt, B2, nullptr, nullptr, h->dt_d, 0, 0, 2.0 / 3.0, 2.0 / 3.0, s);
-    do_vjp(h, u1, aT[1], aS[1], B2, B1, nullptr, nullptr, h->dt_d, 0, 0, 0.25, 0.25, s);
-    do_vjp(h, Un, aT[0], aS[0], B1, Ub0, Wt, B2, h->dt_d, 1.0 / 3.0, 0.75, 1.0, 1.0, s);
+    do_rhs(h, 2, Un, aT[0], aS[0], u1, Un, kSSP33[0].c0, kSSP33[0].c1, kSSP33[0].c2 * d.value, s, aT[1], aS[1], 0, 0, 1,
+           0, d.dev);
+    do_rhs(h, 2, u1, aT[1], aS[1], u2, Un, kSSP33[1].c0, kSSP33[1].c1, kSSP33[1].c2 * d.value, s, aT[2], aS[2], 0, 0, 1,
+           0, d.dev);
+    do_vjp(h, u2, aT[2], aS[2], Wt, B2, nullptr, nullptr, d.dev, 0, 0, 2.0 / 3.0, 2.0 / 3.0 * d.value, s);
+    do_vjp(h, u1, aT[1], aS[1], B2, B1, nullptr, nullptr, d.dev, 0, 0, 0.25, 0.25 * d.value, s);
+    do_vjp(h, Un, aT[0], aS[0], B1, Ub0, Wt, B2, d.dev, 1.0 / 3.0, 0.75, 1.0, 1.0 * d.value, s);
   }
   HIP_TRY(hipGetLastError());
   return DG_OK;
@@ -1283,7 +1305,8 @@ extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, 
   dg_status st = ready(h);
   if (st != DG_OK) return st;
   if (!U || !dt || nsteps < 1) return fail(DG_EINVAL, "bad autotune arguments");
-  st = upload_dt(h, dt, 0);
+  Dt d;
+  st = take_dt(h, dt, 0, false, &d);
   if (st != DG_OK) return st;
   const int emax = elems_per_block(h->order, h->dim, h->prec == DG_FP64);
   const int cand_e[3] = {emax, emax / 2, emax / 4};
@@ -1306,10 +1329,10 @@ extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, 
       if (st != DG_OK) { h->timing = timing; return st; }
       HIP_TRY(hipMemcpy(W, U, h->state_bytes, hipMemcpyDeviceToDevice));
       int cur = 0;
-      rk_one(h, W, true, &cur, 0);                       // warm-up
+      rk_one(h, W, d, true, &cur, 0);                       // warm-up
       HIP_TRY(hipMemcpy(W, U, h->state_bytes, hipMemcpyDeviceToDevice));
       HIP_TRY(hipEventRecord(e0, 0));
-      for (int i = 0; i < nsteps; ++i) rk_one(h, W, i == 0, &cur, 0, i);
+      for (int i = 0; i < nsteps; ++i) rk_one(h, W, d, i == 0, &cur, 0, i);
       HIP_TRY(hipEventRecord(e1, 0));
       HIP_TRY(hipEventSynchronize(e1));
       float ms = 0.f;
@@ -1347,7 +1370,9 @@ extern "C" dg_status dg_rk_step_graph(dg_handle* h, void* U, const double* dt, i
     HIP_TRY(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
     int cur = 0;
     dg_status cs = DG_OK;
-    for (int i = 0; i < nsteps && cs == DG_OK; ++i) cs = rk_one(h, U, i == 0, &cur, h->cap_stream, i);
+    Dt d;
+    d.dev = h->dt_d;
+    for (int i = 0; i < nsteps && cs == DG_OK; ++i) cs = rk_one(h, U, d, i == 0, &cur, h->cap_stream, i);
     hipGraph_t g = nullptr;
     hipError_t ce = hipStreamEndCapture(h->cap_stream, &g);
     if (cs != DG_OK) { if (g) (void)hipGraphDestroy(g); return cs; }
@@ -1359,7 +1384,8 @@ extern "C" dg_status dg_rk_step_graph(dg_handle* h, void* U, const double* dt, i
     h->graph_epb = h->epb;
     h->graph_persist = h->persist;
   }
-  st = upload_dt(h, dt, s);
+  Dt d;
+  st = take_dt(h, dt, s, true, &d);
   if (st != DG_OK) return st;
   HIP_TRY(hipGraphLaunch(h->graph_exec, s));
   h->splits += (long long)h->nnodes * nsteps * (h->rk == DG_SSPRK43 ? 4 : 3);

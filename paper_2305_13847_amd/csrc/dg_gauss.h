@@ -375,7 +375,7 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
       for (int v = 0; v < NV; ++v) Rv[v] += km * sFs[v * NFB + base] - kp * sFs[v * NFB + base + NF];
     }
     R U0q[NV];
-    const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
+    const double dtm = MODE != 0 && dt_m ? dt_m[item.member] : 1.0;
     if (MODE != 0 && c0 != 0.0) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) U0q[v] = ld(U0, N, v, g);

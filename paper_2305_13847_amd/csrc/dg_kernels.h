@@ -181,7 +181,8 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
 // right-hand side / stage kernel
 // ---------------------------------------------------------------------------
 // MODE 0: out = dU/dt
-// MODE 1: out = c0 U0 + c1 U + c2 dt_member dU/dt  (a Shu-Osher stage)
+// MODE 1: out = c0 U0 + c1 U + c2 dt_member dU/dt  (a Shu-Osher stage; without
+//         dt_m the time step is in c2)
 // MODE 2: as MODE 1, then the split of the new state at every node, written
 //         to (oT, oS); Newton is warm-started and anchored at the input
 //         state's (T, rho_vs).  With kRefreshRvs the stored rho_vs is a fresh
@@ -616,7 +617,7 @@ __device__ __forceinline__ void rhs_item_3d(const KArgs& a, int t, int it_, Elem
     for (int v = 0; v < NV; ++v) Uq[v] = R(0);
   }
   elem_table<K, D>(item, epb, t, tab);
-  const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
+  const double dtm = MODE != 0 && dt_m ? dt_m[item.member] : 1.0;
   const int le = t / NP, n = t - le * NP;
   int idx[3];
   idx[0] = n % P1;
@@ -788,7 +789,7 @@ __device__ __forceinline__ void rhs_item_2d(const KArgs& a, int t, int it_, R* s
   }
   const bool task = t < ntask;
   if (task) pair_gather_2d<R, K, RAIN>(item, g0, t, U, auxT, auxS, N, pr);
-  const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
+  const double dtm = MODE != 0 && dt_m ? dt_m[item.member] : 1.0;
   R Rv[NV];
 #pragma unroll
   for (int v = 0; v < NV; ++v) Rv[v] = R(0);
@@ -944,7 +945,7 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
 #pragma unroll
       for (int v = 0; v < NV; ++v) (out + (size_t)v * N)[g] = Rv[v];
     } else {
-      const R k2 = (R)(c2 * dt_m[item.member]);
+      const R k2 = (R)(c2 * (dt_m ? dt_m[item.member] : 1.0));
       const R k1 = (R)c1;
       R Un[NV];
       if (c0 != 0.0) {

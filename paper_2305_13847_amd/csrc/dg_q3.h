@@ -342,7 +342,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 #pragma unroll
     for (int v = 0; v < NV; ++v) Rv[v] += ld((const R*)a.sip_out, N, v, g);
   }
-  const double dtm = (MODE != 0) ? dt_m[item.member] : 0.0;
+  const double dtm = MODE != 0 && dt_m ? dt_m[item.member] : 1.0;
   int iters = 0, bad = 0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) Uq[v] = sU[v][lane];
