@@ -353,6 +353,37 @@ __device__ __forceinline__ NearOut split_near(const KArgs& a, double rd, double 
   return o;
 }
 
+// A larger change (up to kAnchorX): the quartic's root is within 1e-6 K; one
+// Newton step with rho_vs and its slope from the anchored series completes it
+// (error below 0.25 K^-1 dT^2, see newton_sat).  The series are those of
+// rvs_near for |x| <= kAnchorX, without the choice per wavefront.
+__device__ __forceinline__ NearOut split_mid(const KArgs& a, double rd, double rm, double rr, double re,
+                                             double T0, double r0, double inv0, bool sat, double Tn) {
+  NearOut o;
+  const double x = (Tn - T0) * inv0;
+  const double l = x * (1.0 + x * (-0.5 + x * (1.0 / 3.0 + x * (-0.25 + x * (0.2 + x * (-1.0 / 6.0 + x * (1.0 / 7.0)))))));
+  const double q = 1.0 + x * (-1.0 + x * (1.0 + x * (-1.0 + x * (1.0 + x * (-1.0 + x * (1.0 - x))))));
+  const double d = a.am1 * l + a.b * inv0 * x * q;
+  const double e = d * (1.0 + d * (1.0 / 2 + d * (1.0 / 6 + d * (1.0 / 24 + d * (1.0 / 120 + d * (1.0 / 720 +
+      d * (1.0 / 5040 + d * (1.0 / 40320 + d * (1.0 / 362880 + d * (1.0 / 3628800))))))))));
+  o.T = Tn;
+  o.rvs = r0 + r0 * e;
+  bool small = true;
+  if (sat) {
+    const double dc = a.cvv - a.cl, iT = inv0 * q;
+    const double dr = o.rvs * (a.am1 + a.b * iT) * iT;
+    const double Cv = fma(a.cvd, rd, a.cl * (rm + rr)) + dc * o.rvs;
+    const double Tm = Tn - a.Tref;
+    const double dT = -(Cv * Tm + o.rvs * a.Lp - re) * rcp64(Cv + dr * (dc * Tm + a.Lp));
+    o.T += dT;
+    o.rvs += dr * dT;
+    small = dT * dT <= 4.0 * fmin(a.rtol, 1e-14) * Tn;
+  }
+  const bool branch = sat ? o.rvs <= rm : rm <= o.rvs;
+  o.ok = branch && small && fabs(x) <= kAnchorX && T0 > 150.0 && T0 < 600.0 && r0 > 0.0;
+  return o;
+}
+
 // The split warm-started at the node's previous (T, rho_vs(T)); the branch that
 // held there before is tried first.
 __device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double rm, double rr, double re, double T,
@@ -362,7 +393,12 @@ __device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double
   SplitOut o;
   o.iters = sat ? 1 : 0;
   o.bad = 0;
-  const NearOut n = split_near(a, rd, rm, rr, re, T, rvs, inv, sat);
+  NearOut n = split_near(a, rd, rm, rr, re, T, rvs, inv, sat);
+  const bool pos = fma(a.cvd, rd, a.cl * (rm + rr)) + (a.cvv - a.cl) * rm > 0.0;
+  if (!n.ok && pos) {
+    n = split_mid(a, rd, rm, rr, re, T, rvs, inv, sat, n.T);
+    o.iters = sat ? 2 : 0;
+  }
   o.T = n.T;
   o.rvs = n.rvs;
   if (!n.ok || a.maxit <= kEstIters) {

@@ -69,6 +69,15 @@ constexpr int q3_brick_rows(bool fp64) { return fp64 ? 1 : 2; }
 template <typename R>
 constexpr int q3_brick_rows() { return q3_brick_rows(sizeof(R) == 8); }
 
+// Threads of a block of the 2D and 3D block kernels for `nodes` nodes: whole
+// wavefronts; at 2D Q2, where an element has 12 face nodes to its 9 nodes, as
+// many as there are face tasks (one pass instead of two).
+constexpr int block_kernel_threads(int K, int D, int nodes) {
+  const int tasks = K == 2 && D == 2 ? nodes / 9 * 12 : 0;
+  const int n = K >= 2 && tasks > nodes ? tasks : nodes;
+  return K >= 2 ? (n + 63) / 64 * 64 : n;
+}
+
 __host__ __device__ inline int grid_for_items(int nitems) { return ((nitems + 7) >> 3) << 3; }
 
 // flags of a stage launch
@@ -702,7 +711,7 @@ __device__ __forceinline__ void rhs_item_3d(const KArgs& a, int t, int it_, Elem
 
 // 2D right-hand side / stage of one work item (K >= 2).  A 2D element has
 // about as many face nodes (4 (K+1)) as nodes, so a block's face tasks are one
-// pass of its threads (two for K = 2); they are numbered element by element,
+// pass of its threads; they are numbered element by element,
 // and every load of a thread (its node, the neighbour's trace of its first
 // task, both backgrounds) is issued before any arithmetic: the state is read
 // in one round trip, and nothing waits for memory between the barriers.
@@ -991,7 +1000,7 @@ template <typename R>
 constexpr int min_waves() { return sizeof(R) == 4 ? 4 : 1; }
 
 template <typename R, int K, int D, int RAIN, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves<R>())))
+__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R>())))
 rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
            const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
            const double* __restrict__ dt_m, double c0, double c1, double c2,
@@ -1024,7 +1033,7 @@ rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 
 // persistent: a grid smaller than the item count walks the items
 template <typename R, int K, int D, int RAIN, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(min_waves<R>())))
+__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R>())))
 rhs_kernel_persistent(KArgs a, const KArgs* __restrict__ a_dev, const R* __restrict__ U,
                       const double* __restrict__ auxT,
                       const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,

@@ -92,8 +92,8 @@ bool LaunchStage<R>::rhs(const KArgs& a, const KArgs* a_dev, LaunchCfg lc, int K
   return dispatch_shape(K, D, rain, [&](auto k, auto d, auto r) {
     constexpr int K_ = decltype(k)::value, D_ = decltype(d)::value, R_ = decltype(r)::value;
     dim3 grid(lc.grid), block(lc.threads);
-    // (K >= 2: whole wavefronts; the threads beyond the nodes take face tasks)
-    if (K_ >= 2) block = dim3((lc.threads + 63) / 64 * 64);
+    // (the threads beyond the nodes take face tasks)
+    block = dim3(block_kernel_threads(K_, D_, lc.threads));
 #define DGM_RHS(KER, M)                                                                           \
 hipLaunchKernelGGL((KER<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, auxT, auxS,       \
                    (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
