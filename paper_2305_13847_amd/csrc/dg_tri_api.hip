@@ -73,6 +73,8 @@ struct dg_tri {
   size_t state_bytes = 0;
   double* xy_d = nullptr;
   int* nbr_d = nullptr;
+  int* layer_d = nullptr;
+  double* bgm_d = nullptr;
   double* bgl_d = nullptr;
   void* stage[2] = {nullptr, nullptr};
   double* aux[2] = {nullptr, nullptr};   // (T_h, rho_v,h) coefficients, ping-pong
@@ -123,6 +125,8 @@ struct TriTimer {
 static void tri_free(dg_tri* h) {
   (void)hipFree(h->xy_d);
   (void)hipFree(h->nbr_d);
+  (void)hipFree(h->layer_d);
+  (void)hipFree(h->bgm_d);
   (void)hipFree(h->bgl_d);
   for (auto p : h->stage) (void)hipFree(p);
   for (auto p : h->aux) (void)hipFree(p);
@@ -173,13 +177,17 @@ extern "C" dg_status dg_tri_create(const dg_tri_mesh* m, int order, int nvars, c
   if (m->nz < 1 || !(m->dz > 0.0) || !std::isfinite(m->dz) || !std::isfinite(m->z0))
     return tfail(DG_EINVAL, "background layers need nz >= 1 and a finite dz > 0");
   const int ne = m->ne;
-  std::vector<int> nbr((size_t)ne * 3);
+  std::vector<int> nbr((size_t)ne * 3), layer(ne);
   for (int e = 0; e < ne; ++e) {
     const double* v = m->xy + (size_t)e * 6;
     for (int i = 0; i < 6; ++i)
       if (!std::isfinite(v[i])) return tfail(DG_EINVAL, "non-finite vertex in element %d", e);
     const double det = (v[2] - v[0]) * (v[5] - v[1]) - (v[4] - v[0]) * (v[3] - v[1]);
     if (!(det > 0.0)) return tfail(DG_EINVAL, "element %d is not counter-clockwise (det A = %g)", e, det);
+    // the background layer that holds the centroid
+    const double zc = (v[1] + v[3] + v[5]) * (1.0 / 3.0);
+    const double l = std::floor((zc - m->z0) * (1.0 / m->dz));
+    layer[e] = l < 0.0 ? 0 : (l >= m->nz ? m->nz - 1 : (int)l);
     for (int f = 0; f < 3; ++f) {
       const int e2 = m->nb[(size_t)e * 3 + f], f2 = m->nbf[(size_t)e * 3 + f];
       if (e2 < 0) { nbr[(size_t)e * 3 + f] = -1; continue; }
@@ -201,7 +209,9 @@ extern "C" dg_status dg_tri_create(const dg_tri_mesh* m, int order, int nvars, c
   auto A = [&](void** ptr, size_t bytes) { return hipMalloc(ptr, bytes) == hipSuccess; };
   ok = ok && A((void**)&h->xy_d, sizeof(double) * 6 * ne);
   ok = ok && A((void**)&h->nbr_d, sizeof(int) * 3 * ne);
+  ok = ok && A((void**)&h->layer_d, sizeof(int) * ne);
   ok = ok && A((void**)&h->bgl_d, sizeof(double) * 5 * m->nz * (order + 1));
+  ok = ok && A((void**)&h->bgm_d, sizeof(double) * 6 * m->nz * (order + 1));
   ok = ok && A(&h->stage[0], h->state_bytes) && A(&h->stage[1], h->state_bytes);
   ok = ok && A((void**)&h->aux[0], sizeof(double) * 2 * ne * h->np);
   ok = ok && A((void**)&h->aux[1], sizeof(double) * 2 * ne * h->np);
@@ -213,12 +223,14 @@ extern "C" dg_status dg_tri_create(const dg_tri_mesh* m, int order, int nvars, c
   }
   hipError_t e1 = hipMemcpy(h->xy_d, m->xy, sizeof(double) * 6 * ne, hipMemcpyHostToDevice);
   hipError_t e2 = hipMemcpy(h->nbr_d, nbr.data(), sizeof(int) * 3 * ne, hipMemcpyHostToDevice);
+  hipError_t e5 = hipMemcpy(h->layer_d, layer.data(), sizeof(int) * ne, hipMemcpyHostToDevice);
   hipError_t e3 = hipMemset(h->stats, 0, sizeof(unsigned) * kStatsWords);
   hipError_t e4 = p->precision == DG_FP64 ? (order == 1 ? upload_tab<double, 1>() : order == 2 ? upload_tab<double, 2>()
                                              : order == 3 ? upload_tab<double, 3>() : upload_tab<double, 4>())
                                           : (order == 1 ? upload_tab<float, 1>() : order == 2 ? upload_tab<float, 2>()
                                              : order == 3 ? upload_tab<float, 3>() : upload_tab<float, 4>());
-  if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess) {
+  if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess || e4 != hipSuccess ||
+      e5 != hipSuccess) {
     tri_free(h);
     delete h;
     return tfail(DG_EHIP, "initial upload failed");
@@ -227,10 +239,10 @@ extern "C" dg_status dg_tri_create(const dg_tri_mesh* m, int order, int nvars, c
   h->ka.stats = h->stats;
   h->ta.xy = h->xy_d;
   h->ta.nbr = h->nbr_d;
-  h->ta.bgl = h->bgl_d;
+  h->ta.layer = h->layer_d;
+  h->ta.bgm = h->bgm_d;
   h->ta.z0 = m->z0;
   h->ta.inv_dz = 1.0 / m->dz;
-  h->ta.nz = m->nz;
   h->ta.ne = ne;
   *out = h;
   return DG_OK;
@@ -270,6 +282,21 @@ extern "C" dg_status dg_tri_set_background(dg_tri* h, const double* rd, const do
   for (int i = 0; i < n; ++i)
     if (!std::isfinite(b[(size_t)i * 5 + 4]) || !(b[(size_t)i * 5 + 4] > 0))
       return tfail(DG_EINVAL, "background state at index %d has no valid temperature", i);
+  // each layer's interpolant as coefficients of xi^i (TriArgs::bgm)
+  const int p1 = h->order + 1;
+  double xg[8], wg[8], f[8], c[8];
+  gl_rule(p1, xg, wg);
+  std::vector<double> cm((size_t)h->nz * p1 * 6);
+  for (int l = 0; l < h->nz; ++l)
+    for (int k = 0; k < 6; ++k) {
+      for (int i = 0; i < p1; ++i) {
+        const double* v = &b[((size_t)l * p1 + i) * 5];
+        f[i] = k == 0 ? v[0] : k == 1 ? v[1] : k == 2 ? v[4] : k == 3 ? v[3] + v[4] : k == 4 ? v[2] : v[3];
+      }
+      monomials(h->order, xg, f, c);
+      for (int i = 0; i < p1; ++i) cm[((size_t)l * p1 + i) * 6 + k] = c[i];
+    }
+  TRI_HIP(hipMemcpy(h->bgm_d, cm.data(), sizeof(double) * cm.size(), hipMemcpyHostToDevice));
   h->bg_set = true;
   return DG_OK;
 }

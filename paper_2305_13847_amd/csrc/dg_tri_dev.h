@@ -23,22 +23,25 @@ struct TriShape {
   static constexpr int NP = (K + 1) * (K + 2) / 2;   // modes
   static constexpr int NQ = (K + 1) * (K + 2);       // volume points
   static constexpr int NF = K + 1;                   // points per face
+  // rows of NP values padded to whole 16-byte LDS reads (single and double)
+  static constexpr int NPP = (NP + 3) / 4 * 4, NPD = (NP + 1) / 2 * 2;
 };
 
 // Reference tables of order K (filled on the host at handle creation).
 template <typename R, int K>
-struct TriTab {
+struct alignas(16) TriTab {
   static constexpr int NP = TriShape<K>::NP, NQ = TriShape<K>::NQ, NF = TriShape<K>::NF;
-  R psi[NQ][NP], dr[NQ][NP], ds[NQ][NP];   // basis and reference gradient at the volume points
-  R w[NQ];                                  // volume weights (sum 1/2)
-  double psid[NQ][NP];                      // the basis in FP64 (T, rho_v, split, projection)
-  double wd[NQ];
+  static constexpr int NPP = TriShape<K>::NPP, NPD = TriShape<K>::NPD;
+  R psi[NQ][NPP];                           // basis at the volume points
+  R g3[NQ][NP][4];                          // its reference gradient (r, s) and value, together
+  double psid[NQ][NPD];                     // the basis in FP64 (T, rho_v, split, projection)
+  R psif[3][NF][NPP];                       // basis at the face points
+  double psifd[3][NF][NPD];
+  double wd[NQ];                            // volume weights (sum 1/2)
   double rq[NQ], sq[NQ];                    // volume points
-  R psif[3][NF][NP];                        // basis at the face points
-  double psifd[3][NF][NP];
-  R wf[NF];                                 // half the face Gauss weights
   double rf[3][NF], sf[3][NF];              // face points
-  double xg[NF], lagd[NF];                  // layer Gauss heights on [-1, 1], 1 / prod_{j != i} (x_i - x_j)
+  R w[(NQ + 3) / 4 * 4];                    // volume weights
+  R wf[(NF + 3) / 4 * 4];                   // half the face Gauss weights
 };
 
 __constant__ TriTab<float, 1> c_tri_f1;
@@ -68,13 +71,15 @@ __device__ __forceinline__ const TriTab<R, K>& ttab() {
 struct TriArgs {
   const double* xy;   // ne x 3 x (x, z)
   const int* nbr;     // ne x 3: neighbour * 4 + its face; -1 slip wall
-  const double* bgl;  // background [layer][height i][field]: rho_d, rho_m, rho_r, E, p
+  const int* layer;   // ne: the background layer that holds the centroid
+  // background: per layer the degree-K interpolant through its Gauss heights as
+  // coefficients of xi^i on [-1, 1], fields (rho_d, rho_m, p, E + p, rho_r, E)
+  const double* bgm;
   double z0, inv_dz;
-  int nz, ne;
+  int ne;
 };
 
-// Vertex heights and layer of element e; the layer is the one holding the
-// centroid.
+// Vertex heights and layer of element e.
 struct TriZ {
   double z0, dz1, dz2;
   int layer;
@@ -86,34 +91,24 @@ __device__ __forceinline__ TriZ tri_z(const TriArgs& t, int e) {
   g.z0 = v[1];
   g.dz1 = v[3] - v[1];
   g.dz2 = v[5] - v[1];
-  const double zc = (v[1] + v[3] + v[5]) * (1.0 / 3.0);
-  int l = (int)floor((zc - t.z0) * t.inv_dz);
-  g.layer = l < 0 ? 0 : (l >= t.nz ? t.nz - 1 : l);
+  g.layer = t.layer[e];
   return g;
 }
 
-// Background (rho_d, rho_m, rho_r, E, p) at height z from layer l's
-// degree-K interpolant through its Gauss heights.
-template <typename R, int K>
-__device__ __forceinline__ void tri_bg(const TriArgs& t, const TriTab<R, K>& T, int l, double z, double* b) {
+// Background at height z from layer l's interpolant.
+template <int K>
+__device__ __forceinline__ Bg tri_bg(const TriArgs& t, int l, double z) {
   const double xi = 2.0 * ((z - t.z0) * t.inv_dz - (double)l) - 1.0;
-  double ell[K + 1];
+  const double2* c = (const double2*)t.bgm + (size_t)l * (3 * (K + 1));
+  double2 x = c[3 * K], y = c[3 * K + 1], w = c[3 * K + 2];
 #pragma unroll
-  for (int i = 0; i <= K; ++i) {
-    double p = T.lagd[i];
-#pragma unroll
-    for (int j = 0; j <= K; ++j)
-      if (j != i) p *= xi - T.xg[j];
-    ell[i] = p;
+  for (int i = K - 1; i >= 0; --i) {
+    const double2 a = c[3 * i], b = c[3 * i + 1], d = c[3 * i + 2];
+    x.x = fma(x.x, xi, a.x); x.y = fma(x.y, xi, a.y);
+    y.x = fma(y.x, xi, b.x); y.y = fma(y.y, xi, b.y);
+    w.x = fma(w.x, xi, d.x); w.y = fma(w.y, xi, d.y);
   }
-  const double* B = t.bgl + (size_t)l * (K + 1) * 5;
-#pragma unroll
-  for (int f = 0; f < 5; ++f) {
-    double v = 0.0;
-#pragma unroll
-    for (int i = 0; i <= K; ++i) v += ell[i] * B[i * 5 + f];
-    b[f] = v;
-  }
+  return Bg{x.x, x.y, y.x, y.y, w.x, w.y};
 }
 
 // The flux of Section 2.3 along the direction (nx, nz): F(q) . n for every
@@ -148,30 +143,43 @@ __device__ __forceinline__ R speed_dir(const Pt<R, 2, RAIN>& q, R nx, R nz) {
 // Split (Section 2.2) of the state with perturbation Uq (FP64) over background
 // b at one point, from the guess Tg: T and rho_v = min(rho_vs(T), rho_m).
 template <int RAIN>
-__device__ __forceinline__ SplitOut tri_split_point(const KArgs& a, const double* Uq, const double* b, double Tg,
+__device__ __forceinline__ SplitOut tri_split_point(const KArgs& a, const double* Uq, const Bg& b, double Tg,
                                                     double* rv) {
   using V = Vars<2, RAIN>;
-  const double rd = b[0] + Uq[V::RD];
-  const double rm = b[1] + Uq[V::RM];
-  const double rr = RAIN ? b[2] + Uq[V::RR] : 0.0;
-  const double rho = rd + rm + rr;
+  const double rd = b.rd + Uq[V::RD];
+  const double rm = b.rm + Uq[V::RM];
+  const double rr = RAIN ? b.rr + Uq[V::RR] : 0.0;
   const double m0 = Uq[V::M0], m1 = Uq[V::M0 + 1];
-  const double re = (b[3] + Uq[V::E]) - 0.5 * (m0 * m0 + m1 * m1) / rho;
+  const double re = (b.E + Uq[V::E]) - 0.5 * (m0 * m0 + m1 * m1) * rcp64(rd + rm + rr);
   const SplitOut s = split_scratch(a, rd, rm, rr, re, Tg);
   *rv = fmin(s.rvs, rm);
   return s;
 }
 
+// eval_core with the background of tri_bg
+template <typename R, int RAIN>
+__device__ __forceinline__ void tri_eval(const KArgs& a, const R* U, double T, double rv, const Bg& b,
+                                         Pt<R, 2, RAIN>& q) {
+  eval_core<R, 2, RAIN>(a, U, T, rv, RAIN ? rho_vs(a, T) : 0.0, b.rd, b.rm, RAIN ? b.rr : 0.0, b.p, b.Ep, q);
+}
+
 // Work layout: a block of 256 threads holds EPB elements, one thread per
 // volume point of each (EPB NQ threads; the rest idle).  The elements'
 // coefficients, their projected T and rho_v and the per-point results sit in
-// LDS; the contractions between modes and points read them from there:
+// LDS, in rows padded to 16-byte reads; the contractions between modes and
+// points read them from there:
 //   points:  thread (element, q) evaluates the state at volume point q, its
 //            flux along the two columns of A^{-T} and its sources;
-//   modes:   thread (element, m), m < NP, sums the volume point results and
-//            the weighted face fluxes against psi_m, and forms the update;
+//   modes:   thread (element, m + half NP) sums all variables of mode m over
+//            half of the volume points; the halves then exchange partial sums
+//            and each finishes half of the variables (faces, update);
 //   faces:   thread (element, j), j < 3 NF, handles face point j: its own
-//            trace from LDS, the neighbour's from global memory.
+//            trace from LDS, the neighbour's from coefficients parked there.
+// Bound by instruction issue and LDS latency.  At 256 x 128 x 2, P3, FP32 a
+// stage took 133 us with 2503 VALU instructions per wavefront, a third of them
+// index arithmetic (one division chain per loaded value), Lagrange weights of
+// the background evaluated twice per point, conversions in the split, and
+// single-word LDS reads; now 96 us with 1531.
 template <int K>
 struct TriBlock {
   static constexpr int NQ = TriShape<K>::NQ;
@@ -182,23 +190,28 @@ struct TriBlock {
 template <typename R, int K, int RAIN>
 struct TriLds {
   static constexpr int NV = Vars<2, RAIN>::NV, NP = TriShape<K>::NP, NQ = TriShape<K>::NQ;
+  static constexpr int NPP = TriShape<K>::NPP, NPD = TriShape<K>::NPD;
   static constexpr int NF = TriShape<K>::NF, EPB = TriBlock<K>::EPB;
-  static constexpr bool HAS_AUX = true;
+  static constexpr int NVP = (NV + 3) / 4 * 4, PF = (3 * NV + 3) / 4 * 4;
   // the reference tables (FP32; in FP64 they would halve the blocks per CU and
   // stay in constant memory)
   struct Empty {};
   std::conditional_t<sizeof(R) == 4, TriTab<R, K>, Empty> tab;
-  double aux[EPB][2][NP];   // projected T and rho_v of the stage input
-  double ts[EPB][NQ][2];    // the split of the updated state at the volume points
-  R c[EPB][NV][NP];         // coefficients of the stage input, then of its update
+  alignas(16) double aux[EPB][2][NPD];   // projected T and rho_v of the stage input
+  alignas(16) double ts[EPB][NQ][2];     // the weighted split of the updated state at the volume points
+  alignas(16) R c[EPB][NV][NPP];         // coefficients of the stage input
   union {
-    R pf[EPB][NQ][3 * NV];  // per volume point: w F.G0, w F.G1, w G
-    struct {                // then the neighbours across the three faces
-      double aux[EPB][3][2][NP];
-      R c[EPB][3][NV][NP];
+    alignas(16) R pf[EPB][NQ][PF];       // per volume point: w F.G0, w F.G1, w G
+    struct {                             // then the neighbours across the three faces
+      alignas(16) double aux[EPB][3][2][NPD];
+      alignas(16) R c[EPB][3][NV][NPP];
     } nb;
+    alignas(16) double cd[EPB][NV][NPD]; // then the updated coefficients, for the split
   } u;
-  R ff[EPB][3 * NF][NV];    // per face point: the weighted normal flux
+  union {
+    alignas(16) R px[EPB][NP][NVP];      // partial sums of the modes
+    alignas(16) R ff[EPB][3 * NF][NVP];  // then per face point the weighted normal flux
+  } f;
   TriZ fz[EPB];             // heights of the vertices and background layer
   R fn[EPB][3][3];          // per face: n_x, n_z, |e_f| / det A
 };
@@ -219,13 +232,14 @@ __device__ __forceinline__ long long tri_first_element(int ne) {
 // LDS of the split kernel: coefficients and the split values only
 template <typename R, int K, int RAIN>
 struct TriLdsSplit {
-  static constexpr int NV = Vars<2, RAIN>::NV, NP = TriShape<K>::NP, NQ = TriShape<K>::NQ;
+  static constexpr int NV = Vars<2, RAIN>::NV, NQ = TriShape<K>::NQ, NPD = TriShape<K>::NPD;
   static constexpr int EPB = TriBlock<K>::EPB;
-  static constexpr bool HAS_AUX = false;
   struct Empty {};
   std::conditional_t<sizeof(R) == 4, TriTab<R, K>, Empty> tab;
-  double ts[EPB][NQ][2];
-  R c[EPB][NV][NP];
+  alignas(16) double ts[EPB][NQ][2];
+  struct {
+    alignas(16) double cd[EPB][NV][NPD];
+  } u;
 };
 
 // Copy the reference tables (a plain struct) from constant memory into LDS
@@ -246,33 +260,11 @@ __device__ __forceinline__ const TriTab<R, K>& tri_tab(const L& S) {
   else return ttab<R, K>();
 }
 
-// Load the block's coefficients (and aux) into LDS with coalesced reads;
-// elements past the end repeat the last one (their results are never stored).
+// The split of the state S.u.cd at volume point q of element slot el (thread
+// (el, q)), from the guess Tg, weighted, to S.ts.
 template <typename R, int K, int RAIN, typename L>
-__device__ __forceinline__ void tri_load_block(L& S, const TriArgs& t, long long e0, const R* __restrict__ U,
-                                               const double* __restrict__ aux) {
-  constexpr int NV = Vars<2, RAIN>::NV, NP = TriShape<K>::NP, EPB = TriBlock<K>::EPB;
-  const size_t N = (size_t)t.ne * NP;
-  for (int idx = threadIdx.x; idx < NV * EPB * NP; idx += blockDim.x) {
-    const int v = idx / (EPB * NP), r = idx - v * (EPB * NP);
-    const int le = r / NP, m = r - le * NP;
-    const long long e = min(e0 + le, (long long)t.ne - 1);
-    S.c[le][v][m] = U[v * N + (size_t)e * NP + m];
-  }
-  if constexpr (L::HAS_AUX)
-    for (int idx = threadIdx.x; idx < 2 * EPB * NP; idx += blockDim.x) {
-      const int v = idx / (EPB * NP), r = idx - v * (EPB * NP);
-      const int le = r / NP, m = r - le * NP;
-      const long long e = min(e0 + le, (long long)t.ne - 1);
-      S.aux[le][v][m] = aux[v * N + (size_t)e * NP + m];
-    }
-}
-
-// The split of the block's state S.c at volume point q of element slot el
-// (thread (el, q)), written to S.ts; Tguess (optional) from S.aux.
-template <typename R, int K, int RAIN, typename L>
-__device__ __forceinline__ void tri_split_at(const KArgs& a, const TriArgs& t, L& S, int el, int q, const TriZ& g,
-                                             int* iters, int* bad) {
+__device__ __forceinline__ void tri_split_at(const KArgs& a, L& S, int el, int q, const Bg& b, double Tg, int* iters,
+                                             int* bad) {
   constexpr int NV = Vars<2, RAIN>::NV, NP = TriShape<K>::NP;
   const auto& T = tri_tab<R, K>(S);
   double X[NV];
@@ -280,36 +272,27 @@ __device__ __forceinline__ void tri_split_at(const KArgs& a, const TriArgs& t, L
   for (int v = 0; v < NV; ++v) {
     double s = 0.0;
 #pragma unroll
-    for (int m = 0; m < NP; ++m) s += (double)S.c[el][v][m] * T.psid[q][m];
+    for (int m = 0; m < NP; ++m) s += S.u.cd[el][v][m] * T.psid[q][m];
     X[v] = s;
   }
-  double Tg = 0.0;
-  if constexpr (L::HAS_AUX) {
-#pragma unroll
-    for (int m = 0; m < NP; ++m) Tg += S.aux[el][0][m] * T.psid[q][m];
-  }
-  double b[5];
-  tri_bg<R, K>(t, T, g.layer, g.z0 + g.dz1 * T.rq[q] + g.dz2 * T.sq[q], b);
   double rv;
   const SplitOut o = tri_split_point<RAIN>(a, X, b, Tg, &rv);
-  S.ts[el][q][0] = o.T;
-  S.ts[el][q][1] = rv;
+  S.ts[el][q][0] = o.T * T.wd[q];
+  S.ts[el][q][1] = rv * T.wd[q];
   *iters = o.iters;
   *bad = o.bad;
 }
 
-// The L2 projections of the split values S.ts onto P^k, by thread (el, j),
-// j < 2 NP (j < NP: T, else rho_v), stored to Tn / Rn.
+// The L2 projections of the split values onto P^k, by thread (el, m + c NP)
+// (c = 0: T, 1: rho_v), stored to Tn / Rn.
 template <typename R, int K, int RAIN, typename L>
-__device__ __forceinline__ void tri_project_split(const L& S, int el, int j, long long e, bool act,
+__device__ __forceinline__ void tri_project_split(const L& S, int el, int m, int c, long long e, bool act,
                                                   double* __restrict__ Tn, double* __restrict__ Rn) {
   constexpr int NP = TriShape<K>::NP, NQ = TriShape<K>::NQ;
   const auto& T = tri_tab<R, K>(S);
-  if (j >= 2 * NP) return;
-  const int c = j >= NP ? 1 : 0, m = j - c * NP;
   double s = 0.0;
 #pragma unroll 4
-  for (int qq = 0; qq < NQ; ++qq) s += T.wd[qq] * T.psid[qq][m] * S.ts[el][qq][c];
+  for (int qq = 0; qq < NQ; ++qq) s += T.psid[qq][m] * S.ts[el][qq][c];
   if (act) (c ? Rn : Tn)[(size_t)e * NP + m] = s;
 }
 
@@ -317,86 +300,113 @@ __device__ __forceinline__ void tri_project_split(const L& S, int el, int j, lon
 template <typename R, int K, int RAIN>
 __global__ void __launch_bounds__(256) tri_split_kernel(KArgs a, TriArgs t, const R* __restrict__ U,
                                                         double* __restrict__ Tn, double* __restrict__ Rn) {
-  constexpr int NQ = TriShape<K>::NQ, EPB = TriBlock<K>::EPB, NT = TriBlock<K>::NT;
+  constexpr int NV = Vars<2, RAIN>::NV, NP = TriShape<K>::NP, NQ = TriShape<K>::NQ;
+  constexpr int EPB = TriBlock<K>::EPB, NT = TriBlock<K>::NT, NH = (NV + 1) / 2;
   __shared__ TriLdsSplit<R, K, RAIN> S;
   const int tid = threadIdx.x;
   const bool lane = tid < NT;
   const int el = lane ? tid / NQ : 0, q = lane ? tid - el * NQ : 0;
+  const int half = q >= NP ? 1 : 0, m = q - half * NP;
   const long long e0 = tri_first_element<K>(t.ne);
   if (e0 < 0) return;
   const int seen = stats_seen(a);
   const bool act = lane && e0 + el < t.ne;
-  const long long e = min(e0 + el, (long long)t.ne - 1);
+  // (elements past the end repeat the last one; their results are never stored)
+  const int e = (int)min(e0 + el, (long long)t.ne - 1);
+  const size_t N = (size_t)t.ne * NP;
   tri_copy_tab<R, K>(S);
-  tri_load_block<R, K, RAIN>(S, t, e0, U, nullptr);
+  if (lane) {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int v = half * NH + h;
+      if (v < NV) S.u.cd[el][v][m] = (double)U[v * N + (size_t)e * NP + m];
+    }
+  }
   __syncthreads();
   int it = 0, bd = 0;
-  if (lane) tri_split_at<R, K, RAIN>(a, t, S, el, q, tri_z(t, (int)e), &it, &bd);
+  if (lane) {
+    const auto& T = tri_tab<R, K>(S);
+    const TriZ g = tri_z(t, e);
+    tri_split_at<R, K, RAIN>(a, S, el, q, tri_bg<K>(t, g.layer, g.z0 + g.dz1 * T.rq[q] + g.dz2 * T.sq[q]), 0.0, &it,
+                             &bd);
+  }
   __syncthreads();
-  if (lane) tri_project_split<R, K, RAIN>(S, el, q, e, act, Tn, Rn);
+  if (lane) tri_project_split<R, K, RAIN>(S, el, m, half, e, act, Tn, Rn);
   record_stats(a, seen, act ? it : 0, act ? bd : 0);
 }
 
 // Stage kernel.  MODE 0: out = dC/dt.  MODE 2: out = c0 U0 + c1 U + c2 dt dC/dt
 // and the split of out into (Tn, Rn) for the next stage.  aux holds the
 // projected T and rho_v of U: aux[0 .. N) and aux[N .. 2N), N = ne NP.
+// FP32: 4 wavefronts per SIMD (128 registers, 7 spilled at P3; left free, 148
+// and 3 wavefronts: 2.12 against 1.97 ms for five steps).  FP64: 3, what the
+// LDS allows.
+template <typename R>
+constexpr int tri_min_waves() { return sizeof(R) == 4 ? 4 : 3; }
+
 template <typename R, int K, int RAIN, int MODE>
-__global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, const R* __restrict__ U,
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_min_waves<R>()))) tri_stage_kernel(KArgs a, TriArgs t, const R* __restrict__ U,
                                                         const double* __restrict__ aux, R* __restrict__ out,
                                                         const R* __restrict__ U0, double c0, double c1, double c2dt,
                                                         double* __restrict__ Tn, double* __restrict__ Rn) {
   using V = Vars<2, RAIN>;
   constexpr int NV = V::NV, NP = TriShape<K>::NP, NQ = TriShape<K>::NQ, NF = TriShape<K>::NF;
   constexpr int EPB = TriBlock<K>::EPB, NT = TriBlock<K>::NT;
+  constexpr int NH = (NV + 1) / 2;
+  static_assert(NQ == 2 * NP, "the Duffy rule has twice as many points as P^k has modes");
   __shared__ TriLds<R, K, RAIN> S;
   const auto& T = tri_tab<R, K>(S);
   const int tid = threadIdx.x;
   const bool lane = tid < NT;
   const int el = lane ? tid / NQ : 0, q = lane ? tid - el * NQ : 0;
+  // as a mode thread: mode m; variables half NH .. (half + 1) NH of the update
+  const int half = q >= NP ? 1 : 0, m = q - half * NP;
   const long long e0 = tri_first_element<K>(t.ne);
   if (e0 < 0) return;
-  const int seen = stats_seen(a);
+  const int seen = MODE == 2 ? stats_seen(a) : 0;
   const bool act = lane && e0 + el < t.ne;
+  // (elements past the end repeat the last one; their results are never stored)
   const int e = (int)min(e0 + el, (long long)t.ne - 1);
   const size_t N = (size_t)t.ne * NP;
 
-  // the neighbours' coefficients across the three faces of the block's
-  // elements, read now (coalesced runs of NP values) and parked in LDS once
-  // the volume phase has released its storage
-  constexpr int NNC = (EPB * 3 * NV * NP + 255) / 256, NNA = (EPB * 3 * 2 * NP + 255) / 256;
-  R nreg[NNC];
-  double areg[NNA];
+  // the element's coefficients, and those of the neighbours across its faces
+  // (parked in registers until the volume phase has released its LDS): thread
+  // (el, m, half) takes mode m of its variables everywhere, so consecutive
+  // threads read consecutive values and no index needs a division
+  R nreg[3][NH];
+  double areg[3];
+  {
+    const unsigned long long em = (unsigned long long)e * NP + m;
+    if (lane) {
 #pragma unroll
-  for (int k = 0; k < NNC; ++k) {
-    const int idx = tid + 256 * k;
-    nreg[k] = R(0);
-    if (idx < EPB * 3 * NV * NP) {
-      const int m = idx % NP, r = idx / NP, v = r % NV, r2 = r / NV, f = r2 % 3, le = r2 / 3;
-      const long long ee = min(e0 + le, (long long)t.ne - 1);
-      const int nb = t.nbr[(size_t)ee * 3 + f];
-      if (nb >= 0) nreg[k] = U[v * N + (size_t)(nb >> 2) * NP + m];
+      for (int h = 0; h < NH; ++h) {
+        const int v = half * NH + h;
+        if (v < NV) S.c[el][v][m] = U[v * N + em];
+      }
+      S.aux[el][half][m] = aux[half * N + em];
     }
-  }
 #pragma unroll
-  for (int k = 0; k < NNA; ++k) {
-    const int idx = tid + 256 * k;
-    areg[k] = 0.0;
-    if (idx < EPB * 3 * 2 * NP) {
-      const int m = idx % NP, r = idx / NP, v = r % 2, r2 = r / 2, f = r2 % 3, le = r2 / 3;
-      const long long ee = min(e0 + le, (long long)t.ne - 1);
-      const int nb = t.nbr[(size_t)ee * 3 + f];
-      if (nb >= 0) areg[k] = aux[v * N + (size_t)(nb >> 2) * NP + m];
+    for (int f = 0; f < 3; ++f) {
+      const int nb = lane ? t.nbr[(size_t)e * 3 + f] : -1;
+      const unsigned long long nm = (unsigned long long)(nb >> 2) * NP + m;
+      areg[f] = 0.0;
+#pragma unroll
+      for (int h = 0; h < NH; ++h) {
+        const int v = half * NH + h;
+        nreg[f][h] = R(0);
+        if (nb >= 0 && v < NV) nreg[f][h] = U[v * N + nm];
+      }
+      if (nb >= 0) areg[f] = aux[half * N + nm];
     }
   }
   tri_copy_tab<R, K>(S);
-  tri_load_block<R, K, RAIN>(S, t, e0, U, aux);
 
   // geometry: A = [V1 - V0, V2 - V0], G = A^{-T}
   const double* xv = t.xy + (size_t)e * 6;
   const TriZ g = tri_z(t, e);
   const double a00 = xv[2] - xv[0], a01 = xv[4] - xv[0], a10 = g.dz1, a11 = g.dz2;
   const double det = a00 * a11 - a01 * a10;
-  const double idet = 1.0 / det;
+  const double idet = rcp64(det);
   // the face geometry, for whichever threads take the element's face points
   if (lane && q < 3) {
     const double ex = q == 0 ? a00 : (q == 1 ? a01 - a00 : -a01);
@@ -410,72 +420,73 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
   __syncthreads();
 
   // volume point q: flux along the columns of A^{-T} and sources, weighted
+  Bg b{};
   if (lane) {
     R Uq[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       R s = R(0);
 #pragma unroll
-      for (int m = 0; m < NP; ++m) s += S.c[el][v][m] * T.psi[q][m];
+      for (int k = 0; k < NP; ++k) s += S.c[el][v][k] * T.psi[q][k];
       Uq[v] = s;
     }
     double Tq = 0.0, Rq = 0.0;
 #pragma unroll
-    for (int m = 0; m < NP; ++m) {
-      Tq += S.aux[el][0][m] * T.psid[q][m];
-      Rq += S.aux[el][1][m] * T.psid[q][m];
+    for (int k = 0; k < NP; ++k) {
+      Tq += S.aux[el][0][k] * T.psid[q][k];
+      Rq += S.aux[el][1][k] * T.psid[q][k];
     }
-    double b[5];
-    tri_bg<R, K>(t, T, g.layer, g.z0 + g.dz1 * T.rq[q] + g.dz2 * T.sq[q], b);
+    b = tri_bg<K>(t, g.layer, g.z0 + g.dz1 * T.rq[q] + g.dz2 * T.sq[q]);
     Pt<R, 2, RAIN> p;
-    eval_core<R, 2, RAIN>(a, Uq, Tq, Rq, RAIN ? rho_vs(a, Tq) : 0.0, b[0], b[1], b[2], b[4], b[3] + b[4], p);
+    tri_eval<R, RAIN>(a, Uq, Tq, Rq, b, p);
     const R wq = T.w[q];
-    R Fr[NV], Fs[NV], Gs[NV];
-    flux_dir<R, RAIN>(p, wq * (R)(a11 * idet), wq * (R)(-a01 * idet), Fr);
-    flux_dir<R, RAIN>(p, wq * (R)(-a10 * idet), wq * (R)(a00 * idet), Fs);
+    R P[3 * NV];
+    flux_dir<R, RAIN>(p, wq * (R)(a11 * idet), wq * (R)(-a01 * idet), P);
+    flux_dir<R, RAIN>(p, wq * (R)(-a10 * idet), wq * (R)(a00 * idet), P + NV);
+    R Gs[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) Gs[v] = R(0);
     sources<R, 2, RAIN>(a, Uq, p, Gs);
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-      S.u.pf[el][q][v] = Fr[v];
-      S.u.pf[el][q][NV + v] = Fs[v];
-      S.u.pf[el][q][2 * NV + v] = wq * Gs[v];
-    }
+    for (int v = 0; v < NV; ++v) P[2 * NV + v] = wq * Gs[v];
+#pragma unroll
+    for (int v = 0; v < 3 * NV; ++v) S.u.pf[el][q][v] = P[v];
   }
   __syncthreads();
 
-  // modes: (F, grad psi_m) + (G, psi_m) over the volume points.  NQ = 2 NP,
-  // so thread (el, q) takes mode m = q mod NP for the variables v = par,
-  // par + 2, ... with par = q / NP.
-  static_assert(NQ == 2 * NP, "the Duffy rule has twice as many points as P^k has modes");
-  constexpr int NH = (NV + 1) / 2;
-  const int m = q % NP, par = q / NP;
-  R acc[NH];
+  // modes: (F, grad psi_m) + (G, psi_m), all variables over half of the points
+  R acc[NV];
 #pragma unroll
-  for (int h = 0; h < NH; ++h) acc[h] = R(0);
+  for (int v = 0; v < NV; ++v) acc[v] = R(0);
   if (lane) {
 #pragma unroll 2
-    for (int qq = 0; qq < NQ; ++qq) {
-      const R dr = T.dr[qq][m], ds = T.ds[qq][m], ps = T.psi[qq][m];
+    for (int i = 0; i < NP; ++i) {
+      const int qq = half * NP + i;
+      const R dr = T.g3[qq][m][0], ds = T.g3[qq][m][1], ps = T.g3[qq][m][2];
 #pragma unroll
-      for (int h = 0; h < NH; ++h) {
-        const int v = par + 2 * h;
-        if (v < NV)
-          acc[h] += S.u.pf[el][qq][v] * dr + S.u.pf[el][qq][NV + v] * ds + S.u.pf[el][qq][2 * NV + v] * ps;
-      }
+      for (int v = 0; v < NV; ++v)
+        acc[v] += S.u.pf[el][qq][v] * dr + S.u.pf[el][qq][NV + v] * ds + S.u.pf[el][qq][2 * NV + v] * ps;
     }
+    // each half leaves the partial sums that the other one finishes
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      if ((v >= NH) == (half == 0)) S.f.px[el][m][v] = acc[v];
   }
   __syncthreads();
+  R r[NH];
+  if (lane) {
 #pragma unroll
-  for (int k = 0; k < NNC; ++k) {
-    const int idx = tid + 256 * k;
-    if (idx < EPB * 3 * NV * NP) (&S.u.nb.c[0][0][0][0])[idx] = nreg[k];
-  }
+    for (int h = 0; h < NH; ++h) {
+      const R own = half ? (NH + h < NV ? acc[NH + h < NV ? NH + h : 0] : R(0)) : acc[h];
+      r[h] = half * NH + h < NV ? own + S.f.px[el][m][half * NH + h] : R(0);
+    }
 #pragma unroll
-  for (int k = 0; k < NNA; ++k) {
-    const int idx = tid + 256 * k;
-    if (idx < EPB * 3 * 2 * NP) (&S.u.nb.aux[0][0][0][0])[idx] = areg[k];
+    for (int f = 0; f < 3; ++f) {
+#pragma unroll
+      for (int h = 0; h < NH; ++h)
+        if (half * NH + h < NV) S.u.nb.c[el][f][half * NH + h][m] = nreg[f][h];
+      S.u.nb.aux[el][f][half][m] = areg[f];
+    }
   }
   __syncthreads();
 
@@ -494,31 +505,34 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
     const int nb = t.nbr[(size_t)ef * 3 + f];
     const bool wall = nb < 0;
     const double z = gf.z0 + gf.dz1 * T.rf[f][i] + gf.dz2 * T.sf[f][i];
+    const int lp_ = wall ? gf.layer : t.layer[nb >> 2];
     R Um[NV], Up[NV], Fm[NV], Fp[NV], lm, lp;
     double Tm = 0.0, Rm = 0.0;
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
       R s = R(0);
 #pragma unroll
-      for (int m = 0; m < NP; ++m) s += S.c[fe][v][m] * T.psif[f][i][m];
+      for (int k = 0; k < NP; ++k) s += S.c[fe][v][k] * T.psif[f][i][k];
       Um[v] = s;
+      asm volatile("" : "+v"(Um[v]));
+      __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int m = 0; m < NP; ++m) {
-      Tm += S.aux[fe][0][m] * T.psifd[f][i][m];
-      Rm += S.aux[fe][1][m] * T.psifd[f][i][m];
+    for (int k = 0; k < NP; ++k) {
+      Tm += S.aux[fe][0][k] * T.psifd[f][i][k];
+      Rm += S.aux[fe][1][k] * T.psifd[f][i][k];
     }
-    double b[5];
-    tri_bg<R, K>(t, T, gf.layer, z, b);
-    const double rvsm = RAIN ? rho_vs(a, Tm) : 0.0;
     {
       Pt<R, 2, RAIN> pm;
-      eval_core<R, 2, RAIN>(a, Um, Tm, Rm, rvsm, b[0], b[1], b[2], b[4], b[3] + b[4], pm);
+      tri_eval<R, RAIN>(a, Um, Tm, Rm, tri_bg<K>(t, gf.layer, z), pm);
       flux_dir<R, RAIN>(pm, nx, nz, Fm);
       lm = speed_dir<R, RAIN>(pm, nx, nz);
     }
+    // (the neighbour's LDS reads wait here: in flight with the own ones they
+    // would need more registers than the kernel has)
+    __builtin_amdgcn_sched_barrier(0);
     {
-      Pt<R, 2, RAIN> pp;
+      double Tp = Tm, Rp = Rm;
       if (wall) {
         // slip wall: m+ = m- - 2 (m-.n) n, everything else copied
 #pragma unroll
@@ -526,27 +540,28 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
         const R mn = Um[V::M0] * nx + Um[V::M0 + 1] * nz;
         Up[V::M0] = Um[V::M0] - R(2) * mn * nx;
         Up[V::M0 + 1] = Um[V::M0 + 1] - R(2) * mn * nz;
-        eval_core<R, 2, RAIN>(a, Up, Tm, Rm, rvsm, b[0], b[1], b[2], b[4], b[3] + b[4], pp);
       } else {
         // the neighbour's trace at its face point K - i (the same physical point)
-        const int e2 = nb >> 2, f2 = nb & 3, i2 = K - i;
-        double Tp = 0.0, Rp = 0.0;
+        const int f2 = nb & 3, i2 = K - i;
+        Tp = 0.0;
+        Rp = 0.0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
           R s = R(0);
 #pragma unroll
-          for (int m = 0; m < NP; ++m) s += S.u.nb.c[fe][f][v][m] * T.psif[f2][i2][m];
+          for (int k = 0; k < NP; ++k) s += S.u.nb.c[fe][f][v][k] * T.psif[f2][i2][k];
           Up[v] = s;
+          asm volatile("" : "+v"(Up[v]));
+          __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
-        for (int m = 0; m < NP; ++m) {
-          Tp += S.u.nb.aux[fe][f][0][m] * T.psifd[f2][i2][m];
-          Rp += S.u.nb.aux[fe][f][1][m] * T.psifd[f2][i2][m];
+        for (int k = 0; k < NP; ++k) {
+          Tp += S.u.nb.aux[fe][f][0][k] * T.psifd[f2][i2][k];
+          Rp += S.u.nb.aux[fe][f][1][k] * T.psifd[f2][i2][k];
         }
-        double b2[5];
-        tri_bg<R, K>(t, T, tri_z(t, e2).layer, z, b2);
-        eval_core<R, 2, RAIN>(a, Up, Tp, Rp, RAIN ? rho_vs(a, Tp) : 0.0, b2[0], b2[1], b2[2], b2[4], b2[3] + b2[4], pp);
       }
+      Pt<R, 2, RAIN> pp;
+      tri_eval<R, RAIN>(a, Up, Tp, Rp, tri_bg<K>(t, lp_, z), pp);
       flux_dir<R, RAIN>(pp, nx, nz, Fp);
       lp = speed_dir<R, RAIN>(pp, nx, nz);
     }
@@ -554,7 +569,16 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
     const R wgt = S.fn[fe][f][2] * T.wf[i];
 #pragma unroll
     for (int v = 0; v < NV; ++v)
-      S.ff[fe][j][v] = wgt * (R(0.5) * (Fm[v] + Fp[v]) + R(0.5) * L * (Um[v] - Up[v]));
+      S.f.ff[fe][j][v] = wgt * (R(0.5) * (Fm[v] + Fp[v]) + R(0.5) * L * (Um[v] - Up[v]));
+  }
+  // the mode threads' share of U0, in flight while the faces finish
+  R u0[NH];
+  if (MODE != 0 && c0 != 0.0 && lane) {
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int v = half * NH + h;
+      if (v < NV) u0[h] = U0[v * N + (size_t)e * NP + m];
+    }
   }
   __syncthreads();
 
@@ -564,36 +588,36 @@ __global__ void __launch_bounds__(256) tri_stage_kernel(KArgs a, TriArgs t, cons
     for (int j = 0; j < 3 * NF; ++j) {
       const R ps = T.psif[j / NF][j % NF][m];
 #pragma unroll
-      for (int h = 0; h < NH; ++h) {
-        const int v = par + 2 * h;
-        if (v < NV) acc[h] -= S.ff[el][j][v] * ps;
-      }
+      for (int h = 0; h < NH; ++h)
+        if (half * NH + h < NV) r[h] -= S.f.ff[el][j][half * NH + h] * ps;
     }
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
-      const int v = par + 2 * h;
+      const int v = half * NH + h;
       if (v < NV) {
-        R x = acc[h];
+        R x = r[h];
         if (MODE != 0) {
-          x = (R)c1 * S.c[el][v][m] + (R)c2dt * acc[h];
-          if (c0 != 0.0) x += (R)c0 * U0[v * N + (size_t)e * NP + m];
+          x = (R)c1 * S.c[el][v][m] + (R)c2dt * r[h];
+          if (c0 != 0.0) x += (R)c0 * u0[h];
+          S.u.cd[el][v][m] = (double)x;
         }
-        S.c[el][v][m] = x;
+        if (act) out[v * N + (size_t)e * NP + m] = x;
       }
     }
   }
-  __syncthreads();
-  for (int idx = tid; idx < NV * EPB * NP; idx += blockDim.x) {
-    const int v = idx / (EPB * NP), r = idx - v * (EPB * NP);
-    const int le = r / NP, m = r - le * NP;
-    if (e0 + le < t.ne) out[v * N + (size_t)(e0 + le) * NP + m] = S.c[le][v][m];
-  }
   if constexpr (MODE == 2) {
-    // the split of the updated state for the next stage (Section 3.4)
-    int it = 0, bd = 0;
-    if (lane) tri_split_at<R, K, RAIN>(a, t, S, el, q, g, &it, &bd);
+    // the split of the updated state for the next stage (Section 3.4), from the
+    // projected T of the stage input
     __syncthreads();
-    if (lane) tri_project_split<R, K, RAIN>(S, el, q, e, act, Tn, Rn);
+    int it = 0, bd = 0;
+    if (lane) {
+      double Tg = 0.0;
+#pragma unroll
+      for (int k = 0; k < NP; ++k) Tg += S.aux[el][0][k] * T.psid[q][k];
+      tri_split_at<R, K, RAIN>(a, S, el, q, b, Tg, &it, &bd);
+    }
+    __syncthreads();
+    if (lane) tri_project_split<R, K, RAIN>(S, el, m, half, e, act, Tn, Rn);
     record_stats(a, seen, act ? it : 0, act ? bd : 0);
   }
 }

@@ -111,8 +111,9 @@ inline void fill_tab(TriTab<R, K>& T) {
       dubiner(K, r, s, psi, dr, ds);
       for (int m = 0; m < NP; ++m) {
         T.psi[q][m] = (R)psi[m];
-        T.dr[q][m] = (R)dr[m];
-        T.ds[q][m] = (R)ds[m];
+        T.g3[q][m][0] = (R)dr[m];
+        T.g3[q][m][1] = (R)ds[m];
+        T.g3[q][m][2] = (R)psi[m];
         T.psid[q][m] = psi[m];
       }
       T.w[q] = (R)w;
@@ -135,13 +136,20 @@ inline void fill_tab(TriTab<R, K>& T) {
       T.sf[f][i] = s;
     }
   }
-  for (int i = 0; i < NF; ++i) {
-    T.wf[i] = (R)(0.5 * wa[i]);
-    T.xg[i] = xa[i];
-    double d = 1.0;
-    for (int j = 0; j < NF; ++j)
-      if (j != i) d *= xa[i] - xa[j];
-    T.lagd[i] = 1.0 / d;
+  for (int i = 0; i < NF; ++i) T.wf[i] = (R)(0.5 * wa[i]);
+}
+
+// Coefficients c_i of xi^i of the polynomial of degree k through (x_i, f_i), i
+// = 0..k: Newton's divided differences, expanded.
+inline void monomials(int k, const double* x, const double* f, double* c) {
+  double d[8];
+  for (int i = 0; i <= k; ++i) d[i] = f[i];
+  for (int o = 1; o <= k; ++o)
+    for (int i = k; i >= o; --i) d[i] = (d[i] - d[i - 1]) / (x[i] - x[i - o]);
+  for (int i = 0; i <= k; ++i) c[i] = 0.0;
+  for (int i = k; i >= 0; --i) {            // c <- c (xi - x_i) + d_i
+    for (int j = k; j > 0; --j) c[j] = c[j - 1] - x[i] * c[j];
+    c[0] = d[i] - x[i] * c[0];
   }
 }
 
