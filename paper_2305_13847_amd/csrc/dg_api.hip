@@ -85,7 +85,7 @@ struct dg_handle {
   std::vector<MemberDesc> mem;
   std::vector<Item> items;
   std::vector<int> item_off;     // first item of each member (+ total)
-  std::vector<Item> bricks;      // Q3 hexahedra, Lobatto basis: the stage kernel's items
+  std::vector<Item> bricks;      // Q3 hexahedra: the stage kernels' items
   std::vector<int> hoff;         // first background index of each member (+ total)
   std::vector<char> bg_set;
   long long etot = 0, nnodes = 0;
@@ -416,7 +416,11 @@ static void build_items(dg_handle* h, int epb, int order = -1) {
   h->items.clear();
   h->item_off.clear();
   h->bricks.clear();
-  const bool q3 = h->dim == 3 && h->order == 3 && h->P.basis == DG_BASIS_LOBATTO;
+  // (Gauss basis: the brick kernel addresses the trace buffers with 32-bit byte
+  // offsets, 96 FP64 values per element; larger handles take the block kernel)
+  long long etot = 0;
+  for (const MemberDesc& md : h->mem) etot += md.ne;
+  const bool q3 = h->dim == 3 && h->order == 3 && (h->P.basis == DG_BASIS_LOBATTO || etot * 96 * 8 < (1LL << 32));
   for (int m = 0; m < h->nmembers; ++m) {
     h->item_off.push_back((int)h->items.size());
     const MemberDesc& md = h->mem[m];

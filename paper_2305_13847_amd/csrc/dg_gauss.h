@@ -8,6 +8,10 @@
 // (k+1 nodes per side), and the face flux is lifted back to every node of
 // that line.
 //
+// This file's kernel serves every order and dimension but Q3 hexahedra, which
+// dg_gauss_q3.h does by bricks of elements (and those too on handles whose trace
+// buffers outgrow its 32-bit offsets).
+//
 // A block owns a work item of EPB elements, one thread per node:
 //   1. node pass: the point state, its fluxes (LDS) and the perturbation, T
 //      and rho_v (LDS), then the volume term and the sources;

@@ -5,6 +5,7 @@
 #include "dg_launch.h"
 #include "dg_q3.h"
 #include "dg_gauss.h"
+#include "dg_gauss_q3.h"
 #include "dg_sip.h"
 #include "dg_vjp.h"
 
@@ -133,6 +134,19 @@ bool LaunchGauss<R>::rhs_gauss(const KArgs& a, LaunchCfg lc, int K, int D, int r
 #define DGM_RHS(M)                                                                                \
 hipLaunchKernelGGL((rhs_gauss_kernel<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, auxT, \
                    auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
+    if constexpr (K_ == 3 && D_ == 3) {
+      if (a.nbricks > 0) {
+        const dim3 bgrid(grid_for_items(a.nbricks)), bblock(128 * q3_brick_rows<R>());
+#define DGM_GQ3(M)                                                                                    \
+  hipLaunchKernelGGL((rhs_gauss_q3_kernel<R, R_, M>), bgrid, bblock, 0, s, a, (const R*)U, auxT, auxS, \
+                     (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
+        if (mode == 0) DGM_GQ3(0);
+        else if (mode == 1) DGM_GQ3(1);
+        else DGM_GQ3(2);
+#undef DGM_GQ3
+        return;
+      }
+    }
     if (mode == 0) DGM_RHS(0);
     else if (mode == 1) DGM_RHS(1);
     else DGM_RHS(2);
