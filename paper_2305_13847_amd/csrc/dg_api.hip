@@ -147,6 +147,10 @@ struct dg_handle {
   long long t_n[4] = {0, 0, 0, 0};
 };
 
+// Artificial diffusion on Q3 hexahedra is part of the stage kernel; the other
+// shapes run it as kernels of its own ahead of each right-hand side.
+static bool sip_fused(const dg_handle* h) { return h->order == 3 && h->dim == 3; }
+
 static const int kEvPairs = 2048;
 
 static void timing_flush(dg_handle* h) {
@@ -599,9 +603,13 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   }
   h->sip = p->sip_gamma > 0.0;
   if (h->sip) {
-    ok = ok && A((void**)&h->sip_aK, sizeof(double) * 2 * eoff);
-    ok = ok && A((void**)&h->sip_av, sizeof(double) * 2 * nvert_tot);
-    ok = ok && A(&h->sip_out, h->state_bytes);
+    // (the fused kernel reads one state's alpha_K while it writes the next's)
+    const bool fused = sip_fused(h);
+    ok = ok && A((void**)&h->sip_aK, sizeof(double) * (fused ? 4 : 2) * eoff);
+    if (!fused) {
+      ok = ok && A((void**)&h->sip_av, sizeof(double) * 2 * nvert_tot);
+      ok = ok && A(&h->sip_out, h->state_bytes);
+    }
   }
   ok = ok && A((void**)&h->dt_d, sizeof(double) * nmembers);
   ok = ok && A((void**)&h->partial, sizeof(double) * 3 * h->items_cap);
@@ -820,8 +828,9 @@ static bool do_split(dg_handle* h, const void* U, const double* guess, double* o
 }
 
 // dt: time steps of the members (null: c2 holds the only one)
-// tin / tout: the Gauss basis' trace buffers of the stage state (read) and of
-// the new state (written in mode 2)
+// tin / tout: the Gauss basis' trace buffers, or the element viscosities of the
+// fused diffusion, of the stage state (read) and of the new state (written in
+// mode 2)
 static bool do_rhs(dg_handle* h, int mode, const void* U, const double* aT, const double* aS, void* out,
                    const void* U0, double c0, double c1, double c2, hipStream_t s,
                    double* oT = nullptr, double* oS = nullptr, int flags = 0, int tin = 0, int tout = 1,
@@ -831,6 +840,10 @@ static bool do_rhs(dg_handle* h, int mode, const void* U, const double* aT, cons
   const LaunchCfg lc = launch_cfg(h);
   KArgs ka = h->ka;
   ka.walk_rev = rev;
+  if (h->sip && sip_fused(h)) {
+    ka.sip_aK = h->sip_aK + (size_t)tin * 2 * ka.etot;
+    ka.sip_aK_out = h->sip_aK + (size_t)tout * 2 * ka.etot;
+  }
   if (h->P.basis == DG_BASIS_GAUSS) {
     ka.tr_u_in = h->tr_u[tin];
     ka.tr_a_in = h->tr_a[tin];
@@ -866,21 +879,18 @@ static void do_gauss_trace(dg_handle* h, const void* U, const double* aT, const 
     Launch<float>::gauss_trace(ka, lc, h->order, h->dim, h->rain, U, aT, aS, s);
 }
 
-// artificial diffusion of the state U into the handle's tendency buffer
-// alpha = false: the stage that produced U already wrote its alpha_K
-static void do_sip(dg_handle* h, const void* U, hipStream_t s, bool alpha = true) {
+// Artificial diffusion of the state U into the handle's tendency buffer.  Where
+// the stage kernel forms the tendency itself, only alpha_K of a state that no
+// stage produced (alpha = true), into the first of its two buffers.
+static void do_sip(dg_handle* h, const void* U, hipStream_t s, bool alpha) {
+  const bool fused = sip_fused(h);
+  if (fused && !alpha) return;
   KTimer kt(h, DG_K_OTHER, s);
   const LaunchCfg lc = launch_cfg(h);
   if (h->prec == DG_FP64)
-    Launch<double>::sip(h->ka, lc, h->order, h->dim, h->rain, h->nmembers, h->nvert.data(), U, alpha, s);
+    Launch<double>::sip(h->ka, lc, h->order, h->dim, h->rain, h->nmembers, h->nvert.data(), U, s);
   else
-    Launch<float>::sip(h->ka, lc, h->order, h->dim, h->rain, h->nmembers, h->nvert.data(), U, alpha, s);
-}
-
-// The Q3 hexahedral stage kernel (Lobatto basis) can leave alpha_K of the
-// state it writes for the next stage's diffusion (kSipAlpha).
-static bool stage_writes_alpha(const dg_handle* h) {
-  return h->sip && h->P.basis == DG_BASIS_LOBATTO && h->order == 3 && h->dim == 3;
+    Launch<float>::sip(h->ka, lc, h->order, h->dim, h->rain, h->nmembers, h->nvert.data(), U, s);
 }
 
 extern "C" dg_status dg_rhs(dg_handle* h, const void* U, void* dUdt, hipStream_t s) {
@@ -889,7 +899,7 @@ extern "C" dg_status dg_rhs(dg_handle* h, const void* U, void* dUdt, hipStream_t
   if (!U || !dUdt) return fail(DG_EINVAL, "null state pointer");
   if (U == dUdt) return fail(DG_EINVAL, "U and dUdt must not alias");
   if (!do_split(h, U, nullptr, h->auxT, h->auxS, nullptr, 0, s)) return fail(DG_EUNSUPPORTED, "no kernel for this shape");
-  if (h->sip) do_sip(h, U, s);
+  if (h->sip) do_sip(h, U, s, true);
   do_gauss_trace(h, U, h->auxT, h->auxS, 0, s);
   do_rhs(h, 0, U, h->auxT, h->auxS, dUdt, nullptr, 0, 0, 0, s, nullptr, nullptr, h->sip ? kSip : 0, 0, 1);
   HIP_TRY(hipGetLastError());
@@ -1016,10 +1026,9 @@ static dg_status rk_one(dg_handle* h, void* U, const Dt& dt, bool first, int* cu
     // the last stage ends the step and applies the sponge
     const bool last = st == ns - 1;
     const int flags = (last && (step & 3) == 3 ? kRefreshRvs : 0) | (last && h->sponge ? kSponge : 0) |
-                      (h->sip ? kSip : 0) | (stage_writes_alpha(h) ? kSipAlpha : 0);
-    // alpha_K of the stage input: written by the previous stage kernel,
-    // except at the first stage of a call
-    if (h->sip) do_sip(h, in, s, !(stage_writes_alpha(h) && !(first && st == 0)));
+                      (h->sip ? kSip : 0);
+    // (the fused kernel also writes alpha_K of its new state for the next stage)
+    if (h->sip) do_sip(h, in, s, first && st == 0);
     // every other stage walks its elements in reverse: it starts on what the
     // previous stage wrote last, which the last-level cache still holds.
     // Only states well beyond the L2s take this order (a small state, held

@@ -101,6 +101,7 @@ struct KArgs {
   double Dm[kMaxP1 * kMaxP1];
   double xn[kMaxP1];
   double* sip_aK;
+  double* sip_aK_out;              // (Q3 hexahedra) the new state's, written by MODE 2
   double* sip_av;
   void* sip_out;
   long long nvert;

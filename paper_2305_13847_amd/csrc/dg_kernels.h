@@ -83,32 +83,29 @@ __host__ __device__ inline int grid_for_items(int nitems) { return ((nitems + 7)
 // flags of a stage launch
 constexpr int kRefreshRvs = 1;   // store a fresh rho_vs(T) evaluation (anchors later splits)
 constexpr int kSponge = 2;       // the stage ends a time step: apply the sponge
-// the diffusive tendency in a.sip_out is added to the right-hand side
+// the diffusive tendency is part of the right-hand side: read from a.sip_out,
+// or (Q3 hexahedra) formed by the stage kernel itself
 constexpr int kSip = 4;
-// (Q3 stage kernel) the element viscosity alpha_K of the new state is written
-// to a.sip_aK, so the next stage's diffusion need not compute it
-constexpr int kSipAlpha = 8;
 
 // One node's share of the element viscosity of Section 3.5: with quadrature
-// weight w, w |u|^2 and w |u - v_r e_z|^2 (full densities rd, rm, rr, momentum
-// m).  sip_alpha_kernel and the Q3 stage epilogue both call this, and both
+// weight w, w |u|^2 and w |u - v_r e_z|^2 (full density of rain rr, inverse
+// density irho, momentum m).  sip_alpha_kernel and the Q3 stage epilogue both call this, and both
 // sum the shares over the element in the same pairwise order, so alpha_K has
 // the same bits whichever kernel formed it.
 template <int D, int RAIN>
-__device__ __forceinline__ void sip_alpha_terms(const KArgs& a, double w, double rd, double rm, double rr,
+__device__ __forceinline__ void sip_alpha_terms(const KArgs& a, double w, double rr, double irho,
                                                 const double* m, double& s0, double& s1) {
-  const double irho = 1.0 / (rd + rm + rr);
   double vr = 0.0;
   if (RAIN) vr = a.vr_mode == 0 ? a.vr_const : (rr > 0.0 ? a.vr_pref * pow(rr, 0.125) : 0.0);
-  s0 = 0.0;
-  s1 = 0.0;
+  double h = 0.0;   // the horizontal part is common to both
 #pragma unroll
-  for (int i = 0; i < D; ++i) {
+  for (int i = 0; i < D - 1; ++i) {
     const double ui = m[i] * irho;
-    const double ur = (i == D - 1) ? ui - vr : ui;
-    s0 += w * ui * ui;
-    s1 += w * ur * ur;
+    h = fma(ui, ui, h);
   }
+  const double uz = m[D - 1] * irho, ur = uz - vr;
+  s0 = w * fma(uz, uz, h);
+  s1 = w * fma(ur, ur, h);
 }
 
 // The sponge at the end of a step (Section 3.6):
@@ -527,7 +524,7 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const Bg& bg, int
                                                double* Snew = nullptr, double wq = 0.0,
                                                double* alpha_terms = nullptr) {
   // (Unew, Tnew, Snew), when given, receive the stored new state and its
-  // stored (T, rho_vs); alpha_terms, when given with kSipAlpha, the node's
+  // stored (T, rho_vs); alpha_terms, when given, the node's
   // shares of the new state's element viscosity (weight wq)
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
@@ -550,12 +547,13 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const Bg& bg, int
   if (flags & kSponge) sponge_point<R, D, RAIN>(a, iz, Un);
 #pragma unroll
   for (int v = 0; v < NV; ++v) st(out, N, v, g, Un[v]);
-  if (alpha_terms && (flags & kSipAlpha)) {
+  if (alpha_terms) {
     double m[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) m[i] = (double)Un[V::M0 + i];
-    sip_alpha_terms<D, RAIN>(a, wq, bg.rd + (double)Un[V::RD], bg.rm + (double)Un[V::RM],
-                             RAIN ? bg.rr + (double)Un[V::RR] : 0.0, m, alpha_terms[0], alpha_terms[1]);
+    const double rr = RAIN ? bg.rr + (double)Un[V::RR] : 0.0;
+    const double irho = rcp64((bg.rd + (double)Un[V::RD]) + (bg.rm + (double)Un[V::RM]) + rr);
+    sip_alpha_terms<D, RAIN>(a, wq, rr, irho, m, alpha_terms[0], alpha_terms[1]);
   }
   if (Unew) {
 #pragma unroll

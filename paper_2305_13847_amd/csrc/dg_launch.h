@@ -29,7 +29,7 @@ struct LaunchPoint {
   // artificial diffusion: alpha_K (unless the previous stage wrote it),
   // vertex means (all members), tendency
   static bool sip(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int nmembers, const long long* nvert,
-                  const void* U, bool alpha, hipStream_t s);
+                  const void* U, hipStream_t s);
   static bool sponge_vjp(const KArgs& a, LaunchCfg lc, int K, int D, int rain, const void* W, void* Wp,
                          hipStream_t s);
   static bool mass(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int item0, int nitems,

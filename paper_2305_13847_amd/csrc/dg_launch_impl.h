@@ -51,17 +51,17 @@ bool LaunchPoint<R>::split(const KArgs& a, LaunchCfg lc, int K, int D, int rain,
 
 template <typename R>
 bool LaunchPoint<R>::sip(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int nmembers, const long long* nvert,
-    const void* U, bool alpha, hipStream_t s) {
+    const void* U, hipStream_t s) {
   return dispatch_shape(K, D, rain, [&](auto k, auto d, auto r) {
     constexpr int K_ = decltype(k)::value, D_ = decltype(d)::value, R_ = decltype(r)::value;
     // one block per work item whatever the persistence setting (the SIP
     // kernels have no item loop)
     const dim3 grid(grid_for_items(a.nitems));
-    if (alpha)
-      hipLaunchKernelGGL((sip_alpha_kernel<R, K_, D_, R_>), grid, dim3(lc.threads), 0, s, a,
-                         (const R*)U);
-    hipLaunchKernelGGL((sip_vertex_kernel<D_>), dim3((unsigned)((a.nvert + 127) / 128)), dim3(128), 0, s, a);
-    hipLaunchKernelGGL((sip_kernel<R, K_, D_, R_>), grid, dim3(lc.threads), 0, s, a, (const R*)U);
+    hipLaunchKernelGGL((sip_alpha_kernel<R, K_, D_, R_>), grid, dim3(lc.threads), 0, s, a, (const R*)U);
+    if constexpr (K_ != 3 || D_ != 3) {   // (Q3 hexahedra: the stage kernel does the rest)
+      hipLaunchKernelGGL((sip_vertex_kernel<D_>), dim3((unsigned)((a.nvert + 127) / 128)), dim3(128), 0, s, a);
+      hipLaunchKernelGGL((sip_kernel<R, K_, D_, R_>), grid, dim3(lc.threads), 0, s, a, (const R*)U);
+    }
   });
 }
 
@@ -104,18 +104,21 @@ hipLaunchKernelGGL((KER<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, a
       // Q3 hexahedra: one block per brick whatever the launch geometry of the
       // other kernels
       grid = dim3(grid_for_items(a.nbricks));
-#define DGM_Q3(M)                                                                                   \
-  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M>), grid, dim3(128 * q3_brick_rows<R>()), 0, s, a,        \
+#define DGM_Q3(M, SIP)                                                                              \
+  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M, SIP>), grid, dim3(128 * q3_brick_rows<R>()), 0, s, a,   \
                      (const R*)U, auxT, auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
-      if (mode == 0) DGM_Q3(0);
-      else if (mode == 1) DGM_Q3(1);
-      else DGM_Q3(2);
+      if (flags & kSip) {
+        if (mode == 0) DGM_Q3(0, 1);
+        else DGM_Q3(2, 1);
+      } else {
+        if (mode == 0) DGM_Q3(0, 0);
+        else DGM_Q3(2, 0);
+      }
 #undef DGM_Q3
     } else if (mode != 2 || !persist) {
       // rhs_kernel takes one work item per block: the full grid
       grid = dim3(grid_for_items(a.nitems));
       if (mode == 0) DGM_RHS(rhs_kernel, 0);
-      else if (mode == 1) DGM_RHS(rhs_kernel, 1);
       else DGM_RHS(rhs_kernel, 2);
     } else
       hipLaunchKernelGGL((rhs_kernel_persistent<R, K_, D_, R_, 2>), grid, block, 0, s, a, a_dev, (const R*)U,
@@ -141,14 +144,12 @@ hipLaunchKernelGGL((rhs_gauss_kernel<R, K_, D_, R_, M>), grid, block, 0, s, a, (
   hipLaunchKernelGGL((rhs_gauss_q3_kernel<R, R_, M>), bgrid, bblock, 0, s, a, (const R*)U, auxT, auxS, \
                      (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
         if (mode == 0) DGM_GQ3(0);
-        else if (mode == 1) DGM_GQ3(1);
         else DGM_GQ3(2);
 #undef DGM_GQ3
         return;
       }
     }
     if (mode == 0) DGM_RHS(0);
-    else if (mode == 1) DGM_RHS(1);
     else DGM_RHS(2);
 #undef DGM_RHS
   });

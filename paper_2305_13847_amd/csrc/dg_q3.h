@@ -146,15 +146,129 @@ __device__ __forceinline__ int q3_step(int c, int n, int side) {
   return side ? (c == n - 1 ? 1 - n : 1) : (c == 0 ? n - 1 : -1);
 }
 
+// ---------------------------------------------------------------------------
+// Artificial diffusion (Section 3.5, the form in dg_sip.h) inside the stage
+// kernel: the tendency starts from S = -M^{-1} A_h instead of zero, in the tiles
+// that the fluxes use afterwards.
+//   1. the vertex means of alpha_K (27 elements share this one's vertices) and
+//      the Q1 viscosity at the nodes;
+//   2. the viscous fluxes -alpha G_j to LDS, their volume term;
+//   3. at each face point alpha [U] and alpha ({G_j} - tau [U]): the outer faces'
+//      neighbour gradients from their lines in memory, the inner ones' from the
+//      partner's tile;
+//   4. both lifted to the nodes of the point's line.
+// A separate kernel wrote the tendency and the stage kernel read it (165 MB and
+// 35 us a stage at 48 x 40 x 24 in FP32), loaded the state and its neighbours a
+// second time, and took the vertex means from a third kernel.  48 x 40 x 24 with
+// rain, two SSPRK(4,3) steps: FP32 1.82 -> 1.53 ms, FP64 3.9 -> 3.1; 5 x 4 x 3
+// (launches) 0.2 -> 0.12.  Bound by VALU issue (70 % busy, 1690 instructions per
+// element against 800 without diffusion) at 4 wavefronts per SIMD.
+// ---------------------------------------------------------------------------
+
+// The neighbour's line behind an outer face point, from the face inwards.
+template <typename R, int RAIN>
+struct SipLine {
+  R u[4][Vars<3, RAIN>::NV];
+};
+
+template <typename R, int RAIN>
+__device__ __forceinline__ void sip_line_load(const R* __restrict__ U, unsigned N, const FaceTask& f,
+                                              SipLine<R, RAIN>& l) {
+  const int str = f.J == 0 ? 1 : (f.J == 1 ? 4 : 16);
+  // (on a wall gn is the own node: inwards is the other way; the values are not used)
+  const int step = (f.side != 0) != f.wall ? str : -str;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+#pragma unroll
+    for (int v = 0; v < Vars<3, RAIN>::NV; ++v) l.u[b][v] = ld(U, N, v, f.gn + (unsigned)(b * step));
+  }
+}
+
+// alpha [U] and alpha ({G_J} - tau_J [U]) at a face point, [U] lower minus upper
+// (a0, a1: the viscosities there).
+template <typename R, int RAIN>
+struct SipPoint {
+  R j[Vars<3, RAIN>::NV], q[Vars<3, RAIN>::NV];
+};
+
+template <typename R, int RAIN>
+__device__ __forceinline__ void sip_outer(const MemberDesc& md, const FaceTask& f, const SipLine<R, RAIN>& l,
+                                          const R* Dm, const R (*sF)[Vars<3, RAIN>::NV][64], const R (*sU)[64],
+                                          R a0, R a1, SipPoint<R, RAIN>& p) {
+  using V = Vars<3, RAIN>;
+  const int J = f.J;
+  const R dj = (R)(J == 0 ? md.two_over_h[0] : (J == 1 ? md.two_over_h[1] : md.two_over_h[2]));
+  const R ct = (R)(J == 0 ? md.sip_tau[0] : (J == 1 ? md.sip_tau[1] : md.sip_tau[2]));
+  // the end rows of D are each other's negative mirror image
+  const R sg = f.side ? dj : -dj;
+  R w[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) w[b] = sg * Dm[b];
+#pragma unroll
+  for (int v = 0; v < V::NV; ++v) {
+    const R al = RAIN && v == V::RR ? a1 : a0;
+    R gn = w[0] * l.u[0][v];
+#pragma unroll
+    for (int b = 1; b < 4; ++b) gn = fma(w[b], l.u[b][v], gn);
+    const R uo = sU[v][f.n], d = uo - l.u[0][v];
+    const R ju = al * (f.side ? d : -d);
+    const R q = R(0.5) * (al * gn - sF[J][v][f.n]) - ct * ju;
+    p.j[v] = f.wall ? R(0) : ju;
+    p.q[v] = f.wall ? R(0) : q;
+  }
+}
+
+// The viscosity of both fields at this lane's node.  sK: scratch of 70 doubles.
+template <typename R, int RAIN>
+__device__ __forceinline__ void sip_viscosity(const KArgs& a, const Item& item, int ex, int ey, int ez, int lane, int li,
+                                              int lj, int ll, double k0, double k1, double* sK, R& al0, R& al1) {
+  if (lane < 27) {
+    sK[lane] = k0;
+    if (RAIN) sK[27 + lane] = k1;
+  }
+  wave_lds_sync();
+  if (lane < (RAIN ? 16 : 8)) {
+    const int cx = lane & 1, cy = (lane >> 1) & 1, cz = (lane >> 2) & 1;
+    const double* k = sK + (lane >> 3) * 27 + 13 + cx + 3 * cy + 9 * cz;
+    double s = 0.0;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) s += k[-((c & 1) + 3 * ((c >> 1) & 1) + 9 * (c >> 2))];
+    // a vertex on a wall is shared by half as many elements (their entries are 0)
+    const bool wx = item.bc[0] == 1 && ex == (cx ? item.n[0] - 1 : 0);
+    const bool wy = item.bc[1] == 1 && ey == (cy ? item.n[1] - 1 : 0);
+    const bool wz = item.bc[2] == 1 && ez == (cz ? item.n[2] - 1 : 0);
+    s *= 0.125 * (wx ? 2.0 : 1.0) * (wy ? 2.0 : 1.0) * (wz ? 2.0 : 1.0);
+    sK[54 + lane] = s;
+  }
+  wave_lds_sync();
+  const double p1 = 0.5 * (1.0 + a.xn[1]), p2 = 0.5 * (1.0 + a.xn[2]);
+  auto up = [&](int i) { return i == 0 ? 0.0 : (i == 1 ? p1 : (i == 2 ? p2 : 1.0)); };
+  const double px = up(li), py = up(lj), pz = up(ll);
+  auto at = [&](const double* v) {
+    double r[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const double y0 = (1.0 - px) * v[4 * c] + px * v[4 * c + 1];
+      const double y1 = (1.0 - px) * v[4 * c + 2] + px * v[4 * c + 3];
+      r[c] = (1.0 - py) * y0 + py * y1;
+    }
+    return (R)((1.0 - pz) * r[0] + pz * r[1]);
+  };
+  al0 = at(sK + 54);
+  al1 = RAIN ? at(sK + 62) : al0;
+  wave_lds_sync();
+}
+
 // FP32: 2 x 2 bricks, 5 wavefronts per SIMD (96 registers; the LDS of five
 // blocks fills a CU).  FP64: the tiles are twice as large, and blocks of four
 // would leave room for two (8 wavefronts per CU; 31 x 33 x 17, two steps: 609
 // us): 2 x 1 bricks, five blocks.
-template <typename R>
-constexpr int q3_min_waves() { return sizeof(R) == 4 ? 5 : 2; }
+template <typename R, int SIP>
+constexpr int q3_min_waves() { return sizeof(R) == 4 ? (SIP ? 4 : 5) : 2; }
 
-template <typename R, int RAIN, int MODE>
-__global__ void __launch_bounds__(128 * q3_brick_rows<R>()) __attribute__((amdgpu_waves_per_eu(q3_min_waves<R>())))
+template <typename R, int RAIN, int MODE, int SIP>
+__global__ void __launch_bounds__(128 * q3_brick_rows<R>())
+__attribute__((amdgpu_waves_per_eu(q3_min_waves<R, SIP>())))
 rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
               const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
               const double* __restrict__ dt_m, double c0, double c1, double c2, double* __restrict__ oT,
@@ -173,8 +287,8 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   // heights of the neighbours below and above: the same for its elements, and
   // each wavefront writes all of it (the same values) before it reads
   __shared__ double2 sB[6][kBgStride / 2];
-  __shared__ R sD[P1 * P1];
-  if (threadIdx.x < P1 * P1) sD[threadIdx.x] = (R)a.Dhat[threadIdx.x];
+  __shared__ R sD[P1 * P1], sDm[SIP ? P1 * P1 : 1];
+  if (!SIP && threadIdx.x < P1 * P1) sD[threadIdx.x] = (R)a.Dhat[threadIdx.x];
 
   const ItemWalk walk(a.nbricks, a.walk_rev);
   const int it_ = walk.item(0);
@@ -222,6 +336,159 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   R Uq[NV], Rv[NV];
   double T = 300.0, rvs = 0.0;
   Pair<R, D, RAIN> nb0, nb1;
+#pragma unroll
+  for (int v = 0; v < NV; ++v) Rv[v] = R(0);
+  if constexpr (SIP) {
+    R al0 = R(0), al1 = R(0);
+    R Dm[P1];
+#pragma unroll
+    for (int b = 0; b < P1; ++b) Dm[b] = (R)a.Dm[b];
+    SipLine<R, RAIN> l0;
+    if (act) {
+      // alpha_K of the elements around this one (0 beyond a wall)
+      double k0 = 0.0, k1 = 0.0;
+      if (lane < 27) {
+        const int oz = lane / 9, oy = (lane - 9 * oz) / 3, ox = lane - 9 * oz - 3 * oy;
+        int cx = ex + ox - 1, cy = ey + oy - 1, cz = ez + oz - 1;
+        const bool in = (b0 == 0 || (cx >= 0 && cx < n0)) && (b1 == 0 || (cy >= 0 && cy < n1)) &&
+                        (b2 == 0 || (cz >= 0 && cz < n2));
+        cx = cx < 0 ? cx + n0 : (cx >= n0 ? cx - n0 : cx);
+        cy = cy < 0 ? cy + n1 : (cy >= n1 ? cy - n1 : cy);
+        cz = cz < 0 ? cz + n2 : (cz >= n2 ? cz - n2 : cz);
+        if (in) {
+          const unsigned ek = (unsigned)(item.eoff + cx + n0 * (cy + n1 * cz));
+          k0 = a.sip_aK[ek];
+          if (RAIN) k1 = a.sip_aK[a.etot + ek];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
+      sip_line_load<R, RAIN>(U, N, f0, l0);
+      const R dh = lane < P1 * P1 ? (R)a.Dhat[lane] : R(0), dm = lane < P1 * P1 ? (R)a.Dm[lane] : R(0);
+      // (every wavefront writes the same tables before it reads)
+      if (lane < P1 * P1) {
+        sD[lane] = dh;
+        sDm[lane] = dm;
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) sU[v][lane] = Uq[v];
+      sip_viscosity<R, RAIN>(a, item, ex, ey, ez, lane, li, lj, ll, k0, k1, (double*)&sF[0][0][0], al0, al1);
+      const R d0 = (R)md.two_over_h[0], d1 = (R)md.two_over_h[1], d2 = (R)md.two_over_h[2];
+      const int bx = lane - li, by = lane - P1 * lj, bz = lane - 16 * ll;
+      R wx_[P1], wy_[P1], wz_[P1];
+#pragma unroll
+      for (int b = 0; b < P1; ++b) {
+        wx_[b] = d0 * sDm[li * P1 + b];
+        wy_[b] = d1 * sDm[lj * P1 + b];
+        wz_[b] = d2 * sDm[ll * P1 + b];
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        R gx = R(0), gy = R(0), gz = R(0);
+#pragma unroll
+        for (int b = 0; b < P1; ++b) {
+          gx = fma(wx_[b], sU[v][bx + b], gx);
+          gy = fma(wy_[b], sU[v][by + P1 * b], gy);
+          gz = fma(wz_[b], sU[v][bz + 16 * b], gz);
+        }
+        const R al = RAIN && v == V::RR ? al1 : al0;
+        sF[0][v][lane] = -al * gx;
+        sF[1][v][lane] = -al * gy;
+        sF[2][v][lane] = -al * gz;
+      }
+    }
+    __syncthreads();   // the partners' states and fluxes
+    constexpr int VH = (NV + 1) / 2;
+    SipPoint<R, RAIN> p0, p1;
+    R ij[VH], iq[VH];
+    // inner face points: lanes 0..31, and 32..63 for the other half of the variables
+    const int ji = (lane >> 4) & 1, v0 = (lane >> 5) * (NV - VH);
+    const int si = ji ? 1 - dy : 1 - dx;
+    const bool inner = ji ? py : px;
+    if (act) {
+      sip_outer<R, RAIN>(md, f0, l0, Dm, sF, sU, __shfl(al0, f0.n), RAIN ? __shfl(al1, f0.n) : R(0), p0);
+      if (!px || !py) {   // wave-uniform
+        const R a0 = __shfl(al0, f1.n), a1 = RAIN ? __shfl(al1, f1.n) : R(0);   // (by every lane)
+        if (far1) {
+          SipLine<R, RAIN> l1;
+          sip_line_load<R, RAIN>(U, N, f1, l1);
+          sip_outer<R, RAIN>(md, f1, l1, Dm, sF, sU, a0, a1, p1);
+        }
+      }
+      int match;
+      const int n = face_node<K, 3>(ji, si, ta, tb, match);
+      const R a0 = __shfl(al0, n), a1 = RAIN ? __shfl(al1, n) : a0;
+      if (inner) {
+        const int ww = w ^ (1 << ji), nn = n + match;
+        const R ct = (R)(ji ? md.sip_tau[1] : md.sip_tau[0]);
+#pragma unroll
+        for (int i = 0; i < VH; ++i) {
+          const int v = v0 + i;
+          const R al = RAIN && v == V::RR ? a1 : a0;
+          const R d = sU[v][n] - sU_all[ww][v][nn];
+          ij[i] = al * (si ? d : -d);
+          iq[i] = R(-0.5) * (sF[ji][v][n] + sF_all[ww][ji][v][nn]) - ct * ij[i];
+        }
+      }
+      volume_q3<R, RAIN>(md, li, lj, ll, lane, sF, Rv, sD);
+    }
+    __syncthreads();   // every read of the viscous fluxes is over
+    if (act) {
+      // rows of 96 face points: alpha [U] of each variable, then the other term
+      R(*sX)[96] = (R(*)[96])&sF[0][0][0];
+      const int fp = lane & 15;
+      const int r0 = (2 * f0.J + f0.side) * 16 + fp;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+        sX[v][r0] = p0.j[v];
+        sX[NV + v][r0] = p0.q[v];
+      }
+      if (far1) {
+        const int r1 = (2 * f1.J + 1) * 16 + fp;
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          sX[v][r1] = p1.j[v];
+          sX[NV + v][r1] = p1.q[v];
+        }
+      }
+      if (inner) {
+        const int ri = (2 * ji + si) * 16 + fp;
+#pragma unroll
+        for (int i = 0; i < VH; ++i) {
+          sX[v0 + i][ri] = ij[i];
+          sX[NV + v0 + i][ri] = iq[i];
+        }
+      }
+      wave_lds_sync();
+      // d_j / w_{i_j} (d_j/2 D[f_j][i_j] alpha [U] + [i_j = f_j] s alpha ({G_j} - tau_j [U]))
+      const int idx[3] = {li, lj, ll};
+      const int at[3] = {lj + P1 * ll, 32 + li + P1 * ll, 64 + li + P1 * lj};
+      R cm[3], cp[3], cq[3];
+      int aq[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const R dj = (R)md.two_over_h[j];
+        // (the Lobatto weights of k = 3 are 1/6, 5/6, 5/6, 1/6)
+        const R kw = (R)md.lift[j][0] * (idx[j] == 0 || idx[j] == K ? R(1) : R(0.2));
+        cm[j] = kw * R(0.5) * dj * sDm[idx[j]];
+        cp[j] = kw * R(0.5) * dj * sDm[P1 * K + idx[j]];
+        cq[j] = idx[j] == 0 ? -kw : (idx[j] == K ? kw : R(0));
+        aq[j] = at[j] + (idx[j] == K ? 16 : 0);
+      }
+#pragma unroll
+      for (int v = 0; v < NV; ++v) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          Rv[v] = fma(cm[j], sX[v][at[j]], Rv[v]);
+          Rv[v] = fma(cp[j], sX[v][at[j] + 16], Rv[v]);
+          Rv[v] = fma(cq[j], sX[NV + v][aq[j]], Rv[v]);
+        }
+        asm volatile("" : "+v"(Rv[v]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      wave_lds_sync();   // the tiles go on to the fluxes
+    }
+  }
   if (act) {
     // background table: lane 6 h + f loads field f at height h
     double bgt = 0.0;
@@ -233,8 +500,10 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
       bgt = a.bgt[(unsigned)(bh < 4 ? izb + bh : (bh == 4 ? zlo : zhi)) * kBgStride + bf];
     }
     // 1. own state
+    if constexpr (!SIP) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
+      for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
+    }
     T = ld(auxT, N, 0, g);
     rvs = ld(auxS, N, 0, g);
     if (lane < 6 * kBgStride) (&sB[0][0].x)[lane] = bgt;
@@ -255,13 +524,13 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 #pragma unroll
       for (int v = 0; v < NV; ++v) sF[2][v][lane] = F[v];
     }
+    if constexpr (!SIP) {
 #pragma unroll
-    for (int v = 0; v < NV; ++v) sU[v][lane] = Uq[v];
+      for (int v = 0; v < NV; ++v) sU[v][lane] = Uq[v];
+    }
     if (li == 0 || li == K) sL[0][(li ? 16 : 0) + lj + P1 * ll] = wave_speed<R, D, RAIN, 0>(q);
     if (lj == 0 || lj == K) sL[1][(lj ? 16 : 0) + li + P1 * ll] = wave_speed<R, D, RAIN, 1>(q);
     if (ll == 0 || ll == K) sL[2][(ll ? 16 : 0) + li + P1 * lj] = wave_speed<R, D, RAIN, 2>(q);
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Rv[v] = R(0);
     sources<R, D, RAIN>(a, Uq, q, Rv);
     // the neighbour traces of the outer faces: in flight until the face pass
     pair_load<R, D, RAIN>(U, auxT, auxS, N, f0.gn, nb0);
@@ -338,31 +607,28 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 #pragma unroll
     for (int v = 0; v < NV; ++v) Rv[v] += sF[2][v][lane];
   }
-  if (flags & kSip) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) Rv[v] += ld((const R*)a.sip_out, N, v, g);
-  }
   const double dtm = MODE != 0 && dt_m ? dt_m[item.member] : 1.0;
   int iters = 0, bad = 0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) Uq[v] = sU[v][lane];
-  // with kSipAlpha, the new state's element viscosity (Section 3.5) for the
-  // next stage's diffusion: the node shares, then the pairwise sum over the
-  // wavefront in the order of sip_alpha_kernel's tree
+  // with diffusion, the new state's element viscosity (Section 3.5) for the
+  // next stage: the node shares, then the pairwise sum over the wavefront in
+  // the order of sip_alpha_kernel's tree
+  constexpr bool ALPHA = SIP && MODE == 2;
   double at[2] = {0.0, 0.0};
-  const double wq = md.J * a.w[li] * a.w[lj] * a.w[ll];
+  const double wq = ALPHA ? md.J * a.w[li] * a.w[lj] * a.w[ll] : 0.0;
   stage_epilogue<R, D, RAIN, MODE>(a, bg, iz, g, N, Uq, U0q, Rv, T, rvs, out, dtm, c0, c1, c2, oT, oS, flags,
-                                   iters, bad, nullptr, nullptr, nullptr, wq, at);
+                                   iters, bad, nullptr, nullptr, nullptr, wq, ALPHA ? at : nullptr);
   if (MODE == 2) record_stats(a, seen, iters, bad);
-  if (MODE == 2 && (flags & kSipAlpha)) {
+  if constexpr (ALPHA) {
 #pragma unroll
     for (int h = 1; h < NP; h <<= 1) {
       at[0] += __shfl_down(at[0], h);
       at[1] += __shfl_down(at[1], h);
     }
     if (lane == 0) {
-      a.sip_aK[item.eoff + e] = md.sip_pre * sqrt(at[0]);
-      a.sip_aK[a.etot + item.eoff + e] = md.sip_pre * sqrt(at[1]);
+      a.sip_aK_out[item.eoff + e] = md.sip_pre * sqrt(at[0]);
+      a.sip_aK_out[a.etot + item.eoff + e] = md.sip_pre * sqrt(at[1]);
     }
   }
 }

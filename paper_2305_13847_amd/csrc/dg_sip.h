@@ -3,10 +3,11 @@
 // unknowns, with the element-wise viscosity
 //   alpha_K = gamma 0.5 h^(1-d/2) ||u||_{0,K}   (||u - v_r e_z||_{0,K} for rho_r)
 // carried to a continuous Q1 field by the mean over the elements that share
-// each vertex.  Three kernels per right-hand side:
+// each vertex.  On Q3 hexahedra the stage kernel forms the tendency itself
+// (dg_q3.h) and takes from here only the alpha_K of a state that no stage
+// produced.  The other shapes run three kernels per right-hand side:
 //   1. sip_alpha_kernel: alpha_K of every element (two fields), an LDS
-//      reduction over the element's nodes (the Q3 stage kernel forms the same
-//      values for the state it writes, and then this launch is skipped);
+//      reduction over the element's nodes;
 //   2. sip_vertex_kernel: the vertex means (all members in one launch);
 //   3. sip_kernel: the tendency S = -M^{-1} A_h(U, .) at every node, written
 //      in the state layout; the stage kernels add it to the right-hand side.
@@ -58,7 +59,7 @@ sip_alpha_kernel(KArgs a, const R* __restrict__ U) {
     double m[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) m[i] = (double)ld(U, N, V::M0 + i, g);
-    sip_alpha_terms<D, RAIN>(a, w, rd, rm, rr, m, s0, s1);
+    sip_alpha_terms<D, RAIN>(a, w, rr, rcp64(rd + rm + rr), m, s0, s1);
   }
   sm[0][t] = s0;
   sm[1][t] = s1;
