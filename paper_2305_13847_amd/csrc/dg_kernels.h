@@ -991,14 +991,19 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
 }
 
 // one work item per block
-// FP32: at least 4 wavefronts per SIMD (the register budget the kernel fits
-// without spills); FP64 kernels need more registers than that and are left to
-// the compiler (spills cost far more than the occupancy they buy).
-template <typename R>
-constexpr int min_waves() { return sizeof(R) == 4 ? 4 : 1; }
+// FP32 in 2D (Q2 and up): 7 wavefronts per SIMD, what the LDS allows.  Left at 5
+// (94 registers, which only the split's rarely taken slow path needs) the kernel
+// waits for memory half of its time; bound to 72 registers that path spills a few
+// values and the rest does not.  64 members of 160 x 80 Q3 at most, five steps:
+// 2.83 ms at 5, 2.75 at 6, 2.61 at 7; 400 x 200 Q2 583, 532, 495 us.  Q1 takes
+// another path, which spills in its loops at 6 (390 -> 545 us).  In 3D the LDS
+// holds it at 5.  FP64 kernels are left to the compiler: 2D Q2 to Q7 measured the
+// same at 5 and 6.
+template <typename R, int K, int D>
+constexpr int min_waves() { return sizeof(R) == 4 ? (D == 2 && K >= 2 ? 7 : 4) : 1; }
 
 template <typename R, int K, int D, int RAIN, int MODE>
-__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R>())))
+__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R, K, D>())))
 rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
            const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
            const double* __restrict__ dt_m, double c0, double c1, double c2,
@@ -1031,7 +1036,7 @@ rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 
 // persistent: a grid smaller than the item count walks the items
 template <typename R, int K, int D, int RAIN, int MODE>
-__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R>())))
+__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 1)))
 rhs_kernel_persistent(KArgs a, const KArgs* __restrict__ a_dev, const R* __restrict__ U,
                       const double* __restrict__ auxT,
                       const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
