@@ -269,9 +269,8 @@ dg_status dg_destroy(dg_handle* h);
  * blocks per compute unit (0: one block per work item; n > 0: a grid of
  * n x CUs blocks that walk the work items).  Persistence applies to the
  * Lobatto-basis stage kernel of dg_rk_step only; every other kernel takes
- * one block per work item.  The Q3 hexahedral right-hand side (Lobatto basis)
- * takes fixed bricks of 2 x 2 elements (FP64: 2 x 1) per block, whatever is
- * set here.  Not a hot call: synchronises. */
+ * one block per work item.  The Q3 hexahedral right-hand sides take
+ * fixed bricks of 2 x 2 elements per block, whatever is set here.  Not a hot call: synchronises. */
 dg_status dg_set_launch(dg_handle* h, int elems_per_block, int persist_per_cu);
 dg_status dg_get_launch(const dg_handle* h, int* elems_per_block, int* persist_per_cu);
 

@@ -435,8 +435,7 @@ static void build_items(dg_handle* h, int epb, int order = -1) {
         h->items.push_back(make_item(md, m, e0 - r0, c1, c2));
     });
     if (q3) {
-      const int rows = q3_brick_rows(h->prec == DG_FP64);
-      for_rows(md, 3, (md.n[0] + 1) / 2, rows, order, [&](int c1, int c2) {
+      for_rows(md, 3, (md.n[0] + 1) / 2, 2, order, [&](int c1, int c2) {
         for (int c0 = 0; c0 < md.n[0]; c0 += 2) h->bricks.push_back(make_item(md, m, c0, c1, c2));
       });
     }

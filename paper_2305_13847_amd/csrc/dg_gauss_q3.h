@@ -1,7 +1,7 @@
 // Right-hand side / stage kernel of the Gauss basis on Q3 hexahedra: the method
 // of dg_gauss.h (its trace buffers included) on the bricks of dg_q3.h.
 //
-// One wavefront per element, a 2 x 2 brick (x, y; FP64 2 x 1) per block.
+// One wavefront per element, a 2 x 2 brick (x, y) per block.
 // Everything that depends on the element alone is wave-uniform.  Of an
 // element's 96 face points the 64 on the brick's outside are one pass of its
 // lanes: the own trace from its LDS tiles, the neighbour's from the trace
@@ -15,7 +15,7 @@
 // elements, and its sources, index work and neighbour loads come before the
 // volume term, which is what frees the registers for 4 wavefronts per SIMD.
 // 48 x 48 x 24 elements with rain, two SSPRK(4,3) steps: FP32 2.25 -> 1.66 ms,
-// FP64 4.35 -> 3.12; 21 x 21 x 11: 291 -> 228 us and 423 -> 340; 5 x 4 x 3
+// FP64 4.35 -> 2.94; 21 x 21 x 11: 291 -> 228 us and 423 -> 350; 5 x 4 x 3
 // (launches and one wave's chain): 137 -> 100 and 139 -> 107.
 #pragma once
 #include "dg_gauss.h"
@@ -133,12 +133,12 @@ template <typename R>
 constexpr int gq3_min_waves() { return sizeof(R) == 4 ? 4 : 2; }
 
 template <typename R, int RAIN, int MODE>
-__global__ void __launch_bounds__(128 * q3_brick_rows<R>()) __attribute__((amdgpu_waves_per_eu(gq3_min_waves<R>())))
+__global__ void __launch_bounds__(64 * kBrick) __attribute__((amdgpu_waves_per_eu(gq3_min_waves<R>())))
 rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
                     const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
                     const double* __restrict__ dt_m, double c0, double c1, double c2, double* __restrict__ oT,
                     double* __restrict__ oS, int flags) {
-  constexpr int P1 = 4, NP = 64, D = 3, BY = q3_brick_rows<R>(), WPB = 2 * BY;
+  constexpr int P1 = 4, NP = 64, D = 3, WPB = kBrick;
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
   // per element: fluxes of the three directions (after the volume term the
@@ -180,10 +180,10 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   // element (scalar): coordinates, partners inside the brick, outer faces
   const int n0 = item.n[0], n1 = item.n[1], n2 = item.n[2];
   const int b0 = item.bc[0], b1 = item.bc[1], b2 = item.bc[2];
-  const int dx = w & 1, dy = w >> 1;       // (BY = 1: dy = 0)
+  const int dx = w & 1, dy = w >> 1;
   const int ex = item.c0 + dx, ey = (item.c12 & 0xffff) + dy, ez = item.c12 >> 16;
   const bool act = ex < n0 && ey < n1;     // wave-uniform (odd mesh sizes)
-  const bool px = dx == 1 || ex + 1 < n0, py = BY == 2 && (dy == 1 || ey + 1 < n1);
+  const bool px = dx == 1 || ex + 1 < n0, py = dy == 1 || ey + 1 < n1;
   const int e = item.eoff + item.e0 + dx + dy * n0;
   const unsigned N = a.nnodes, ntr = (unsigned)a.etot * 96u;
   const unsigned g = (unsigned)e * NP + lane;
@@ -207,7 +207,7 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
 
   R Uq[NV], Rv[NV];
   double T = 300.0, rvs = 0.0;
-  GNb<R, RAIN> nb0, nb1;
+  GNb<R, RAIN> nb0;
   if (act) {
     // background table: lane 6 h + f loads field f (KArgs::bgt) of row h
     const int bh = lane / kBgStride, bf = lane - kBgStride * bh;
@@ -255,25 +255,24 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     sources<R, D, RAIN>(a, Uq, q, Rv);
     // the neighbours' traces: in flight until the face pass
     gq3_load<R, RAIN>(a, f0, ntr, nb0);
-    if (BY == 1 && far1) gq3_load<R, RAIN>(a, f1, ntr, nb1);
   }
   __syncthreads();   // the small tables, and the partners' tiles
   if (act) {
     volume_q3<R, RAIN>(md, li, lj, ll, lane, sF, Rv, sD);
     wave_lds_sync();   // the volume term has read sF before the face fluxes replace it
     gq3_outer<R, RAIN>(a, f0, nb0, sU, sT_all[w], sRv_all[w], sW, sWd, sB, sX);
-    if (!px || !py) {   // wave-uniform; BY = 2: the last brick of an odd mesh only
+    if (!px || !py) {   // wave-uniform: the last brick of an odd mesh
       if (far1) {
-        if (BY == 2) gq3_load<R, RAIN>(a, f1, ntr, nb1);
-        gq3_outer<R, RAIN>(a, f1, nb1, sU, sT_all[w], sRv_all[w], sW, sWd, sB, sX);
+        gq3_load<R, RAIN>(a, f1, ntr, nb0);
+        gq3_outer<R, RAIN>(a, f1, nb0, sU, sT_all[w], sRv_all[w], sW, sWd, sB, sX);
       }
     }
     // the faces inside the brick, one per wavefront: x faces of rows 0, 1, then
-    // y faces of columns 0, 1 (BY = 1: the only x face).  Lanes 0..15 the lower
+    // y faces of columns 0, 1.  Lanes 0..15 the lower
     // element's side, 16..31 the upper's.
-    const int J = BY == 2 ? w >> 1 : 0, k = BY == 2 ? w & 1 : 0;
+    const int J = w >> 1, k = w & 1;
     const int cx = item.c0 + (J ? k : 1), cy = (item.c12 & 0xffff) + (J ? 1 : k);
-    if ((BY == 2 || w == 0) && cx < n0 && cy < n1) {
+    if (cx < n0 && cy < n1) {
       const int up = (lane >> 4) & 1;
       const int ww = J ? k + 2 * up : 2 * k + up;
       int l0, str;

@@ -64,10 +64,8 @@ struct ItemWalk {
   }
 };
 
-// Q3 hexahedra: rows of elements per brick (2 x rows elements per block)
-constexpr int q3_brick_rows(bool fp64) { return fp64 ? 1 : 2; }
-template <typename R>
-constexpr int q3_brick_rows() { return q3_brick_rows(sizeof(R) == 8); }
+// Q3 hexahedra: elements per block, a 2 x 2 brick
+constexpr int kBrick = 4;
 
 // Threads of a block of the 2D and 3D block kernels for `nodes` nodes: whole
 // wavefronts; at 2D Q2, where an element has 12 face nodes to its 9 nodes, as

@@ -105,7 +105,7 @@ hipLaunchKernelGGL((KER<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, a
       // other kernels
       grid = dim3(grid_for_items(a.nbricks));
 #define DGM_Q3(M, SIP)                                                                              \
-  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M, SIP>), grid, dim3(128 * q3_brick_rows<R>()), 0, s, a,   \
+  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M, SIP>), grid, dim3(64 * kBrick), 0, s, a,                \
                      (const R*)U, auxT, auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
       if (flags & kSip) {
         if (mode == 0) DGM_Q3(0, 1);
@@ -139,7 +139,7 @@ hipLaunchKernelGGL((rhs_gauss_kernel<R, K_, D_, R_, M>), grid, block, 0, s, a, (
                    auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
     if constexpr (K_ == 3 && D_ == 3) {
       if (a.nbricks > 0) {
-        const dim3 bgrid(grid_for_items(a.nbricks)), bblock(128 * q3_brick_rows<R>());
+        const dim3 bgrid(grid_for_items(a.nbricks)), bblock(64 * kBrick);
 #define DGM_GQ3(M)                                                                                    \
   hipLaunchKernelGGL((rhs_gauss_q3_kernel<R, R_, M>), bgrid, bblock, 0, s, a, (const R*)U, auxT, auxS, \
                      (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)

@@ -18,21 +18,23 @@
 //      table; issue the loads of the outer faces' neighbour traces at once
 //      (their addresses depend on the element only);
 //   2. evaluate the point state (FP64 reconstruction of p' and rho e), stage
-//      F_x, F_y, F_z, U and the wave speeds in LDS; the sources;
+//      F_x, F_y, F_z and, for the partners, U and the wave speeds at the faces
+//      inside the brick in LDS; the sources;
 //   3. volume term from the LDS lines;
 //   4. faces: each lane evaluates one outer neighbour trace (on a slip wall
 //      its own, mirrored), forms the Lax-Friedrichs flux with the own trace
-//      from LDS, and leaves the lifted correction in LDS; the faces inside
+//      (state across the lanes, flux from LDS), and leaves the lifted
+//      correction in LDS; the faces inside
 //      the brick need no evaluation;
 //   5. every node adds the corrections of its faces, then the stage update,
 //      the sponge, the store and the split of the new state (stage_epilogue).
-// (FP64: 2 x 1 bricks, five outer faces, the fifth in a quarter pass.)
 //
 // Bound by HBM traffic and VALU issue together: on 64 x 64 x 32 in FP32 a stage
 // moves 0.95 GB (0.66 GB is algorithmic, the rest neighbour data missed by the
 // L2s) at 77 % of a copy's rate with the VALU 72 % busy.  Five steps 5.73 ->
 // 5.38 ms against one element per wavefront without bricks (1.04 GB per stage,
-// four blocks per CU); FP64 31 x 33 x 17, two steps, 580 -> 545 us.
+// four blocks per CU).  FP64, 33 x 31 x 17, two steps: 580 us without bricks, 545
+// with 2 x 1 bricks and a tile of the state, 510 now; 64 x 64 x 32 4.25 -> 3.84 ms.
 #pragma once
 #include "dg_kernels.h"
 
@@ -113,10 +115,11 @@ __device__ __forceinline__ FaceTask face_task(int J, int side, int ta, int tb, b
 }
 
 // Outer face task: evaluate the neighbour's trace, the Lax-Friedrichs flux with
-// the own trace from LDS; the correction replaces F_J at the own node.
+// the own trace (Uo; its wave speed along z, lz; the others in LDS); the
+// correction replaces F_J at the own node.
 template <typename R, int RAIN>
 __device__ __forceinline__ void q3_outer(const KArgs& a, const FaceTask& f, Pair<R, 3, RAIN>& nb,
-                                         R (*sF)[Vars<3, RAIN>::NV][64], const R (*sU)[64], const R (*sL)[32],
+                                         R (*sF)[Vars<3, RAIN>::NV][64], const R* Uo, R lz, const R (*sL)[32],
                                          const double2 (*sB)[kBgStride / 2], R hx, R hy, R hz) {
   using V = Vars<3, RAIN>;
   constexpr int NV = V::NV;
@@ -130,14 +133,14 @@ __device__ __forceinline__ void q3_outer(const KArgs& a, const FaceTask& f, Pair
   flux_sel<R, 3, RAIN>(qn, J, uj, Fn);
   R ln = fabs(uj) + qn.cm;
   if (RAIN) ln += J == 2 ? fabs(qn.vr) : R(0);
-  const R lo = sL[J][f.side * 16 + (int)(threadIdx.x & 15)];
+  const R lo = J == 2 ? lz : sL[J & 1][f.side * 16 + (int)(threadIdx.x & 15)];
   // Lambda = max over the two sides, ties to the minus side
   const bool own = f.side ? (lo >= ln) : !(ln >= lo);
   const R hl = J == 0 ? hx : (J == 1 ? hy : hz);
   const R kf = f.side ? -hl : hl;
   const R kj = hl * (own ? lo : ln);
 #pragma unroll
-  for (int v = 0; v < NV; ++v) sF[J][v][f.n] = fma(kf, sF[J][v][f.n] + Fn[v], kj * (nb.nb.U[v] - sU[v][f.n]));
+  for (int v = 0; v < NV; ++v) sF[J][v][f.n] = fma(kf, sF[J][v][f.n] + Fn[v], kj * (nb.nb.U[v] - Uo[v]));
 }
 
 __device__ __forceinline__ bool q3_wall(int bc, int c, int n, int side) { return bc == 1 && (side ? c == n - 1 : c == 0); }
@@ -259,15 +262,15 @@ __device__ __forceinline__ void sip_viscosity(const KArgs& a, const Item& item, 
   wave_lds_sync();
 }
 
-// FP32: 2 x 2 bricks, 5 wavefronts per SIMD (96 registers; the LDS of five
-// blocks fills a CU).  FP64: the tiles are twice as large, and blocks of four
-// would leave room for two (8 wavefronts per CU; 31 x 33 x 17, two steps: 609
-// us): 2 x 1 bricks, five blocks.
+// FP32: 5 wavefronts per SIMD, 96 registers (six fit the LDS, but the split's
+// slow path then spills and the blocks in flight outgrow the L2s: 64 x 64 x 32,
+// five steps, 5.15 -> 5.35 ms).  FP64: 3, what the LDS allows.  With diffusion
+// the tile of the state and its registers leave 4 and 2.
 template <typename R, int SIP>
-constexpr int q3_min_waves() { return sizeof(R) == 4 ? (SIP ? 4 : 5) : 2; }
+constexpr int q3_min_waves() { return sizeof(R) == 4 ? (SIP ? 4 : 5) : (SIP ? 2 : 3); }
 
 template <typename R, int RAIN, int MODE, int SIP>
-__global__ void __launch_bounds__(128 * q3_brick_rows<R>())
+__global__ void __launch_bounds__(64 * kBrick)
 __attribute__((amdgpu_waves_per_eu(q3_min_waves<R, SIP>())))
 rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
               const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
@@ -276,13 +279,14 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   constexpr int K = 3, P1 = 4, NP = 64, D = 3;
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
-  constexpr int BY = q3_brick_rows<R>();
-  constexpr int WPB = 2 * BY;   // wavefronts (elements) per block
+  constexpr int WPB = kBrick;   // wavefronts (elements) per block
   // per-wavefront LDS tiles: fluxes of the three directions (later the face
-  // corrections), the state, the wave speeds
+  // corrections), and what the faces inside the brick need of the state and the
+  // wave speeds
   __shared__ R sF_all[WPB][D][NV][NP];
-  __shared__ R sU_all[WPB][NV][NP];
-  __shared__ R sL_all[WPB][D][2 * P1 * P1];   // at the face nodes: side, face node
+  __shared__ R sI_all[SIP ? 1 : WPB][2][NV][P1 * P1];   // state at the nodes of the inner x and y face
+  __shared__ R sL_all[WPB][2][2 * P1 * P1];   // along x and y at the face nodes: side, face node
+  __shared__ R sU_all[SIP ? WPB : 1][NV][SIP ? NP : 1];   // (with diffusion, whose gradients need it) all of it
   // background (KArgs::bgt fields) at the brick's four heights and at the face
   // heights of the neighbours below and above: the same for its elements, and
   // each wavefront writes all of it (the same values) before it reads
@@ -299,16 +303,16 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   const Item item = a.bricks[it_];
   const MemberDesc& md = a.mem[item.member];
   R(*sF)[NV][NP] = sF_all[w];
-  R(*sU)[NP] = sU_all[w];
+  R(*sI)[NV][P1 * P1] = sI_all[SIP ? 0 : w];
   R(*sL)[2 * P1 * P1] = sL_all[w];
 
   // element (scalar): coordinates, partners inside the brick, outer faces
   const int n0 = item.n[0], n1 = item.n[1], n2 = item.n[2];
   const int b0 = item.bc[0], b1 = item.bc[1], b2 = item.bc[2];
-  const int dx = w & 1, dy = w >> 1;       // (BY = 1: dy = 0)
+  const int dx = w & 1, dy = w >> 1;
   const int ex = item.c0 + dx, ey = (item.c12 & 0xffff) + dy, ez = item.c12 >> 16;
   const bool act = ex < n0 && ey < n1;     // wave-uniform (odd mesh sizes)
-  const bool px = dx == 1 || ex + 1 < n0, py = BY == 2 && (dy == 1 || ey + 1 < n1);
+  const bool px = dx == 1 || ex + 1 < n0, py = dy == 1 || ey + 1 < n1;
   const int e = item.e0 + dx + dy * n0;
   const unsigned N = a.nnodes;
   const unsigned gbase = (unsigned)(item.eoff + e) * NP;   // first node of the element
@@ -335,10 +339,12 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 
   R Uq[NV], Rv[NV];
   double T = 300.0, rvs = 0.0;
-  Pair<R, D, RAIN> nb0, nb1;
+  R lz = R(0);
+  Pair<R, D, RAIN> nb0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) Rv[v] = R(0);
   if constexpr (SIP) {
+    R(*sU)[NP] = sU_all[w];
     R al0 = R(0), al1 = R(0);
     R Dm[P1];
 #pragma unroll
@@ -508,6 +514,10 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
     rvs = ld(auxS, N, 0, g);
     if (lane < 6 * kBgStride) (&sB[0][0].x)[lane] = bgt;
     wave_lds_sync();
+    if constexpr (SIP) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) Uq[v] = sU_all[w][v][lane];
+    }
 
     // 2. point state, fluxes, wave speeds to LDS; the sources
     Pt<R, D, RAIN> q;
@@ -524,17 +534,20 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 #pragma unroll
       for (int v = 0; v < NV; ++v) sF[2][v][lane] = F[v];
     }
-    if constexpr (!SIP) {
+    if (!SIP && li == (dx ? 0 : K)) {
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sU[v][lane] = Uq[v];
+      for (int v = 0; v < NV; ++v) sI[0][v][lj + P1 * ll] = Uq[v];
+    }
+    if (!SIP && lj == (dy ? 0 : K)) {
+#pragma unroll
+      for (int v = 0; v < NV; ++v) sI[1][v][li + P1 * ll] = Uq[v];
     }
     if (li == 0 || li == K) sL[0][(li ? 16 : 0) + lj + P1 * ll] = wave_speed<R, D, RAIN, 0>(q);
     if (lj == 0 || lj == K) sL[1][(lj ? 16 : 0) + li + P1 * ll] = wave_speed<R, D, RAIN, 1>(q);
-    if (ll == 0 || ll == K) sL[2][(ll ? 16 : 0) + li + P1 * lj] = wave_speed<R, D, RAIN, 2>(q);
+    lz = wave_speed<R, D, RAIN, 2>(q);
     sources<R, D, RAIN>(a, Uq, q, Rv);
     // the neighbour traces of the outer faces: in flight until the face pass
     pair_load<R, D, RAIN>(U, auxT, auxS, N, f0.gn, nb0);
-    if (BY == 1 && far1) pair_load<R, D, RAIN>(U, auxT, auxS, N, f1.gn, nb1);
   }
   // the only block-wide barrier: the D-hat table, and the partners' tiles for
   // the faces inside the brick
@@ -549,11 +562,21 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   // +-(lift/2)(F + F_n) + (lift/2) Lambda (U_n - U), + on the minus face.
   // (the Lobatto weights are symmetric: both sides lift alike)
   const R hx = R(0.5) * (R)md.lift[0][0], hy = R(0.5) * (R)md.lift[1][0], hz = R(0.5) * (R)md.lift[2][0];
-  q3_outer<R, RAIN>(a, f0, nb0, sF, sU, sL, sB, hx, hy, hz);
-  if (!px || !py) {   // wave-uniform; BY = 2: the last brick of an odd mesh only
+  // (the own traces come across the lanes, so no tile of the state is needed)
+  auto own = [&](int v, int n) { return SIP ? sU_all[SIP ? w : 0][v][SIP ? n : 0] : __shfl(Uq[v], n); };
+  {
+    R Uo[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Uo[v] = own(v, f0.n);
+    q3_outer<R, RAIN>(a, f0, nb0, sF, Uo, __shfl(lz, f0.n), sL, sB, hx, hy, hz);
+  }
+  if (!px || !py) {   // wave-uniform: the last brick of an odd mesh
+    R Uo[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) Uo[v] = own(v, f1.n);   // (by every lane)
     if (far1) {
-      if (BY == 2) pair_load<R, D, RAIN>(U, auxT, auxS, N, f1.gn, nb1);
-      q3_outer<R, RAIN>(a, f1, nb1, sF, sU, sL, sB, hx, hy, hz);
+      pair_load<R, D, RAIN>(U, auxT, auxS, N, f1.gn, nb0);
+      q3_outer<R, RAIN>(a, f1, nb0, sF, Uo, R(0), sL, sB, hx, hy, hz);
     }
   }
   // faces inside the brick: both traces and fluxes are in LDS.  Lanes 0..31
@@ -578,9 +601,12 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
       const R kj = hl * (own ? lo : ln);
       const int v0 = (lane >> 5) * (NV - VH);
 #pragma unroll
-      for (int i = 0; i < VH; ++i)
-        sF[j][v0 + i][in] = fma(kf, sF[j][v0 + i][n] + sF_all[ww][j][v0 + i][nn],
-                                kj * (sU_all[ww][v0 + i][nn] - sU[v0 + i][n]));
+      for (int i = 0; i < VH; ++i) {
+        const int v = v0 + i, fp = lane & 15;
+        const R d = SIP ? sU_all[SIP ? ww : 0][v][SIP ? nn : 0] - sU_all[SIP ? w : 0][v][SIP ? n : 0]
+                        : sI_all[SIP ? 0 : ww][j][v][fp] - sI[j][v][fp];
+        sF[j][v][in] = fma(kf, sF[j][v][n] + sF_all[ww][j][v][nn], kj * d);
+      }
     }
   }
   // operands of the update and the split, fetched while the faces finish
@@ -609,8 +635,10 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   }
   const double dtm = MODE != 0 && dt_m ? dt_m[item.member] : 1.0;
   int iters = 0, bad = 0;
+  if constexpr (SIP) {
 #pragma unroll
-  for (int v = 0; v < NV; ++v) Uq[v] = sU[v][lane];
+    for (int v = 0; v < NV; ++v) Uq[v] = sU_all[w][v][lane];
+  }
   // with diffusion, the new state's element viscosity (Section 3.5) for the
   // next stage: the node shares, then the pairwise sum over the wavefront in
   // the order of sip_alpha_kernel's tree
