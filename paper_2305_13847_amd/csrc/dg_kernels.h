@@ -164,7 +164,7 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
       const double mi = (double)Uq[V::M0 + i];
       ke += mi * mi;
     }
-    const double re = bg.E + (double)Uq[V::E] - 0.5 * ke / rho;
+    const double re = bg.E + (double)Uq[V::E] - 0.5 * ke * rcp64(rho);
     const double guess = Tguess ? Tguess[g] : 0.0;
     const SplitOut s = split_scratch(a, rd, rm, rr, re, guess);
     iters = s.iters;
