@@ -179,7 +179,8 @@ __device__ __forceinline__ void tri_eval(const KArgs& a, const R* U, double T, d
 // stage took 133 us with 2503 VALU instructions per wavefront, a third of them
 // index arithmetic (one division chain per loaded value), Lagrange weights of
 // the background evaluated twice per point, conversions in the split, and
-// single-word LDS reads; now 96 us with 1531.
+// single-word LDS reads; now 88 us with 1460.  The LDS is busy nearly as long as
+// the VALU: rows of several elements in the same banks alone cost 4 of 92 us.
 template <int K>
 struct TriBlock {
   static constexpr int NQ = TriShape<K>::NQ;
@@ -201,7 +202,10 @@ struct TriLds {
   alignas(16) double ts[EPB][NQ][2];     // the weighted split of the updated state at the volume points
   alignas(16) R c[EPB][NV][NPP];         // coefficients of the stage input
   union {
-    alignas(16) R pf[EPB][NQ][PF];       // per volume point: w F.G0, w F.G1, w G
+    // per volume point: w F.G0, w F.G1, w G.  The last 16 bytes shift the next
+    // element's banks: NQ PF is a multiple of 64 words at P2 and P3, and a
+    // wavefront reads the same row of three or four elements at once.
+    alignas(16) R pf[EPB][NQ * PF + 4];
     struct {                             // then the neighbours across the three faces
       alignas(16) double aux[EPB][3][2][NPD];
       alignas(16) R c[EPB][3][NV][NPP];
@@ -210,7 +214,7 @@ struct TriLds {
   } u;
   union {
     alignas(16) R px[EPB][NP][NVP];      // partial sums of the modes
-    alignas(16) R ff[EPB][3 * NF][NVP];  // then per face point the weighted normal flux
+    alignas(16) R ff[EPB][3 * NF * NVP + 4];  // then per face point the weighted normal flux
   } f;
   TriZ fz[EPB];             // heights of the vertices and background layer
   R fn[EPB][3][3];          // per face: n_x, n_z, |e_f| / det A
@@ -354,7 +358,8 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
   constexpr int EPB = TriBlock<K>::EPB, NT = TriBlock<K>::NT;
   constexpr int NH = (NV + 1) / 2;
   static_assert(NQ == 2 * NP, "the Duffy rule has twice as many points as P^k has modes");
-  __shared__ TriLds<R, K, RAIN> S;
+  using LD = TriLds<R, K, RAIN>;
+  __shared__ LD S;
   const auto& T = tri_tab<R, K>(S);
   const int tid = threadIdx.x;
   const bool lane = tid < NT;
@@ -436,6 +441,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
       Tq += S.aux[el][0][k] * T.psid[q][k];
       Rq += S.aux[el][1][k] * T.psid[q][k];
     }
+    if (MODE == 2) S.ts[el][q][0] = Tq;   // the split's guess, by the same thread
     b = tri_bg<K>(t, g.layer, g.z0 + g.dz1 * T.rq[q] + g.dz2 * T.sq[q]);
     Pt<R, 2, RAIN> p;
     tri_eval<R, RAIN>(a, Uq, Tq, Rq, b, p);
@@ -450,7 +456,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
 #pragma unroll
     for (int v = 0; v < NV; ++v) P[2 * NV + v] = wq * Gs[v];
 #pragma unroll
-    for (int v = 0; v < 3 * NV; ++v) S.u.pf[el][q][v] = P[v];
+    for (int v = 0; v < 3 * NV; ++v) S.u.pf[el][q * LD::PF + v] = P[v];
   }
   __syncthreads();
 
@@ -462,10 +468,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
 #pragma unroll 2
     for (int i = 0; i < NP; ++i) {
       const int qq = half * NP + i;
+      const R* const pf = &S.u.pf[el][qq * LD::PF];
       const R dr = T.g3[qq][m][0], ds = T.g3[qq][m][1], ps = T.g3[qq][m][2];
 #pragma unroll
       for (int v = 0; v < NV; ++v)
-        acc[v] += S.u.pf[el][qq][v] * dr + S.u.pf[el][qq][NV + v] * ds + S.u.pf[el][qq][2 * NV + v] * ps;
+        acc[v] += pf[v] * dr + pf[NV + v] * ds + pf[2 * NV + v] * ps;
     }
     // each half leaves the partial sums that the other one finishes
 #pragma unroll
@@ -569,7 +576,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
     const R wgt = S.fn[fe][f][2] * T.wf[i];
 #pragma unroll
     for (int v = 0; v < NV; ++v)
-      S.f.ff[fe][j][v] = wgt * (R(0.5) * (Fm[v] + Fp[v]) + R(0.5) * L * (Um[v] - Up[v]));
+      S.f.ff[fe][j * LD::NVP + v] = wgt * (R(0.5) * (Fm[v] + Fp[v]) + R(0.5) * L * (Um[v] - Up[v]));
   }
   // the mode threads' share of U0, in flight while the faces finish
   R u0[NH];
@@ -589,7 +596,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
       const R ps = T.psif[j / NF][j % NF][m];
 #pragma unroll
       for (int h = 0; h < NH; ++h)
-        if (half * NH + h < NV) r[h] -= S.f.ff[el][j][half * NH + h] * ps;
+        if (half * NH + h < NV) r[h] -= S.f.ff[el][j * LD::NVP + half * NH + h] * ps;
     }
 #pragma unroll
     for (int h = 0; h < NH; ++h) {
@@ -611,10 +618,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
     __syncthreads();
     int it = 0, bd = 0;
     if (lane) {
-      double Tg = 0.0;
-#pragma unroll
-      for (int k = 0; k < NP; ++k) Tg += S.aux[el][0][k] * T.psid[q][k];
-      tri_split_at<R, K, RAIN>(a, S, el, q, b, Tg, &it, &bd);
+      tri_split_at<R, K, RAIN>(a, S, el, q, b, S.ts[el][q][0], &it, &bd);
     }
     __syncthreads();
     if (lane) tri_project_split<R, K, RAIN>(S, el, m, half, e, act, Tn, Rn);
