@@ -15,7 +15,7 @@
 // elements, and its sources, index work and neighbour loads come before the
 // volume term, which is what frees the registers for 4 wavefronts per SIMD.
 // 48 x 48 x 24 elements with rain, two SSPRK(4,3) steps: FP32 2.25 -> 1.66 ms,
-// FP64 4.35 -> 2.94; 21 x 21 x 11: 291 -> 228 us and 423 -> 350; 5 x 4 x 3
+// FP64 4.35 -> 2.59; 21 x 21 x 11: 291 -> 228 us and 423 -> 320; 5 x 4 x 3
 // (launches and one wave's chain): 137 -> 100 and 139 -> 107.
 #pragma once
 #include "dg_gauss.h"
@@ -129,8 +129,43 @@ __device__ __forceinline__ void gq3_outer(const KArgs& a, const GTask& t, GNb<R,
     sX[v][at] = R(0.5) * (Fo[v] + Fn[v]) + hL * (t.side ? Uo[v] - nb.U[v] : nb.U[v] - Uo[v]);
 }
 
+// One direction's share of the volume term: the point's flux to the wavefront's
+// tile (rows of 64 nodes), then R_v += (2/h_J) sum_b Dhat[i_J][b] F_J,v(node b on
+// the lane's J-line).  `i`: the lane's index along J, `str`: the line's stride.
+template <typename R, int RAIN, int J>
+__device__ __forceinline__ void gq3_volume(const MemberDesc& md, const Pt<R, 3, RAIN>& q, int i, int lane,
+                                           R (*sF)[64], const R* sD, R* Rv) {
+  constexpr int NV = Vars<3, RAIN>::NV, str = J == 0 ? 1 : (J == 1 ? 4 : 16);
+  R F[NV];
+  flux<R, 3, RAIN, J>(q, F);
+#pragma unroll
+  for (int v = 0; v < NV; ++v) sF[v][lane] = F[v];
+  wave_lds_sync();
+  const R s = (R)md.two_over_h[J];
+  const int b0 = lane - i * str;
+  R d[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b) d[b] = sD[i * 4 + b];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) {
+    R x = d[0] * sF[v][b0];
+#pragma unroll
+    for (int b = 1; b < 4; ++b) x += d[b] * sF[v][b0 + b * str];
+    Rv[v] += s * x;
+    asm volatile("" : "+v"(Rv[v]));   // (not sunk to its use: the LDS values would stay in registers)
+  }
+  wave_lds_sync();
+}
+
 template <typename R>
-constexpr int gq3_min_waves() { return sizeof(R) == 4 ? 4 : 2; }
+constexpr int gq3_min_waves() { return sizeof(R) == 4 ? 4 : 3; }
+
+// Directions of the volume term in LDS at once.  FP32: all three (one at a time,
+// 24 instead of 34 KB a brick, 1.68 -> 1.71 ms at the same 4 wavefronts per SIMD,
+// and 1.82 at 5, where 96 registers spill; 48 x 48 x 24, two steps).  FP64: one,
+// which makes room for a third brick per CU (2.93 -> 2.59 ms).
+template <typename R>
+constexpr int gq3_tiles() { return sizeof(R) == 4 ? 3 : 1; }
 
 template <typename R, int RAIN, int MODE>
 __global__ void __launch_bounds__(64 * kBrick) __attribute__((amdgpu_waves_per_eu(gq3_min_waves<R>())))
@@ -141,18 +176,18 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   constexpr int P1 = 4, NP = 64, D = 3, WPB = kBrick;
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
-  // per element: fluxes of the three directions (after the volume term the
-  // fluxes of its outer face points), the state, T and rho_v
-  __shared__ R sF_all[WPB][D][NV][NP];
+  constexpr int TILES = gq3_tiles<R>();
+  // per element: the fluxes of TILES directions (after the volume term those of its
+  // outer face points), the state, T and rho_v
+  __shared__ R sF_all[WPB][TILES == 3 ? D * NV * NP : NV * 96];
   __shared__ R sU_all[WPB][NV][NP];
   __shared__ double sT_all[WPB][NP], sRv_all[WPB][NP];
-  __shared__ R sI[NV][96];                 // fluxes of the faces inside the brick, 16 points each
+  __shared__ R sI[NV][64];                 // fluxes of the faces inside the brick, 16 points each
   // background: the four node heights, the faces below and above of this row
   // of elements, and their outer sides
   __shared__ double2 sB[8][kBgStride / 2];
   __shared__ R sD[P1 * P1], sW[2][P1], sK[D][P1][2];
   __shared__ double sWd[2][P1];
-  static_assert(NV * 96 <= D * NV * NP, "the face fluxes reuse the flux tile");
 
   const ItemWalk walk(a.nbricks, a.walk_rev);
   const int it_ = walk.item(0);
@@ -162,7 +197,8 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   const int lane = (int)(threadIdx.x & 63);
   const Item item = a.bricks[it_];
   const MemberDesc& md = a.mem[item.member];
-  if (threadIdx.x < P1 * P1) sD[threadIdx.x] = (R)a.Dhat[threadIdx.x];
+  // (every wavefront writes the tables that it reads before the block meets)
+  if (lane < P1 * P1) sD[lane] = (R)a.Dhat[lane];
   if (threadIdx.x < 2 * P1) {
     const int s = threadIdx.x >> 2, i = threadIdx.x & 3;
     const double l = s ? a.gl_p[i] : a.gl_m[i];
@@ -173,9 +209,9 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     const int j = threadIdx.x >> 3, i = (threadIdx.x >> 1) & 3, s = threadIdx.x & 1;
     sK[j][i][s] = (R)(md.two_over_h[j] * (s ? a.lift_p[i] : a.lift_m[i]));
   }
-  R(*sF)[NV][NP] = sF_all[w];
   R(*sU)[NP] = sU_all[w];
-  R(*sX)[96] = (R(*)[96])&sF_all[w][0][0][0];
+  R(*sX)[96] = (R(*)[96])sF_all[w];
+  R(*sF)[NP] = (R(*)[NP])sF_all[w];
 
   // element (scalar): coordinates, partners inside the brick, outer faces
   const int n0 = item.n[0], n1 = item.n[1], n2 = item.n[2];
@@ -201,8 +237,11 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   const GTask f0 = gq3_task(tf < 2 ? tf : 2, tf == 0 ? dx : (tf == 1 ? dy : tf - 2), fp,
                             tf == 0 ? wx : (tf == 1 ? wy : (tf == 2 ? wz0 : wz1)),
                             e + (tf == 0 ? qx : (tf == 1 ? qy : (tf == 2 ? qz0 : qz1))));
-  const GTask f1 = gq3_task(tf & 1, 1, fp, (tf & 1) ? q3_wall(b1, ey, n1, 1) : q3_wall(b0, ex, n0, 1),
-                            e + ((tf & 1) ? q3_step(ey, n1, 1) * n0 : q3_step(ex, n0, 1)));
+  // (formed where it is used: a brick of an odd mesh alone needs it)
+  auto far = [&]() {
+    return gq3_task(tf & 1, 1, fp, (tf & 1) ? q3_wall(b1, ey, n1, 1) : q3_wall(b0, ex, n0, 1),
+                    e + ((tf & 1) ? q3_step(ey, n1, 1) * n0 : q3_step(ex, n0, 1)));
+  };
   const bool far1 = (tf == 0 && !px) || (tf == 1 && !py);
 
   R Uq[NV], Rv[NV];
@@ -234,17 +273,17 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     Pt<R, D, RAIN> q;
     const Bg b = q3_bg(sB[ll]);
     eval_bg<R, D, RAIN>(a, Uq, T, rvs, b, q);
-    {
+    if constexpr (TILES == 3) {
       R F[NV];
       flux<R, D, RAIN, 0>(q, F);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sF[0][v][lane] = F[v];
+      for (int v = 0; v < NV; ++v) sF[v][lane] = F[v];
       flux<R, D, RAIN, 1>(q, F);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sF[1][v][lane] = F[v];
+      for (int v = 0; v < NV; ++v) sF[NV + v][lane] = F[v];
       flux<R, D, RAIN, 2>(q, F);
 #pragma unroll
-      for (int v = 0; v < NV; ++v) sF[2][v][lane] = F[v];
+      for (int v = 0; v < NV; ++v) sF[2 * NV + v][lane] = F[v];
     }
 #pragma unroll
     for (int v = 0; v < NV; ++v) sU[v][lane] = Uq[v];
@@ -255,14 +294,22 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     sources<R, D, RAIN>(a, Uq, q, Rv);
     // the neighbours' traces: in flight until the face pass
     gq3_load<R, RAIN>(a, f0, ntr, nb0);
+    if constexpr (TILES == 1) {
+      gq3_volume<R, RAIN, 0>(md, q, li, lane, sF, sD, Rv);
+      gq3_volume<R, RAIN, 1>(md, q, lj, lane, sF, sD, Rv);
+      gq3_volume<R, RAIN, 2>(md, q, ll, lane, sF, sD, Rv);
+    }
   }
   __syncthreads();   // the small tables, and the partners' tiles
   if (act) {
-    volume_q3<R, RAIN>(md, li, lj, ll, lane, sF, Rv, sD);
-    wave_lds_sync();   // the volume term has read sF before the face fluxes replace it
+    if constexpr (TILES == 3) {
+      volume_q3<R, RAIN>(md, li, lj, ll, lane, (R(*)[NV][NP])sF_all[w], Rv, sD);
+      wave_lds_sync();   // the volume term has read sF before the face fluxes replace it
+    }
     gq3_outer<R, RAIN>(a, f0, nb0, sU, sT_all[w], sRv_all[w], sW, sWd, sB, sX);
     if (!px || !py) {   // wave-uniform: the last brick of an odd mesh
       if (far1) {
+        const GTask f1 = far();
         gq3_load<R, RAIN>(a, f1, ntr, nb0);
         gq3_outer<R, RAIN>(a, f1, nb0, sU, sT_all[w], sRv_all[w], sW, sWd, sB, sX);
       }
@@ -302,17 +349,19 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   // lifting: + l_i(-1)/w_i F*(minus face) - l_i(+1)/w_i F*(plus face)
   {
     // inner face numbers of this element: x face of row dy, y face of column dx
-    const R(*xm)[96] = (const R(*)[96])(dx == 1 ? &sI[0][16 * dy] : &sX[0][0]);
-    const R(*xp)[96] = (const R(*)[96])(dx == 0 && px ? &sI[0][16 * dy] : &sX[0][16]);
-    const R(*ym)[96] = (const R(*)[96])(dy == 1 ? &sI[0][32 + 16 * dx] : &sX[0][32]);
-    const R(*yp)[96] = (const R(*)[96])(dy == 0 && py ? &sI[0][32 + 16 * dx] : &sX[0][48]);
+    const R* const xm = dx == 1 ? &sI[0][16 * dy] : &sX[0][0];
+    const R* const xp = dx == 0 && px ? &sI[0][16 * dy] : &sX[0][16];
+    const R* const ym = dy == 1 ? &sI[0][32 + 16 * dx] : &sX[0][32];
+    const R* const yp = dy == 0 && py ? &sI[0][32 + 16 * dx] : &sX[0][48];
+    const int sxm = dx == 1 ? 64 : 96, sxp = dx == 0 && px ? 64 : 96;   // their rows
+    const int sym = dy == 1 ? 64 : 96, syp = dy == 0 && py ? 64 : 96;
     const int fx = lj + P1 * ll, fy = li + P1 * ll, fz = li + P1 * lj;
     const R kxm = sK[0][li][0], kxp = sK[0][li][1], kym = sK[1][lj][0], kyp = sK[1][lj][1];
     const R kzm = sK[2][ll][0], kzp = sK[2][ll][1];
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      Rv[v] += kxm * xm[v][fx] - kxp * xp[v][fx];
-      Rv[v] += kym * ym[v][fy] - kyp * yp[v][fy];
+      Rv[v] += kxm * xm[v * sxm + fx] - kxp * xp[v * sxp + fx];
+      Rv[v] += kym * ym[v * sym + fy] - kyp * yp[v * syp + fy];
       Rv[v] += kzm * sX[v][64 + fz] - kzp * sX[v][80 + fz];
     }
   }
@@ -320,6 +369,7 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   int iters = 0, bad = 0;
 #pragma unroll
   for (int v = 0; v < NV; ++v) Uq[v] = sU[v][lane];
+  T = sT_all[w][lane];
   const Bg bg = q3_bg(sB[ll]);
   if constexpr (MODE == 2) {
     R Unew[NV];
@@ -347,7 +397,7 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     };
     write(f0);
     if (!px || !py) {
-      if (far1) write(f1);
+      if (far1) write(far());
     }
   } else {
     stage_epilogue<R, D, RAIN, MODE>(a, bg, iz, g, N, Uq, U0q, Rv, T, rvs, out, dtm, c0, c1, c2, oT, oS, flags, iters,
