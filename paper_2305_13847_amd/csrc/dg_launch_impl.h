@@ -160,6 +160,13 @@ bool LaunchGauss<R>::gauss_trace(const KArgs& a, LaunchCfg lc, int K, int D, int
     const double* auxT, const double* auxS, hipStream_t s) {
   return dispatch_shape(K, D, rain, [&](auto k, auto d, auto r) {
     constexpr int K_ = decltype(k)::value, D_ = decltype(d)::value, R_ = decltype(r)::value;
+    if constexpr (K_ == 3 && D_ == 3) {
+      if (a.nbricks > 0) {
+        hipLaunchKernelGGL((gauss_q3_trace_kernel<R, R_>), dim3(grid_for_items(a.nbricks)), dim3(64 * kBrick), 0, s,
+                           a, (const R*)U, auxT, auxS);
+        return;
+      }
+    }
     hipLaunchKernelGGL((gauss_trace_kernel<R, K_, D_, R_>), dim3(lc.grid), dim3(lc.threads), 0, s, a,
                        (const R*)U, auxT, auxS);
   });
