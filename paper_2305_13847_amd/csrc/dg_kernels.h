@@ -3,8 +3,9 @@
 //
 // Work decomposition: a block owns EPB consecutive elements of one member
 // (a work item); one thread owns one node of one element and computes every
-// variable there.  Elements are consecutive in x, so a block's loads are
-// contiguous per variable.
+// variable there (and takes face tasks; threads beyond the nodes only those).
+// Elements are consecutive in x, so a block's loads are contiguous per variable.
+// Q3 hexahedra have kernels of their own (dg_q3.h, dg_gauss_q3.h).
 #pragma once
 #include "dg_device.h"
 
@@ -185,14 +186,13 @@ split_kernel(KArgs a, int item0, int nitems, const R* __restrict__ U, const doub
 // right-hand side / stage kernel
 // ---------------------------------------------------------------------------
 // MODE 0: out = dU/dt
-// MODE 1: out = c0 U0 + c1 U + c2 dt_member dU/dt  (a Shu-Osher stage; without
-//         dt_m the time step is in c2)
-// MODE 2: as MODE 1, then the split of the new state at every node, written
-//         to (oT, oS); Newton is warm-started and anchored at the input
-//         state's (T, rho_vs).  With kRefreshRvs the stored rho_vs is a fresh
-//         evaluation at the new T (once per step), otherwise the anchored one.
-// With kSponge (MODE 1, 2) the new state is the end of a step: the sponge
-// acts on it before it is stored and split.
+// MODE 2: out = c0 U0 + c1 U + c2 dt_member dU/dt  (a Shu-Osher stage; without
+//         dt_m the time step is in c2), then the split of the new state at
+//         every node, written to (oT, oS), warm-started and anchored at the
+//         input state's (T, rho_vs).  With kRefreshRvs the stored rho_vs is a
+//         fresh evaluation at the new T, otherwise the anchored one.  With
+//         kSponge the new state is the end of a step: the sponge acts on it
+//         before it is stored and split.
 template <typename R, int D, int RAIN>
 struct Nb {
   R U[Vars<D, RAIN>::NV];

@@ -26,8 +26,8 @@ struct LaunchPoint {
   static bool split(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int item0, int nitems,
                     const void* U, const double* guess, double* oT, double* o1, double* o2, int api,
                     hipStream_t s);
-  // artificial diffusion: alpha_K (unless the previous stage wrote it),
-  // vertex means (all members), tendency
+  // artificial diffusion: alpha_K, vertex means (all members), tendency (Q3
+  // hexahedra: alpha_K only, the stage kernel does the rest)
   static bool sip(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int nmembers, const long long* nvert,
                   const void* U, hipStream_t s);
   static bool sponge_vjp(const KArgs& a, LaunchCfg lc, int K, int D, int rain, const void* W, void* Wp,
@@ -38,8 +38,7 @@ struct LaunchPoint {
 
 template <typename R>
 struct LaunchStage {
-  // mode 0: out = dU/dt; mode 1: out = c0 U0 + c1 U + c2 dt dU/dt; mode 2: mode 1 and the split
-  // of out into (oT, oS)
+  // mode 0: out = dU/dt; mode 2: out = c0 U0 + c1 U + c2 dt dU/dt and the split of out into (oT, oS)
   static bool rhs(const KArgs& a, const KArgs* a_dev, LaunchCfg lc, int K, int D, int rain, int mode, const void* U,
                   const double* auxT, const double* auxS, void* out, const void* U0,
                   const double* dt, double c0, double c1, double c2, double* oT, double* oS,
@@ -48,8 +47,8 @@ struct LaunchStage {
 
 template <typename R>
 struct LaunchGauss {
-  // the modes of LaunchStage::rhs on Gauss nodes: one block per work item
-  // whatever the persistence setting (the kernel has no item loop)
+  // the modes of LaunchStage::rhs on Gauss nodes: one block per work item, or per
+  // brick of Q3 hexahedra, whatever the persistence setting (no item loops)
   static bool rhs_gauss(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int mode, const void* U,
                         const double* auxT, const double* auxS, void* out, const void* U0, const double* dt,
                         double c0, double c1, double c2, double* oT, double* oS, int flags, hipStream_t s);
