@@ -30,11 +30,11 @@
 //      the sponge, the store and the split of the new state (stage_epilogue).
 //
 // Bound by HBM traffic and VALU issue together: on 64 x 64 x 32 in FP32 a stage
-// moves 0.95 GB (0.66 GB is algorithmic, the rest neighbour data missed by the
-// L2s) at 77 % of a copy's rate with the VALU 72 % busy.  Five steps 5.73 ->
-// 5.38 ms against one element per wavefront without bricks (1.04 GB per stage,
-// four blocks per CU).  FP64, 33 x 31 x 17, two steps: 580 us without bricks, 545
-// with 2 x 1 bricks and a tile of the state, 510 now; 64 x 64 x 32 4.25 -> 3.84 ms.
+// takes 255 us and moves 1.04 GB (0.66 GB is algorithmic, the rest neighbour data
+// that the L2s miss), 86 % of a copy's rate, with the VALU 76 % busy.  Five steps
+// 5.73 -> 5.20 ms against one element per wavefront without bricks (four blocks per
+// CU, 30 % more L2 requests).  FP64, 33 x 31 x 17, two steps: 580 us without bricks,
+// 545 with 2 x 1 bricks and a tile of the state, 485 now; 64 x 64 x 32 4.25 -> 3.84.
 #pragma once
 #include "dg_kernels.h"
 

@@ -339,20 +339,49 @@ __global__ void __launch_bounds__(256) tri_split_kernel(KArgs a, TriArgs t, cons
   record_stats(a, seen, act ? it : 0, act ? bd : 0);
 }
 
+// A mode thread's share of the coefficients, and of the projected T and rho_v, of
+// the neighbours across the element's faces (none on a wall).
+template <typename R, int K, int RAIN>
+__device__ __forceinline__ void tri_neighbours(const TriArgs& t, const R* __restrict__ U,
+                                               const double* __restrict__ aux, size_t N, int e, int m, int half,
+                                               bool lane, R (*nreg)[(Vars<2, RAIN>::NV + 1) / 2], double* areg) {
+  constexpr int NV = Vars<2, RAIN>::NV, NH = (NV + 1) / 2, NP = TriShape<K>::NP;
+#pragma unroll
+  for (int f = 0; f < 3; ++f) {
+    const int nb = lane ? t.nbr[(size_t)e * 3 + f] : -1;
+    const unsigned long long nm = (unsigned long long)(nb >> 2) * NP + m;
+    areg[f] = 0.0;
+#pragma unroll
+    for (int h = 0; h < NH; ++h) {
+      const int v = half * NH + h;
+      nreg[f][h] = R(0);
+      if (nb >= 0 && v < NV) nreg[f][h] = U[v * N + nm];
+    }
+    if (nb >= 0) areg[f] = aux[half * N + nm];
+  }
+}
+
 // Stage kernel.  MODE 0: out = dC/dt.  MODE 2: out = c0 U0 + c1 U + c2 dt dC/dt
 // and the split of out into (Tn, Rn) for the next stage.  aux holds the
 // projected T and rho_v of U: aux[0 .. N) and aux[N .. 2N), N = ne NP.
-// FP32: 4 wavefronts per SIMD (128 registers, 7 spilled at P3; left free, 148
-// and 3 wavefronts: 2.12 against 1.97 ms for five steps).  FP64: 3, what the
-// LDS allows.
-template <typename R>
-constexpr int tri_min_waves() { return sizeof(R) == 4 ? 4 : 3; }
+// Wavefronts per SIMD that the registers are bound to.  FP32 4 (128 registers, 8
+// spilled at P3; left free, 148 and 3 wavefronts: 2.12 against 1.97 ms for five
+// steps), FP64 3.  With rain at P3 and P4 the LDS allows less, and a bound that it
+// forbids is no bound: the compiler took 197 and more than 256 registers in FP32.
+// Three steps of 200 x 100 x 2 with rain: P3 FP32 1050 -> 943 us, FP64 2008 -> 1340;
+// P4 FP32 (100 x 50 x 2) 875 -> 640.  P4 in FP64 keeps one wavefront (two would
+// spill 150 registers, 4.4 -> 5.3 ms).
+template <typename R, int K, int RAIN>
+constexpr int tri_min_waves() {
+  if (RAIN && K >= 3) return sizeof(R) == 4 ? (K == 4 ? 2 : 3) : (K == 4 ? 1 : 2);
+  return sizeof(R) == 4 ? 4 : 3;
+}
 
 template <typename R, int K, int RAIN, int MODE>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_min_waves<R>()))) tri_stage_kernel(KArgs a, TriArgs t, const R* __restrict__ U,
-                                                        const double* __restrict__ aux, R* __restrict__ out,
-                                                        const R* __restrict__ U0, double c0, double c1, double c2dt,
-                                                        double* __restrict__ Tn, double* __restrict__ Rn) {
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_min_waves<R, K, RAIN>())))
+tri_stage_kernel(KArgs a, TriArgs t, const R* __restrict__ U, const double* __restrict__ aux, R* __restrict__ out,
+                 const R* __restrict__ U0, double c0, double c1, double c2dt, double* __restrict__ Tn,
+                 double* __restrict__ Rn) {
   using V = Vars<2, RAIN>;
   constexpr int NV = V::NV, NP = TriShape<K>::NP, NQ = TriShape<K>::NQ, NF = TriShape<K>::NF;
   constexpr int EPB = TriBlock<K>::EPB, NT = TriBlock<K>::NT;
@@ -378,6 +407,13 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
   // (parked in registers until the volume phase has released its LDS): thread
   // (el, m, half) takes mode m of its variables everywhere, so consecutive
   // threads read consecutive values and no index needs a division
+  //
+  // With rain at P3 and P4, where registers are short, what lives across the volume
+  // phase is cut: the neighbours are loaded after the points (in flight during the
+  // mode sums), and the split forms the background a second time (P3 FP64, three
+  // steps 1851 -> 1340 us).  Elsewhere both cost time (P3 FP32 without rain 1.17 ->
+  // 1.25 ms).
+  constexpr bool LATE = RAIN && K >= 3;
   R nreg[3][NH];
   double areg[3];
   {
@@ -390,19 +426,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
       }
       S.aux[el][half][m] = aux[half * N + em];
     }
-#pragma unroll
-    for (int f = 0; f < 3; ++f) {
-      const int nb = lane ? t.nbr[(size_t)e * 3 + f] : -1;
-      const unsigned long long nm = (unsigned long long)(nb >> 2) * NP + m;
-      areg[f] = 0.0;
-#pragma unroll
-      for (int h = 0; h < NH; ++h) {
-        const int v = half * NH + h;
-        nreg[f][h] = R(0);
-        if (nb >= 0 && v < NV) nreg[f][h] = U[v * N + nm];
-      }
-      if (nb >= 0) areg[f] = aux[half * N + nm];
-    }
+    if constexpr (!LATE) tri_neighbours<R, K, RAIN>(t, U, aux, N, e, m, half, lane, nreg, areg);
   }
   tri_copy_tab<R, K>(S);
 
@@ -458,6 +482,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
 #pragma unroll
     for (int v = 0; v < 3 * NV; ++v) S.u.pf[el][q * LD::PF + v] = P[v];
   }
+  if constexpr (LATE) tri_neighbours<R, K, RAIN>(t, U, aux, N, e, m, half, lane, nreg, areg);
   __syncthreads();
 
   // modes: (F, grad psi_m) + (G, psi_m), all variables over half of the points
@@ -618,6 +643,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_mi
     __syncthreads();
     int it = 0, bd = 0;
     if (lane) {
+      if constexpr (LATE) {
+        const TriZ z = tri_z(t, e);
+        b = tri_bg<K>(t, z.layer, z.z0 + z.dz1 * T.rq[q] + z.dz2 * T.sq[q]);
+      }
       tri_split_at<R, K, RAIN>(a, S, el, q, b, S.ts[el][q][0], &it, &bd);
     }
     __syncthreads();
