@@ -283,7 +283,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   // per-wavefront LDS tiles: fluxes of the three directions (later the face
   // corrections), and what the faces inside the brick need of the state and the
   // wave speeds
-  __shared__ R sF_all[WPB][D][NV][NP];
+  __shared__ alignas(16) R sF_all[WPB][D][NV][NP];   // (diffusion: also doubles)
   __shared__ R sI_all[SIP ? 1 : WPB][2][NV][P1 * P1];   // state at the nodes of the inner x and y face
   __shared__ R sL_all[WPB][2][2 * P1 * P1];   // along x and y at the face nodes: side, face node
   __shared__ R sU_all[SIP ? WPB : 1][NV][SIP ? NP : 1];   // (with diffusion, whose gradients need it) all of it
