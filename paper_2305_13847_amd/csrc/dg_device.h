@@ -78,6 +78,21 @@ __device__ __forceinline__ void st(T* base, unsigned n, int v, unsigned i, T x) 
   buf_store(buf_rsrc(base + (size_t)v * n, n), i, x);
 }
 
+// Value i of an FP64 array of one value per node (T, rho_vs) beside a state in
+// R.  An FP32 handle holds up to 2^30 nodes, and from 2^29 on such an array
+// outgrows a 32-bit byte offset: there it is addressed by pointer (one 64-bit
+// add per access, in bounds by the caller).
+template <typename R>
+__device__ __forceinline__ double ld_f64(const double* base, unsigned n, unsigned i) {
+  if constexpr (sizeof(R) == 4) return base[i];
+  else return ld(base, n, 0, i);
+}
+template <typename R>
+__device__ __forceinline__ void st_f64(double* base, unsigned n, unsigned i, double x) {
+  if constexpr (sizeof(R) == 4) base[i] = x;
+  else st(base, n, 0, i, x);
+}
+
 // ---------------------------------------------------------------------------
 // saturation vapour density and the split (FP64)
 // ---------------------------------------------------------------------------

@@ -237,8 +237,8 @@ struct FaceVjp {
 };
 
 template <typename R, int K, int D, int RAIN, int J>
-__device__ __forceinline__ void face_load(const Item& item, const ElemCoord<D>& ec, int ij, int iz, unsigned g,
-                                          unsigned N, const R* __restrict__ U, const double* __restrict__ auxT,
+__device__ __forceinline__ void face_load(const Item& item, const ElemCoord<D>& ec, int ij, int iz, bool active,
+                                          unsigned g, unsigned N, const R* __restrict__ U, const double* __restrict__ auxT,
                                           const double* __restrict__ auxS, const R* __restrict__ lam,
                                           FaceVjp<R, D, RAIN>& f) {
   using S = Shape<K, D, block_threads<R>()>;
@@ -247,7 +247,9 @@ __device__ __forceinline__ void face_load(const Item& item, const ElemCoord<D>& 
   const bool plus = ij == K;
   const int c = ec.c[J], n = item.n[J];
   const bool at_end = plus ? c == n - 1 : c == 0;
-  f.face = ij == 0 || ij == K;
+  // (a thread past the item's end holds no face node: in FP32 it reads the item's
+  // first node throughout, in FP64 the buffer's bounds check covers what it reads)
+  f.face = (sizeof(R) == 8 || active) && (ij == 0 || ij == K);
   f.wall = f.face && at_end && item.bc[J] == 1;
   const int step = at_end ? (plus ? 1 - n : n - 1) : (plus ? 1 : -1);
   const bool nb = f.face && !f.wall;
@@ -256,8 +258,8 @@ __device__ __forceinline__ void face_load(const Item& item, const ElemCoord<D>& 
   for (int v = 0; v < NV; ++v) f.U[v] = ld(U, N, v, gn);
 #pragma unroll
   for (int v = 0; v < NV; ++v) f.L[v] = ld(lam, N, v, gn);
-  f.T = ld(auxT, N, 0, gn);
-  f.rvs = ld(auxS, N, 0, gn);
+  f.T = ld_f64<R>(auxT, N, gn);
+  f.rvs = ld_f64<R>(auxS, N, gn);
   f.izn = J == D - 1 && nb ? item.hoff + (c + step) * P1 + (plus ? 0 : K) : iz;
 }
 
@@ -360,12 +362,12 @@ rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT
   for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
 #pragma unroll
   for (int v = 0; v < NV; ++v) Lq[v] = ld(lam, N, v, g);
-  const double T = ld(auxT, N, 0, g), rvs = ld(auxS, N, 0, g);
+  const double T = ld_f64<R>(auxT, N, g), rvs = ld_f64<R>(auxS, N, g);
   const Bg bg = bg_at(a, iz);
   // a direction's neighbour values are in flight while the previous one is
   // worked on
   FaceVjp<R, D, RAIN> f;
-  face_load<R, K, D, RAIN, 0>(item, ec, idx[0], iz, g, N, U, auxT, auxS, lam, f);
+  face_load<R, K, D, RAIN, 0>(item, ec, idx[0], iz, active, g, N, U, auxT, auxS, lam, f);
 #pragma unroll
   for (int v = 0; v < NV; ++v) sL[v * S::NT + t] = (double)Lq[v];
   __syncthreads();
@@ -379,10 +381,10 @@ rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT
   for (int v = 0; v < NV; ++v) Ub[v] = 0.0;
   {
     FaceVjp<R, D, RAIN> f1;
-    face_load<R, K, D, RAIN, 1>(item, ec, idx[1], iz, g, N, U, auxT, auxS, lam, f1);
+    face_load<R, K, D, RAIN, 1>(item, ec, idx[1], iz, active, g, N, U, auxT, auxS, lam, f1);
     direction_vjp<R, K, D, RAIN, 0>(a, md, t, idx[0], sL, sD, Uq, Lq, wave_speed<R, D, RAIN, 0>(q), f, rev, Ub);
     if constexpr (D == 3)
-      face_load<R, K, D, RAIN, 2>(item, ec, idx[2], iz, g, N, U, auxT, auxS, lam, f);
+      face_load<R, K, D, RAIN, 2>(item, ec, idx[2], iz, active, g, N, U, auxT, auxS, lam, f);
     direction_vjp<R, K, D, RAIN, 1>(a, md, t, idx[1], sL, sD, Uq, Lq, wave_speed<R, D, RAIN, 1>(q), f1, rev, Ub);
   }
   if constexpr (D == 3)
