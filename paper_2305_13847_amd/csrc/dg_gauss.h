@@ -245,8 +245,8 @@ gauss_trace_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ 
     if (active) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
-      T = ld(auxT, N, 0, g);
-      rvs = ld(auxS, N, 0, g);
+      T = ld_f64<R>(auxT, N, g);
+      rvs = ld_f64<R>(auxS, N, g);
     } else {
 #pragma unroll
       for (int v = 0; v < NV; ++v) Uq[v] = R(0);
@@ -319,8 +319,8 @@ rhs_gauss_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ au
   if (active) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
-    T = ld(auxT, N, 0, g);
-    rvs = ld(auxS, N, 0, g);
+    T = ld_f64<R>(auxT, N, g);
+    rvs = ld_f64<R>(auxS, N, g);
   } else {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = R(0);

@@ -436,8 +436,8 @@ __device__ __forceinline__ void pair_load(const R* __restrict__ U, const double*
                                           Pair<R, D, RAIN>& pr) {
 #pragma unroll
   for (int v = 0; v < Vars<D, RAIN>::NV; ++v) pr.nb.U[v] = ld(U, N, v, gn);
-  pr.nb.T = ld(auxT, N, 0, gn);
-  pr.nb.rvs = ld(auxS, N, 0, gn);
+  pr.nb.T = ld_f64<R>(auxT, N, gn);
+  pr.nb.rvs = ld_f64<R>(auxS, N, gn);
 }
 
 // 3D task q (direction, element, side, face node): the own node, and the
@@ -574,8 +574,8 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const Bg& bg, int
     iters = s.iters;
     bad = s.bad;
     const double rvs_st = ((flags & kRefreshRvs) && s.bad == 0) ? rho_vs(a, s.T) : s.rvs;
-    st(oT, N, 0, g, s.T);
-    st(oS, N, 0, g, rvs_st);
+    st_f64<R>(oT, N, g, s.T);
+    st_f64<R>(oS, N, g, rvs_st);
     if (Tnew) *Tnew = s.T;
     if (Snew) *Snew = rvs_st;
   }
@@ -615,8 +615,8 @@ __device__ __forceinline__ void rhs_item_3d(const KArgs& a, int t, int it_, Elem
   if (active) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
-    T = ld(auxT, N, 0, g);
-    rvs = ld(auxS, N, 0, g);
+    T = ld_f64<R>(auxT, N, g);
+    rvs = ld_f64<R>(auxS, N, g);
   } else {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = R(0);
@@ -785,8 +785,8 @@ __device__ __forceinline__ void rhs_item_2d(const KArgs& a, int t, int it_, R* s
   if (active) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
-    T = ld(auxT, N, 0, g);
-    rvs = ld(auxS, N, 0, g);
+    T = ld_f64<R>(auxT, N, g);
+    rvs = ld_f64<R>(auxS, N, g);
     iz = item.hoff + item_coord<D>(item, le).c[1] * P1 + idx[1];
   } else {
 #pragma unroll

@@ -510,8 +510,8 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 #pragma unroll
       for (int v = 0; v < NV; ++v) Uq[v] = ld(U, N, v, g);
     }
-    T = ld(auxT, N, 0, g);
-    rvs = ld(auxS, N, 0, g);
+    T = ld_f64<R>(auxT, N, g);
+    rvs = ld_f64<R>(auxS, N, g);
     if (lane < 6 * kBgStride) (&sB[0][0].x)[lane] = bgt;
     wave_lds_sync();
     if constexpr (SIP) {

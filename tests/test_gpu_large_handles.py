@@ -75,3 +75,15 @@ def test_rhs_vjp(name):
     want = ds.rhs_vjp(U, lam)
     got = db.rhs_vjp(_repeat(U, c, big, rep), _repeat(lam, c, big, rep))
     _same(got, want, c, rep)
+
+
+@pytest.mark.parametrize("name", ["2d-q2", "2d-q4", "3d-q2", "3d-q3", "2d-q3-gauss"])
+def test_rhs_and_step(name):
+    c, big, rep, ds, db = _handles(name, states=14 if "gauss" in name else 9)
+    U = torch.tensor(c.U, dtype=torch.float32, device="cuda")
+    X = _repeat(U, c, big, rep)
+    R = torch.empty_like(X)
+    _same(db.rhs(X, out=R), ds.rhs(U), c, rep)
+    db.rk_step(X, c.dt, 1)
+    ds.rk_step(U, c.dt, 1)
+    _same(X, U, c, rep)
