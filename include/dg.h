@@ -211,7 +211,9 @@ dg_status dg_saturation_split(dg_handle* h, const void* U, double* T, int use_gu
  * the Shu-Osher update; with the sponge on, Section 3.6's relaxation closes
  * every step.  U: caller-owned device array in the state layout.  dt: HOST
  * array of 1 value (single mesh) or nmembers values (batch), each positive
- * and finite, otherwise DG_EINVAL.  Uses the handle's stage buffers. */
+ * and finite, otherwise DG_EINVAL; it is read before the call returns, and a
+ * call that is queued, or captured by the caller into a graph of its own,
+ * keeps the values it was given.  Uses the handle's stage buffers. */
 dg_status dg_rk_step(dg_handle* h, void* U, const double* dt, int nsteps, hipStream_t stream);
 
 /* Vector-Jacobian product of dg_rhs: U_bar = (d rhs / d U)^T dUdt_bar, the
@@ -292,7 +294,7 @@ dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, int nsteps,
 
 /* dg_rk_step (Section 3.3) replayed from a captured hipGraph: the first call
  * for a given (U, nsteps, launch geometry) captures every kernel of the
- * nsteps steps, later calls replay it; dt is uploaded before each replay.
+ * nsteps steps, later calls replay it with the dt they are given.
  * Arguments as dg_rk_step.  Kernel timing must be disabled (DG_EINVAL). */
 dg_status dg_rk_step_graph(dg_handle* h, void* U, const double* dt, int nsteps, hipStream_t stream);
 

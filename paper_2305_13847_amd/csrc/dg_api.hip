@@ -119,7 +119,6 @@ struct dg_handle {
   double* auxT4 = nullptr;
   double* auxS4 = nullptr;
   double* dt_d = nullptr;
-  double* dt_h = nullptr;        // pinned staging for dt
   double* partial = nullptr;
   double* red_out = nullptr;
   unsigned* stats = nullptr;
@@ -359,7 +358,6 @@ static void free_all(dg_handle* h) {
   F(h->auxT); F(h->auxS); F(h->auxT2); F(h->auxS2);
   F(h->auxT3); F(h->auxS3); F(h->auxT4); F(h->auxS4);
   F(h->dt_d); F(h->partial); F(h->red_out); F(h->stats);
-  if (h->dt_h) (void)hipHostFree(h->dt_h);
   if (h->graph_exec) (void)hipGraphExecDestroy(h->graph_exec);
   if (h->graph) (void)hipGraphDestroy(h->graph);
   if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
@@ -615,7 +613,6 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   ok = ok && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) == hipSuccess;
   ok = ok && A((void**)&h->red_out, sizeof(double) * 4);
   ok = ok && A((void**)&h->stats, sizeof(unsigned) * kStatsWords);
-  ok = ok && hipHostMalloc((void**)&h->dt_h, sizeof(double) * nmembers) == hipSuccess;
   if (!ok) {
     const size_t sb = h->state_bytes;
     free_all(h);
@@ -975,13 +972,35 @@ static const Stage kSSP43[4] = {{0, 1, 0.5}, {0, 1, 0.5}, {2.0 / 3.0, 1.0 / 3.0,
 static const Stage kSSP33[3] = {{0, 1, 1}, {0.75, 0.25, 0.25}, {1.0 / 3.0, 2.0 / 3.0, 2.0 / 3.0}};
 
 // The time step(s) of a call: one value goes to the kernels with their
-// arguments; an ensemble's, and those a captured graph reads, are uploaded.
-// (A small copy in the stream costs about 3 us between kernels: the gradient of
-// 20 steps on 64 x 32 Q3, 38 of them, 2.14 -> 2.03 ms.)
+// arguments; an ensemble's, and those a captured graph reads, to the handle's
+// device array.  They travel as arguments of a kernel too, which the launch
+// copies: a queued call, and a launch captured by the caller, keeps its own
+// whatever is called next.  (A host buffer would be read when the stream gets
+// there, and by then hold a later call's.  One value costs nothing this way,
+where a small copy in the stream cost about 3 us between kernels: the gradient
+of 20 steps on 64 x 32 Q3, 38 of them, 2.14 -> 2.03 ms.)
 struct Dt {
   const double* dev = nullptr;
   double value = 1.0;
 };
+
+template <int N>
+struct DtArgs {
+  double v[N];
+};
+
+template <int N>
+__global__ void set_dt_kernel(DtArgs<N> a, int n, double* __restrict__ dt) {
+  const int i = threadIdx.x;
+  if (i < n) dt[i] = a.v[i];
+}
+
+template <int N>
+static void set_dt(const double* dt, int n, double* dst, hipStream_t s) {
+  DtArgs<N> a{};
+  for (int i = 0; i < n; ++i) a.v[i] = dt[i];
+  hipLaunchKernelGGL(set_dt_kernel<N>, dim3(1), dim3(N), 0, s, a, n, dst);
+}
 
 static dg_status take_dt(dg_handle* h, const double* dt, hipStream_t s, bool device, Dt* out) {
   for (int m = 0; m < h->nmembers; ++m)
@@ -990,8 +1009,13 @@ static dg_status take_dt(dg_handle* h, const double* dt, hipStream_t s, bool dev
     out->value = dt[0];
     return DG_OK;
   }
-  for (int m = 0; m < h->nmembers; ++m) h->dt_h[m] = dt[m];
-  HIP_TRY(hipMemcpyAsync(h->dt_d, h->dt_h, sizeof(double) * h->nmembers, hipMemcpyHostToDevice, s));
+  for (int m = 0; m < h->nmembers; m += 256) {
+    const int n = std::min(256, h->nmembers - m);
+    if (n > 64) set_dt<256>(dt + m, n, h->dt_d + m, s);
+    else if (n > 8) set_dt<64>(dt + m, n, h->dt_d + m, s);
+    else set_dt<8>(dt + m, n, h->dt_d + m, s);
+  }
+  HIP_TRY(hipGetLastError());
   out->dev = h->dt_d;
   return DG_OK;
 }
@@ -1366,7 +1390,7 @@ extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, 
 
 // nsteps RK steps replayed from a captured hipGraph.  The graph holds the
 // split and stage kernels of all steps; dt is read from device memory, which
-// is updated before each replay.  It is captured again when U, nsteps or the
+// a kernel ahead of each replay sets.  It is captured again when U, nsteps or the
 // launch geometry change.
 extern "C" dg_status dg_rk_step_graph(dg_handle* h, void* U, const double* dt, int nsteps, hipStream_t s) {
   dg_status st = ready(h);
