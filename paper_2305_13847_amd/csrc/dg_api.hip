@@ -977,8 +977,8 @@ static const Stage kSSP33[3] = {{0, 1, 1}, {0.75, 0.25, 0.25}, {1.0 / 3.0, 2.0 /
 // copies: a queued call, and a launch captured by the caller, keeps its own
 // whatever is called next.  (A host buffer would be read when the stream gets
 // there, and by then hold a later call's.  One value costs nothing this way,
-where a small copy in the stream cost about 3 us between kernels: the gradient
-of 20 steps on 64 x 32 Q3, 38 of them, 2.14 -> 2.03 ms.)
+// where a small copy in the stream cost about 3 us between kernels: the gradient
+// of 20 steps on 64 x 32 Q3, 38 of them, 2.14 -> 2.03 ms.)
 struct Dt {
   const double* dev = nullptr;
   double value = 1.0;
