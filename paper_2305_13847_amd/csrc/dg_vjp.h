@@ -152,17 +152,18 @@ struct Reverse {
     if (RAIN) {
       const double Sb = Gb[V::RM] - Gb[V::RR];
       const double dvs = rvs - rv;                    // 0 on the saturated branch
-      double rcb = 0.0, dvsb = 0.0;
+      double rcb = 0.0, dvsb = 0.0, ip12 = 0.0;
       if (rr > 0.0) {
         const double Aev = 3.86e-3 - 9.41e-5 * Tm;
         double p316, p12, p78;
         kessler_pow(rr, p316, p12, p78);
-        const double irr = rcp64(rr);
+        // (1/rr only by halves: it overflows for the thinnest rain, its square root does not)
+        ip12 = rcp64(p12);
         const double Bev = 1.0 + 9.1 * p316;
         Tb += Sb * (-9.41e-5) * Bev * dvs * p12;
         dvsb += Sb * Aev * Bev * p12;
         // p12' = p12 / (2 rr), p316' = 3/16 p316 / rr, p78' = 7/8 p78 / rr
-        rrb += Sb * irr * (Aev * dvs * p12 * (9.1 * 0.1875 * p316 + 0.5 * Bev) - 1.72 * 0.875 * rc * p78);
+        rrb += Sb * (Aev * dvs * ip12 * (9.1 * 0.1875 * p316 + 0.5 * Bev) - 1.72 * 0.875 * rc * (p78 * ip12 * ip12));
         rcb -= Sb * 1.72 * p78;
       }
       if (rc - a.q_au * rho > 0.0) {                    // autoconversion
@@ -176,7 +177,7 @@ struct Reverse {
       }
       rmb += rcb;
       rvb -= rcb;
-      if (a.vr_mode != 0 && rr > 0.0) rrb += vrb * vr * 0.125 * rcp64(rr);
+      if (a.vr_mode != 0 && rr > 0.0) rrb += vrb * (vr * 0.125 * ip12 * ip12);
     }
     // H = E + p, p' = p - p_bar
     Eb += Hb;
