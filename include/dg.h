@@ -93,8 +93,13 @@ typedef struct {
   double q_au;                /* autoconversion threshold (0 in the paper)     */
   int precision;              /* DG_FP64 or DG_FP32_BULK                       */
   int rk;                     /* DG_SSPRK43 (default) or DG_SSPRK33            */
-  double newton_rtol;         /* split stops when |dT| <= rtol * T (1e-14)     */
-  int newton_maxit;           /* iteration cap (30); counted as non-converged  */
+  /* The split's solve: Newton iterations stop when |dT| <= rtol T, or above
+   * 150 K when dT^2 <= 4 rtol T (then the next one would be below rounding);
+   * a solve that reaches maxit counts as non-converged.  With rtol >= 1e-14 and
+   * maxit > 8 a closed form, exact to about 1e-14 of T, takes the place of the
+   * iterations wherever its own test accepts it. */
+  double newton_rtol;         /* > 0 (1e-14)                                   */
+  int newton_maxit;           /* >= 1 (30)                                     */
   /* Rayleigh sponge layer (Section 3.6): at the end of
    * every RK step, (rho_m', rho_r', m, E') <- (1 - delta(z)) (rho_m', rho_r',
    * m, E') with delta(z) = alpha/2 (1 - cos(pi (z - zD)/(zT - zD))) above zD
@@ -131,7 +136,9 @@ typedef struct {
 typedef struct {
   long long splits;           /* node splits performed since the last reset    */
   long long nonconverged;     /* splits that hit newton_maxit                  */
-  int max_iters;              /* largest Newton iteration count seen           */
+  int max_iters;              /* largest count of one saturated solve: Newton
+                                 steps, or of the closed form the steps of its
+                                 single precision start and its FP64 steps     */
   int nonfinite;              /* 1 if a non-finite or invalid state was seen   */
 } dg_stats;
 

@@ -73,6 +73,9 @@ void fill_thermo(KArgs& a, const dg_params* p) {
   a.q_au = p->q_au;
   a.rain = p->rain; a.vr_mode = p->vr_mode;
   a.rtol = p->newton_rtol; a.maxit = p->newton_maxit;
+  // the closed form is exact to about 1e-14 of T and takes up to kEstIters + 1
+  // steps; settings that ask for more, or allow less, iterate
+  a.closed = a.maxit > kEstIters && a.rtol >= 1e-14;
 }
 }  // namespace dgm
 

@@ -74,6 +74,7 @@ struct KArgs {
   int rain, vr_mode;
   double rtol;
   int maxit;
+  int closed;                      // the split may solve in closed form (kEstIters)
   // nodal tables of the basis (Lobatto, or Gauss for basis 1):
   // Dhat[i*(k+1)+a] = w_a D_ai / w_i, weights w
   double Dhat[kMaxP1 * kMaxP1];

@@ -422,7 +422,7 @@ __device__ __forceinline__ NearOut split_mid(const KArgs& a, double rd, double r
     const double dT = -(Cv * Tm + o.rvs * a.Lp - re) * rcp64(Cv + dr * (dc * Tm + a.Lp));
     o.T += dT;
     o.rvs += dr * dT;
-    small = dT * dT <= 4.0 * fmin(a.rtol, 1e-14) * Tn;
+    small = dT * dT <= 4.0e-14 * Tn;
   }
   const bool branch = sat ? o.rvs <= rm : rm <= o.rvs;
   o.ok = branch && small && fabs(x) <= kAnchorX && T0 > 150.0 && T0 < 600.0 && r0 > 0.0;
@@ -446,7 +446,7 @@ __device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double
   }
   o.T = n.T;
   o.rvs = n.rvs;
-  if (!n.ok || a.maxit <= kEstIters) {
+  if (!n.ok || !a.closed) {
     Anchor A;
     A.T0 = 0.0; A.r0 = 0.0; A.inv0 = 0.0;
     if (T > 150.0 && T < 600.0 && rvs > 0.0) {
@@ -475,7 +475,7 @@ __device__ __forceinline__ float rho_vs_est(const KArgs& a, float T, float* q) {
 // returned rho_vs(T) comes from a fresh evaluation at most 0.03 K away (the
 // estimate's error), so it can anchor later splits.  `iters` counts the
 // estimate's steps and the FP64 solve; a cap (newton_maxit) below what this
-// may use takes the general path.
+// may use, or a tolerance below what it gives, takes the general path.
 // FP64 iterations throughout took 970-1100 VALU instructions per wavefront
 // (three or four exp/log anchors) and kept the VALU 75-100 % busy; two cold
 // splits and a right-hand side on 50 x 42 x 26 Q3 in FP32: 272 -> 177 us.
@@ -484,7 +484,7 @@ __device__ __forceinline__ SplitOut split_scratch(const KArgs& a, double rd, dou
                                                   double guess) {
   SplitOut o;
   bool ok = false;
-  if (a.maxit > kEstIters) {
+  if (a.closed) {
     const double Cs = fma(a.cvd, rd, a.cl * (rm + rr));
     const double Cu = fma(a.cvv - a.cl, rm, Cs);
     const double Tu = a.Tref + (re - rm * a.Lp) * rcp64(Cu);
