@@ -60,7 +60,7 @@ typedef struct dg_handle dg_handle;
 typedef enum {
   DG_OK = 0,
   DG_EINVAL = -1,        /* bad argument (sizes, orders, pointers)            */
-  DG_ENOMEM = -2,        /* device allocation failed in dg_create*            */
+  DG_ENOMEM = -2,        /* device allocation failed (dg_create*, dg_set_launch) */
   DG_EHIP = -3,          /* a HIP runtime call failed                          */
   DG_ENOCONV = -4,       /* dg_get_stats: some Newton solve did not converge  */
   DG_ENONFINITE = -5,    /* dg_get_stats: non-finite or invalid state seen    */
@@ -279,7 +279,10 @@ dg_status dg_destroy(dg_handle* h);
  * n x CUs blocks that walk the work items).  Persistence applies to the
  * Lobatto-basis stage kernel of dg_rk_step only; every other kernel takes
  * one block per work item.  The Q3 hexahedral right-hand sides take
- * fixed bricks of 2 x 2 elements per block, whatever is set here.  Not a hot call: synchronises. */
+ * fixed bricks of 2 x 2 elements per block, whatever is set here.  Not a hot
+ * call: synchronises.  Blocks smaller than the default need a larger table of
+ * work items (64 bytes each), allocated when they are first set; DG_ENOMEM if
+ * that fails, with the geometry as it was. */
 dg_status dg_set_launch(dg_handle* h, int elems_per_block, int persist_per_cu);
 dg_status dg_get_launch(const dg_handle* h, int* elems_per_block, int* persist_per_cu);
 

@@ -96,7 +96,8 @@ struct dg_handle {
   size_t state_bytes = 0;
   // device
   MemberDesc* mem_d = nullptr;
-  Item* items_d = nullptr;
+  Item* items_d = nullptr;       // holds items_cap items
+  std::vector<Item*> items_old;  // outgrown tables: launches captured by the caller may read them
   Item* bricks_d = nullptr;
   double* bg_d[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // rd, rm, rr, E, p
   void* stage[2] = {nullptr, nullptr};
@@ -352,6 +353,7 @@ static void gauss_tables(int k, double* x, double* w, double* Dhat, double* lm, 
 static void free_all(dg_handle* h) {
   auto F = [](void* p) { if (p) (void)hipFree(p); };
   F(h->mem_d); F(h->items_d); F(h->bricks_d); F(h->ka_d);
+  for (auto b : h->items_old) F(b);
   for (auto& b : h->bg_d) F(b);
   for (auto& b : h->stage) F(b);
   for (auto& b : h->stage_x) F(b);
@@ -550,7 +552,7 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
     nvert_tot += h->nvert[m];
   }
   build_items(h, epb);
-  h->items_cap = items_max;
+  h->items_cap = (long long)h->items.size();   // (more when dg_set_launch asks for smaller blocks)
   {
     int dev = 0;
     hipDeviceProp_t prop;
@@ -612,7 +614,7 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
     }
   }
   ok = ok && A((void**)&h->dt_d, sizeof(double) * nmembers);
-  ok = ok && A((void**)&h->partial, sizeof(double) * 3 * h->items_cap);
+  ok = ok && A((void**)&h->partial, sizeof(double) * 3 * items_max);
   ok = ok && hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking) == hipSuccess;
   ok = ok && A((void**)&h->red_out, sizeof(double) * 4);
   ok = ok && A((void**)&h->stats, sizeof(unsigned) * kStatsWords);
@@ -1286,7 +1288,22 @@ extern "C" dg_status dg_timing_read(dg_handle* h, int kclass, double* total_ms, 
   return DG_OK;
 }
 
+// The table goes where the last one was, or into a larger allocation: a full one
+// from the start (an item per element) would be 64 bytes an element, nearly a
+// state's size at 2D Q1 in FP32.
 static dg_status upload_items(dg_handle* h) {
+  const long long n = (long long)h->items.size();
+  if (n > h->items_cap) {
+    Item* p = nullptr;
+    if (hipMalloc((void**)&p, sizeof(Item) * n) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(DG_ENOMEM, "device allocation failed (%lld work items)", n);
+    }
+    h->items_old.push_back(h->items_d);
+    h->items_d = p;
+    h->items_cap = n;
+    h->ka.items = p;
+  }
   HIP_TRY(hipMemcpy(h->items_d, h->items.data(), sizeof(Item) * h->items.size(), hipMemcpyHostToDevice));
   if (!h->bricks.empty())
     HIP_TRY(hipMemcpy(h->bricks_d, h->bricks.data(), sizeof(Item) * h->bricks.size(), hipMemcpyHostToDevice));
@@ -1303,8 +1320,10 @@ extern "C" dg_status dg_set_launch(dg_handle* h, int epb, int persist) {
   if (persist < 0 || persist > 64) return fail(DG_EINVAL, "persistent blocks per CU must be in 0..64");
   HIP_TRY(hipDeviceSynchronize());
   if (epb != h->epb) {
+    const int before = h->epb;
     build_items(h, epb);
     dg_status st = upload_items(h);
+    if (st == DG_ENOMEM) build_items(h, before);   // (the table on the device is still the one before)
     if (st != DG_OK) return st;
   }
   h->persist = persist;
@@ -1365,6 +1384,7 @@ extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, 
     for (int ip = 0; ip < 4; ++ip) {
       st = dg_set_item_order(h, io);
       if (st == DG_OK) st = dg_set_launch(h, cand_e[ie], cand_p[ip]);
+      if (st == DG_ENOMEM) continue;
       if (st != DG_OK) { h->timing = timing; return st; }
       HIP_TRY(hipMemcpy(W, U, h->state_bytes, hipMemcpyDeviceToDevice));
       int cur = 0;
