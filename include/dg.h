@@ -279,7 +279,8 @@ dg_status dg_destroy(dg_handle* h);
  * n x CUs blocks that walk the work items).  Persistence applies to the
  * Lobatto-basis stage kernel of dg_rk_step only; every other kernel takes
  * one block per work item.  The Q3 hexahedral right-hand sides take
- * fixed bricks of 2 x 2 elements per block, whatever is set here.  Not a hot
+ * fixed bricks of 2 x 2 elements per block (1 along x or y where no member has
+ * more), whatever is set here.  Not a hot
  * call: synchronises.  Blocks smaller than the default need a larger table of
  * work items (64 bytes each), allocated when they are first set; DG_ENOMEM if
  * that fails, with the geometry as it was. */

@@ -88,7 +88,8 @@ struct dg_handle {
   std::vector<MemberDesc> mem;
   std::vector<Item> items;
   std::vector<int> item_off;     // first item of each member (+ total)
-  std::vector<Item> bricks;      // Q3 hexahedra: the stage kernels' items
+  std::vector<Item> bricks;      // Q3 hexahedra: the stage kernels' items,
+  int brick[2] = {1, 1};         // of this many elements along x and y: 2 unless no member has two
   std::vector<int> hoff;         // first background index of each member (+ total)
   std::vector<char> bg_set;
   long long etot = 0, nnodes = 0;
@@ -438,8 +439,9 @@ static void build_items(dg_handle* h, int epb, int order = -1) {
         h->items.push_back(make_item(md, m, e0 - r0, c1, c2));
     });
     if (q3) {
-      for_rows(md, 3, (md.n[0] + 1) / 2, 2, order, [&](int c1, int c2) {
-        for (int c0 = 0; c0 < md.n[0]; c0 += 2) h->bricks.push_back(make_item(md, m, c0, c1, c2));
+      const int bx = h->brick[0];
+      for_rows(md, 3, (md.n[0] + bx - 1) / bx, h->brick[1], order, [&](int c1, int c2) {
+        for (int c0 = 0; c0 < md.n[0]; c0 += bx) h->bricks.push_back(make_item(md, m, c0, c1, c2));
       });
     }
   }
@@ -551,6 +553,9 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
     h->mem[m].voff = nvert_tot;
     nvert_tot += h->nvert[m];
   }
+  for (const MemberDesc& md : h->mem)
+    for (int a = 0; a < 2; ++a)
+      if (md.n[a] > 1) h->brick[a] = 2;
   build_items(h, epb);
   h->items_cap = (long long)h->items.size();   // (more when dg_set_launch asks for smaller blocks)
   {
@@ -667,6 +672,8 @@ extern "C" dg_status dg_create_batch(const dg_mesh* meshes, int nmembers, int or
   a.epb = h->epb;
   a.bricks = h->bricks_d;
   a.nbricks = (int)h->bricks.size();
+  a.brick[0] = h->brick[0];
+  a.brick[1] = h->brick[1];
   a.nmembers = nmembers;
   a.etot = h->etot;
   a.nnodes = (unsigned)h->nnodes;

@@ -113,6 +113,7 @@ struct KArgs {
   int epb;                         // elements per work item
   const Item* bricks;              // Q3 hexahedra: bricks (first element and its coordinates)
   int nbricks;
+  int brick[2];                    // their elements along x and y
   int nmembers;
   long long etot;                  // elements of all members
   unsigned nnodes;                 // nodes of all members: the stride between variables

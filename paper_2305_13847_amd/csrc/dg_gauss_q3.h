@@ -1,7 +1,7 @@
 // Right-hand side / stage kernel of the Gauss basis on Q3 hexahedra: the method
 // of dg_gauss.h (its trace buffers included) on the bricks of dg_q3.h.
 //
-// One wavefront per element, a 2 x 2 brick (x, y) per block.
+// One wavefront per element, a 2 x 2 brick (x, y) per block (Brick).
 // Everything that depends on the element alone is wave-uniform.  Of an
 // element's 96 face points the 64 on the brick's outside are one pass of its
 // lanes: the own trace from its LDS tiles, the neighbour's from the trace
@@ -185,16 +185,17 @@ constexpr int gq3_min_waves() { return sizeof(R) == 4 ? 4 : 3; }
 template <typename R>
 constexpr int gq3_tiles() { return sizeof(R) == 4 ? 3 : 1; }
 
-template <typename R, int RAIN, int MODE>
-__global__ void __launch_bounds__(64 * kBrick) __attribute__((amdgpu_waves_per_eu(gq3_min_waves<R>())))
+template <typename R, int RAIN, int MODE, int BX, int BY>
+__global__ void __launch_bounds__(64 * BX * BY) __attribute__((amdgpu_waves_per_eu(gq3_min_waves<R>())))
 rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
                     const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
                     const double* __restrict__ dt_m, double c0, double c1, double c2, double* __restrict__ oT,
                     double* __restrict__ oS, int flags) {
-  constexpr int P1 = 4, NP = 64, D = 3, WPB = kBrick;
+  constexpr int P1 = 4, NP = 64, D = 3, WPB = BX * BY;
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
   constexpr int TILES = gq3_tiles<R>();
+  constexpr int XF = BX == 2 ? BY : 0, YF = BY == 2 ? BX : 0;   // x and y faces inside the brick
   // per element: the fluxes of TILES directions (after the volume term those of its
   // outer face points), the state, T and rho_v
   __shared__ R sF_all[WPB][TILES == 3 ? D * NV * NP : NV * 96];
@@ -234,10 +235,9 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
   // element (scalar): coordinates, partners inside the brick, outer faces
   const int n0 = item.n[0], n1 = item.n[1], n2 = item.n[2];
   const int b0 = item.bc[0], b1 = item.bc[1], b2 = item.bc[2];
-  const int dx = w & 1, dy = w >> 1;
-  const int ex = item.c0 + dx, ey = (item.c12 & 0xffff) + dy, ez = item.c12 >> 16;
-  const bool act = ex < n0 && ey < n1;     // wave-uniform (odd mesh sizes)
-  const bool px = dx == 1 || ex + 1 < n0, py = dy == 1 || ey + 1 < n1;
+  const Brick<BX, BY> br(item, w);
+  const int dx = br.dx, dy = br.dy, ex = br.ex, ey = br.ey, ez = br.ez;
+  const bool act = br.act, px = br.px, py = br.py;   // wave-uniform
   const int e = item.eoff + item.e0 + dx + dy * n0;
   const unsigned N = a.nnodes, ntr = (unsigned)a.etot * 96u;
   const unsigned g = (unsigned)e * NP + lane;
@@ -332,14 +332,14 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
         gq3_outer<R, RAIN>(a, f1, nb0, sU, sT_all[w], sRv_all[w], sW, sWd, sB, sX);
       }
     }
-    // the faces inside the brick, one per wavefront: x faces of rows 0, 1, then
-    // y faces of columns 0, 1.  Lanes 0..15 the lower
+    // the faces inside the brick, one per wavefront: the x faces of its rows, then
+    // the y faces of its columns.  Lanes 0..15 the lower
     // element's side, 16..31 the upper's.
-    const int J = w >> 1, k = w & 1;
+    const int J = w < XF ? 0 : 1, k = w - (J ? XF : 0);
     const int cx = item.c0 + (J ? k : 1), cy = (item.c12 & 0xffff) + (J ? 1 : k);
-    if (cx < n0 && cy < n1) {
+    if (w < XF + YF && cx < n0 && cy < n1) {
       const int up = (lane >> 4) & 1;
-      const int ww = J ? k + 2 * up : 2 * k + up;
+      const int ww = J ? k + BX * up : BX * k + up;
       int l0, str;
       gq3_line(J, fp & 3, fp >> 2, l0, str);
       R Uo[NV], Fo[NV], lo;
@@ -369,8 +369,8 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     // inner face numbers of this element: x face of row dy, y face of column dx
     const R* const xm = dx == 1 ? &sI[0][16 * dy] : &sX[0][0];
     const R* const xp = dx == 0 && px ? &sI[0][16 * dy] : &sX[0][16];
-    const R* const ym = dy == 1 ? &sI[0][32 + 16 * dx] : &sX[0][32];
-    const R* const yp = dy == 0 && py ? &sI[0][32 + 16 * dx] : &sX[0][48];
+    const R* const ym = dy == 1 ? &sI[0][16 * (XF + dx)] : &sX[0][32];
+    const R* const yp = dy == 0 && py ? &sI[0][16 * (XF + dx)] : &sX[0][48];
     const int sxm = dx == 1 ? 64 : 96, sxp = dx == 0 && px ? 64 : 96;   // their rows
     const int sym = dy == 1 ? 64 : 96, syp = dy == 0 && py ? 64 : 96;
     const int fx = lj + P1 * ll, fy = li + P1 * ll, fz = li + P1 * lj;
@@ -414,14 +414,14 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
 // Traces of a state that no stage produced, at the outer faces of the bricks.  The
 // block kernel (gauss_trace_kernel) wrote all 96 face points of an element, those
 // inside a brick for nothing: 48 x 48 x 24 in FP32 with rain 74 -> 62 us.
-template <typename R, int RAIN>
-__global__ void __launch_bounds__(64 * kBrick)
+template <typename R, int RAIN, int BX, int BY>
+__global__ void __launch_bounds__(64 * BX * BY)
 gauss_q3_trace_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
                       const double* __restrict__ auxS) {
   using V = Vars<3, RAIN>;
-  constexpr int NV = V::NV, NP = 64;
-  __shared__ R sU_all[kBrick][NV][NP];
-  __shared__ double sT_all[kBrick][NP], sRv_all[kBrick][NP];
+  constexpr int NV = V::NV, NP = 64, WPB = BX * BY;
+  __shared__ R sU_all[WPB][NV][NP];
+  __shared__ double sT_all[WPB][NP], sRv_all[WPB][NP];
   __shared__ R sW[2][4];
   __shared__ double sWd[2][4];
   const int it_ = ItemWalk(a.nbricks).item(0);
@@ -429,11 +429,10 @@ gauss_q3_trace_kernel(KArgs a, const R* __restrict__ U, const double* __restrict
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int lane = (int)(threadIdx.x & 63);
   const Item item = a.bricks[it_];
-  const int dx = w & 1, dy = w >> 1;
-  const int n0 = item.n[0], n1 = item.n[1];
-  const int ex = item.c0 + dx, ey = (item.c12 & 0xffff) + dy, ez = item.c12 >> 16;
-  if (ex >= n0 || ey >= n1) return;        // wave-uniform; the block never meets
-  const bool px = dx == 1 || ex + 1 < n0, py = dy == 1 || ey + 1 < n1;
+  const Brick<BX, BY> br(item, w);
+  const int dx = br.dx, dy = br.dy, n0 = item.n[0], ez = br.ez;
+  const bool px = br.px, py = br.py;
+  if (!br.act) return;                     // wave-uniform; the block never meets
   const int e = item.eoff + item.e0 + dx + dy * n0;
   const unsigned N = a.nnodes, ntr = (unsigned)a.etot * 96u, g = (unsigned)e * NP + lane;
   R Uq[NV];

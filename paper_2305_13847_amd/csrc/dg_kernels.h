@@ -65,8 +65,27 @@ struct ItemWalk {
   }
 };
 
-// Q3 hexahedra: elements per block, a 2 x 2 brick
-constexpr int kBrick = 4;
+// Q3 hexahedra: a block is a brick of BX x BY elements (x, y), 2 x 2; meshes of
+// one element along x or y throughout take 1 there.  (Half or three quarters of a
+// 2 x 2 brick's wavefronts would have nothing to do, and its LDS still keeps
+// others out: with rain, two steps, 1 x 1 x 8192 in FP32 298 -> 182 us, FP64
+// 546 -> 266, 160 x 1 x 80 with diffusion in FP64 1375 -> 905.)  Element (dx, dy)
+// of the brick is wavefront dx + BX dy.
+template <int BX, int BY>
+struct Brick {
+  static constexpr int WPB = BX * BY;
+  int dx, dy, ex, ey, ez;   // this wavefront's element: in the brick, in the mesh
+  bool act, px, py;         // it exists (odd mesh sizes); its partners in x and y do
+  __device__ __forceinline__ Brick(const Item& item, int w)
+      : dx(BX == 2 ? w & 1 : 0),
+        dy(BY == 2 ? w >> (BX - 1) : 0),
+        ex(item.c0 + dx),
+        ey((item.c12 & 0xffff) + dy),
+        ez(item.c12 >> 16),
+        act(ex < item.n[0] && ey < item.n[1]),
+        px(BX == 2 && (dx == 1 || ex + 1 < item.n[0])),
+        py(BY == 2 && (dy == 1 || ey + 1 < item.n[1])) {}
+};
 
 // Threads of a block of the 2D and 3D block kernels for `nodes` nodes: whole
 // wavefronts; at 2D Q2, where an element has 12 face nodes to its 9 nodes, as

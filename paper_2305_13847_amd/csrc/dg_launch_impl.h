@@ -30,6 +30,17 @@ bool dispatch_shape(int K, int D, int rain, F&& f) {
   return false;
 }
 
+// f(BX, BY) with the brick of the handle
+template <typename F>
+void dispatch_brick(const KArgs& a, F&& f) {
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 2> two{};
+  if (a.brick[0] == 2 && a.brick[1] == 2) f(two, two);
+  else if (a.brick[0] == 2) f(two, one);
+  else if (a.brick[1] == 2) f(one, two);
+  else f(one, one);
+}
+
 template <typename R>
 bool LaunchPoint<R>::split(const KArgs& a, LaunchCfg lc, int K, int D, int rain, int item0, int nitems,
     const void* U, const double* guess, double* oT, double* o1, double* o2, int api,
@@ -104,16 +115,19 @@ hipLaunchKernelGGL((KER<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, a
       // Q3 hexahedra: one block per brick whatever the launch geometry of the
       // other kernels
       grid = dim3(grid_for_items(a.nbricks));
+      dispatch_brick(a, [&](auto bx, auto by) {
+        constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
 #define DGM_Q3(M, SIP)                                                                              \
-  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M, SIP>), grid, dim3(64 * kBrick), 0, s, a,                \
+  hipLaunchKernelGGL((rhs_q3_kernel<R, R_, M, SIP, BX, BY>), grid, dim3(64 * BX * BY), 0, s, a,      \
                      (const R*)U, auxT, auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
-      if (flags & kSip) {
-        if (mode == 0) DGM_Q3(0, 1);
-        else DGM_Q3(2, 1);
-      } else {
-        if (mode == 0) DGM_Q3(0, 0);
-        else DGM_Q3(2, 0);
-      }
+        if (flags & kSip) {
+          if (mode == 0) DGM_Q3(0, 1);
+          else DGM_Q3(2, 1);
+        } else {
+          if (mode == 0) DGM_Q3(0, 0);
+          else DGM_Q3(2, 0);
+        }
+      });
 #undef DGM_Q3
     } else if (mode != 2 || !persist) {
       // rhs_kernel takes one work item per block: the full grid
@@ -139,12 +153,15 @@ hipLaunchKernelGGL((rhs_gauss_kernel<R, K_, D_, R_, M>), grid, block, 0, s, a, (
                    auxS, (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
     if constexpr (K_ == 3 && D_ == 3) {
       if (a.nbricks > 0) {
-        const dim3 bgrid(grid_for_items(a.nbricks)), bblock(64 * kBrick);
+        dispatch_brick(a, [&](auto bx, auto by) {
+          constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
 #define DGM_GQ3(M)                                                                                    \
-  hipLaunchKernelGGL((rhs_gauss_q3_kernel<R, R_, M>), bgrid, bblock, 0, s, a, (const R*)U, auxT, auxS, \
-                     (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
-        if (mode == 0) DGM_GQ3(0);
-        else DGM_GQ3(2);
+  hipLaunchKernelGGL((rhs_gauss_q3_kernel<R, R_, M, BX, BY>), dim3(grid_for_items(a.nbricks)),         \
+                     dim3(64 * BX * BY), 0, s, a, (const R*)U, auxT, auxS, (R*)out, (const R*)U0, dt,  \
+                     c0, c1, c2, oT, oS, flags)
+          if (mode == 0) DGM_GQ3(0);
+          else DGM_GQ3(2);
+        });
 #undef DGM_GQ3
         return;
       }
@@ -162,8 +179,11 @@ bool LaunchGauss<R>::gauss_trace(const KArgs& a, LaunchCfg lc, int K, int D, int
     constexpr int K_ = decltype(k)::value, D_ = decltype(d)::value, R_ = decltype(r)::value;
     if constexpr (K_ == 3 && D_ == 3) {
       if (a.nbricks > 0) {
-        hipLaunchKernelGGL((gauss_q3_trace_kernel<R, R_>), dim3(grid_for_items(a.nbricks)), dim3(64 * kBrick), 0, s,
-                           a, (const R*)U, auxT, auxS);
+        dispatch_brick(a, [&](auto bx, auto by) {
+          constexpr int BX = decltype(bx)::value, BY = decltype(by)::value;
+          hipLaunchKernelGGL((gauss_q3_trace_kernel<R, R_, BX, BY>), dim3(grid_for_items(a.nbricks)),
+                             dim3(64 * BX * BY), 0, s, a, (const R*)U, auxT, auxS);
+        });
         return;
       }
     }

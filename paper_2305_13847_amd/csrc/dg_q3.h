@@ -1,5 +1,5 @@
 // Stage kernel for Q3 hexahedra (Lobatto basis): one wavefront per element, a
-// 2 x 2 brick (x, y) of elements per block.
+// 2 x 2 brick (x, y) of elements per block (Brick; thinner on columns and slabs).
 //
 // A Q3 hexahedron has (3+1)^3 = 64 nodes, so lane n of a wavefront owns node
 // n = i + 4 j + 16 l of one element.  Everything that depends on the element
@@ -269,8 +269,8 @@ __device__ __forceinline__ void sip_viscosity(const KArgs& a, const Item& item, 
 template <typename R, int SIP>
 constexpr int q3_min_waves() { return sizeof(R) == 4 ? (SIP ? 4 : 5) : (SIP ? 2 : 3); }
 
-template <typename R, int RAIN, int MODE, int SIP>
-__global__ void __launch_bounds__(64 * kBrick)
+template <typename R, int RAIN, int MODE, int SIP, int BX, int BY>
+__global__ void __launch_bounds__(64 * BX * BY)
 __attribute__((amdgpu_waves_per_eu(q3_min_waves<R, SIP>())))
 rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
               const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
@@ -279,7 +279,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   constexpr int K = 3, P1 = 4, NP = 64, D = 3;
   using V = Vars<D, RAIN>;
   constexpr int NV = V::NV;
-  constexpr int WPB = kBrick;   // wavefronts (elements) per block
+  constexpr int WPB = BX * BY;   // wavefronts (elements) per block
   // per-wavefront LDS tiles: fluxes of the three directions (later the face
   // corrections), and what the faces inside the brick need of the state and the
   // wave speeds
@@ -309,10 +309,9 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   // element (scalar): coordinates, partners inside the brick, outer faces
   const int n0 = item.n[0], n1 = item.n[1], n2 = item.n[2];
   const int b0 = item.bc[0], b1 = item.bc[1], b2 = item.bc[2];
-  const int dx = w & 1, dy = w >> 1;
-  const int ex = item.c0 + dx, ey = (item.c12 & 0xffff) + dy, ez = item.c12 >> 16;
-  const bool act = ex < n0 && ey < n1;     // wave-uniform (odd mesh sizes)
-  const bool px = dx == 1 || ex + 1 < n0, py = dy == 1 || ey + 1 < n1;
+  const Brick<BX, BY> br(item, w);
+  const int dx = br.dx, dy = br.dy, ex = br.ex, ey = br.ey, ez = br.ez;
+  const bool act = br.act, px = br.px, py = br.py;   // wave-uniform
   const int e = item.e0 + dx + dy * n0;
   const unsigned N = a.nnodes;
   const unsigned gbase = (unsigned)(item.eoff + e) * NP;   // first node of the element
@@ -410,7 +409,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
     // inner face points: lanes 0..31, and 32..63 for the other half of the variables
     const int ji = (lane >> 4) & 1, v0 = (lane >> 5) * (NV - VH);
     const int si = ji ? 1 - dy : 1 - dx;
-    const bool inner = ji ? py : px;
+    const bool inner = WPB > 1 && (ji ? py : px);
     if (act) {
       sip_outer<R, RAIN>(md, f0, l0, Dm, sF, sU, __shfl(al0, f0.n), RAIN ? __shfl(al1, f0.n) : R(0), p0);
       if (!px || !py) {   // wave-uniform
@@ -425,7 +424,7 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
       const int n = face_node<K, 3>(ji, si, ta, tb, match);
       const R a0 = __shfl(al0, n), a1 = RAIN ? __shfl(al1, n) : a0;
       if (inner) {
-        const int ww = w ^ (1 << ji), nn = n + match;
+        const int ww = w ^ (ji ? BX : 1), nn = n + match;
         const R ct = (R)(ji ? md.sip_tau[1] : md.sip_tau[0]);
 #pragma unroll
         for (int i = 0; i < VH; ++i) {
@@ -534,11 +533,11 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 #pragma unroll
       for (int v = 0; v < NV; ++v) sF[2][v][lane] = F[v];
     }
-    if (!SIP && li == (dx ? 0 : K)) {
+    if (!SIP && BX == 2 && li == (dx ? 0 : K)) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) sI[0][v][lj + P1 * ll] = Uq[v];
     }
-    if (!SIP && lj == (dy ? 0 : K)) {
+    if (!SIP && BY == 2 && lj == (dy ? 0 : K)) {
 #pragma unroll
       for (int v = 0; v < NV; ++v) sI[1][v][li + P1 * ll] = Uq[v];
     }
@@ -587,9 +586,9 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
   {
     constexpr int VH = (NV + 1) / 2;
     const int j = (lane >> 4) & 1;         // 0: x, 1: y
-    if (j ? py : px) {
+    if (WPB > 1 && (j ? py : px)) {
       const int side = j ? 1 - dy : 1 - dx;
-      const int ww = w ^ (1 << j);
+      const int ww = w ^ (j ? BX : 1);
       int match;
       const int n = face_node<K, 3>(j, side, ta, tb, match);
       const int nn = n + match;
