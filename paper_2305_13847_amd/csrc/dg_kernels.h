@@ -891,7 +891,7 @@ __device__ __forceinline__ void rhs_item_2d(const KArgs& a, int t, int it_, R* s
 }
 
 template <typename R, int K, int D, int RAIN, int MODE>
-__device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D, RAIN>::NV * Shape<K, D, block_threads<R>()>::NT],
+__device__ __forceinline__ void rhs_item(const KArgs& a, int t, int it_, R (*sF)[Vars<D, RAIN>::NV * Shape<K, D, block_threads<R>()>::NT],
                                          const R* sD, const R* __restrict__ U,
                                          const double* __restrict__ auxT,
                                          const double* __restrict__ auxS, R* __restrict__ out,
@@ -902,7 +902,6 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int it_, R (*sF)[Vars<D
   using V = Vars<D, RAIN>;
   constexpr int P1 = S::P1, NP = S::NP, NV = V::NV;
   const int seen = MODE == 2 ? stats_seen(a) : 0;
-  const int t = threadIdx.x;
   const Item item = a.items[it_];
   const MemberDesc& md = a.mem[item.member];
   const int le = t / NP, n = t - le * NP;
@@ -1048,12 +1047,20 @@ rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
                                   c1, c2, oT, oS, flags);
   }
   else
-    rhs_item<R, K, D, RAIN, MODE>(a, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
+    rhs_item<R, K, D, RAIN, MODE>(a, threadIdx.x, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
 }
+
+// FP32: 4 wavefronts per SIMD, four blocks per CU; at 2D Q2, whose blocks have 6
+// wavefronts, 5 (470 x 230, 4 blocks per CU, two steps: 468 us at 4, where two
+// blocks fit, 392 at 5, 418 at 6, which spills in the loop).  At Q1 the loop used to
+// keep the argument block's values in registers: 189 spilled at 3D Q1, 22 now,
+// 64 x 60 x 30, 4 blocks per CU 958 -> 355 us.
+template <typename R, int K, int D>
+constexpr int persistent_waves() { return sizeof(R) == 4 ? (block_kernel_threads(K, D, 256) > 256 ? 5 : 4) : 1; }
 
 // persistent: a grid smaller than the item count walks the items
 template <typename R, int K, int D, int RAIN, int MODE>
-__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 4 : 1)))
+__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(persistent_waves<R, K, D>())))
 rhs_kernel_persistent(KArgs a, const KArgs* __restrict__ a_dev, const R* __restrict__ U,
                       const double* __restrict__ auxT,
                       const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
@@ -1092,8 +1099,11 @@ rhs_kernel_persistent(KArgs a, const KArgs* __restrict__ a_dev, const R* __restr
     else if constexpr (PAIRS)
       rhs_item_2d<R, K, RAIN, MODE>(*ap, t, it_, &sF[0][0], sU, sL, sC, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2,
                                     oT, oS, flags);
+    else if constexpr (sizeof(R) == 4)
+      rhs_item<R, K, D, RAIN, MODE>(*ap, t, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
     else
-      rhs_item<R, K, D, RAIN, MODE>(a, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
+      // (FP64 has the registers; through ap it rounds differently from rhs_kernel)
+      rhs_item<R, K, D, RAIN, MODE>(a, threadIdx.x, it_, sF, sD, U, auxT, auxS, out, U0, dt_m, c0, c1, c2, oT, oS, flags);
     __syncthreads();   // the LDS tiles are reused by the next item
   }
 }
