@@ -297,8 +297,8 @@ dg_status dg_get_item_order(const dg_handle* h, int* order);
 
 /* Autotuner: times nsteps RK steps of a copy of U (device) for every
  * candidate geometry (elements per block {max, max/2, max/4} x persistent
- * blocks per CU {0, 1, 2, 4} x item order {0, 1, 2, 3} in 3D), keeps the
- * fastest and reports it (any output pointer may be NULL; best_ms is per
+ * blocks per CU {0, 1, 2, 4} x item order {0, 1, 2, 3} in 3D; on Q3 hexahedra
+ * the first two stay as they are), keeps the fastest and reports it (any output pointer may be NULL; best_ms is per
  * step; the order is read back with dg_get_item_order).  U is not modified. */
 dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, int nsteps, int* best_epb,
                       int* best_persist, double* best_ms);

@@ -1364,7 +1364,9 @@ extern "C" dg_status dg_get_launch(const dg_handle* h, int* epb, int* persist) {
 
 // Time `nsteps` RK steps of a copy of U for each launch geometry and keep the
 // fastest: elements per block in {max, max/2, max/4} x persistent blocks per
-// CU in {0, 1, 2, 4}.
+// CU in {0, 1, 2, 4} (as they are where bricks take no account of them: the
+// choice would be noise, and the other kernels of the handle would run with it)
+// x item orders.
 extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, int nsteps, int* best_epb,
                                  int* best_persist, double* best_ms) {
   dg_status st = ready(h);
@@ -1374,8 +1376,9 @@ extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, 
   st = take_dt(h, dt, 0, false, &d);
   if (st != DG_OK) return st;
   const int emax = elems_per_block(h->order, h->dim, h->prec == DG_FP64);
-  const int cand_e[3] = {emax, emax / 2, emax / 4};
-  const int cand_p[4] = {0, 1, 2, 4};
+  const bool bricks = !h->bricks.empty();
+  const int cand_e[3] = {bricks ? h->epb : emax, bricks ? 0 : emax / 2, bricks ? 0 : emax / 4};
+  const int cand_p[4] = {bricks ? h->persist : 0, 1, 2, 4};
   const int norders = h->dim == 3 ? 4 : 1;   // 2D items are always in element order
   void* W = h->stage_x[0];
   hipEvent_t e0, e1;
@@ -1388,7 +1391,7 @@ extern "C" dg_status dg_autotune(dg_handle* h, const void* U, const double* dt, 
   for (int io = 0; io < norders; ++io)
   for (int ie = 0; ie < 3; ++ie) {
     if (cand_e[ie] < 1 || (ie > 0 && cand_e[ie] == cand_e[ie - 1])) continue;
-    for (int ip = 0; ip < 4; ++ip) {
+    for (int ip = 0; ip < (bricks ? 1 : 4); ++ip) {
       st = dg_set_item_order(h, io);
       if (st == DG_OK) st = dg_set_launch(h, cand_e[ie], cand_p[ip]);
       if (st == DG_ENOMEM) continue;
