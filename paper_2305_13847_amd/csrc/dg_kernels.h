@@ -726,7 +726,8 @@ __device__ __forceinline__ void rhs_item_3d(const KArgs& a, int t, int it_, Elem
 
 // 2D right-hand side / stage of one work item (K >= 2).  A 2D element has
 // about as many face nodes (4 (K+1)) as nodes, so a block's face tasks are one
-// pass of its threads; they are numbered element by element,
+// pass of its threads (a loop over further ones, which no shape has, cost 2 to 10 %
+// in registers and code); they are numbered element by element,
 // and every load of a thread (its node, the neighbour's trace of its first
 // task, both backgrounds) is issued before any arithmetic: the state is read
 // in one round trip, and nothing waits for memory between the barriers.
@@ -794,7 +795,8 @@ __device__ __forceinline__ void rhs_item_2d(const KArgs& a, int t, int it_, R* s
   const int nel = min(a.epb, item.ne - item.e0);   // elements of this item
   const unsigned g0 = (unsigned)(item.eoff + item.e0) * NP, g = g0 + (unsigned)t;
   const bool active = t < nel * NP;
-  const int ntask = nel * 4 * P1;
+  const int ntask = nel * 4 * P1;   // at most one a thread
+  static_assert(K == 2 || 4 * P1 <= NP, "an element's face tasks fit its threads (K = 2: block_kernel_threads)");
   R Uq[NV];
   double T = 300.0, rvs = 0.0;
   Pair<R, D, RAIN> pr;
@@ -846,14 +848,6 @@ __device__ __forceinline__ void rhs_item_2d(const KArgs& a, int t, int it_, R* s
   if (!L::SEP) {
     __syncthreads();   // the volume term has read sF
     if (task) pair_flux<R, K, D, RAIN>(md, pr, Fn, ln, sF, sU, sL, dest(t, pr), dst);
-  }
-  // further tasks (K = 2); every task runs the same code, so the rounding of a
-  // face flux does not depend on the pass (the launch geometry)
-#pragma clang loop unroll(disable)
-  for (int k = (int)blockDim.x + t; k < ntask; k += (int)blockDim.x) {
-    pair_gather_2d<R, K, RAIN>(item, g0, k, U, auxT, auxS, N, pr);
-    pair_eval<R, D, RAIN>(a, pr, Fn, ln);
-    pair_flux<R, K, D, RAIN>(md, pr, Fn, ln, sF, sU, sL, dest(k, pr), dst);
   }
   // operands of the stage update and the split, fetched while the faces of
   // the other wavefronts finish
@@ -1052,7 +1046,7 @@ rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
 
 // FP32: 4 wavefronts per SIMD, four blocks per CU; at 2D Q2, whose blocks have 6
 // wavefronts, 5 (470 x 230, 4 blocks per CU, two steps: 468 us at 4, where two
-// blocks fit, 392 at 5, 418 at 6, which spills in the loop).  At Q1 the loop used to
+// blocks fit, 372 at 5; 6 spills in the loop).  At Q1 the loop used to
 // keep the argument block's values in registers: 189 spilled at 3D Q1, 22 now,
 // 64 x 60 x 30, 4 blocks per CU 958 -> 355 us.
 template <typename R, int K, int D>
