@@ -111,7 +111,7 @@ hipLaunchKernelGGL((KER<R, K_, D_, R_, M>), grid, block, 0, s, a, (const R*)U, a
                    (R*)out, (const R*)U0, dt, c0, c1, c2, oT, oS, flags)
     // the persistent (looping) variant only when the grid is smaller than the items
     const bool persist = (int)grid.x < grid_for_items(a.nitems);
-    if (K_ == 3 && D_ == 3) {
+    if constexpr (K_ == 3 && D_ == 3) {
       // Q3 hexahedra: one block per brick whatever the launch geometry of the
       // other kernels
       grid = dim3(grid_for_items(a.nbricks));
