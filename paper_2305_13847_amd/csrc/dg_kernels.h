@@ -1001,19 +1001,25 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int t, int it_, R (*sF)
 }
 
 // one work item per block
-// FP32 in 2D (Q2 and up): 7 wavefronts per SIMD, what the LDS allows.  Left at 5
+// FP32 in 2D (Q2 and up): 7 wavefronts per SIMD, what the LDS allows; with rain it
+// allows 6 at Q3, Q4, Q5 and Q7 (a bound above that would be none).  Left at 5
 // (94 registers, which only the split's rarely taken slow path needs) the kernel
-// waits for memory half of its time; bound to 72 registers that path spills a few
-// values and the rest does not.  64 members of 160 x 80 Q3 at most, five steps:
-// 2.83 ms at 5, 2.75 at 6, 2.61 at 7; 400 x 200 Q2 583, 532, 495 us.  Q1 takes
-// another path, which spills in its loops at 6 (390 -> 545 us).  In 3D the LDS
-// holds it at 5.  FP64 kernels are left to the compiler: 2D Q2 to Q7 measured the
-// same at 5 and 6.
-template <typename R, int K, int D>
-constexpr int min_waves() { return sizeof(R) == 4 ? (D == 2 && K >= 2 ? 7 : 4) : 1; }
+// waits for memory half of its time; bound to 72 or 80 registers that path spills a
+// few values and the rest does not.  64 members of 160 x 80 Q3 at most, five steps:
+// 2.83 ms at 5, 2.75 at 6, 2.61 at 7.  About 980 000 nodes, two steps, left at 5
+// against bound: Q2 324 -> 273 us, Q3 214 -> 202, Q4 236 -> 219, Q5 224 -> 209, Q6
+// 242 -> 217, Q7 220 -> 205; with rain Q2 357 -> 301, Q3 238 -> 224, Q4 254 -> 245,
+// Q5 242 -> 236, Q6 256 -> 243, Q7 236 -> 226.  Q1 takes another path, which spills in
+// its loops at 6 (390 -> 545 us).  In 3D the LDS holds it at 5.  FP64 kernels are left
+// to the compiler: 2D Q2 to Q7 measured the same at 5 and 6.
+template <typename R, int K, int D, int RAIN>
+constexpr int min_waves() {
+  if (sizeof(R) == 8) return 1;
+  return D == 2 && K >= 2 ? (RAIN && K != 2 && K != 6 ? 6 : 7) : 4;
+}
 
 template <typename R, int K, int D, int RAIN, int MODE>
-__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R, K, D>())))
+__global__ void __launch_bounds__(block_kernel_threads(K, D, 256)) __attribute__((amdgpu_waves_per_eu(min_waves<R, K, D, RAIN>())))
 rhs_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
            const double* __restrict__ auxS, R* __restrict__ out, const R* __restrict__ U0,
            const double* __restrict__ dt_m, double c0, double c1, double c2,
