@@ -329,8 +329,14 @@ __device__ __forceinline__ void direction_vjp(const KArgs& a, const MemberDesc& 
   rev.template flux_reverse<J>(a, Fb, Wb, lb);
 }
 
+// Wavefronts per SIMD that the registers are bound to: two, but one at 3D Q1 with
+// rain in FP64, where two spill 78 registers (64 x 60 x 30 164 -> 128 us; in FP32,
+// which spills 35, 114 and 112).  The other shapes measured the same or slower at one.
 template <typename R, int K, int D, int RAIN>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+constexpr int vjp_min_waves() { return sizeof(R) == 8 && K == 1 && D == 3 && RAIN ? 1 : 2; }
+
+template <typename R, int K, int D, int RAIN>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(vjp_min_waves<R, K, D, RAIN>())))
 rhs_vjp_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
                const double* __restrict__ auxS, const R* __restrict__ lam, R* __restrict__ out,
                const R* __restrict__ X1, const R* __restrict__ X2, const double* __restrict__ dt_m,
