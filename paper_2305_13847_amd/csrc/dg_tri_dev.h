@@ -194,6 +194,13 @@ struct TriLds {
   static constexpr int NPP = TriShape<K>::NPP, NPD = TriShape<K>::NPD;
   static constexpr int NF = TriShape<K>::NF, EPB = TriBlock<K>::EPB;
   static constexpr int NVP = (NV + 3) / 4 * 4, PF = (3 * NV + 3) / 4 * 4;
+  // Values after an element's rows that shift the next one's banks: a wavefront
+  // reads the same row of several elements at once, and NQ PF is a multiple of 64
+  // words at P2 and P3.  Without the shift, steps in FP64 take 1 to 9 % more (P2 910
+  // -> 995 us on 300 x 150 x 2, P1 719 -> 770) and in FP32 at P2 and P3 4 to 5 %;
+  // rain and P4 do not care.  At P1 in FP32 it costs a fourth block per CU (400 x 200
+  // x 2, two steps: 473 us with it, 453 without).
+  static constexpr int SHIFT = K == 1 && sizeof(R) == 4 ? 0 : 4;
   // the reference tables (FP32; in FP64 they would halve the blocks per CU and
   // stay in constant memory)
   struct Empty {};
@@ -202,10 +209,8 @@ struct TriLds {
   alignas(16) double ts[EPB][NQ][2];     // the weighted split of the updated state at the volume points
   alignas(16) R c[EPB][NV][NPP];         // coefficients of the stage input
   union {
-    // per volume point: w F.G0, w F.G1, w G.  The last 16 bytes shift the next
-    // element's banks: NQ PF is a multiple of 64 words at P2 and P3, and a
-    // wavefront reads the same row of three or four elements at once.
-    alignas(16) R pf[EPB][NQ * PF + 4];
+    // per volume point: w F.G0, w F.G1, w G, and the shift
+    alignas(16) R pf[EPB][NQ * PF + SHIFT];
     struct {                             // then the neighbours across the three faces
       alignas(16) double aux[EPB][3][2][NPD];
       alignas(16) R c[EPB][3][NV][NPP];
@@ -214,7 +219,7 @@ struct TriLds {
   } u;
   union {
     alignas(16) R px[EPB][NP][NVP];      // partial sums of the modes
-    alignas(16) R ff[EPB][3 * NF * NVP + 4];  // then per face point the weighted normal flux
+    alignas(16) R ff[EPB][3 * NF * NVP + SHIFT];  // then per face point the weighted normal flux
   } f;
   TriZ fz[EPB];             // heights of the vertices and background layer
   R fn[EPB][3][3];          // per face: n_x, n_z, |e_f| / det A
@@ -361,22 +366,24 @@ __device__ __forceinline__ void tri_neighbours(const TriArgs& t, const R* __rest
   }
 }
 
-// Stage kernel.  MODE 0: out = dC/dt.  MODE 2: out = c0 U0 + c1 U + c2 dt dC/dt
-// and the split of out into (Tn, Rn) for the next stage.  aux holds the
-// projected T and rho_v of U: aux[0 .. N) and aux[N .. 2N), N = ne NP.
 // Wavefronts per SIMD that the registers are bound to.  FP32 4 (128 registers, 8
 // spilled at P3; left free, 148 and 3 wavefronts: 2.12 against 1.97 ms for five
 // steps), FP64 3.  With rain at P3 and P4 the LDS allows less, and a bound that it
 // forbids is no bound: the compiler took 197 and more than 256 registers in FP32.
 // Three steps of 200 x 100 x 2 with rain: P3 FP32 1050 -> 943 us, FP64 2008 -> 1340;
 // P4 FP32 (100 x 50 x 2) 875 -> 640.  P4 in FP64 keeps one wavefront (two would
-// spill 150 registers, 4.4 -> 5.3 ms).
+// spill 150 registers, 4.4 -> 5.3 ms).  The tendency alone (MODE 0) with rain at P3
+// spills 22 and 20 registers (its own bound was not tried: 240 x 120 x 2 125 and
+// 176 us, 230 and 413 before these bounds).
 template <typename R, int K, int RAIN>
 constexpr int tri_min_waves() {
   if (RAIN && K >= 3) return sizeof(R) == 4 ? (K == 4 ? 2 : 3) : (K == 4 ? 1 : 2);
   return sizeof(R) == 4 ? 4 : 3;
 }
 
+// Stage kernel.  MODE 0: out = dC/dt.  MODE 2: out = c0 U0 + c1 U + c2 dt dC/dt
+// and the split of out into (Tn, Rn) for the next stage.  aux holds the
+// projected T and rho_v of U: aux[0 .. N) and aux[N .. 2N), N = ne NP.
 template <typename R, int K, int RAIN, int MODE>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(tri_min_waves<R, K, RAIN>())))
 tri_stage_kernel(KArgs a, TriArgs t, const R* __restrict__ U, const double* __restrict__ aux, R* __restrict__ out,
