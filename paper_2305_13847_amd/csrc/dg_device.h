@@ -107,8 +107,8 @@ __device__ __forceinline__ double rcp64(double v) {
 // rho_vs(T) = e_s(T) / (R_v T) with the Clausius-Clapeyron e_s of Section 2.1,
 // written as one exponential: C0 exp((a - 1) ln(T/T_ref) + b (1/T_ref - 1/T)).
 // The logarithm is 2 atanh((m - 1)/(m + 1)) of the mantissa m in [1/sqrt 2,
-// sqrt 2) (its Taylor series to z^10, remainder 1e-17), the exponential a Taylor
-// polynomial on |r| <= (ln 2)/2 (to r^13, remainder 2e-16).  What counts is the
+// sqrt 2) (its Taylor series to z^10, remainder 2e-19), the exponential a Taylor
+// polynomial on |r| <= (ln 2)/2 (to r^13, remainder 4e-18).  What counts is the
 // absolute error of the exponent (up to 30 in size), so a logarithm to 3e-16
 // absolute serves; the library's, correct to the last bit near 1, and its
 // exponential took 100 of this function's 155 VALU instructions (65 now).

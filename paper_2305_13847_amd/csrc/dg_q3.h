@@ -6,8 +6,8 @@
 // alone (its coordinates, neighbours, wall flags, offsets) is wave-uniform and
 // lives in scalar registers; per-lane indices are bit fields of the lane id.
 // Each wavefront works in its own LDS tiles; the block meets once, after the
-// fluxes are staged, so that the faces inside the brick take both sides from
-// LDS.  With partners on one x and one y side an element has four outer
+// fluxes are staged (with diffusion twice more, for the viscous ones), so that the
+// faces inside the brick take both sides from LDS.  With partners on one x and one y side an element has four outer
 // faces, 64 face nodes: one full pass of its lanes evaluates the neighbours
 // (a single row of elements has 96, two passes with one half empty).
 //
@@ -548,8 +548,8 @@ rhs_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__ auxT,
     // the neighbour traces of the outer faces: in flight until the face pass
     pair_load<R, D, RAIN>(U, auxT, auxS, N, f0.gn, nb0);
   }
-  // the only block-wide barrier: the D-hat table, and the partners' tiles for
-  // the faces inside the brick
+  // block-wide (without diffusion the only one): the D-hat table, and the partners'
+  // tiles for the faces inside the brick
   __syncthreads();
   if (!act) return;
 
