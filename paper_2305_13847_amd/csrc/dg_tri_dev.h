@@ -373,8 +373,8 @@ __device__ __forceinline__ void tri_neighbours(const TriArgs& t, const R* __rest
 // Three steps of 200 x 100 x 2 with rain: P3 FP32 1050 -> 943 us, FP64 2008 -> 1340;
 // P4 FP32 (100 x 50 x 2) 875 -> 640.  P4 in FP64 keeps one wavefront (two would
 // spill 150 registers, 4.4 -> 5.3 ms).  The tendency alone (MODE 0) with rain at P3
-// spills 22 and 20 registers (its own bound was not tried: 240 x 120 x 2 125 and
-// 176 us, 230 and 413 before these bounds).
+// spills 22 and 20 registers, and is slower still with a wavefront less: 240 x 120 x
+// 2 129 -> 133 us in FP32, 178 -> 230 in FP64 (230 and 413 before these bounds).
 template <typename R, int K, int RAIN>
 constexpr int tri_min_waves() {
   if (RAIN && K >= 3) return sizeof(R) == 4 ? (K == 4 ? 2 : 3) : (K == 4 ? 1 : 2);
