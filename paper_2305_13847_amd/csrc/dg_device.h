@@ -438,15 +438,19 @@ __device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double
   SplitOut o;
   o.iters = sat ? 1 : 0;
   o.bad = 0;
-  NearOut n = split_near(a, rd, rm, rr, re, T, rvs, inv, sat);
-  const bool pos = fma(a.cvd, rd, a.cl * (rm + rr)) + (a.cvv - a.cl) * rm > 0.0;
-  if (!n.ok && pos) {
-    n = split_mid(a, rd, rm, rr, re, T, rvs, inv, sat, n.T);
-    o.iters = sat ? 2 : 0;
+  bool ok = false;
+  if (a.closed) {   // uniform
+    NearOut n = split_near(a, rd, rm, rr, re, T, rvs, inv, sat);
+    const bool pos = fma(a.cvd, rd, a.cl * (rm + rr)) + (a.cvv - a.cl) * rm > 0.0;
+    if (!n.ok && pos) {
+      n = split_mid(a, rd, rm, rr, re, T, rvs, inv, sat, n.T);
+      o.iters = sat ? 2 : 0;
+    }
+    ok = n.ok;
+    o.T = n.T;
+    o.rvs = n.rvs;
   }
-  o.T = n.T;
-  o.rvs = n.rvs;
-  if (!n.ok || !a.closed) {
+  if (!ok) {
     Anchor A;
     A.T0 = 0.0; A.r0 = 0.0; A.inv0 = 0.0;
     if (T > 150.0 && T < 600.0 && rvs > 0.0) {
