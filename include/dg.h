@@ -280,10 +280,11 @@ dg_status dg_destroy(dg_handle* h);
  * Lobatto-basis stage kernel of dg_rk_step only; every other kernel takes
  * one block per work item.  The Q3 hexahedral right-hand sides take
  * fixed bricks of 2 x 2 elements per block (1 along x or y where no member has
- * more), whatever is set here.  Not a hot
- * call: synchronises.  Blocks smaller than the default need a larger table of
- * work items (64 bytes each), allocated when they are first set; DG_ENOMEM if
- * that fails, with the geometry as it was. */
+ * more), whatever is set here.  Not a hot call: synchronises, and calls that the
+ * caller captured into a graph of its own are to be captured again.  Blocks
+ * smaller than the default need a larger table of work items (64 bytes each),
+ * allocated when they are first set; DG_ENOMEM if that fails, with the geometry
+ * as it was. */
 dg_status dg_set_launch(dg_handle* h, int elems_per_block, int persist_per_cu);
 dg_status dg_get_launch(const dg_handle* h, int* elems_per_block, int* persist_per_cu);
 

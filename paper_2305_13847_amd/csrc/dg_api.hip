@@ -98,7 +98,7 @@ struct dg_handle {
   // device
   MemberDesc* mem_d = nullptr;
   Item* items_d = nullptr;       // holds items_cap items
-  std::vector<Item*> items_old;  // outgrown tables: launches captured by the caller may read them
+  std::vector<Item*> items_old;  // outgrown tables, kept: launches captured by the caller may still read them
   Item* bricks_d = nullptr;
   double* bg_d[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // rd, rm, rr, E, p
   void* stage[2] = {nullptr, nullptr};

@@ -727,15 +727,15 @@ __device__ __forceinline__ void rhs_item_3d(const KArgs& a, int t, int it_, Elem
 // 2D right-hand side / stage of one work item (K >= 2).  A 2D element has
 // about as many face nodes (4 (K+1)) as nodes, so a block's face tasks are one
 // pass of its threads (a loop over further ones, which no shape has, cost 2 to 10 %
-// in registers and code); they are numbered element by element,
-// and every load of a thread (its node, the neighbour's trace of its first
-// task, both backgrounds) is issued before any arithmetic: the state is read
-// in one round trip, and nothing waits for memory between the barriers.
+// in registers and code); they are numbered element by element, and every load of
+// a thread (its node, the neighbour's trace of its task, both backgrounds) is issued
+// before any arithmetic: the state is read in one round trip, and nothing waits for
+// memory between the barriers.
 //
 // Small calls are one wavefront's chain of dependent instructions, large ones
-// are bound by VALU issue; with the self-contained work items, ten steps on
-// 16 x 16 Q2 (FP64) 405 -> 283 us, 128 x 64 Q4 (FP64) 482 -> 443 us, five of a
-// 64-member Q3 ensemble (FP32) 3.01 -> 2.83 ms.
+// are bound by VALU issue; with the self-contained work items and without the loop,
+// ten steps on 16 x 16 Q2 (FP64) 405 -> 240 us, 128 x 64 Q4 (FP64) 482 -> 428 us; with
+// the items, five of a 64-member Q3 ensemble (FP32) 3.01 -> 2.83 ms.
 //
 // In FP32 the corrections have an LDS tile of their own (SEP), so the faces
 // need not wait for the volume term; in FP64 that tile would cost a quarter

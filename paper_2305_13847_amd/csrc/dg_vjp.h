@@ -50,8 +50,8 @@ __device__ __forceinline__ void split_reverse(const KArgs& a, bool sat, double r
 // accumulators, so the seeds of one direction only are live (held for all
 // three at once, with the wall ghosts' own reverse passes, the kernel took
 // 375 registers: one wavefront per SIMD).  Bound by FP64 issue and latency at
-// two wavefronts per SIMD (185 registers; 168 would spill 27): a tendency and
-// its product on 40 x 36 x 20 Q3 (FP32) 358 -> 211 us.
+// two wavefronts per SIMD (193 registers): a tendency and its product on 40 x 36 x
+// 20 Q3 (FP32) 358 -> 204 us.
 template <int D, int RAIN>
 struct Reverse {
   using V = Vars<D, RAIN>;
