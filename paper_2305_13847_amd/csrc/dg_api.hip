@@ -1021,9 +1021,11 @@ static dg_status take_dt(dg_handle* h, const double* dt, hipStream_t s, bool dev
     out->value = dt[0];
     return DG_OK;
   }
-  for (int m = 0; m < h->nmembers; m += 256) {
-    const int n = std::min(256, h->nmembers - m);
-    if (n > 64) set_dt<256>(dt + m, n, h->dt_d + m, s);
+  constexpr int kMax = 480;   // 3840 of the 4096 bytes that a launch takes
+  for (int m = 0; m < h->nmembers; m += kMax) {
+    const int n = std::min(kMax, h->nmembers - m);
+    if (n > 256) set_dt<kMax>(dt + m, n, h->dt_d + m, s);
+    else if (n > 64) set_dt<256>(dt + m, n, h->dt_d + m, s);
     else if (n > 8) set_dt<64>(dt + m, n, h->dt_d + m, s);
     else set_dt<8>(dt + m, n, h->dt_d + m, s);
   }

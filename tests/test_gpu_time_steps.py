@@ -28,8 +28,8 @@ def _synchronised(dg, U0, dt, factors):
     return U
 
 
-# 300 members: more than one launch takes as arguments
-@pytest.mark.parametrize("members", [1, 3, 300])
+# 600 members: more than one launch takes as arguments
+@pytest.mark.parametrize("members", [1, 3, 300, 600])
 @pytest.mark.parametrize("graph", [False, True])
 def test_queued_calls_keep_their_time_steps(members, graph):
     dg, U0, dt = _setup(members)
@@ -46,7 +46,7 @@ def test_queued_calls_keep_their_time_steps(members, graph):
     assert torch.equal(U, want)
 
 
-@pytest.mark.parametrize("members", [1, 3, 300])
+@pytest.mark.parametrize("members", [1, 3, 300, 600])
 def test_a_captured_call_keeps_its_time_steps(members):
     dg, U0, dt = _setup(members)
     want = _synchronised(dg, U0, dt, (0.5,))
