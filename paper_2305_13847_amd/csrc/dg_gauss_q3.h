@@ -140,7 +140,10 @@ __device__ __forceinline__ void gq3_outer(const KArgs& a, const GTask& t, GNb<R,
     nb.rv = Rvo;
   }
   gq3_side<R, RAIN>(a, t.J, nb.U, nb.T, nb.rv, q3_bg(sB[t.bn]), Fn, ln);
-  const R hL = R(0.5) * (lo >= ln ? lo : ln);
+  // Lambda = max over the two sides, ties to the minus side: both elements take the
+  // same one, also where a side's speed is not a number (a trace with T < 0)
+  const R lm = t.side ? lo : ln, lp = t.side ? ln : lo;
+  const R hL = R(0.5) * (lm >= lp ? lm : lp);
   const int at = (2 * t.J + t.side) * 16 + t.fp;
 #pragma unroll
   for (int v = 0; v < NV; ++v)
@@ -347,7 +350,7 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
       gq3_trace<R, RAIN>(l0, str, 1 - up, sU_all[ww], sT_all[ww], sRv_all[ww], sW, sWd, Uo, To, Rvo);
       gq3_side<R, RAIN>(a, J, Uo, To, Rvo, q3_bg(sB[fp >> 2]), Fo, lo);
       const R ln = __shfl_xor(lo, 16);
-      const R hL = R(0.5) * (lo >= ln ? lo : ln);
+      const R hL = R(0.5) * (lo >= ln ? lo : ln);   // (lanes 0..15: the minus side is their own)
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
         const R Fn = __shfl_xor(Fo[v], 16), Un = __shfl_xor(Uo[v], 16);
