@@ -430,7 +430,12 @@ __device__ __forceinline__ NearOut split_mid(const KArgs& a, double rd, double r
 }
 
 // The split warm-started at the node's previous (T, rho_vs(T)); the branch that
-// held there before is tried first.
+// held there before is tried first.  Without the closed form (KArgs::closed) 2D
+// kernels skip it (two steps on 350 x 175 Q2 in FP32, cap 8: 241 -> 218 us); in 3D
+// the quartic is solved and thrown away, as the branch around it costs registers
+// that the FP64 kernels do not have (Gauss basis with rain, 32 x 31 x 16 Q3, two
+// steps: 863 -> 900 us).
+template <int D>
 __device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double rm, double rr, double re, double T,
                                                double rvs) {
   const double inv = rcp64(T);
@@ -439,14 +444,14 @@ __device__ __forceinline__ SplitOut split_warm(const KArgs& a, double rd, double
   o.iters = sat ? 1 : 0;
   o.bad = 0;
   bool ok = false;
-  if (a.closed) {   // uniform
+  if (D == 3 || a.closed) {
     NearOut n = split_near(a, rd, rm, rr, re, T, rvs, inv, sat);
     const bool pos = fma(a.cvd, rd, a.cl * (rm + rr)) + (a.cvv - a.cl) * rm > 0.0;
-    if (!n.ok && pos) {
+    if (!n.ok && pos && a.closed) {
       n = split_mid(a, rd, rm, rr, re, T, rvs, inv, sat, n.T);
       o.iters = sat ? 2 : 0;
     }
-    ok = n.ok;
+    ok = n.ok && a.closed;
     o.T = n.T;
     o.rvs = n.rvs;
   }

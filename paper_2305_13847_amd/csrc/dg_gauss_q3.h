@@ -338,9 +338,9 @@ rhs_gauss_q3_kernel(KArgs a, const R* __restrict__ U, const double* __restrict__
     // the faces inside the brick, one per wavefront: the x faces of its rows, then
     // the y faces of its columns.  Lanes 0..15 the lower
     // element's side, 16..31 the upper's.
-    const int J = w < XF ? 0 : 1, k = w - (J ? XF : 0);
+    const int J = WPB == 4 ? w >> 1 : (BX == 2 ? 0 : 1), k = WPB == 4 ? w & 1 : w;
     const int cx = item.c0 + (J ? k : 1), cy = (item.c12 & 0xffff) + (J ? 1 : k);
-    if (w < XF + YF && cx < n0 && cy < n1) {
+    if ((WPB == 4 || w < XF + YF) && cx < n0 && cy < n1) {
       const int up = (lane >> 4) & 1;
       const int ww = J ? k + BX * up : BX * k + up;
       int l0, str;

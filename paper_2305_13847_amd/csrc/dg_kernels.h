@@ -589,7 +589,7 @@ __device__ __forceinline__ void stage_epilogue(const KArgs& a, const Bg& bg, int
       ke += mi * mi;
     }
     const double re = bg.E + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
-    const SplitOut s = split_warm(a, rd, rm, rr, re, T, rvs);
+    const SplitOut s = split_warm<D>(a, rd, rm, rr, re, T, rvs);
     iters = s.iters;
     bad = s.bad;
     const double rvs_st = ((flags & kRefreshRvs) && s.bad == 0) ? rho_vs(a, s.T) : s.rvs;
@@ -989,7 +989,7 @@ __device__ __forceinline__ void rhs_item(const KArgs& a, int t, int it_, R (*sF)
           ke += mi * mi;
         }
         const double re = bg.E + (double)Un[V::E] - 0.5 * ke * rcp64(rd + rm + rr);
-        const SplitOut s = split_warm(a, rd, rm, rr, re, T, rvs);
+        const SplitOut s = split_warm<D>(a, rd, rm, rr, re, T, rvs);
         iters = s.iters;
         bad = s.bad;
         oT[g] = s.T;
