@@ -198,9 +198,10 @@ struct TriLds {
   // reads the same row of several elements at once, and NQ PF is a multiple of 64
   // words at P2 and P3.  Without the shift, steps in FP64 take 1 to 9 % more (P2 910
   // -> 995 us on 300 x 150 x 2, P1 719 -> 770) and in FP32 at P2 and P3 4 to 5 %;
-  // rain and P4 do not care.  At P1 in FP32 it costs a fourth block per CU (400 x 200
-  // x 2, two steps: 473 us with it, 453 without).
-  static constexpr int SHIFT = K == 1 && sizeof(R) == 4 ? 0 : 4;
+  // rain and P4 do not care.  At P1 in FP32 it costs a fourth block per CU on large
+  // meshes (400 x 200 x 2, two steps: 473 us with it, 453 without) and pays on small
+  // ones (8 x 4 x 2, five steps: 179 and 185.5 us).
+  static constexpr int SHIFT = 4;
   // the reference tables (FP32; in FP64 they would halve the blocks per CU and
   // stay in constant memory)
   struct Empty {};
